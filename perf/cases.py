@@ -40,7 +40,6 @@ SHAPES = {
 MAX_TOKENS = {"tiny": 16384, "vit-300m": 12 * TILE, "llm-7b": 16384, "vit-6b": 16 * TILE, "llm-20b": 32768,
               "llm-small": 16384, "vit-small": 12 * TILE}
 CONNECTORS = {"vit-300m": (1024, 4096), "vit-6b": (3200, 6144)}
-WEIGHTS = ("n1_g", "n1_b", "w_qkv", "b_qkv", "w_o", "b_o", "n2_g", "n2_b", "w_up", "b_up", "w_down", "b_down")
 
 
 def _block(name, shape, op, layout, tokens, lens_seed=0):
