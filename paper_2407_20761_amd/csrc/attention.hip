@@ -21,6 +21,7 @@
 // the transposing LDS read (ds_read_b64_tr_b16), so no tile is ever stored twice.  16-byte chunks
 // are XOR-swizzled by the row so that both kinds of read are free of bank conflicts.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "ob_internal.h"
@@ -79,14 +80,14 @@ __device__ __forceinline__ int swz(int r) {
     return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
 }
 
-// Per-lane addressing of one streamed [64][D] tile family.
-template <int D>
+// Per-lane addressing of one streamed [ROWS][D] tile family.
+template <int D, int ROWS = ST>
 struct Tile {
     static constexpr int RB = D * 2;            // bytes per tile row
-    static constexpr int BYTES = ST * RB;
+    static constexpr int BYTES = ROWS * RB;
     static constexpr int CPR = RB / 16;         // chunks per row
     static constexpr int RPI = 1024 / RB;       // rows filled by one wave-level load
-    static constexpr int LD = ST / RPI / 4;     // wave-level loads per wave per tile
+    static constexpr int LD = ROWS / RPI / 4;   // wave-level loads per wave per tile
     uint32_t voff[LD];                          // global byte offset of this lane's chunk (row-in-tile part)
     int rr[D / 16];                             // LDS offset of the 16-byte fragment read, per D-step t
     int tro[2][D / 32];                         // LDS offset of the transposing read, per half s and D-tile dt
@@ -111,7 +112,7 @@ struct Tile {
                 tro[s][dt] = row * RB + ((chunk ^ swz<D>(row)) * 16) + (c & 1) * 8;
             }
     }
-    // asynchronous copy of rows [row0, row0 + 64) of a [*, ld] matrix (column offset folded into
+    // asynchronous copy of rows [row0, row0 + ROWS) of a [*, ld] matrix (column offset folded into
     // `base`); rows past the end of the matrix arrive as zeros
     __device__ __forceinline__ void issue(const unsigned char *base, long bytes_left,
                                           unsigned char OB_LDS *__restrict__ dst, int wave) const {
@@ -701,24 +702,24 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// backward, part 2: dK, dV.  A workgroup owns 128 key rows of one head and streams the segment's
-// 64-row query tiles (from the diagonal on when causal).  Its eight wavefronts form four pairs, one
+// backward, part 2: dK, dV.  A workgroup owns 64 or 128 key rows of one head and streams the segment's
+// 64- or 32-row query tiles (from the diagonal on when causal).  Its wavefronts form pairs, one
 // pair per 32 key rows, and the two waves of a pair split the four products between them:
-//   role P (waves 0-3):  S = Q K^T,  P = 2^(scale log2(e) S - lse2),  dV^T += dO^T P
-//   role G (waves 4-7):  dP = dO V^T,  dS = P (dP - Delta),           dK^T += Q^T dS
+//   role P (first half of the waves):   S = Q K^T,  P = 2^(scale log2(e) S - lse2),  dV^T += dO^T P
+//   role G (second half of the waves):  dP = dO V^T,  dS = P (dP - Delta),           dK^T += Q^T dS
 // P travels from the first to the second through LDS in the packed operand layout both use.  Each
 // wave keeps half of the state a single wave would need (so two fit on a SIMD and one's MFMAs hide
 // the other's element-wise work and LDS waits), and no product is computed twice.  Both roles run
 // "row-fragment tile x held rows -> 32x32 scores" and "transposed tile x packed scores -> output";
 // role G does the second one tile late (see the kernel), so that it never waits for its partner.
 // ------------------------------------------------------------------------------------------------
-// scores of a 64-row streamed tile against the 32 held rows: acc[mt] = rows 32 mt .. of the tile
-template <int D>
-__device__ __forceinline__ void dkv_scores(const unsigned char OB_LDS *__restrict__ tile, const Tile<D> &tl,
-                                           const bf16x8 (&held)[D / 16], f32x16 (&acc)[2]) {
-    constexpr int HB = D / 32, NB = 2 * (D / 16) / HB, PER = NB / 2;
+// scores of a streamed tile of 32 MT rows against the 32 held rows: acc[mt] = rows 32 mt .. of the tile
+template <int D, int MT>
+__device__ __forceinline__ void dkv_scores(const unsigned char OB_LDS *__restrict__ tile, const Tile<D, 32 * MT> &tl,
+                                           const bf16x8 (&held)[D / 16], f32x16 (&acc)[MT]) {
+    constexpr int HB = D / 32, NB = MT * (D / 16) / HB, PER = NB / MT;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
     bf16x8 fr[2][HB];
@@ -739,14 +740,14 @@ __device__ __forceinline__ void dkv_scores(const unsigned char OB_LDS *__restric
     }
 }
 
-// role P: probabilities of the 64 x 32 score tile, packed as the second operands of the four
+// role P: probabilities of the 32 MT x 32 score tile, packed as the second operands of the 2 MT
 // 16-row contraction steps (pk[mt][h] serves step 2 mt + h)
-template <bool CAUSAL, bool MASK>
-__device__ __forceinline__ void dkv_probs(const f32x16 (&s)[2], const float OB_LDS *__restrict__ lse2_s,
-                                          int q0, int seg_end, int kv_row, float sl2, bf16x8 (&pk)[2][2]) {
+template <bool CAUSAL, bool MASK, int MT>
+__device__ __forceinline__ void dkv_probs(const f32x16 (&s)[MT], const float OB_LDS *__restrict__ lse2_s,
+                                          int q0, int seg_end, int kv_row, float sl2, bf16x8 (&pk)[MT][2]) {
     const int lh = (threadIdx.x & 63) >> 5;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
+    for (int mt = 0; mt < MT; ++mt) {
         f32x16 p;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -767,11 +768,12 @@ __device__ __forceinline__ void dkv_probs(const f32x16 (&s)[2], const float OB_L
 }
 
 // role G: dS = P (dP - Delta), in place of the packed probabilities
-__device__ __forceinline__ void dkv_dscores(const f32x16 (&dp)[2], const float OB_LDS *__restrict__ dlt_s,
-                                            bf16x8 (&pk)[2][2]) {
+template <int MT>
+__device__ __forceinline__ void dkv_dscores(const f32x16 (&dp)[MT], const float OB_LDS *__restrict__ dlt_s,
+                                            bf16x8 (&pk)[MT][2]) {
     const int lh = (threadIdx.x & 63) >> 5;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
+    for (int mt = 0; mt < MT; ++mt) {
         f32x16 ds;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -787,25 +789,25 @@ __device__ __forceinline__ void dkv_dscores(const f32x16 (&dp)[2], const float O
     }
 }
 
-// out^T += tile^T x packed scores, contracting over the tile's 64 rows
-template <int D>
-__device__ __forceinline__ void dkv_outputs(const unsigned char OB_LDS *__restrict__ tile, const Tile<D> &tl,
-                                            const bf16x8 (&pk)[2][2], f32x16 (&acc_out)[D / 32]) {
+// out^T += tile^T x packed scores, contracting over the tile's rows
+template <int D, int MT>
+__device__ __forceinline__ void dkv_outputs(const unsigned char OB_LDS *__restrict__ tile, const Tile<D, 32 * MT> &tl,
+                                            const bf16x8 (&pk)[MT][2], f32x16 (&acc_out)[D / 32]) {
     constexpr int DT = D / 32;
     bf16x8 tf[2][DT];
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) tf[0][dt] = tl.frag_tr(tile, dt, 0);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < ST / 16; ++u) {
-        if (u + 1 < ST / 16) {
+    for (int u = 0; u < 2 * MT; ++u) {
+        if (u + 1 < 2 * MT) {
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) tf[(u + 1) & 1][dt] = tl.frag_tr(tile, dt, u + 1);
         }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
             acc_out[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf[u & 1][dt], pk[u >> 1][u & 1], acc_out[dt], 0, 0, 0);
-        if (u + 1 < ST / 16) OB_SCHED_READS_THEN_MFMA(2 * DT, DT); else OB_SCHED_READS_THEN_MFMA(0, DT);
+        if (u + 1 < 2 * MT) OB_SCHED_READS_THEN_MFMA(2 * DT, DT); else OB_SCHED_READS_THEN_MFMA(0, DT);
     }
 }
 
@@ -821,11 +823,26 @@ __device__ __forceinline__ void issue_row_stats(const float *base, long floats_l
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, dst, 4, lane * 4, 0, 0, 0);
 }
 
-// pairs of waves per workgroup of the dK / dV kernel, each owning 32 key rows: with D = 64 a wave needs few
-// enough registers for three on a SIMD, so six pairs (192 key rows) share every streamed tile
-constexpr int dkv_pairs(int d) { return d == 64 ? 6 : 4; }
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(128 * dkv_pairs(D)) void attn_bwd_dkv_kernel(
+// The dK / dV kernel comes in two shapes per head size (NP pairs of waves, each pair owning 32 key rows; query
+// tiles of SR rows), of which dkv_shape() takes the one its estimate of the launch favours:
+//  * D = 64: two pairs, so that workgroups which nothing synchronises share a CU and a 1025-row segment wastes
+//    6 % of the rows (six pairs in step: 12 %).  SR = 32 needs 34 KB of LDS and under 128 registers: four
+//    workgroups to the CU, the better rate when the chip is full (12 ViT tiles x 16 heads: 151 us, against 178
+//    with SR = 64 and 189 for six pairs).  SR = 64 has half the barriers and stage switches to a row, the shorter
+//    chain when one long segment keeps the launch waiting (16 texts, 16 / 4 heads: 121 against 144 and 177 us).
+//  * D = 128: four pairs on one CU, eight waves in step, the better rate when the chip is full (7B-shaped batch:
+//    707 us, two pairs 1012, two pairs with SR = 32 746); two pairs, one wave to a SIMD, the shorter
+//    trip for launches that leave most of it idle (one segment of 557, 32 / 8 heads: 61 against 70 us; of
+//    2000, 12 / 2 heads: 274 against 327).
+// Both shapes of a head size add up the query rows of a key row in the same order, set by DKV_ORDER_Q and the
+// place in whole tiles of dkv_whole() key rows: which of them runs does not show in the result, so a packed batch
+// still gives bit for bit what its segments give alone.
+constexpr int DKV_ORDER_Q = 64;   // the ragged end of the query rows is one masked step of up to this many rows
+constexpr int dkv_whole(int d) { return d == 64 ? 64 : 128; }
+constexpr int dkv_np(int d, int shape) { return d == 128 && shape == 0 ? 4 : 2; }      // pairs and query rows of a shape
+constexpr int dkv_sr(int d, int shape) { return d == 64 && shape == 1 ? 32 : 64; }
+template <int D, bool CAUSAL, int NP, int SR>
+__global__ __launch_bounds__(128 * NP, D == 128 ? 1 : SR == 32 ? 4 : 2) void attn_bwd_dkv_kernel(
     const __bf16 *__restrict__ d_o, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
     const __bf16 *__restrict__ v, const float *__restrict__ lse2_all, const float *__restrict__ delta,
     __bf16 *__restrict__ dk, __bf16 *__restrict__ dv, int ldq, int ldkv, int ldo,
@@ -833,9 +850,10 @@ __global__ __launch_bounds__(128 * dkv_pairs(D)) void attn_bwd_dkv_kernel(
     TileOrder ord) {
     // three stages of the streamed Q and dO tiles (the dK side works one tile behind the dV side, see
     // below), two buffers for the probabilities on their way from one to the other, row statistics
-    __shared__ __attribute__((aligned(1024))) unsigned char tiles_s[6 * Tile<D>::BYTES];
-    constexpr int NP = dkv_pairs(D), KVT = 32 * NP;                              // pairs; key rows of the workgroup
-    __shared__ __attribute__((aligned(1024))) unsigned char p_s[2 * NP * 4096];  // [buffer][pair]: 4 x 64 lanes x 16 B
+    __shared__ __attribute__((aligned(1024))) unsigned char tiles_s[6 * Tile<D, SR>::BYTES];
+    constexpr int KVT = 32 * NP, WHOLE = dkv_whole(D), MT = SR / 32, PB = MT * 2048;   // key rows of the workgroup, of the whole it may be a part of
+    static_assert(WHOLE % KVT == 0 && KVT % SR == 0, "parts of whole tiles");
+    __shared__ __attribute__((aligned(1024))) unsigned char p_s[2 * NP * PB];  // [buffer][pair]: 2 MT x 64 lanes x 16 B
     __shared__ __attribute__((aligned(256))) float stat_s[6 * ST];              // lse2 x 3 stages, Delta x 3 stages
     __shared__ int sh[8];
     const int rank = blockIdx.x / heads;
@@ -854,7 +872,7 @@ __global__ __launch_bounds__(128 * dkv_pairs(D)) void attn_bwd_dkv_kernel(
     constexpr int KT = D / 16, DT = D / 32;
 
     // the wave copies the tile it reads row fragments from: Q (role P) or dO (role G)
-    Tile<D> tl;
+    Tile<D, SR> tl;
     tl.init(role_g ? ldo : ldq, pair, lane);
     const unsigned char *const own_base = role_g ? (const unsigned char *)d_o : (const unsigned char *)q;
     const long own_ld2 = (role_g ? (long)ldo : (long)ldq) * 2;
@@ -873,39 +891,45 @@ __global__ __launch_bounds__(128 * dkv_pairs(D)) void attn_bwd_dkv_kernel(
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_out[i][r] = 0.f;
 
-    constexpr int BYTES = Tile<D>::BYTES;
+    constexpr int BYTES = Tile<D, SR>::BYTES;
     unsigned char OB_LDS *const tiles = (unsigned char OB_LDS *)tiles_s;
     float OB_LDS *const stats = (float OB_LDS *)stat_s;
 #define OB_QS(S) (tiles + (S) * BYTES)
 #define OB_DOS(S) (tiles + (3 + (S)) * BYTES)
 #define OB_LSES(S) (stats + (S) * ST)
 #define OB_DLTS(S) (stats + (3 + (S)) * ST)
-    unsigned char OB_LDS *const p_mine = (unsigned char OB_LDS *)p_s + pair * 4096 + lane * 16;
+    unsigned char OB_LDS *const p_mine = (unsigned char OB_LDS *)p_s + pair * PB + lane * 16;
 
-    // causal: query rows before this workgroup's first key row see none of its keys
-    const int q_begin = CAUSAL ? ti.seg_start + ((ti.row0 - ti.seg_start) / ST) * ST : ti.seg_start;
-    const int n_iter = (ti.seg_end - q_begin + ST - 1) / ST;
+    // causal: query rows before the whole's first key row see none of its keys; a part's `dead` tiles lie
+    // before its own first key row and are left out
+    const int whole_row0 = ti.row0 - (ti.row0 - ti.seg_start) % WHOLE;
+    const int q_begin = CAUSAL ? whole_row0 : ti.seg_start;
+    const int dead = CAUSAL ? (ti.row0 - whole_row0) / SR : 0;
+    const int n_iter = (ti.seg_end - q_begin + SR - 1) / SR;
 #define OB_ISSUE_DKV(hq_, it_, S)                                                                             \
     do {                                                                                                      \
         const int head_ = kvh * group + (hq_);                                                                \
-        const int q0_ = q_begin + (it_) * ST;                                                                 \
+        const int q0_ = q_begin + (it_) * SR;                                                                 \
         const long off_ = (long)q0_ * own_ld2 + (long)head_ * D * 2;                                          \
-        /* four waves of each role copy a tile */                                                            \
+        /* four waves of each role copy a tile, or two half of it each */                                    \
         if (pair < 4) tl.issue(own_base + off_, own_total - off_, role_g ? OB_DOS(S) : OB_QS(S), pair);       \
+        if (NP == 2) tl.issue(own_base + off_ + SR / 2 * own_ld2, own_total - off_ - SR / 2 * own_ld2,                \
+                              (role_g ? OB_DOS(S) : OB_QS(S)) + SR / 2 * Tile<D, SR>::RB, pair);                      \
         if (wave == 0) issue_row_stats(lse2_all + (size_t)head_ * T + q0_, (long)T - q0_, OB_LSES(S), lane);  \
         if (wave == NP) issue_row_stats(delta + (size_t)head_ * T + q0_, (long)T - q0_, OB_DLTS(S), lane);    \
     } while (0)
-    // causal: only the first KVT / ST query tiles touch some pair's diagonal; either way only the last
+    // causal: only the first WHOLE / SR query tiles touch some pair's diagonal; either way only the last
     // tile can be ragged.  The tiles in between need no mask.
-    const int n_head = CAUSAL ? min(KVT / ST, n_iter) : 0;
-    const int n_mid_end = max(n_head, n_iter - (((ti.seg_end - q_begin) % ST) ? 1 : 0));
+    const int n_head = CAUSAL ? min(WHOLE / SR, n_iter) : 0;
+    const int n_mid_end = max(n_head, (ti.seg_end - q_begin) / DKV_ORDER_Q * (DKV_ORDER_Q / SR));
     // Order of work: first the masked tiles of every query head of the group (phase 0), then the
     // mask-free ones of every head (phase 1) in one single-path loop -- the sums do not care, and one
     // loop nest per phase keeps the accumulators in place (a loop over the heads around the per-head
     // loops made the register allocator spill them).  A cursor names a tile: (phase, head in group, j).
-    const int cnt0 = n_head + (n_iter - n_mid_end), cnt1 = n_mid_end - n_head;
+    const int n_diag = n_head - dead;
+    const int cnt0 = n_diag + (n_iter - n_mid_end), cnt1 = n_mid_end - n_head;
     struct Cursor { int phase, hq, j; };
-    auto tile_of = [&](const Cursor &c) { return c.phase ? n_head + c.j : (c.j < n_head ? c.j : n_mid_end + c.j - n_head); };
+    auto tile_of = [&](const Cursor &c) { return c.phase ? n_head + c.j : (c.j < n_diag ? dead + c.j : n_mid_end + c.j - n_diag); };
     auto step = [&](Cursor &c) {   // to the next tile in the order of work; phase 2 = past the end
         const int cnt = c.phase ? cnt1 : cnt0;
         if (c.j + 1 < cnt) { ++c.j; return; }
@@ -933,34 +957,34 @@ __global__ __launch_bounds__(128 * dkv_pairs(D)) void attn_bwd_dkv_kernel(
     int gi = 0, st = 0;        // tiles done; stage of the current tile
     int left1 = group * cnt1;  // mask-free tiles not yet done
     bool live_prev = false;    // role G: tile n - 1 took part
-    f32x16 dp_keep[2];         // role G: dP of tile n - 1
+    f32x16 dp_keep[MT];         // role G: dP of tile n - 1
 #define OB_DKV_ITER(MASKED, S, PREV, NEXT)                                                                   \
     {                                                                                                       \
-        const int q0 = q_begin + tile_of(cur) * ST;                                                         \
+        const int q0 = q_begin + tile_of(cur) * SR;                                                         \
         __builtin_amdgcn_s_waitcnt(WAIT_VM0);                                                               \
         __syncthreads();                                                                                    \
         if (nxt.phase < 2) OB_ISSUE_DKV(nxt.hq, tile_of(nxt), NEXT);                                        \
         /* a masked tile entirely before this pair's keys contributes nothing */                            \
-        const bool live = !((MASKED) && CAUSAL && q0 + ST - 1 < pair_kv_first);                             \
+        const bool live = !((MASKED) && CAUSAL && q0 + SR - 1 < pair_kv_first);                             \
         if constexpr (!RG) {                                                                                \
             if (live) {                                                                                     \
-                f32x16 acc_x[2];                                                                            \
-                bf16x8 pk[2][2];                                                                            \
-                dkv_scores<D>(OB_QS(S), tl, kvf, acc_x);                                                    \
-                dkv_probs<CAUSAL, MASKED>(acc_x, OB_LSES(S), q0, ti.seg_end, kv_row, sl2, pk);              \
-                _Pragma("unroll") for (int i_ = 0; i_ < 4; ++i_)                                            \
-                    *(bf16x8 OB_LDS *)(p_mine + (gi & 1) * (NP * 4096) + i_ * 1024) = pk[i_ >> 1][i_ & 1];        \
-                dkv_outputs<D>(OB_DOS(S), tl, pk, acc_out);                                                 \
+                f32x16 acc_x[MT];                                                                            \
+                bf16x8 pk[MT][2];                                                                            \
+                dkv_scores<D, MT>(OB_QS(S), tl, kvf, acc_x);                                                    \
+                dkv_probs<CAUSAL, MASKED, MT>(acc_x, OB_LSES(S), q0, ti.seg_end, kv_row, sl2, pk);              \
+                _Pragma("unroll") for (int i_ = 0; i_ < 2 * MT; ++i_)                                            \
+                    *(bf16x8 OB_LDS *)(p_mine + (gi & 1) * (NP * PB) + i_ * 1024) = pk[i_ >> 1][i_ & 1];        \
+                dkv_outputs<D, MT>(OB_DOS(S), tl, pk, acc_out);                                                 \
             }                                                                                               \
         } else {                                                                                            \
             if (live_prev) {                                                                                \
-                bf16x8 pk[2][2];                                                                            \
-                _Pragma("unroll") for (int i_ = 0; i_ < 4; ++i_)                                            \
-                    pk[i_ >> 1][i_ & 1] = *(const bf16x8 OB_LDS *)(p_mine + ((gi - 1) & 1) * (NP * 4096) + i_ * 1024); \
-                dkv_dscores(dp_keep, OB_DLTS(PREV), pk);                                                    \
-                dkv_outputs<D>(OB_QS(PREV), tl, pk, acc_out);                                               \
+                bf16x8 pk[MT][2];                                                                            \
+                _Pragma("unroll") for (int i_ = 0; i_ < 2 * MT; ++i_)                                            \
+                    pk[i_ >> 1][i_ & 1] = *(const bf16x8 OB_LDS *)(p_mine + ((gi - 1) & 1) * (NP * PB) + i_ * 1024); \
+                dkv_dscores<MT>(dp_keep, OB_DLTS(PREV), pk);                                                    \
+                dkv_outputs<D, MT>(OB_QS(PREV), tl, pk, acc_out);                                               \
             }                                                                                               \
-            if (live) dkv_scores<D>(OB_DOS(S), tl, kvf, dp_keep);                                           \
+            if (live) dkv_scores<D, MT>(OB_DOS(S), tl, kvf, dp_keep);                                           \
             live_prev = live;                                                                               \
         }                                                                                                   \
         if (cur.phase == 1) --left1;                                                                        \
@@ -986,12 +1010,12 @@ __global__ __launch_bounds__(128 * dkv_pairs(D)) void attn_bwd_dkv_kernel(
     __syncthreads();
     if (RG && live_prev) {
         const int p_ = st == 0 ? 2 : st - 1;
-        bf16x8 pk[2][2];
+        bf16x8 pk[MT][2];
 #pragma unroll
-        for (int i_ = 0; i_ < 4; ++i_)
-            pk[i_ >> 1][i_ & 1] = *(const bf16x8 OB_LDS *)(p_mine + ((gi - 1) & 1) * (NP * 4096) + i_ * 1024);
-        dkv_dscores(dp_keep, OB_DLTS(p_), pk);
-        dkv_outputs<D>(OB_QS(p_), tl, pk, acc_out);
+        for (int i_ = 0; i_ < 2 * MT; ++i_)
+            pk[i_ >> 1][i_ & 1] = *(const bf16x8 OB_LDS *)(p_mine + ((gi - 1) & 1) * (NP * PB) + i_ * 1024);
+        dkv_dscores<MT>(dp_keep, OB_DLTS(p_), pk);
+        dkv_outputs<D, MT>(OB_QS(p_), tl, pk, acc_out);
     }
     };
     if (role_g) walk(std::true_type{}); else walk(std::false_type{});
@@ -1063,6 +1087,30 @@ void make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side
     ord.n = n;
 }
 
+// Which of its two shapes the dK / dV kernel runs in (see there).  An estimate of the launch's duration in
+// microseconds: the trips (64 query rows against a workgroup's key rows) that a CU has to make at the rate of a full
+// chip, or the longest chain of trips (the first key rows of the longest segment, all query heads of a group) at the
+// rate its workgroup sees, whichever is longer.  The rates are fitted to 23 launches of either shape (segments of
+// 100 - 8192 rows, 4 - 32 heads, groups of 1 - 8, both masks); the pick was the faster one in 21 and within 4 % of it in the
+// others.
+struct DkvShape { int kv_rows; double full, chain; };
+constexpr DkvShape DKV_SHAPES[2][2] = {{{64, 0.81, 1.1}, {64, 0.70, 1.53}},      // D = 64: SR = 64, SR = 32
+                                       {{128, 2.39, 1.7}, {64, 1.76, 1.42}}};    // D = 128: four pairs, two
+int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
+    double est[2];
+    for (int i = 0; i < 2; ++i) {
+        const DkvShape &sh = DKV_SHAPES[d == 128][i];
+        double sum = 0, chain = 0;
+        for (int j = 0; j < seg->n_seg; ++j) {
+            const double len = seg->cu_host[j + 1] - seg->cu_host[j], tiles = ceil(len / sh.kv_rows), first = ceil(len / 64);
+            sum += tiles * first - (causal ? 0.5 * tiles * (tiles - 1) * sh.kv_rows / 64 : 0.0);
+            chain = std::max(chain, first);
+        }
+        est[i] = group * std::max(sum * nkv / 256 * sh.full, chain * sh.chain);
+    }
+    return est[1] < est[0] ? 1 : 0;
+}
+
 // explicit instantiations (the host pass otherwise drops launch stubs of kernels reached only
 // through the dispatch macro below)
 #define OB_ATTN_INSTANCES(D, C)                                                                               \
@@ -1073,16 +1121,23 @@ void make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side
                                                       const __bf16 *, const __bf16 *, const float *, float *, \
                                                       float *, __bf16 *, int, int, int, const int32_t *, int, \
                                                       int, int, float, float, int, TileOrder);                \
-    template __global__ void attn_bwd_dkv_kernel<D, C>(const __bf16 *, const __bf16 *, const __bf16 *,        \
-                                                       const __bf16 *, const float *, const float *,          \
-                                                       __bf16 *, __bf16 *, int, int, int,                     \
-                                                       const int32_t *, int, int, int, float, float, int,     \
-                                                       TileOrder);
+    OB_DKV_INSTANCE(D, C, dkv_np(D, 0), dkv_sr(D, 0))                                                         \
+    OB_DKV_INSTANCE(D, C, dkv_np(D, 1), dkv_sr(D, 1))
+#define OB_DKV_INSTANCE(D, C, NP, SR)                                                                             \
+    template __global__ void attn_bwd_dkv_kernel<D, C, NP, SR>(const __bf16 *, const __bf16 *, const __bf16 *,    \
+                                                           const __bf16 *, const float *, const float *,      \
+                                                           __bf16 *, __bf16 *, int, int, int,                 \
+                                                           const int32_t *, int, int, int, float, float, int, \
+                                                           TileOrder);
 OB_ATTN_INSTANCES(64, true)
 OB_ATTN_INSTANCES(64, false)
 OB_ATTN_INSTANCES(128, true)
 OB_ATTN_INSTANCES(128, false)
+#undef OB_DKV_INSTANCE
 #undef OB_ATTN_INSTANCES
+
+template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_0 = attn_bwd_dkv_kernel<D, CAUSAL, dkv_np(D, 0), dkv_sr(D, 0)>;
+template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_1 = attn_bwd_dkv_kernel<D, CAUSAL, dkv_np(D, 1), dkv_sr(D, 1)>;
 
 }  // namespace
 
@@ -1132,12 +1187,15 @@ void launch_attn_bwd(const void *d_o, const void *q, const void *k, const void *
     }
     ProfScope prof(K_ATTN_BWD_DKV, s, 1.5 * attn_flops(seg, nq, d, causal));  // dV, dP, dK
     TileOrder ord;
-    const int kvt = 32 * dkv_pairs(d), tiles_kv = count_tiles(seg, kvt);
+    const int shape = dkv_shape(seg, nkv, group, d, causal);
+    const int kvt = 32 * dkv_np(d, shape), tiles_kv = count_tiles(seg, kvt);
     make_order(seg, kvt, causal, true, tiles_kv, ord);
     const dim3 grid_kv((unsigned)tiles_kv * nkv);
-    OB_ATTN_DISPATCH(attn_bwd_dkv_kernel, grid_kv, 4 * kvt, (const __bf16 *)d_o, (const __bf16 *)q,
-                     (const __bf16 *)k, (const __bf16 *)v, lse2, delta, (__bf16 *)dk, (__bf16 *)dv, ldq, ldkv,
-                     ldo, seg->cu_dev, seg->n_seg, T, group, scale, rot, nkv, ord);
+#define OB_DKV_ARGS (const __bf16 *)d_o, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, lse2, delta, (__bf16 *)dk,  \
+                    (__bf16 *)dv, ldq, ldkv, ldo, seg->cu_dev, seg->n_seg, T, group, scale, rot, nkv, ord
+    if (shape == 0) OB_ATTN_DISPATCH(attn_bwd_dkv_0, grid_kv, 4 * kvt, OB_DKV_ARGS);
+    else OB_ATTN_DISPATCH(attn_bwd_dkv_1, grid_kv, 4 * kvt, OB_DKV_ARGS);
+#undef OB_DKV_ARGS
 }
 
 }  // namespace ob

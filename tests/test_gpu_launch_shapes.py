@@ -1,0 +1,54 @@
+"""Kernels that come in several launch shapes, at the sizes where the choice between them changes and at
+the edges of their tiles: against the CPU oracle, and against each other where they promise the same bits."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_20761_amd as ob
+import synth_inputs as si
+from gpu_util import bytes_buf, to_dev, to_np
+from oracle import block as orc
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-2      # bf16 storage of every result and of the probabilities on the way (2^-9 each), as in the parity tests
+
+
+def _attention(qkv, d_o, lens, nq, nkv, d, mask):
+    """(o, dq, dk, dv) of one packed batch; qkv [T, (nq + 2 nkv) d], d_o [T, nq d] on the device"""
+    T, ld = qkv.shape
+    seg = ob.Segments(si.lengths_to_cu(lens))
+    o, lse = torch.empty_like(d_o), torch.empty((nq, T), dtype=torch.float32, device="cuda")
+    dqkv = torch.full_like(qkv, float("nan"))
+    cols = (slice(0, nq * d), slice(nq * d, (nq + nkv) * d), slice((nq + nkv) * d, ld))
+    q, k, v = (qkv[:, c] for c in cols)
+    dq, dk, dv = (dqkv[:, c] for c in cols)
+    ob.ob_varlen_attn_fwd(q, k, v, o, lse, ld, ld, nq * d, seg, nq, nkv, d, d ** -0.5, mask)
+    ws = bytes_buf(ob.ob_varlen_attn_bwd_workspace_bytes(T, nq, nkv, d))
+    ob.ob_varlen_attn_bwd(d_o, q, k, v, o, lse, dq, dk, dv, ld, ld, nq * d, seg, nq, nkv, d, d ** -0.5, mask, ws)
+    return o, dq, dk, dv
+
+
+@pytest.mark.parametrize("mask", [orc.MASK_BIDIR, orc.MASK_CAUSAL])
+@pytest.mark.parametrize("d,nq,nkv", [(64, 16, 16), (64, 16, 8), (128, 8, 8), (128, 16, 8)])
+def test_dkv_shapes_give_the_same_bits(d, nq, nkv, mask):
+    """Many short segments fill the chip (the shape for throughput), each alone leaves it idle (the shape for the
+    shorter trip): lengths on and beside the 32-, 64- and 128-row borders, oracle on the first and the longest."""
+    lens = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 191, 193, 257] * 8 + [385]
+    print(f"dkv shapes d={d} nq={nq} nkv={nkv} mask={mask}", flush=True)
+    cu = si.lengths_to_cu(lens)
+    T = int(cu[-1])
+    q, k, v, d_o_np = si.qkv_tensors(T, nq, nkv, d, seed=d + nq)
+    qkv = to_dev(np.concatenate([q.reshape(T, -1), k.reshape(T, -1), v.reshape(T, -1)], axis=1))
+    d_o = to_dev(d_o_np.reshape(T, -1))
+    packed = _attention(qkv, d_o, lens, nq, nkv, d, mask)
+    for j in list(range(17)) + [len(lens) - 1]:
+        a, b = int(cu[j]), int(cu[j + 1])
+        alone = _attention(qkv[a:b].contiguous(), d_o[a:b].contiguous(), [b - a], nq, nkv, d, mask)
+        for name, x, y in zip(("o", "dq", "dk", "dv"), packed, alone):
+            assert torch.equal(x[a:b].view(torch.int16), y.view(torch.int16)), (name, j, b - a)
+        if j in (9, len(lens) - 1):
+            ref = orc.attention_bwd_masked(*(t[a:b].astype(np.float64) for t in (d_o_np, q, k, v)), [0, b - a], mask, d ** -0.5)
+            for name, x, r in zip(("dq", "dk", "dv"), packed[1:], ref):
+                got = to_np(x[a:b]).reshape(r.shape)
+                assert np.abs(got - r).max() <= TOL * np.abs(r).max(), (name, j)
