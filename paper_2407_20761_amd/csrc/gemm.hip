@@ -51,7 +51,6 @@ namespace {
 
 constexpr int BK = 32;           // k per ring slot: 4 chunks of 16 bytes = 64 bytes per row of a K-contiguous operand
 constexpr int ROW_BYTES = BK * 2;
-constexpr int NS = 4;            // ring slots
 constexpr int KSTEP = 64;        // k per "K step", the unit the host's plan counts and slices in (two slots)
 
 // Workgroups are dealt round-robin to the 8 XCDs; give each XCD one contiguous range of the `count`
@@ -268,7 +267,7 @@ constexpr int waitcnt(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) |
 //    are 2 T runs.  A has three pairs: the pair freed last is filled for three K steps further on, so
 //    any of those runs will do.  B has two: the pair freed is the one read next but one, so its loads
 //    go out in the odd slot's own runs and the barrier two slots on waits for them.
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS>
 struct KLoop {
     using C = Cfg<BM, BN, WM, WN>;
     static constexpr int T = C::T;
@@ -314,7 +313,7 @@ struct KLoop {
     // one's in pairs: B's two, A's three (160 KB of LDS hold 64 + 96 KB).  A's pairs are used in turn,
     // which does not go into the four slots of a trip: where k-contiguous A is read and filled are
     // run-time offsets.
-    static constexpr int A_SLOT = BM * ROW_BYTES, B_SLOT = BN * ROW_BYTES, A_PAIRS = 3;
+    static constexpr int A_SLOT = BM * ROW_BYTES, B_SLOT = BN * ROW_BYTES, A_PAIRS = NS / 2 + 1;
     static constexpr int A_BYTES = AK ? NS * A_SLOT : A_PAIRS * 2 * A_SLOT, RING_BYTES = A_BYTES + NS * B_SLOT;
     static constexpr int A_BASE = AK ? 0 : NS * B_SLOT, B_BASE = AK ? A_BYTES : 0;   // (transposing reads stay in the lower 128 KB)
     int a_cur, a_nxt, a_fill;                    // k-contiguous A: the pair of the slot at hand, of the one after, the one being filled
@@ -426,7 +425,7 @@ struct KLoop {
     // the loads of at most this many slots, the newest, may still be on their way at a barrier
     // (both operands k-contiguous: at the barrier of an odd slot, behind which B's pair filled two slots
     // before is read, the T loads of A since; at that of an even slot nothing new is read)
-    static constexpr int vm_pending(int S) { return AK || BKM ? T * (NS - 2) : (S & 1) ? T : 63; }
+    static constexpr int vm_pending(int S) { return AK || BKM ? T * (NS - 2) : (S & 1) ? T * (NS - 3) : 63; }
     // The slot in ring position S.  On entry bfr[S & 1] and af[0 .. T-2] hold its fragments; on return
     // those of the slot after.
     template <int S>
@@ -445,10 +444,10 @@ struct KLoop {
     // in front of the loop's first would have asked for (positions 0 .. T-2).
     // prologue_later(): the number of loads it issues after the last one that the first slot needs.
     static constexpr int prologue_later() {
-        if (!AK && !BKM) return 2 * T;
+        if (!AK && !BKM) return (NS - 2) * T;
         int n = 0;
         for (int q = 0; q < T - 1; ++q) n += piece_a(q) >= 0 ? 1 : 0;
-        n += AK ? (NS - 1) * T / 2 : T;
+        n += AK ? (NS - 1) * T / 2 : (NS / 2 - 1) * T;
         n += (NS - 1) * T / 2 - (AK ? 1 : 0);
         return n;
     }
@@ -480,23 +479,23 @@ struct KLoop {
                 for (int p = 0; p < T / 2; ++p)
                     if (!(AK && sl == NS - 1 && p == T / 2 - 1)) opb.load(rb, ring + B_BASE + sl * B_SLOT, wave, p);
             }
-            if (!BKM && sl == 1) {
+            if (!BKM && (sl & 1) && sl < NS - 1) {
                 next_b();
 #pragma unroll
-                for (int p = 0; p < T; ++p) opb.load_pair(rb, ring + B_BASE + 2 * B_SLOT, wave, p);
+                for (int p = 0; p < T; ++p) opb.load_pair(rb, ring + B_BASE + (sl + 1) * B_SLOT, wave, p);
             }
-            if (!AK && sl == 1) {
+            if (!AK && (sl & 1) && sl < NS - 1) {
                 next_a();
 #pragma unroll
-                for (int p = 0; p < T; ++p) opa.load_pair(ra, ring + A_BASE + 2 * A_SLOT, wave, p);
+                for (int p = 0; p < T; ++p) opa.load_pair(ra, ring + A_BASE + (sl + 1) * A_SLOT, wave, p);
             }
             if (!AK && sl == NS - 1) {
                 next_a();
 #pragma unroll
                 for (int q = 0; q < T - 1; ++q)
-                    if (piece_a(q) >= 0) opa.load_pair(ra, ring + A_BASE + 4 * A_SLOT, wave, piece_a(q));
+                    if (piece_a(q) >= 0) opa.load_pair(ra, ring + A_BASE + NS * A_SLOT, wave, piece_a(q));
                 a_cur = a_nxt = 0;
-                a_fill = 4 * A_SLOT;
+                a_fill = NS * A_SLOT;
             }
         }
         // what runs 2 - 4 of the slot before the first would have left: the descriptors that take over
@@ -508,21 +507,21 @@ struct KLoop {
 
 // One workgroup's work: tile (tile_m, tile_n) of C, whole, or (sliced) K steps [kz k_chunk, ...) of it with
 // the fp32 sums left at part[kz][tail_tile].
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS>
 __device__ __forceinline__ void gemm_tile(
     int M, int N, int K, const __bf16 *__restrict__ A, int lda, const __bf16 *__restrict__ B,
     int ldb, __bf16 *__restrict__ Cm, int ldc, const __bf16 *__restrict__ bias,
     const __bf16 *R, int ldr, int tile_m, int tile_n, bool sliced, int kz, int tail_tile, const TailSplit &ts) {
     using C = Cfg<BM, BN, WM, WN>;
     constexpr int T = C::T;
-    __shared__ __attribute__((aligned(1024))) unsigned char ring_mem[KLoop<BM, BN, WM, WN, AK, BKM>::RING_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char ring_mem[KLoop<BM, BN, WM, WN, AK, BKM, NS>::RING_BYTES];
     const int m0 = __builtin_amdgcn_readfirstlane(tile_m) * BM;
     const int n0 = __builtin_amdgcn_readfirstlane(tile_n) * BN;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
 
-    KLoop<BM, BN, WM, WN, AK, BKM> lp;
+    KLoop<BM, BN, WM, WN, AK, BKM, NS> lp;
     lp.wave = wave;
     lp.opa.init(A, lda, m0, (AK ? (long)K : (long)M) * lda * 2, wave, lane, wm * (BM / WM), lp.A_BASE);
     lp.opb.init(B, ldb, n0, (BKM ? (long)K : (long)N) * ldb * 2, wave, lane, wn * (BN / WN), lp.B_BASE);
@@ -547,7 +546,7 @@ __device__ __forceinline__ void gemm_tile(
             for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
             asm volatile("" : "+a"(acc[i][j]));
         }
-    constexpr int later = KLoop<BM, BN, WM, WN, AK, BKM>::prologue_later();
+    constexpr int later = KLoop<BM, BN, WM, WN, AK, BKM, NS>::prologue_later();
     __builtin_amdgcn_s_waitcnt(waitcnt(later < 63 ? later : 63, 0));
     wg_barrier();
 #pragma unroll
@@ -565,8 +564,15 @@ __device__ __forceinline__ void gemm_tile(
         lp.template slot<1>(acc, ring);
         lp.template slot<2>(acc, ring);
         lp.template slot<3>(acc, ring);
+        if constexpr (NS == 8) {
+            if (kt + 4 >= 2 * nk) break;
+            lp.template slot<4>(acc, ring);
+            lp.template slot<5>(acc, ring);
+            lp.template slot<6>(acc, ring);
+            lp.template slot<7>(acc, ring);
+        }
     }
-    static_assert(NS == 4, "the trip above names the slots");
+    static_assert(NS == 4 || NS == 8, "the trip above names the slots");
 
     // the MFMAs above are opaque to the compiler's hazard handling: let the last ones retire before
     // the accumulators are read
@@ -584,8 +590,8 @@ __device__ __forceinline__ void gemm_tile(
     constexpr int RSTR = CW * 4 + 16;      // fp32 row stride in LDS, padded against bank conflicts
     constexpr int LPR = CW / 8;            // lanes per row on the way out (8 columns each)
     constexpr int RPI = 64 / LPR;          // rows per read instruction
-    static_assert(32 * RSTR <= NS * C::SLOT / C::NW, "slab does not fit the wave's LDS share");
-    unsigned char OB_LDS *slab = ring + wave * (NS * C::SLOT / C::NW);
+    static_assert(32 * RSTR <= 4 * C::SLOT / C::NW, "slab does not fit the wave's LDS share");
+    unsigned char OB_LDS *slab = ring + wave * (4 * C::SLOT / C::NW);
     const int lx = lane & 15, lq = lane >> 4;
     const int n_out = n0 + wn * CW + (lane % LPR) * 8;
     float bv[8];
@@ -664,7 +670,7 @@ __device__ __forceinline__ void gemm_tile(
     else out(integral_constant<int, 0>{}, integral_constant<bool, true>{});
 }
 
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
     int M, int N, int K, const __bf16 *__restrict__ A, int lda, const __bf16 *__restrict__ B,
     int ldb, __bf16 *__restrict__ Cm, int ldc, const __bf16 *__restrict__ bias,
@@ -677,7 +683,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
     const int tail_tile = sliced ? xcd_chunk((pid - n_whole) % ts.n_tail, ts.n_tail, interleave) : 0;
     int tile_m, tile_n;
     tile_of_id(sliced ? n_whole + tail_tile : xcd_chunk(pid, n_whole, interleave), tiles_m, tiles_n, tile_m, tile_n);
-    gemm_tile<BM, BN, WM, WN, AK, BKM>(M, N, K, A, lda, B, ldb, Cm, ldc, bias, R, ldr, tile_m, tile_n, sliced, kz,
+    gemm_tile<BM, BN, WM, WN, AK, BKM, NS>(M, N, K, A, lda, B, ldb, Cm, ldc, bias, R, ldr, tile_m, tile_n, sliced, kz,
                                        tail_tile, ts);
 }
 
@@ -711,21 +717,23 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_group_kernel(GemmGroup g, i
     const int p = group_member(g, tile);
     int tile_m, tile_n;
     tile_of_id(tile - g.first[p], g.tiles_m[p], g.tiles_n[p], tile_m, tile_n);
-    gemm_tile<BM, BN, WM, WN, AK, BKM>(g.M[p], g.N[p], K, g.A[p], g.lda[p], g.B[p], g.ldb[p], g.C[p], g.ldc[p], nullptr,
+    gemm_tile<BM, BN, WM, WN, AK, BKM, 4>(g.M[p], g.N[p], K, g.A[p], g.lda[p], g.B[p], g.ldb[p], g.C[p], g.ldc[p], nullptr,
                                        g.R[p], g.ldr[p], tile_m, tile_n, sliced, kz, tail_tile, ts);
 }
 template __global__ void gemm_group_kernel<256, 256, 2, 2, true, true>(GemmGroup, int, TailSplit);
+template __global__ void gemm_group_kernel<128, 128, 2, 2, true, true>(GemmGroup, int, TailSplit);
 
-#define OB_GEMM_INSTANCE(BM, BN, AK, BKM)                                                        \
-    template __global__ void gemm_kernel<BM, BN, 2, 2, AK, BKM>(                                 \
+#define OB_GEMM_INSTANCE(BM, BN, AK, BKM, NS)                                                        \
+    template __global__ void gemm_kernel<BM, BN, 2, 2, AK, BKM, NS>(                              \
         int, int, int, const __bf16 *, int, const __bf16 *, int, __bf16 *, int, const __bf16 *,    \
         const __bf16 *, int, int, int, TailSplit);
-OB_GEMM_INSTANCE(256, 256, false, false)
-OB_GEMM_INSTANCE(128, 128, false, false)
-OB_GEMM_INSTANCE(256, 256, false, true)
-OB_GEMM_INSTANCE(128, 128, false, true)
-OB_GEMM_INSTANCE(256, 256, true, true)
-OB_GEMM_INSTANCE(128, 128, true, true)
+OB_GEMM_INSTANCE(256, 256, false, false, 4)
+OB_GEMM_INSTANCE(128, 128, false, false, 4)
+OB_GEMM_INSTANCE(128, 128, false, false, 8)
+OB_GEMM_INSTANCE(256, 256, false, true, 4)
+OB_GEMM_INSTANCE(128, 128, false, true, 4)
+OB_GEMM_INSTANCE(256, 256, true, true, 4)
+OB_GEMM_INSTANCE(128, 128, true, true, 4)
 #undef OB_GEMM_INSTANCE
 
 // C = sum over the slices of the tail tiles' fp32 sums (+ bias) (+ R); 8 outputs per lane, slices
@@ -801,31 +809,14 @@ __global__ __launch_bounds__(256) void tail_sum_group_kernel(TailSplit ts, GemmG
     *(bf16x8 *)(g.C[p] + (size_t)m * g.ldc[p] + n) = o;
 }
 
-// How a GEMM is cut into workgroups: tile size, and which tiles have their contraction split.
+// How a GEMM is cut into workgroups: the kind of tile, and which tiles have their contraction split.
+enum TileKind { BIG = 0, SMALL = 1, DEEP = 2 };   // 256 x 256 | 128 x 128, two to a CU | 128 x 128 over a ring of eight slots
 struct Plan {
-    bool big;
+    TileKind kind;
     int n_full, n_tail, splits, k_chunk;   // splits == 1: every tile whole
-    size_t part_bytes() const { return splits > 1 ? (size_t)splits * n_tail * (big ? 256 * 256 : 128 * 128) * 4 : 0; }
+    size_t part_bytes() const { return splits > 1 ? (size_t)splits * n_tail * (kind == BIG ? 256 * 256 : 128 * 128) * 4 : 0; }
 };
 
-// 256x256 tiles run one workgroup per CU, 128x128 tiles two.  Both the tile size and the split are
-// chosen by an estimate of the launch's duration in microseconds, fitted to launches measured on a
-// mostly idle chip:
-//  * big tiles come in rounds of one per CU, and the tiles of an incomplete last round take as long
-//    as a full one (over 16325 tokens: 4096 x 12288, 3 rounds, 1409 TFLOP/s; 4096 x 14336, 3.5
-//    rounds, 1178; 4096 x 5120, 1.25 rounds, 1008); a K step takes 1.3, prologue and epilogue as
-//    much as 5 more (nothing else runs on the CU meanwhile);
-//  * a small tile with a CU to itself takes 0.47 per K step (+3); two to a CU 0.9 each (about 0.72
-//    of a big tile's rate: twice the fragment reads per MFMA), but the one's epilogue hides behind the
-//    other's K loop (+1) and, out of step as they are, they fill the last round gradually (0.4 of a
-//    round on top of tiles / 512).  Measured: 12300 x 4096 x 1024 (3.06 rounds of big tiles) 109
-//    against 118; 12300 x 1024 x 4096 (0.77 rounds) 112 against 86; 6144 x 4096 x 16325 808 against 712;
-//  * when the caller has room for fp32 sums (`can_split`), the contraction of the tiles of the last
-//    round can be cut into as many slices as fill the round, each slice a workgroup with a shorter K
-//    loop; a second kernel adds the slices.  A GEMM of less than one round (the hidden x hidden
-//    weight gradients of a narrow model over all tokens of the batch) is all tail.  The sums cost 4
-//    bytes per element and slice at 4 TB/s (measured: 14 us for 64 MiB) and 3 for the second launch;
-//    a split has to promise 7 %.
 // compute units of the current device, asked once (256 on MI355X, also when no device answers: the
 // size queries must work on a host without a GPU)
 int compute_units() {
@@ -839,49 +830,112 @@ int compute_units() {
     }();
     return cus;
 }
-
-double estimate_us(bool big, int nk, double n_full, double n_tail, int splits, int k_chunk) {
-    const double area = big ? 65536.0 : 16384.0;
-    const double sums = splits > 1 ? splits * n_tail * area * 4.0 / 4e6 + 3.0 : 0.0;
-    const int k_tail = splits > 1 ? k_chunk : nk;
-    const double cus = compute_units(), slots2 = 2.0 * cus;
-    if (big) return n_full / cus * (nk + 5) * 1.3 + ceil(n_tail * splits / cus) * (k_tail + 5) * 1.3 + sums;
-    if (n_full == 0 && n_tail * splits <= cus) return (k_tail + 3) * 0.47 + sums;
-    if (splits == 1) return ((n_full + n_tail) / slots2 + 0.4) * (nk + 1) * 0.9;
-    return n_full / slots2 * (nk + 1) * 0.9 + ceil(n_tail * splits / slots2) * (k_tail + 1) * 0.9 + sums;
+int tiles_of(TileKind kind, int M, int N) {
+    const int t = kind == BIG ? 256 : 128;
+    return ((M + t - 1) / t) * ((N + t - 1) / t);
+}
+int slots_of(TileKind kind) { return (kind == SMALL ? 2 : 1) * compute_units(); }   // workgroups the chip holds at a time
+// The tail of `tiles` tiles cut into at most z slices of whole trips of the two-step loop; false: that cuts nothing.
+bool cut(TileKind kind, int tiles, int nk, int z, Plan &p) {
+    const int n_tail = tiles % slots_of(kind), chunk = ((nk + z - 1) / z + 1) & ~1;
+    if (n_tail == 0 || nk < 16 || nk / z < 8 || (nk + chunk - 1) / chunk < 2) return false;
+    p = Plan{kind, tiles - n_tail, n_tail, (nk + chunk - 1) / chunk, chunk};   // every slice has at least one K step
+    return true;
 }
 
-Plan make_plan(int M, int N, int K, bool can_split) {
-    const int big = ((M + 255) / 256) * ((N + 255) / 256);
-    const int small = ((M + 127) / 128) * ((N + 127) / 128);
+// Duration of a launch in microseconds.  Fitted to 1344 GEMMs (64 - 16400 rows on either side, the linears of seven
+// models, the three layouts; cold operands, N(0, 1) data), each measured with every kind of tile, whole and with
+// its tail in 2, 3, 4, 6, 8 slices: 7 % off in the mean, and the choices made by it are 0.7 % slower than the best
+// ones measured (the estimate before it, without the deep ring: 2.4 %).
+//  * big tiles come in rounds of one per CU, and the tiles of an incomplete last round take as long as a full one; a K
+//    step takes 1.27 on a full chip, 1.09 while half the chip or less is at work (the clock is higher), prologue and
+//    epilogue as much as 4.9 more (nothing else runs on the CU meanwhile);
+//  * a small tile with a CU to itself is bound by what the CU takes in from beyond the L2 (50 - 75 bytes per ns, also
+//    with a ring twice as deep, eight waves, or lines fetched ahead by another wave: 0.5 per K step of 32 KB).  Two to a
+//    CU take 0.95 each, and, out of step as they are, hide each other's epilogues and fill the last round gradually;
+//  * a deep one has the CU to itself as well, with four instead of two K steps on their way.  Only "NT" has it: there
+//    B's loads have a slot and a half to land in the shallow ring, too little when the weights come from HBM
+//    (557 x 4096 x 4096: 50 -> 36 us; 557 x 6144 x 4096: 51 -> 38), and it keeps its rate when tiles are many enough for
+//    rounds;
+//  * the slices' sums cost 4 bytes per element and slice at 3.3 TB/s and 2.9 for the second launch.
+double estimate_us(int layout, TileKind kind, int nk, const Plan &p) {
+    const double cus = compute_units(), sliced = p.splits > 1;
+    const double whole = sliced ? p.n_full : 0, tail = sliced ? (double)p.n_tail * p.splits : p.n_full + p.n_tail;
+    const int k_tail = sliced ? p.k_chunk : nk;
+    const double sums = sliced ? tail * (kind == BIG ? 65536 : 16384) * 4 / 3.27e6 + 2.94 : 0.0;
+    const bool alone = whole == 0 && tail <= cus;
+    double t;
+    if (kind == BIG) {
+        const double step = alone ? 1.09 + 0.18 * fmax(0.0, 2 * tail / cus - 1) : 1.27;
+        t = whole / cus * (nk + 4.87) * 1.27 + ceil(tail / cus) * (k_tail + 4.87) * step;
+    } else if (kind == DEEP) {
+        t = whole / cus * (nk + 3.51) * 0.542 + ceil(tail / cus) * (k_tail + 3.51) * (alone ? 0.516 : 0.542);
+    } else if (alone) {
+        t = (k_tail + 2.66) * (layout == 0 ? 0.553 : 0.544);
+    } else if (!sliced) {
+        t = (tail / (2 * cus) + 0.267) * (nk + 1.25) * 0.953;
+    } else {
+        t = whole / (2 * cus) * (nk + 1.25) * 0.953 + ceil(tail / (2 * cus)) * (k_tail + 1.25) * 0.953;
+    }
+    return t + sums + 1.5;
+}
+
+// The scratch that a GEMM may fill with slice sums, and that the size queries report, is part of the interface:
+// programs size buffers by it, once for the largest batch.  So it is a rule of its own, and the plan of a launch
+// stays within it (that costs 0.2 % of the choices above).
+Plan scratch_plan(TileKind whole_kind, double t_whole, int tiles_big, int tiles_small, int nk) {
+    auto rule = [&](TileKind kind, const Plan &p) {
+        const double cus = compute_units(), w = (double)p.n_tail * p.splits;
+        const double sums = w * (kind == BIG ? 65536.0 : 16384.0) * 4.0 / 4e6 + 3.0;
+        if (kind == BIG) return p.n_full / cus * (nk + 5) * 1.3 + ceil(w / cus) * (p.k_chunk + 5) * 1.3 + sums;
+        if (p.n_full == 0 && w <= cus) return (p.k_chunk + 3) * 0.47 + sums;
+        return p.n_full / (2 * cus) * (nk + 1) * 0.9 + ceil(w / (2 * cus)) * (p.k_chunk + 1) * 0.9 + sums;
+    };
+    Plan best{whole_kind, whole_kind == BIG ? tiles_big : tiles_small, 0, 1, 0}, p;
+    double t_best = 0.93 * t_whole;
+    for (TileKind kind : {SMALL, BIG})
+        for (int z = 2; z <= 8; ++z) {
+            const int tiles = kind == BIG ? tiles_big : tiles_small;
+            if (tiles == 0 || !cut(kind, tiles, nk, z, p)) continue;
+            const double t = rule(kind, p);
+            if (t < t_best) { t_best = t; best = p; }
+        }
+    return best;
+}
+size_t scratch_bytes(int M, int N, int K) {
+    const int big = tiles_of(BIG, M, N), small = tiles_of(SMALL, M, N), nk = (K + KSTEP - 1) / KSTEP;
+    const double cus = compute_units();
+    const double t_big = ceil(big / cus) * (nk + 5) * 1.3;
+    const double t_small = small <= cus ? (nk + 3) * 0.47 : (small / (2 * cus) + 0.4) * (nk + 1) * 0.9;
+    return scratch_plan(t_big <= t_small ? BIG : SMALL, fmin(t_big, t_small), big, small, nk).part_bytes();
+}
+
+// `scratch`: bytes for slice sums
+Plan make_plan(int layout, int M, int N, int K, size_t scratch) {
     const int nk = (K + KSTEP - 1) / KSTEP;
-    const double t_big = estimate_us(true, nk, 0, big, 1, 0), t_small = estimate_us(false, nk, 0, small, 1, 0);
-    const bool use_big = t_big <= t_small;
-    Plan p{use_big, use_big ? big : small, 0, 1, 0};
-    if (can_split && nk >= 16) {
-        double best = 0.93 * (use_big ? t_big : t_small);
-        for (int tile_big = 0; tile_big < 2; ++tile_big) {
-            const int tiles = tile_big ? big : small, slots = (tile_big ? 1 : 2) * compute_units();
-            const int n_tail = tiles % slots, n_full = tiles - n_tail;
-            if (n_tail == 0) continue;
-            for (int z = 2; z <= 8 && nk / z >= 8; ++z) {
-                const int chunk = ((nk + z - 1) / z + 1) & ~1;       // whole trips of the two-step loop
-                const int slices = (nk + chunk - 1) / chunk;         // every slice has at least one K step
-                if (slices < 2) continue;
-                const double t = estimate_us(tile_big, nk, n_full, n_tail, slices, chunk);
-                if (t < best) { best = t; p = Plan{tile_big != 0, n_full, n_tail, slices, chunk}; }
-            }
+    Plan best{BIG, 0, 0, 1, 0}, p;
+    double t_best = -1;
+    for (TileKind kind : {BIG, SMALL, DEEP}) {
+        if (kind == DEEP && layout != 0) continue;
+        const int tiles = tiles_of(kind, M, N);
+        p = Plan{kind, tiles, 0, 1, 0};
+        const double t = estimate_us(layout, kind, nk, p);
+        if (t_best < 0 || t < t_best) { t_best = t; best = p; }
+        for (int z = 2; z <= 8 && scratch; ++z) {
+            if (!cut(kind, tiles, nk, z, p) || p.part_bytes() > scratch) continue;
+            const double ts = estimate_us(layout, kind, nk, p) / 0.95;   // (a split has to promise 5 %)
+            if (ts < t_best) { t_best = ts; best = p; }
         }
     }
-    return p;
+    return best;
 }
 
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS>
 void launch_tile(int M, int N, int K, const void *A, int lda, const void *B, int ldb, void *C, int ldc,
                  const void *bias, const void *R, int ldr, float *part, const Plan &p, hipStream_t s) {
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const TailSplit ts{p.splits > 1 ? part : nullptr, p.n_full, p.n_tail, p.splits, p.k_chunk};
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM>), dim3(p.n_full + p.n_tail * p.splits),
+    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM, NS>), dim3(p.n_full + p.n_tail * p.splits),
                        dim3(WM * WN * 64), 0, s, M, N, K, (const __bf16 *)A, lda, (const __bf16 *)B, ldb,
                        (__bf16 *)C, ldc, (const __bf16 *)bias, (const __bf16 *)R, ldr, tiles_m, tiles_n, ts);
     if (p.splits > 1)
@@ -889,45 +943,32 @@ void launch_tile(int M, int N, int K, const void *A, int lda, const void *B, int
                            tiles_m, tiles_n, (const __bf16 *)bias, (const __bf16 *)R, ldr, (__bf16 *)C, ldc);
 }
 
-// `part` (may be null: nothing is split) has room for the plan's fp32 sums
+// `part` (may be null: nothing is split) has room for scratch_bytes()
 template <bool AK, bool BKM>
-void launch_layout(int M, int N, int K, const void *A, int lda, const void *B, int ldb, void *C, int ldc,
+void launch_layout(int layout, int M, int N, int K, const void *A, int lda, const void *B, int ldb, void *C, int ldc,
                    const void *bias, const void *R, int ldr, float *part, hipStream_t s) {
-    const Plan p = make_plan(M, N, K, part != nullptr);
-    if (p.big)
-        launch_tile<256, 256, 2, 2, AK, BKM>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
-    else
-        launch_tile<128, 128, 2, 2, AK, BKM>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
+    const Plan p = make_plan(layout, M, N, K, part ? scratch_bytes(M, N, K) : 0);
+    if (p.kind == BIG) launch_tile<256, 256, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
+    else if (p.kind == SMALL) launch_tile<128, 128, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
+    else if constexpr (!AK && !BKM) launch_tile<128, 128, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
 }
 
-// A group of "TN" GEMMs over one K, 256 x 256 tiles: the whole tiles of the full rounds of the combined
-// list, then the slices of its tail (same rule and estimate as for a single GEMM).
-Plan make_group_plan(int total_tiles, int K) {
-    const int nk = (K + KSTEP - 1) / KSTEP, slots = compute_units();
-    const int n_tail = total_tiles % slots, n_full = total_tiles - n_tail;
-    Plan p{true, total_tiles, 0, 1, 0};
-    if (n_tail == 0 || nk < 16) return p;
-    double best = 0.93 * estimate_us(true, nk, 0, total_tiles, 1, 0);
-    for (int z = 2; z <= 8 && nk / z >= 8; ++z) {
-        const int chunk = ((nk + z - 1) / z + 1) & ~1;
-        const int slices = (nk + chunk - 1) / chunk;
-        if (slices < 2) continue;
-        const double t = estimate_us(true, nk, n_full, n_tail, slices, chunk);
-        if (t < best) { best = t; p = Plan{true, n_full, n_tail, slices, chunk}; }
-    }
-    return p;
+// The scratch of a group of "TN" GEMMs over one K: 256 x 256 tiles, the slices of the combined list's tail.
+Plan group_scratch_plan(int total_tiles, int K) {
+    const int nk = (K + KSTEP - 1) / KSTEP;
+    return scratch_plan(BIG, ceil((double)total_tiles / compute_units()) * (nk + 5) * 1.3, total_tiles, 0, nk);
 }
 
 }  // namespace
 
 // fp32 sums of the slices of the tiles whose contraction is split; 0 for a GEMM without such tiles
-size_t gemm_workspace_bytes(int, int M, int N, int K) { return make_plan(M, N, K, true).part_bytes(); }
+size_t gemm_workspace_bytes(int, int M, int N, int K) { return scratch_bytes(M, N, K); }
 
 // ws (may be null): gemm_workspace_bytes(0, M, N, K) bytes
 void launch_gemm_nt(int M, int N, int K, const void *A, int lda, const void *B, int ldb, void *C,
                     int ldc, const void *bias, const void *R, int ldr, hipStream_t s, int k_algo, void *ws) {
     ProfScope prof(K_GEMM, s, 2.0 * M * N * (k_algo > 0 ? k_algo : K));
-    launch_layout<false, false>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, (float *)ws, s);
+    launch_layout<false, false>(0, M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, (float *)ws, s);
 }
 
 // The weight gradients of a block in one launch: C_p[M_p, N_p] = A_p[K, M_p]^T B_p[K, N_p] (+ R_p), p < count
@@ -943,43 +984,50 @@ size_t gemm_tn_group_workspace_bytes(int count, const GemmTN *g, int K) {
         const size_t b = gemm_workspace_bytes(2, g[i].M, g[i].N, K);
         if (b > single) single = b;
     }
-    const size_t grouped = make_group_plan(total, K).part_bytes();
+    const size_t grouped = group_scratch_plan(total, K).part_bytes();
     return grouped > single ? grouped : single;
 }
 
 int gemm_tn_group(int count, const GemmTN *g, int K, void *ws, size_t ws_bytes, hipStream_t s) {
     if (count < 1 || count > GemmGroup::MAX) return fail(OB_EINVAL, "gemm group: %d members", count);
     const int nk = (K + KSTEP - 1) / KSTEP;
+    double t_single = 0.0, flops = 0.0;
+    int total[2] = {0, 0};                 // BIG, SMALL
+    for (int i = 0; i < count; ++i) {
+        const Plan p1 = make_plan(2, g[i].M, g[i].N, K, ws ? scratch_bytes(g[i].M, g[i].N, K) : 0);
+        t_single += estimate_us(2, p1.kind, nk, p1);
+        total[BIG] += tiles_of(BIG, g[i].M, g[i].N);
+        total[SMALL] += tiles_of(SMALL, g[i].M, g[i].N);
+        flops += 2.0 * g[i].M * g[i].N * K;
+    }
+    const Plan big = group_scratch_plan(total[BIG], K), small{SMALL, total[SMALL], 0, 1, 0};
+    const double t_big = estimate_us(2, BIG, nk, big), t_small = estimate_us(2, SMALL, nk, small);
+    const Plan p = t_small < t_big ? small : big;
+    if (count == 1 || !ws || ws_bytes < p.part_bytes() || fmin(t_big, t_small) > 0.9 * t_single) {
+        for (int i = 0; i < count; ++i)
+            if (int rc = gemm_any(2, g[i].M, g[i].N, K, g[i].A, g[i].B, g[i].C, nullptr, g[i].R, ws, ws_bytes, s)) return rc;
+        return OB_OK;
+    }
     GemmGroup grp{};
     grp.n = count;
-    double t_single = 0.0, flops = 0.0;
-    int total = 0;
+    int first = 0;
     for (int i = 0; i < count; ++i) {
-        grp.first[i] = total;
+        const int t = p.kind == BIG ? 256 : 128;
+        grp.first[i] = first;
         grp.M[i] = g[i].M; grp.N[i] = g[i].N;
         grp.A[i] = (const __bf16 *)g[i].A; grp.lda[i] = g[i].M;
         grp.B[i] = (const __bf16 *)g[i].B; grp.ldb[i] = g[i].N;
         grp.C[i] = (__bf16 *)g[i].C; grp.ldc[i] = g[i].N;
         grp.R[i] = (const __bf16 *)g[i].R; grp.ldr[i] = g[i].N;
-        grp.tiles_m[i] = (g[i].M + 255) / 256; grp.tiles_n[i] = (g[i].N + 255) / 256;
-        total += grp.tiles_m[i] * grp.tiles_n[i];
-        const Plan p1 = make_plan(g[i].M, g[i].N, K, ws != nullptr);
-        const int t1 = p1.n_full + p1.n_tail;
-        t_single += estimate_us(p1.big, nk, p1.splits > 1 ? p1.n_full : 0, p1.splits > 1 ? p1.n_tail : t1, p1.splits, p1.k_chunk) + 3.0;
-        flops += 2.0 * g[i].M * g[i].N * K;
+        grp.tiles_m[i] = (g[i].M + t - 1) / t; grp.tiles_n[i] = (g[i].N + t - 1) / t;
+        first += grp.tiles_m[i] * grp.tiles_n[i];
     }
-    for (int i = count; i <= GemmGroup::MAX; ++i) grp.first[i] = total;
-    const Plan p = make_group_plan(total, K);
-    const double t_group = estimate_us(true, nk, p.splits > 1 ? p.n_full : 0, p.splits > 1 ? p.n_tail : total, p.splits, p.k_chunk);
-    if (count == 1 || !ws || ws_bytes < p.part_bytes() || t_group > 0.9 * t_single) {
-        for (int i = 0; i < count; ++i)
-            if (int rc = gemm_any(2, g[i].M, g[i].N, K, g[i].A, g[i].B, g[i].C, nullptr, g[i].R, ws, ws_bytes, s)) return rc;
-        return OB_OK;
-    }
+    for (int i = count; i <= GemmGroup::MAX; ++i) grp.first[i] = first;
     ProfScope prof(K_GEMM, s, flops);
     const TailSplit ts{p.splits > 1 ? (float *)ws : nullptr, p.n_full, p.n_tail, p.splits, p.k_chunk};
-    hipLaunchKernelGGL((gemm_group_kernel<256, 256, 2, 2, true, true>), dim3(p.n_full + p.n_tail * p.splits), dim3(256), 0,
-                       s, grp, K, ts);
+    const dim3 grid(p.n_full + p.n_tail * p.splits);
+    if (p.kind == BIG) hipLaunchKernelGGL((gemm_group_kernel<256, 256, 2, 2, true, true>), grid, dim3(256), 0, s, grp, K, ts);
+    else hipLaunchKernelGGL((gemm_group_kernel<128, 128, 2, 2, true, true>), grid, dim3(256), 0, s, grp, K, ts);
     if (p.splits > 1)
         hipLaunchKernelGGL((tail_sum_group_kernel<256, 256>), dim3(p.n_tail * (256 * 256 / 8 / 256)), dim3(256), 0, s, ts, grp);
     return check_launch("gemm group");
@@ -993,11 +1041,11 @@ int gemm_any(int layout, int M, int N, int K, const void *A, const void *B, void
     ProfScope prof(K_GEMM, s, 2.0 * M * N * K);
     float *part = ws && ws_bytes >= gemm_workspace_bytes(layout, M, N, K) ? (float *)ws : nullptr;
     if (layout == 0)
-        launch_layout<false, false>(M, N, K, A, K, B, K, C, N, bias, R, N, part, s);
+        launch_layout<false, false>(0, M, N, K, A, K, B, K, C, N, bias, R, N, part, s);
     else if (layout == 1)
-        launch_layout<false, true>(M, N, K, A, K, B, N, C, N, bias, R, N, part, s);
+        launch_layout<false, true>(1, M, N, K, A, K, B, N, C, N, bias, R, N, part, s);
     else
-        launch_layout<true, true>(M, N, K, A, M, B, N, C, N, bias, R, N, part, s);
+        launch_layout<true, true>(2, M, N, K, A, M, B, N, C, N, bias, R, N, part, s);
     return check_launch("gemm");
 }
 

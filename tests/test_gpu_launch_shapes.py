@@ -52,3 +52,24 @@ def test_dkv_shapes_give_the_same_bits(d, nq, nkv, mask):
             for name, x, r in zip(("dq", "dk", "dv"), packed[1:], ref):
                 got = to_np(x[a:b]).reshape(r.shape)
                 assert np.abs(got - r).max() <= TOL * np.abs(r).max(), (name, j)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 64, 640), (127, 192, 704), (129, 320, 768), (300, 4160, 832), (557, 1088, 1088),
+                                   (257, 256, 4096), (300, 4096, 4096), (200, 768, 4224)])
+def test_gemm_deep_ring(M, N, K):
+    """"NT" launches of few tiles walk K over a ring of eight slots and may leave it in the middle (K of 10 - 66 steps of
+    64, every remainder modulo the four steps of a trip), whole or in slices, on ragged edges; with bias and residual."""
+    print(f"deep ring {M} {N} {K}", flush=True)
+    rng = np.random.default_rng(M + N + K)
+    A = si.round_to_bf16(rng.standard_normal((M, K), dtype=np.float32))
+    B = si.round_to_bf16(rng.standard_normal((N, K), dtype=np.float32))
+    bias = si.round_to_bf16(rng.standard_normal((N,), dtype=np.float32))
+    R = si.round_to_bf16(rng.standard_normal((M, N), dtype=np.float32) * 4)
+    prod = A.astype(np.float64) @ B.astype(np.float64).T
+    for ws in (None, bytes_buf(ob.ob_gemm_workspace_bytes(0, M, N, K))):
+        for b, r in ((None, None), (bias, R)):
+            C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+            ob.ob_gemm_bf16(0, M, N, K, to_dev(A), to_dev(B), C, None if b is None else to_dev(b), None if r is None else to_dev(r), ws)
+            ref = prod if b is None else prod + b + r
+            # one rounding to bf16 (2^-9 of the value) behind fp32 sums
+            assert np.abs(to_np(C) - ref).max() <= 2.0 ** -8 * np.abs(ref).max(), (ws is not None, b is not None)
