@@ -135,6 +135,13 @@ struct Operand {
     // between the two 128-byte halves of the banks, so among the 8 rows of one parity
     // swizzle(x) ^ bit 2 ^ bit 3 has to take 8 different values.
     static __device__ __forceinline__ int row_swizzle(int x) { return (x >> 1) & 7; }
+    // K-major layout: the XOR of a chunk of row k.  X = 64: rows of 128 bytes, two to a pass over the banks; the 32-byte
+    // pieces of a transposing read's rows k, k + 2 and of its groups k, k + 8 are kept apart (the four groups of 512
+    // bytes take two passes anyway).
+    static __device__ __forceinline__ int k_swizzle(int k) {
+        if (X == 64) return 2 * ((k >> 1) & 1) + 4 * ((k >> 3) & 1);
+        return (4 * (k & 3)) ^ (2 * (((k >> 3) ^ (k >> 4)) & 1));
+    }
 
     // ld = source leading dimension (elements); x0 = first tile row; total_bytes = size of the
     // source; wave_x0 = first x-value of this wave's part of the tile; region = where in the ring this
@@ -159,7 +166,7 @@ struct Operand {
 #pragma unroll
             for (int p = 0; p < LD; ++p) {
                 const int blk = wave * LD + p, k = blk * KPB + lane / CPR;
-                const int ch = (lane % CPR) ^ (4 * (k & 3)) ^ (2 * (((k >> 3) ^ (k >> 4)) & 1));
+                const int ch = (lane % CPR) ^ k_swizzle(k);
                 voff[p] = ((uint32_t)k * (uint32_t)ld + ch * 8) * 2u;
             }
             // group b of 16 lanes reads k = 8 b + (0..3) (and + 4 with the second read); inside the
@@ -168,7 +175,7 @@ struct Operand {
 #pragma unroll
             for (int i = 0; i < T; ++i) {
                 const int chunk = (wave_x0 + 16 * i) / 8 + (c >> 1);
-                rd[i] = region + (8 * b + kq) * ROWB + ((chunk ^ (4 * kq) ^ (2 * ((b ^ (b >> 1)) & 1))) * 16) + (c & 1) * 8;
+                rd[i] = region + (8 * b + kq) * ROWB + ((chunk ^ k_swizzle(8 * b + kq)) * 16) + (c & 1) * 8;
             }
         }
     }
@@ -353,7 +360,7 @@ struct KLoop {
     // more, which makes up for run 0).
     template <int S, int g>
     __device__ __forceinline__ void run(f32x4 (&acc)[T][T], unsigned char OB_LDS *__restrict__ ring) {
-        constexpr int AT_RB = 0, AT_RA = 1, AT_RX = T >= 8 ? 2 : 1, AT_DL = T / 2, AT_RQ = T >= 8 ? T / 2 + 2 : T - 1;
+        constexpr int AT_2 = T > 2 ? 2 : 1, AT_RB = 0, AT_RA = 1, AT_RX = T >= 8 ? 2 : 1, AT_DL = T > 2 ? T / 2 + 1 : 1, AT_RQ = T >= 8 ? T / 2 + 2 : T - 1;
         constexpr int set = S & 1, q = position(S, g), pa = piece_a(q), pb = piece_b(q);
         constexpr int N = (S + 1) % NS, P = (S + NS - 1) % NS, pair = pair_of(S, g);
 #pragma unroll
@@ -363,10 +370,10 @@ struct KLoop {
             if (g == 0) {
                 if (j == AT_RA) af[T - 1] = a_frag(ring, S, T - 1, true);
                 // the last load of the slot before, when both operands go straight to LDS
-                if (AK && BKM && j == 2) opb.load(rb, ring + B_BASE + P * B_SLOT, wave, T / 2 - 1);
+                if (AK && BKM && j == AT_2) opb.load(rb, ring + B_BASE + P * B_SLOT, wave, T / 2 - 1);
                 // (small tiles: the descriptors of this slot's loads are worked out here, see below)
                 if (T < 8 && (AK || (S & 1)) && j == 0) prepare_a();
-                if (T < 8 && (BKM || (S & 1)) && j == 2) prepare_b();
+                if (T < 8 && (BKM || (S & 1)) && j == AT_2) prepare_b();
             } else {
                 if (j == AT_RB) bfr[set ^ 1][g] = b_frag(ring, N, g);
                 if (j == AT_RA) af[g - 1] = a_frag(ring, N, g - 1, false);
@@ -400,7 +407,7 @@ struct KLoop {
             }
             if (pa >= 0 && j == AT_RQ) opa.load_pair(ra, ring + A_BASE + a_fill, wave, pa);
             if (pb >= 0 && j == AT_RQ) opb.load_pair(rb, ring + B_BASE + pair * 2 * B_SLOT, wave, pb);
-            if (pb == 0 && j == AT_DL + 1) opb.load_pair(rb, ring + B_BASE + pair * 2 * B_SLOT, wave, T - 1);
+            if (pb == 0 && j == AT_DL) opb.load_pair(rb, ring + B_BASE + pair * 2 * B_SLOT, wave, T - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (g == 0) {
@@ -706,7 +713,7 @@ __device__ __forceinline__ int group_member(const GemmGroup &g, int tile) {
     return __builtin_amdgcn_readfirstlane(p);
 }
 
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_group_kernel(GemmGroup g, int K, TailSplit ts) {
     const int pid = blockIdx.x, n_whole = ts.part ? ts.n_full : (int)gridDim.x;
     const bool sliced = pid >= n_whole;
@@ -717,11 +724,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_group_kernel(GemmGroup g, i
     const int p = group_member(g, tile);
     int tile_m, tile_n;
     tile_of_id(tile - g.first[p], g.tiles_m[p], g.tiles_n[p], tile_m, tile_n);
-    gemm_tile<BM, BN, WM, WN, AK, BKM, 4>(g.M[p], g.N[p], K, g.A[p], g.lda[p], g.B[p], g.ldb[p], g.C[p], g.ldc[p], nullptr,
+    gemm_tile<BM, BN, WM, WN, AK, BKM, NS>(g.M[p], g.N[p], K, g.A[p], g.lda[p], g.B[p], g.ldb[p], g.C[p], g.ldc[p], nullptr,
                                        g.R[p], g.ldr[p], tile_m, tile_n, sliced, kz, tail_tile, ts);
 }
-template __global__ void gemm_group_kernel<256, 256, 2, 2, true, true>(GemmGroup, int, TailSplit);
-template __global__ void gemm_group_kernel<128, 128, 2, 2, true, true>(GemmGroup, int, TailSplit);
+template __global__ void gemm_group_kernel<256, 256, 2, 2, true, true, 4>(GemmGroup, int, TailSplit);
+template __global__ void gemm_group_kernel<128, 128, 2, 2, true, true, 4>(GemmGroup, int, TailSplit);
+template __global__ void gemm_group_kernel<64, 64, 2, 2, true, true, 8>(GemmGroup, int, TailSplit);
 
 #define OB_GEMM_INSTANCE(BM, BN, AK, BKM, NS)                                                        \
     template __global__ void gemm_kernel<BM, BN, 2, 2, AK, BKM, NS>(                              \
@@ -730,6 +738,9 @@ template __global__ void gemm_group_kernel<128, 128, 2, 2, true, true>(GemmGroup
 OB_GEMM_INSTANCE(256, 256, false, false, 4)
 OB_GEMM_INSTANCE(128, 128, false, false, 4)
 OB_GEMM_INSTANCE(128, 128, false, false, 8)
+OB_GEMM_INSTANCE(64, 64, false, false, 8)
+OB_GEMM_INSTANCE(64, 64, false, true, 8)
+OB_GEMM_INSTANCE(64, 64, true, true, 8)
 OB_GEMM_INSTANCE(256, 256, false, true, 4)
 OB_GEMM_INSTANCE(128, 128, false, true, 4)
 OB_GEMM_INSTANCE(256, 256, true, true, 4)
@@ -810,11 +821,13 @@ __global__ __launch_bounds__(256) void tail_sum_group_kernel(TailSplit ts, GemmG
 }
 
 // How a GEMM is cut into workgroups: the kind of tile, and which tiles have their contraction split.
-enum TileKind { BIG = 0, SMALL = 1, DEEP = 2 };   // 256 x 256 | 128 x 128, two to a CU | 128 x 128 over a ring of eight slots
+// 256 x 256 | 128 x 128, two to a CU | 128 x 128 over a ring of eight slots | 64 x 64, eight slots, two to a CU
+enum TileKind { BIG = 0, SMALL = 1, DEEP = 2, FINE = 3 };
+constexpr int tile_edge(TileKind kind) { return kind == BIG ? 256 : kind == FINE ? 64 : 128; }
 struct Plan {
     TileKind kind;
     int n_full, n_tail, splits, k_chunk;   // splits == 1: every tile whole
-    size_t part_bytes() const { return splits > 1 ? (size_t)splits * n_tail * (kind == BIG ? 256 * 256 : 128 * 128) * 4 : 0; }
+    size_t part_bytes() const { return splits > 1 ? (size_t)splits * n_tail * tile_edge(kind) * tile_edge(kind) * 4 : 0; }
 };
 
 // compute units of the current device, asked once (256 on MI355X, also when no device answers: the
@@ -831,10 +844,10 @@ int compute_units() {
     return cus;
 }
 int tiles_of(TileKind kind, int M, int N) {
-    const int t = kind == BIG ? 256 : 128;
+    const int t = tile_edge(kind);
     return ((M + t - 1) / t) * ((N + t - 1) / t);
 }
-int slots_of(TileKind kind) { return (kind == SMALL ? 2 : 1) * compute_units(); }   // workgroups the chip holds at a time
+int slots_of(TileKind kind) { return (kind == SMALL || kind == FINE ? 2 : 1) * compute_units(); }   // workgroups the chip holds at a time
 // The tail of `tiles` tiles cut into at most z slices of whole trips of the two-step loop; false: that cuts nothing.
 bool cut(TileKind kind, int tiles, int nk, int z, Plan &p) {
     const int n_tail = tiles % slots_of(kind), chunk = ((nk + z - 1) / z + 1) & ~1;
@@ -845,44 +858,51 @@ bool cut(TileKind kind, int tiles, int nk, int z, Plan &p) {
 
 // Duration of a launch in microseconds.  Fitted to 1344 GEMMs (64 - 16400 rows on either side, the linears of seven
 // models, the three layouts; cold operands, N(0, 1) data), each measured with every kind of tile, whole and with
-// its tail in 2, 3, 4, 6, 8 slices: 7 % off in the mean, and the choices made by it are 0.7 % slower than the best
-// ones measured (the estimate before it, without the deep ring: 2.4 %).
+// its tail in 2, 3, 4, 6, 8 slices: 8 % off in the mean, and the choices made by it are 0.8 % slower than the best
+// ones measured (the estimate before it, with big and small tiles alone: 8 %).
 //  * big tiles come in rounds of one per CU, and the tiles of an incomplete last round take as long as a full one; a K
-//    step takes 1.27 on a full chip, 1.09 while half the chip or less is at work (the clock is higher), prologue and
-//    epilogue as much as 4.9 more (nothing else runs on the CU meanwhile);
+//    step takes 1.23 on a full chip, 1.1 while half the chip or less is at work (the clock is higher), prologue and
+//    epilogue as much as 4.67 more (nothing else runs on the CU meanwhile);
 //  * a small tile with a CU to itself is bound by what the CU takes in from beyond the L2 (50 - 75 bytes per ns, also
-//    with a ring twice as deep, eight waves, or lines fetched ahead by another wave: 0.5 per K step of 32 KB).  Two to a
-//    CU take 0.95 each, and, out of step as they are, hide each other's epilogues and fill the last round gradually;
+//    with a ring twice as deep, with eight waves, or with lines fetched ahead by another wave: 0.5 per K step of 32 KB).
+//    Two to a CU take 0.94 each, and, out of step as they are, hide each other's epilogues and fill the last round
+//    gradually;
 //  * a deep one has the CU to itself as well, with four instead of two K steps on their way.  Only "NT" has it: there
 //    B's loads have a slot and a half to land in the shallow ring, too little when the weights come from HBM
 //    (557 x 4096 x 4096: 50 -> 36 us; 557 x 6144 x 4096: 51 -> 38), and it keeps its rate when tiles are many enough for
 //    rounds;
-//  * the slices' sums cost 4 bytes per element and slice at 3.3 TB/s and 2.9 for the second launch.
+//  * a fine one takes in half of a small one's bytes per K step, so a launch too small to give every CU a tile is done
+//    in little more than half the time on four times the CUs (557 x 1024 x 1024 10.3 -> 7.0, 1025 x 768 x 2112
+//    15.6 -> 10.9, 768 x 768 over 1500 tokens 13.8 -> 9.4), while a full chip loses by its 16 instead of 8 KB per 1 MFLOP;
+//  * the slices' sums cost 4 bytes per element and slice at 3.4 TB/s and 2.9 for the second launch.
 double estimate_us(int layout, TileKind kind, int nk, const Plan &p) {
-    const double cus = compute_units(), sliced = p.splits > 1;
+    const double cus = compute_units();
+    const bool sliced = p.splits > 1;
     const double whole = sliced ? p.n_full : 0, tail = sliced ? (double)p.n_tail * p.splits : p.n_full + p.n_tail;
     const int k_tail = sliced ? p.k_chunk : nk;
-    const double sums = sliced ? tail * (kind == BIG ? 65536 : 16384) * 4 / 3.27e6 + 2.94 : 0.0;
+    const double sums = sliced ? tail * tile_edge(kind) * tile_edge(kind) * 4 / 3.38e6 + 2.94 : 0.0;
     const bool alone = whole == 0 && tail <= cus;
-    double t;
-    if (kind == BIG) {
-        const double step = alone ? 1.09 + 0.18 * fmax(0.0, 2 * tail / cus - 1) : 1.27;
-        t = whole / cus * (nk + 4.87) * 1.27 + ceil(tail / cus) * (k_tail + 4.87) * step;
-    } else if (kind == DEEP) {
-        t = whole / cus * (nk + 3.51) * 0.542 + ceil(tail / cus) * (k_tail + 3.51) * (alone ? 0.516 : 0.542);
-    } else if (alone) {
-        t = (k_tail + 2.66) * (layout == 0 ? 0.553 : 0.544);
-    } else if (!sliced) {
-        t = (tail / (2 * cus) + 0.267) * (nk + 1.25) * 0.953;
-    } else {
-        t = whole / (2 * cus) * (nk + 1.25) * 0.953 + ceil(tail / (2 * cus)) * (k_tail + 1.25) * 0.953;
+    auto paired = [&](double step, double edge, double last, double least) {   // tiles that share a CU in twos
+        if (sliced) return (whole / (2 * cus) * (nk + edge) + ceil(tail / (2 * cus)) * (k_tail + edge)) * step;
+        return fmax(tail / (2 * cus) + last, least) * (nk + edge) * step;
+    };
+    double t = 0;
+    switch (kind) {
+    case BIG: {
+        const double rounds = ceil(tail / cus), fill = (whole + tail) / (rounds * cus + whole);
+        t = (whole / cus * (nk + 4.67) + rounds * (k_tail + 4.67)) * (1.1 + 0.13 * fmax(0.0, 2 * fill - 1));
+        break;
+    }
+    case SMALL: t = alone ? (k_tail + 2.86) * (layout == 0 ? 0.566 : 0.521) : paired(0.939, 1.17, 0.3, 0); break;
+    case DEEP: t = whole / cus * (nk + 3.82) * 0.536 + ceil(tail / cus) * (k_tail + 3.82) * (alone ? 0.51 : 0.536); break;
+    case FINE: t = alone ? (k_tail + 5.82) * 0.236 : paired(0.453, 3.0, 0.365, 0.955); break;
     }
     return t + sums + 1.5;
 }
 
 // The scratch that a GEMM may fill with slice sums, and that the size queries report, is part of the interface:
 // programs size buffers by it, once for the largest batch.  So it is a rule of its own, and the plan of a launch
-// stays within it (that costs 0.2 % of the choices above).
+// stays within it (that costs 0.15 %).
 Plan scratch_plan(TileKind whole_kind, double t_whole, int tiles_big, int tiles_small, int nk) {
     auto rule = [&](TileKind kind, const Plan &p) {
         const double cus = compute_units(), w = (double)p.n_tail * p.splits;
@@ -915,7 +935,7 @@ Plan make_plan(int layout, int M, int N, int K, size_t scratch) {
     const int nk = (K + KSTEP - 1) / KSTEP;
     Plan best{BIG, 0, 0, 1, 0}, p;
     double t_best = -1;
-    for (TileKind kind : {BIG, SMALL, DEEP}) {
+    for (TileKind kind : {BIG, SMALL, DEEP, FINE}) {
         if (kind == DEEP && layout != 0) continue;
         const int tiles = tiles_of(kind, M, N);
         p = Plan{kind, tiles, 0, 1, 0};
@@ -950,6 +970,7 @@ void launch_layout(int layout, int M, int N, int K, const void *A, int lda, cons
     const Plan p = make_plan(layout, M, N, K, part ? scratch_bytes(M, N, K) : 0);
     if (p.kind == BIG) launch_tile<256, 256, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
     else if (p.kind == SMALL) launch_tile<128, 128, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
+    else if (p.kind == FINE) launch_tile<64, 64, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
     else if constexpr (!AK && !BKM) launch_tile<128, 128, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
 }
 
@@ -972,10 +993,12 @@ void launch_gemm_nt(int M, int N, int K, const void *A, int lda, const void *B, 
 }
 
 // The weight gradients of a block in one launch: C_p[M_p, N_p] = A_p[K, M_p]^T B_p[K, N_p] (+ R_p), p < count
-// <= 4, all over the same K.  Worth it when the GEMMs' own last rounds of tiles are a sizeable part of them:
-// the estimate (as for single GEMMs) has to promise 10 % (measured: the 300M-class ViT's four weight
-// gradients, 192 tiles in all, 38.0 -> 35.3 ms per 24-block step; the 6B-class ViT's, where it promises
-// 5 %, lose 0.4 %); otherwise, or without scratch, they are launched one by one.
+// <= 4, all over the same K, in tiles of one kind.  One list of tiles leaves one incomplete round instead of four, and
+// the last tiles of one GEMM (with their read of R) hide behind the next one's: for up to 8K tokens it is
+// the faster way wherever the estimate does not promise the opposite (backward of a block, us, one by one -> grouped: 300M
+// ViT 1025 tokens 250 -> 226, 12300 1042 -> 940; 6B ViT 3075 1808 -> 1709; 7B model 557 770 -> 744, 4000 3091 -> 3007).
+// Longer contractions keep their own launch order over the XCDs (see INTERLEAVE_MIN_K) unless it promises 10 % (6B ViT
+// 16400 tokens, promised 5 %: 7550 -> 7600; 7B model 16327, 1 %: 11664 -> 11693).
 size_t gemm_tn_group_workspace_bytes(int count, const GemmTN *g, int K) {
     int total = 0;
     size_t single = 0;
@@ -992,18 +1015,21 @@ int gemm_tn_group(int count, const GemmTN *g, int K, void *ws, size_t ws_bytes, 
     if (count < 1 || count > GemmGroup::MAX) return fail(OB_EINVAL, "gemm group: %d members", count);
     const int nk = (K + KSTEP - 1) / KSTEP;
     double t_single = 0.0, flops = 0.0;
-    int total[2] = {0, 0};                 // BIG, SMALL
+    int total[4] = {0, 0, 0, 0};           // tiles of each kind
     for (int i = 0; i < count; ++i) {
         const Plan p1 = make_plan(2, g[i].M, g[i].N, K, ws ? scratch_bytes(g[i].M, g[i].N, K) : 0);
         t_single += estimate_us(2, p1.kind, nk, p1);
-        total[BIG] += tiles_of(BIG, g[i].M, g[i].N);
-        total[SMALL] += tiles_of(SMALL, g[i].M, g[i].N);
+        for (TileKind kind : {BIG, SMALL, FINE}) total[kind] += tiles_of(kind, g[i].M, g[i].N);
         flops += 2.0 * g[i].M * g[i].N * K;
     }
-    const Plan big = group_scratch_plan(total[BIG], K), small{SMALL, total[SMALL], 0, 1, 0};
-    const double t_big = estimate_us(2, BIG, nk, big), t_small = estimate_us(2, SMALL, nk, small);
-    const Plan p = t_small < t_big ? small : big;
-    if (count == 1 || !ws || ws_bytes < p.part_bytes() || fmin(t_big, t_small) > 0.9 * t_single) {
+    Plan p = group_scratch_plan(total[BIG], K);
+    double t_group = estimate_us(2, BIG, nk, p);
+    for (TileKind kind : {SMALL, FINE}) {
+        const Plan q{kind, total[kind], 0, 1, 0};
+        const double t = estimate_us(2, kind, nk, q);
+        if (t < t_group) { t_group = t; p = q; }
+    }
+    if (count == 1 || !ws || ws_bytes < p.part_bytes() || t_group > (K < INTERLEAVE_MIN_K ? 1.0 : 0.9) * t_single) {
         for (int i = 0; i < count; ++i)
             if (int rc = gemm_any(2, g[i].M, g[i].N, K, g[i].A, g[i].B, g[i].C, nullptr, g[i].R, ws, ws_bytes, s)) return rc;
         return OB_OK;
@@ -1012,7 +1038,7 @@ int gemm_tn_group(int count, const GemmTN *g, int K, void *ws, size_t ws_bytes, 
     grp.n = count;
     int first = 0;
     for (int i = 0; i < count; ++i) {
-        const int t = p.kind == BIG ? 256 : 128;
+        const int t = tile_edge(p.kind);
         grp.first[i] = first;
         grp.M[i] = g[i].M; grp.N[i] = g[i].N;
         grp.A[i] = (const __bf16 *)g[i].A; grp.lda[i] = g[i].M;
@@ -1026,8 +1052,9 @@ int gemm_tn_group(int count, const GemmTN *g, int K, void *ws, size_t ws_bytes, 
     ProfScope prof(K_GEMM, s, flops);
     const TailSplit ts{p.splits > 1 ? (float *)ws : nullptr, p.n_full, p.n_tail, p.splits, p.k_chunk};
     const dim3 grid(p.n_full + p.n_tail * p.splits);
-    if (p.kind == BIG) hipLaunchKernelGGL((gemm_group_kernel<256, 256, 2, 2, true, true>), grid, dim3(256), 0, s, grp, K, ts);
-    else hipLaunchKernelGGL((gemm_group_kernel<128, 128, 2, 2, true, true>), grid, dim3(256), 0, s, grp, K, ts);
+    if (p.kind == BIG) hipLaunchKernelGGL((gemm_group_kernel<256, 256, 2, 2, true, true, 4>), grid, dim3(256), 0, s, grp, K, ts);
+    else if (p.kind == SMALL) hipLaunchKernelGGL((gemm_group_kernel<128, 128, 2, 2, true, true, 4>), grid, dim3(256), 0, s, grp, K, ts);
+    else hipLaunchKernelGGL((gemm_group_kernel<64, 64, 2, 2, true, true, 8>), grid, dim3(256), 0, s, grp, K, ts);
     if (p.splits > 1)
         hipLaunchKernelGGL((tail_sum_group_kernel<256, 256>), dim3(p.n_tail * (256 * 256 / 8 / 256)), dim3(256), 0, s, ts, grp);
     return check_launch("gemm group");

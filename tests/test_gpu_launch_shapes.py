@@ -73,3 +73,25 @@ def test_gemm_deep_ring(M, N, K):
             ref = prod if b is None else prod + b + r
             # one rounding to bf16 (2^-9 of the value) behind fp32 sums
             assert np.abs(to_np(C) - ref).max() <= 2.0 ** -8 * np.abs(ref).max(), (ws is not None, b is not None)
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1, 64, 128), (65, 128, 192), (130, 192, 640), (200, 768, 768), (63, 448, 1088),
+                                   (1025, 768, 832), (64, 4096, 4224)])
+def test_gemm_fine_tiles(layout, M, N, K):
+    """Launches that 64 x 64 tiles are chosen for (and their neighbours), all layouts: ragged rows and columns, every
+    remainder of the eight-slot ring, token counts that are no multiple of 32."""
+    if layout == 2:
+        M, K = (M + 63) // 64 * 64, K + 37
+    print(f"fine tiles layout={layout} {M} {N} {K}", flush=True)
+    rng = np.random.default_rng(M + N + K + layout)
+    A = si.round_to_bf16(rng.standard_normal((M, K), dtype=np.float32))
+    B = si.round_to_bf16(rng.standard_normal((N, K), dtype=np.float32))
+    R = si.round_to_bf16(rng.standard_normal((M, N), dtype=np.float32) * 4)
+    ref = A.astype(np.float64) @ B.astype(np.float64).T + R
+    a_dev = to_dev(A if layout != 2 else np.ascontiguousarray(A.T))
+    b_dev = to_dev(B if layout == 0 else np.ascontiguousarray(B.T))
+    for ws in (None, bytes_buf(ob.ob_gemm_workspace_bytes(layout, M, N, K))):
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ob.ob_gemm_bf16(layout, M, N, K, a_dev, b_dev, C, None, to_dev(R), ws)
+        assert np.abs(to_np(C) - ref).max() <= 2.0 ** -8 * np.abs(ref).max(), ws is not None
