@@ -557,66 +557,127 @@ __global__ __launch_bounds__(256) void rotary_kernel(__bf16 *__restrict__ qkv, i
     }
 }
 
-__device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
+// GELU through h = Phi(-|z|) = erfc(|z| / sqrt 2) / 2 = t Q(t) e^(-z^2 / 2), t = 1 / (1 + 0.43 |z| / sqrt 2), Q the degree-7
+// polynomial that is closest in the relative sense to erfc(x) e^(x^2) / t over x <= 9.5 (8.4e-8; a Lawson fit to 8000
+// Chebyshev nodes): an exponential, a reciprocal and 8 FMAs, where erff() takes twice that and 1 + erf(z) cancels for
+// negative z (relative error 5e-4 at z = -4; here 1.3e-6).  The backward uses the same exponential for the density.
+// (These kernels were bound by the vector unit, not by HBM.)
+struct HalfTail { float h, e; };   // Phi(-|z|), e^(-z^2 / 2)
+__device__ __forceinline__ HalfTail half_tail(float z) {
+    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(fabsf(z), 0.30405592f, 1.0f));
+    const float y = z * 0.84932180f;             // e^(-z^2 / 2) = 2^(-y^2)
+    const float e = __builtin_amdgcn_exp2f(-y * y);
+    float q = 0.036854025f;
+    q = __builtin_fmaf(q, t, -0.15518695f);
+    q = __builtin_fmaf(q, t, 0.19185331f);
+    q = __builtin_fmaf(q, t, -0.042863335f);
+    q = __builtin_fmaf(q, t, 0.12342247f);
+    q = __builtin_fmaf(q, t, 0.10247547f);
+    q = __builtin_fmaf(q, t, 0.12218773f);
+    q = __builtin_fmaf(q, t, 0.12125731f);
+    return HalfTail{q * t * e, e};
+}
+__device__ __forceinline__ float gelu_f(float z) {
+    const float h = half_tail(z).h;
+    return z * (z < 0.0f ? h : 1.0f - h);
+}
 __device__ __forceinline__ float gelu_grad_f(float z) {
-    return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * __expf(-0.5f * z * z) * 0.3989422804014327f;
+    const HalfTail k = half_tail(z);
+    return __builtin_fmaf(z * k.e, 0.3989422804014327f, 0.5f + copysignf(0.5f - k.h, z));
 }
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + __expf(-z)); }
 
-// GELU: act[t, f] = gelu(up[t, f]).  SwiGLU: up row = [gate (F) | up (F)], act = silu(gate) * up.
-template <bool SWIGLU>
-__global__ __launch_bounds__(256) void act_fwd_kernel(const __bf16 *__restrict__ up,
-                                                      __bf16 *__restrict__ act, long n_vec, int F) {
-    const int fv = F / 8;
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n_vec; i += (long)gridDim.x * 256) {
-        const long t = i / fv;
-        const int c = (int)(i % fv) * 8;
-        bf16x8 o;
-        if (SWIGLU) {
-            const bf16x8 g = *(const bf16x8 *)(up + t * 2 * F + c);
-            const bf16x8 u = *(const bf16x8 *)(up + t * 2 * F + F + c);
+// GELU: act[t, f] = gelu(up[t, f]): one flat array.  A workgroup takes 512 consecutive vectors of 8, two per thread.
+constexpr int GELU_VECS = 512;
+__global__ __launch_bounds__(256) void gelu_fwd_kernel(const __bf16 *__restrict__ up, __bf16 *__restrict__ act, long n_vec) {
+    for (long base = (long)blockIdx.x * GELU_VECS; base < n_vec; base += (long)gridDim.x * GELU_VECS) {
+        const long i[2] = {base + threadIdx.x, base + 256 + threadIdx.x};
+        bf16x8 u[2];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float gz = (float)g[e];
-                o[e] = (__bf16)(gz * sigmoid_f(gz) * (float)u[e]);
+        for (int k = 0; k < 2; ++k)
+            if (i[k] < n_vec) u[k] = *(const bf16x8 *)(up + i[k] * 8);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (i[k] < n_vec) {
+                bf16x8 o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (__bf16)gelu_f((float)u[k][e]);
+                *(bf16x8 *)(act + i[k] * 8) = o;
             }
-        } else {
-            const bf16x8 u = *(const bf16x8 *)(up + t * F + c);
+    }
+}
+__global__ __launch_bounds__(256) void gelu_bwd_kernel(const __bf16 *__restrict__ dact, const __bf16 *__restrict__ up,
+                                                       __bf16 *__restrict__ dup, long n_vec) {
+    for (long base = (long)blockIdx.x * GELU_VECS; base < n_vec; base += (long)gridDim.x * GELU_VECS) {
+        const long i[2] = {base + threadIdx.x, base + 256 + threadIdx.x};
+        bf16x8 u[2], d[2];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (__bf16)gelu_f((float)u[e]);
+        for (int k = 0; k < 2; ++k)
+            if (i[k] < n_vec) {
+                u[k] = *(const bf16x8 *)(up + i[k] * 8);
+                d[k] = *(const bf16x8 *)(dact + i[k] * 8);
+            }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (i[k] < n_vec) {
+                bf16x8 o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)d[k][e] * gelu_grad_f((float)u[k][e]));
+                *(bf16x8 *)(dup + i[k] * 8) = o;
+            }
+    }
+}
+
+// SwiGLU: up row = [gate (F) | up (F)], act = silu(gate) * up.  A thread's first row and column by one 32-bit division
+// (the launch has less than 2^32 threads), the next ones by adding the grid's stride.
+struct RowCol {
+    long row;
+    unsigned col, drow, dcol, fv;     // in vectors of 8
+    __device__ __forceinline__ RowCol(unsigned fv_) : fv(fv_) {
+        const unsigned i = blockIdx.x * 256u + threadIdx.x, stride = gridDim.x * 256u;
+        row = i / fv;
+        col = i % fv;
+        drow = stride / fv;
+        dcol = stride % fv;
+    }
+    __device__ __forceinline__ void next() {
+        row += drow;
+        col += dcol;
+        if (col >= fv) { col -= fv; ++row; }
+    }
+};
+__global__ __launch_bounds__(256) void swiglu_fwd_kernel(const __bf16 *__restrict__ up, __bf16 *__restrict__ act, int T, int F) {
+    for (RowCol p(F / 8); p.row < T; p.next()) {
+        const long t = p.row;
+        const unsigned c = p.col * 8;
+        const bf16x8 g = *(const bf16x8 *)(up + t * 2 * F + c);
+        const bf16x8 u = *(const bf16x8 *)(up + t * 2 * F + F + c);
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float gz = (float)g[e];
+            o[e] = (__bf16)(gz * sigmoid_f(gz) * (float)u[e]);
         }
         *(bf16x8 *)(act + t * F + c) = o;
     }
 }
-
-template <bool SWIGLU>
-__global__ __launch_bounds__(256) void act_bwd_kernel(const __bf16 *__restrict__ dact,
-                                                      const __bf16 *__restrict__ up,
-                                                      __bf16 *__restrict__ dup, long n_vec, int F) {
-    const int fv = F / 8;
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n_vec; i += (long)gridDim.x * 256) {
-        const long t = i / fv;
-        const int c = (int)(i % fv) * 8;
+__global__ __launch_bounds__(256) void swiglu_bwd_kernel(const __bf16 *__restrict__ dact, const __bf16 *__restrict__ up,
+                                                         __bf16 *__restrict__ dup, int T, int F) {
+    for (RowCol p(F / 8); p.row < T; p.next()) {
+        const long t = p.row;
+        const unsigned c = p.col * 8;
         const bf16x8 da = *(const bf16x8 *)(dact + t * F + c);
-        if (SWIGLU) {
-            const bf16x8 g = *(const bf16x8 *)(up + t * 2 * F + c);
-            const bf16x8 u = *(const bf16x8 *)(up + t * 2 * F + F + c);
-            bf16x8 og, ou;
+        const bf16x8 g = *(const bf16x8 *)(up + t * 2 * F + c);
+        const bf16x8 u = *(const bf16x8 *)(up + t * 2 * F + F + c);
+        bf16x8 og, ou;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float gz = (float)g[e], sg = sigmoid_f(gz), d = (float)da[e];
-                og[e] = (__bf16)(d * (float)u[e] * sg * (1.0f + gz * (1.0f - sg)));
-                ou[e] = (__bf16)(d * gz * sg);
-            }
-            *(bf16x8 *)(dup + t * 2 * F + c) = og;
-            *(bf16x8 *)(dup + t * 2 * F + F + c) = ou;
-        } else {
-            const bf16x8 u = *(const bf16x8 *)(up + t * F + c);
-            bf16x8 o;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)da[e] * gelu_grad_f((float)u[e]));
-            *(bf16x8 *)(dup + t * F + c) = o;
+        for (int e = 0; e < 8; ++e) {
+            const float gz = (float)g[e], sg = sigmoid_f(gz), d = (float)da[e];
+            og[e] = (__bf16)(d * (float)u[e] * sg * (1.0f + gz * (1.0f - sg)));
+            ou[e] = (__bf16)(d * gz * sg);
         }
+        *(bf16x8 *)(dup + t * 2 * F + c) = og;
+        *(bf16x8 *)(dup + t * 2 * F + F + c) = ou;
     }
 }
 
@@ -737,28 +798,27 @@ void launch_rotary(void *qkv, int ld, int T, int n_heads_rot, int d, const int32
                        cu_dev, n_seg, log2f(base), sign);
 }
 
+// workgroups of an element-wise pass over n_vec vectors of 8, `per` to a workgroup: at most 65536
+static int act_blocks(long n_vec, int per) { return (int)((n_vec + per - 1) / per < 65536 ? (n_vec + per - 1) / per : 65536); }
+
 void launch_act_fwd(int mlp, const void *up, void *act, int T, int F, hipStream_t s) {
     ProfScope prof(K_ACT_FWD, s, (mlp == OB_SWIGLU ? 6.0 : 4.0) * T * F);
     const long n_vec = (long)T * (F / 8);
-    const int blocks = (int)((n_vec + 255) / 256 < 65536 ? (n_vec + 255) / 256 : 65536);
     if (mlp == OB_SWIGLU)
-        hipLaunchKernelGGL(act_fwd_kernel<true>, dim3(blocks), dim3(256), 0, s, (const __bf16 *)up,
-                           (__bf16 *)act, n_vec, F);
+        hipLaunchKernelGGL(swiglu_fwd_kernel, dim3(act_blocks(n_vec, 256)), dim3(256), 0, s, (const __bf16 *)up, (__bf16 *)act, T, F);
     else
-        hipLaunchKernelGGL(act_fwd_kernel<false>, dim3(blocks), dim3(256), 0, s, (const __bf16 *)up,
-                           (__bf16 *)act, n_vec, F);
+        hipLaunchKernelGGL(gelu_fwd_kernel, dim3(act_blocks(n_vec, GELU_VECS)), dim3(256), 0, s, (const __bf16 *)up, (__bf16 *)act, n_vec);
 }
 
 void launch_act_bwd(int mlp, const void *dact, const void *up, void *dup, int T, int F, hipStream_t s) {
     ProfScope prof(K_ACT_BWD, s, (mlp == OB_SWIGLU ? 10.0 : 6.0) * T * F);
     const long n_vec = (long)T * (F / 8);
-    const int blocks = (int)((n_vec + 255) / 256 < 65536 ? (n_vec + 255) / 256 : 65536);
     if (mlp == OB_SWIGLU)
-        hipLaunchKernelGGL(act_bwd_kernel<true>, dim3(blocks), dim3(256), 0, s, (const __bf16 *)dact,
-                           (const __bf16 *)up, (__bf16 *)dup, n_vec, F);
+        hipLaunchKernelGGL(swiglu_bwd_kernel, dim3(act_blocks(n_vec, 256)), dim3(256), 0, s, (const __bf16 *)dact,
+                           (const __bf16 *)up, (__bf16 *)dup, T, F);
     else
-        hipLaunchKernelGGL(act_bwd_kernel<false>, dim3(blocks), dim3(256), 0, s, (const __bf16 *)dact,
-                           (const __bf16 *)up, (__bf16 *)dup, n_vec, F);
+        hipLaunchKernelGGL(gelu_bwd_kernel, dim3(act_blocks(n_vec, GELU_VECS)), dim3(256), 0, s, (const __bf16 *)dact,
+                           (const __bf16 *)up, (__bf16 *)dup, n_vec);
 }
 
 void launch_mask(const int32_t *cu_dev, int n_seg, int T, int mask, uint8_t *out, hipStream_t s) {
