@@ -12,28 +12,16 @@
 namespace ob {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 namespace {
 
 constexpr int THREADS = 256;
-constexpr int MAX_VEC = 8;  // 8-element vectors per thread: 4 Hv <= 256 * 8 * 8 = 16384
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
     return v;
-}
-
-__device__ __forceinline__ float block_sum(float v, float *red) {
-    v = wave_sum(v);
-    const int wave = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[wave] = v;
-    __syncthreads();
-    float t = 0.f;
-#pragma unroll
-    for (int w = 0; w < THREADS / 64; ++w) t += red[w];
-    return t;
 }
 
 // first ViT row (patch (2r, 2c)) behind sub-sampled token i
@@ -50,124 +38,190 @@ __device__ __forceinline__ size_t gather_offset(long row0, int c8, int g, int Hv
     return (size_t)(row0 + (b >> 1) * g + (b & 1)) * Hv + off;
 }
 
+// The row kernels below: persistent workgroups of WG threads, split into G groups of S threads that each own a token
+// at a time, NV vectors of 8 channels per thread.  A token's loads are issued one token ahead, so that the barriers of
+// the row sums (one per sum: the LDS words alternate) never leave the memory pipe empty.
+// (WG, S, NV): (1024, 256, 2) for rows of up to 4096 channels; wider ones take four vectors per thread and 512 threads,
+// (512, 256, 4) to 8192 and (512, 512, 4) to 16384, so that the backward's column sums fit 256 registers (with 1024
+// threads and two vectors it spilled 60: 463 us for 10752 x 12800).
+
+// sums of a (and b) over the S threads of the caller's group; `red` alternates between two halves
+template <int WG, int S>
+__device__ __forceinline__ float2 group_sum(float a, float b, float2 *__restrict__ red, int &half) {
+    a = wave_sum(a);
+    b = wave_sum(b);
+    const int wave = threadIdx.x >> 6, first = (threadIdx.x / S) * (S / 64);
+    float2 *r = red + half * (WG / 64);
+    half ^= 1;
+    if ((threadIdx.x & 63) == 0) r[wave] = make_float2(a, b);
+    __syncthreads();
+    float2 t = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < S / 64; ++w) { t.x += r[first + w].x; t.y += r[first + w].y; }
+    return t;
+}
+
 // un[i] = LayerNorm(gather(v, i)) * gamma + beta;  stats[i] = (mean, rstd)
-__global__ __launch_bounds__(THREADS) void subsample_norm_fwd_kernel(
+template <int WG, int S, int NV>
+__global__ __launch_bounds__(WG) void subsample_norm_fwd_kernel(
     const __bf16 *__restrict__ v, const __bf16 *__restrict__ gamma, const __bf16 *__restrict__ beta,
-    __bf16 *__restrict__ un, float *__restrict__ stats, int g, int Hv, float eps) {
-    __shared__ float red[THREADS / 64];
-    const int i = blockIdx.x, W = 4 * Hv, nvec = W / 8;
-    const long row0 = first_patch_row(i, g);
-    float x[MAX_VEC][8];
-    float s = 0.f;
+    __bf16 *__restrict__ un, float *__restrict__ stats, int n_tok, int g, int Hv, float eps) {
+    constexpr int G = WG / S;
+    __shared__ float2 red[2 * (WG / 64)];
+    const int W = 4 * Hv, nvec = W / 8, lane = threadIdx.x % S, stride = gridDim.x * G;
+    bf16x8 gm[NV], bt[NV], nx[NV];
+    int src[NV];                            // offset of this thread's channels from the token's first patch row
 #pragma unroll
-    for (int k = 0; k < MAX_VEC; ++k) {
-        const int c8 = threadIdx.x + k * THREADS;
-        if (c8 < nvec) {
-            const bf16x8 t = *(const bf16x8 *)(v + gather_offset(row0, c8, g, Hv));
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { x[k][e] = (float)t[e]; s += x[k][e]; }
-        }
+    for (int k = 0; k < NV; ++k) {
+        const int c8 = lane + k * S;
+        gm[k] = c8 < nvec ? *(const bf16x8 *)(gamma + c8 * 8) : bf16x8{};
+        bt[k] = c8 < nvec ? *(const bf16x8 *)(beta + c8 * 8) : bf16x8{};
+        src[k] = c8 < nvec ? (int)gather_offset(0, c8, g, Hv) : -1;
+        nx[k] = bf16x8{};
     }
-    const float mean = block_sum(s, red) / W;
-    float q = 0.f;
+    auto fetch = [&](int i) {
+        const __bf16 *row = v + (size_t)first_patch_row(i, g) * Hv;
 #pragma unroll
-    for (int k = 0; k < MAX_VEC; ++k) {
-        const int c8 = threadIdx.x + k * THREADS;
-        if (c8 < nvec) {
+        for (int k = 0; k < NV; ++k)
+            if (src[k] >= 0) nx[k] = *(const bf16x8 *)(row + src[k]);
+    };
+    int half = 0, i = blockIdx.x * G + threadIdx.x / S;
+    if (i < n_tok) fetch(i);
+    for (int first = blockIdx.x * G; first < n_tok; first += stride, i += stride) {   // (same trip count for every thread)
+        float x[NV][8], s = 0.f, q = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { const float d = x[k][e] - mean; q += d * d; }
+        for (int k = 0; k < NV; ++k)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { x[k][e] = (float)nx[k][e]; s += x[k][e]; }
+        if (i + stride < n_tok) fetch(i + stride);
+        const float mean = group_sum<WG, S>(s, 0.f, red, half).x / W;
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            if (src[k] >= 0) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { const float d = x[k][e] - mean; q += d * d; }
+            }
+        const float rstd = rsqrtf(group_sum<WG, S>(q, 0.f, red, half).x / W + eps);
+        if (i >= n_tok) continue;
+        if (lane == 0) {
+            stats[2 * (size_t)i] = mean;
+            stats[2 * (size_t)i + 1] = rstd;
         }
-    }
-    const float rstd = rsqrtf(block_sum(q, red) / W + eps);
-    if (threadIdx.x == 0) {
-        stats[2 * (size_t)i] = mean;
-        stats[2 * (size_t)i + 1] = rstd;
-    }
 #pragma unroll
-    for (int k = 0; k < MAX_VEC; ++k) {
-        const int c8 = threadIdx.x + k * THREADS;
-        if (c8 < nvec) {
-            const bf16x8 gm = *(const bf16x8 *)(gamma + c8 * 8), bt = *(const bf16x8 *)(beta + c8 * 8);
-            bf16x8 o;
+        for (int k = 0; k < NV; ++k)
+            if (src[k] >= 0) {
+                bf16x8 o;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (__bf16)((x[k][e] - mean) * rstd * (float)gm[e] + (float)bt[e]);
-            *(bf16x8 *)(un + (size_t)i * W + c8 * 8) = o;
-        }
+                for (int e = 0; e < 8; ++e) o[e] = (__bf16)((x[k][e] - mean) * rstd * (float)gm[k][e] + (float)bt[k][e]);
+                *(bf16x8 *)(un + (size_t)i * W + (lane + k * S) * 8) = o;
+            }
     }
 }
 
-// Blocks [0, n_tok): du = LayerNorm backward of dun at sub-sampled token i, written to the four
-// patch rows of dv it was gathered from.  Blocks [n_tok, n_tok + n_tiles): zero the class row
-// of a tile (it feeds nothing).  Together they write every element of dv exactly once.
-__global__ __launch_bounds__(THREADS) void subsample_norm_bwd_kernel(
+// du = LayerNorm backward of dun at a sub-sampled token, written to the four patch rows of dv it was gathered from; the
+// class row of every tile is zeroed (it feeds nothing): together every element of dv is written exactly once.  Each
+// group keeps its column sums of dun * xhat (gain) and dun (beta) in registers; the workgroup's groups are added through
+// LDS, in order, into partial[blockIdx.x][2][W].  (A kernel of its own for the column sums read dun and v again.)
+template <int WG, int S, int NV>
+__global__ __launch_bounds__(WG) void subsample_norm_bwd_kernel(
     const __bf16 *__restrict__ dun, const __bf16 *__restrict__ v, const float *__restrict__ stats,
-    const __bf16 *__restrict__ gamma, __bf16 *__restrict__ dv, int n_tok, int g, int Hv) {
-    __shared__ float red[THREADS / 64];
-    const int W = 4 * Hv, nvec = W / 8;
-    if ((int)blockIdx.x >= n_tok) {
-        const size_t row = (size_t)(blockIdx.x - n_tok) * (g * g + 1);
-        bf16x8 z;
+    const __bf16 *__restrict__ gamma, __bf16 *__restrict__ dv, float *__restrict__ partial, int n_tok, int n_tiles, int g,
+    int Hv) {
+    constexpr int G = WG / S;
+    __shared__ float2 red[2 * (WG / 64)];
+    __shared__ __attribute__((aligned(16))) float fold[G > 1 ? WG * NV * 8 : 4];
+    const int W = 4 * Hv, nvec = W / 8, lane = threadIdx.x % S, group = threadIdx.x / S, stride = gridDim.x * G;
+    const bf16x8 zero{};
+    for (int t = blockIdx.x; t < n_tiles; t += gridDim.x)
+        for (int c8 = threadIdx.x; c8 < Hv / 8; c8 += WG) *(bf16x8 *)(dv + (size_t)t * (g * g + 1) * Hv + c8 * 8) = zero;
+    bf16x8 gm[NV], nx[NV], nd[NV];
+    float dg[NV][8], db[NV][8], nmean = 0.f, nrstd = 0.f;
+    int src[NV];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) z[e] = (__bf16)0.f;
-        for (int c8 = threadIdx.x; c8 < Hv / 8; c8 += THREADS) *(bf16x8 *)(dv + row * Hv + c8 * 8) = z;
-        return;
+    for (int k = 0; k < NV; ++k) {
+        const int c8 = lane + k * S;
+        gm[k] = c8 < nvec ? *(const bf16x8 *)(gamma + c8 * 8) : zero;
+        src[k] = c8 < nvec ? (int)gather_offset(0, c8, g, Hv) : -1;
+        nx[k] = nd[k] = zero;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dg[k][e] = db[k][e] = 0.f;
     }
-    const int i = blockIdx.x;
-    const long row0 = first_patch_row(i, g);
-    const float mean = stats[2 * (size_t)i], rstd = stats[2 * (size_t)i + 1];
-    float xh[MAX_VEC][8], dxh[MAX_VEC][8];
-    float s1 = 0.f, s2 = 0.f;
+    auto fetch = [&](int i) {
+        const __bf16 *row = v + (size_t)first_patch_row(i, g) * Hv;
+        nmean = stats[2 * (size_t)i];
+        nrstd = stats[2 * (size_t)i + 1];
 #pragma unroll
-    for (int k = 0; k < MAX_VEC; ++k) {
-        const int c8 = threadIdx.x + k * THREADS;
-        if (c8 < nvec) {
-            const bf16x8 t = *(const bf16x8 *)(v + gather_offset(row0, c8, g, Hv));
-            const bf16x8 d = *(const bf16x8 *)(dun + (size_t)i * W + c8 * 8);
-            const bf16x8 gm = *(const bf16x8 *)(gamma + c8 * 8);
+        for (int k = 0; k < NV; ++k)
+            if (src[k] >= 0) {
+                nx[k] = *(const bf16x8 *)(row + src[k]);
+                nd[k] = *(const bf16x8 *)(dun + (size_t)i * W + (lane + k * S) * 8);
+            }
+    };
+    int half = 0, i = blockIdx.x * G + group;
+    if (i < n_tok) fetch(i);
+    for (int first = blockIdx.x * G; first < n_tok; first += stride, i += stride) {
+        const bool live = i < n_tok;
+        const float mean = nmean, rstd = nrstd;
+        bf16x8 tx[NV], td[NV];
+        float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                xh[k][e] = ((float)t[e] - mean) * rstd;
-                dxh[k][e] = (float)d[e] * (float)gm[e];
-                s1 += dxh[k][e];
-                s2 += dxh[k][e] * xh[k][e];
+        for (int k = 0; k < NV; ++k) { tx[k] = nx[k]; td[k] = nd[k]; }
+        if (i + stride < n_tok) fetch(i + stride);
+        if (live) {
+#pragma unroll
+            for (int k = 0; k < NV; ++k)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {       // (threads past the row hold zeros: dun = 0 adds nothing)
+                    const float d = (float)td[k][e], xh = ((float)tx[k][e] - mean) * rstd, dxh = d * (float)gm[k][e];
+                    dg[k][e] += d * xh;
+                    db[k][e] += d;
+                    s1 += dxh;
+                    s2 += dxh * xh;
+                }
+        }
+        const float2 sum = group_sum<WG, S>(s1, s2, red, half);
+        if (!live) continue;
+        const float m1 = sum.x / W, m2 = sum.y / W;
+        __bf16 *out = dv + (size_t)first_patch_row(i, g) * Hv;
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            if (src[k] >= 0) {
+                bf16x8 o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float xh = ((float)tx[k][e] - mean) * rstd, dxh = (float)td[k][e] * (float)gm[k][e];
+                    o[e] = (__bf16)(rstd * (dxh - m1 - xh * m2));
+                }
+                *(bf16x8 *)(out + src[k]) = o;
+            }
+    }
+    auto write = [&](const float (&a)[NV][8], float *__restrict__ dst) {
+        if constexpr (G == 1) {
+#pragma unroll
+            for (int k = 0; k < NV; ++k)
+                if (src[k] >= 0) {
+                    *(f32x4 *)(dst + (lane + k * S) * 8) = f32x4{a[k][0], a[k][1], a[k][2], a[k][3]};
+                    *(f32x4 *)(dst + (lane + k * S) * 8 + 4) = f32x4{a[k][4], a[k][5], a[k][6], a[k][7]};
+                }
+        } else {
+            constexpr int ROW = S * NV * 8;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                *(f32x4 *)(fold + group * ROW + (lane + k * S) * 8) = f32x4{a[k][0], a[k][1], a[k][2], a[k][3]};
+                *(f32x4 *)(fold + group * ROW + (lane + k * S) * 8 + 4) = f32x4{a[k][4], a[k][5], a[k][6], a[k][7]};
+            }
+            __syncthreads();
+            for (int c = threadIdx.x; c < W; c += WG) {
+                float t = fold[c];
+#pragma unroll
+                for (int j = 1; j < G; ++j) t += fold[j * ROW + c];
+                dst[c] = t;
             }
         }
-    }
-    s1 = block_sum(s1, red) / W;
-    s2 = block_sum(s2, red) / W;
-#pragma unroll
-    for (int k = 0; k < MAX_VEC; ++k) {
-        const int c8 = threadIdx.x + k * THREADS;
-        if (c8 < nvec) {
-            bf16x8 o;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (__bf16)(rstd * (dxh[k][e] - s1 - xh[k][e] * s2));
-            *(bf16x8 *)(dv + gather_offset(row0, c8, g, Hv)) = o;
-        }
-    }
-}
-
-// partial[blockIdx.y][0][c] = sum over tokens blockIdx.y, +gridDim.y, ... of dun * xhat (gain),
-// partial[blockIdx.y][1][c] = the same sum of dun (beta); reduce_partials sums over blockIdx.y.
-__global__ __launch_bounds__(THREADS) void subsample_norm_wgrad_kernel(
-    const __bf16 *__restrict__ dun, const __bf16 *__restrict__ v, const float *__restrict__ stats,
-    float *__restrict__ partial, int n_tok, int g, int Hv) {
-    const int W = 4 * Hv, c8 = blockIdx.x * THREADS + threadIdx.x;
-    if (c8 * 8 >= W) return;
-    float dg[8] = {0, 0, 0, 0, 0, 0, 0, 0}, db[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int i = blockIdx.y; i < n_tok; i += gridDim.y) {
-        const float mean = stats[2 * (size_t)i], rstd = stats[2 * (size_t)i + 1];
-        const bf16x8 t = *(const bf16x8 *)(v + gather_offset(first_patch_row(i, g), c8, g, Hv));
-        const bf16x8 d = *(const bf16x8 *)(dun + (size_t)i * W + c8 * 8);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            dg[e] += (float)d[e] * (((float)t[e] - mean) * rstd);
-            db[e] += (float)d[e];
-        }
-    }
-    float *p = partial + (size_t)blockIdx.y * 2 * W + c8 * 8;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { p[e] = dg[e]; p[W + e] = db[e]; }
+    };
+    write(dg, partial + (size_t)blockIdx.x * 2 * W);
+    write(db, partial + (size_t)blockIdx.x * 2 * W + W);
 }
 
 // SCATTER: big[rows[i]] = small[i];  otherwise small[i] = big[rows[i]].  One workgroup per row.
@@ -183,31 +237,38 @@ __global__ __launch_bounds__(THREADS) void rows_copy_kernel(__bf16 *__restrict__
 
 }  // namespace
 
-int subsample_max_width() { return THREADS * 8 * MAX_VEC; }
+int subsample_max_width() { return 16384; }
+
+// workgroups that there are tokens for
+static int token_groups(int n_tok, int Hv) { return Hv <= 1024 ? (n_tok + 3) / 4 : Hv <= 2048 ? (n_tok + 1) / 2 : n_tok; }
+#define OB_BY_WIDTH(KERNEL, GRID, ...)                                                                          \
+    do {                                                                                                        \
+        if (Hv <= 1024) hipLaunchKernelGGL((KERNEL<1024, 256, 2>), GRID, dim3(1024), 0, s, __VA_ARGS__);         \
+        else if (Hv <= 2048) hipLaunchKernelGGL((KERNEL<512, 256, 4>), GRID, dim3(512), 0, s, __VA_ARGS__);      \
+        else hipLaunchKernelGGL((KERNEL<512, 512, 4>), GRID, dim3(512), 0, s, __VA_ARGS__);                      \
+    } while (0)
 
 void launch_subsample_norm_fwd(const void *v, const void *gamma, const void *beta, void *un, float *stats,
                                int n_tok, int g, int Hv, float eps, hipStream_t s) {
     ProfScope prof(K_CONN_FWD, s, 16.0 * n_tok * Hv);   // 4 Hv bf16 in, 4 Hv bf16 out
-    hipLaunchKernelGGL(subsample_norm_fwd_kernel, dim3(n_tok), dim3(THREADS), 0, s, (const __bf16 *)v,
-                       (const __bf16 *)gamma, (const __bf16 *)beta, (__bf16 *)un, stats, g, Hv, eps);
-}
-
-void launch_subsample_norm_bwd(const void *dun, const void *v, const float *stats, const void *gamma, void *dv,
-                               int n_tok, int n_tiles, int g, int Hv, hipStream_t s) {
-    ProfScope prof(K_CONN_BWD, s, 24.0 * n_tok * Hv);   // dun and v in, dv out
-    hipLaunchKernelGGL(subsample_norm_bwd_kernel, dim3(n_tok + n_tiles), dim3(THREADS), 0, s, (const __bf16 *)dun,
-                       (const __bf16 *)v, stats, (const __bf16 *)gamma, (__bf16 *)dv, n_tok, g, Hv);
+    const int wgs = token_groups(n_tok, Hv);
+    OB_BY_WIDTH(subsample_norm_fwd_kernel, dim3(wgs < 512 ? wgs : 512), (const __bf16 *)v, (const __bf16 *)gamma,
+                (const __bf16 *)beta, (__bf16 *)un, stats, n_tok, g, Hv, eps);
 }
 
 int subsample_wgrad_partials(int n_tok) { return n_tok < 64 ? n_tok : 64; }
 
-void launch_subsample_norm_wgrad(const void *dun, const void *v, const float *stats, float *partial, int n_tok,
-                                 int g, int Hv, hipStream_t s) {
-    ProfScope prof(K_CONN_BWD, s, 16.0 * n_tok * Hv);
-    const int W = 4 * Hv;
-    hipLaunchKernelGGL(subsample_norm_wgrad_kernel, dim3((W / 8 + THREADS - 1) / THREADS, subsample_wgrad_partials(n_tok)),
-                       dim3(THREADS), 0, s, (const __bf16 *)dun, (const __bf16 *)v, stats, partial, n_tok, g, Hv);
+int launch_subsample_norm_bwd_wgrad(const void *dun, const void *v, const float *stats, const void *gamma, void *dv,
+                                    float *partial, int max_partials, int n_tok, int n_tiles, int g, int Hv, hipStream_t s) {
+    ProfScope prof(K_CONN_BWD, s, 24.0 * n_tok * Hv);   // dun and v in, dv out
+    int wgs = token_groups(n_tok, Hv);
+    if (wgs > 256) wgs = 256;
+    if (wgs > max_partials) wgs = max_partials;
+    OB_BY_WIDTH(subsample_norm_bwd_kernel, dim3(wgs), (const __bf16 *)dun, (const __bf16 *)v, stats, (const __bf16 *)gamma,
+                (__bf16 *)dv, partial, n_tok, n_tiles, g, Hv);
+    return wgs;
 }
+#undef OB_BY_WIDTH
 
 void launch_rows_scatter(const void *small, void *big, const int32_t *rows_dev, int n_rows, int H, hipStream_t s) {
     ProfScope prof(K_ROWS, s, 4.0 * n_rows * H);

@@ -17,7 +17,7 @@ struct Bump {
     size_t take(size_t bytes) { const size_t o = off; off += align_up(bytes, 256); return o; }
 };
 struct CSaved { size_t un, h, a, stats, total; };
-struct CWork { size_t z, da, dh, dun, partial, gemm, gemm_bytes, total; };
+struct CWork { size_t z, da, da_bytes, dh, dun, partial, partial_bytes, gemm, gemm_bytes, total; };
 
 CSaved saved_layout(const CDims &m) {
     Bump L; CSaved s; const size_t n = m.n_tok;
@@ -28,10 +28,12 @@ CSaved saved_layout(const CDims &m) {
 CWork work_layout(const CDims &m) {
     Bump L; CWork w; const size_t n = m.n_tok;
     w.z = L.take(n * m.Ht * 2);      // z in the forward, dz in the backward
-    w.da = L.take(n * m.Ht * 2); w.dh = L.take(n * m.Ht * 2); w.dun = L.take(n * m.W * 2);
+    w.da_bytes = n * m.Ht * 2;
+    w.da = L.take(w.da_bytes); w.dh = L.take(n * m.Ht * 2); w.dun = L.take(n * m.W * 2);
     const size_t p_norm = (size_t)subsample_wgrad_partials(m.n_tok) * 2 * m.W * 4;
     const size_t p_bias = (size_t)colsum_partials(m.n_tok) * m.Ht * 4;
-    w.partial = L.take(p_norm > p_bias ? p_norm : p_bias);
+    w.partial_bytes = p_norm > p_bias ? p_norm : p_bias;
+    w.partial = L.take(w.partial_bytes);
     // slice sums of the GEMMs whose last round of tiles is split along K
     size_t g = 0;
     const int shapes[6][4] = {{0, m.n_tok, m.Ht, m.W}, {0, m.n_tok, m.Ht, m.Ht}, {2, m.Ht, m.Ht, m.n_tok},
@@ -165,20 +167,34 @@ extern "C" int ob_connector_bwd(const ob_connector_desc *desc, const ob_connecto
     launch_rows_gather(dz, dx_llm, dst_rows_dev, m.n_tok, m.Ht, s);
     // z = a W2^T + b2
     if ((rc = gemm_any(2, m.Ht, m.Ht, m.n_tok, dz, a, g->w2, nullptr, acc ? g->w2 : nullptr, gws, wk.gemm_bytes, s))) return rc;
-    launch_colsum(dz, m.n_tok, m.Ht, m.Ht, partial, s);
-    launch_reduce_partials(partial, ncs, m.Ht, g->b2, m.Ht, acc, s);
     if ((rc = gemm_any(1, m.n_tok, m.Ht, m.Ht, dz, w->w2, da, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
     // a = GELU(h), h = un W1^T + b1
     launch_act_bwd(OB_GELU, da, h, dh, m.n_tok, m.Ht, s);
     if ((rc = gemm_any(2, m.Ht, m.W, m.n_tok, dh, un, g->w1, nullptr, acc ? g->w1 : nullptr, gws, wk.gemm_bytes, s))) return rc;
-    launch_colsum(dh, m.n_tok, m.Ht, m.Ht, partial, s);
-    launch_reduce_partials(partial, ncs, m.Ht, g->b1, m.Ht, acc, s);
     if ((rc = gemm_any(1, m.n_tok, m.W, m.Ht, dh, w->w1, dun, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
-    // un = LayerNorm(gather(v))
-    launch_subsample_norm_bwd(dun, v, stats, w->n_g, dv, m.n_tok, m.n_tiles, m.g, m.Hv, s);
-    launch_subsample_norm_wgrad(dun, v, stats, partial, m.n_tok, m.g, m.Hv, s);
-    const int nwp = subsample_wgrad_partials(m.n_tok);
-    launch_reduce_partials(partial, nwp, 2 * m.W, g->n_g, m.W, acc, s);
-    launch_reduce_partials(partial + m.W, nwp, 2 * m.W, g->n_b, m.W, acc, s);
+    // un = LayerNorm(gather(v)), and the column reductions: b2 and b1 over dz and dh, gain and beta by the norm's backward.
+    // Their partial sums lie in the region laid out for them and in that of da, which nothing needs any more: the
+    // norm's, which want up to 256 rows of 2 W, in the roomier one, the bias sums in the other, and one launch
+    // adds them all.  Below 256 tokens (a grid of a few patches) neither has room for that: one after the other.
+    const size_t room[2] = {wk.da_bytes, wk.partial_bytes}, norm_row = (size_t)2 * m.W * 4;
+    float *const region[2] = {(float *)da, partial};
+    const int at_norm = m.n_tok >= 256 && room[0] > room[1] ? 0 : 1, at_bias = 1 - at_norm;
+    ReduceBatch sums;
+    if (m.n_tok >= 256) {
+        const int fits = (int)(room[at_bias] / ((size_t)2 * m.Ht * 4)), n = ncs < fits ? ncs : fits;
+        launch_colsum_pair(dz, dh, m.n_tok, m.Ht, n, region[at_bias], s);
+        sums.add(region[at_bias], n, m.Ht, g->b2, m.Ht);
+        sums.add(region[at_bias] + (size_t)n * m.Ht, n, m.Ht, g->b1, m.Ht);
+    } else {
+        launch_colsum(dz, m.n_tok, m.Ht, m.Ht, partial, s);
+        launch_reduce_partials(partial, ncs, m.Ht, g->b2, m.Ht, acc, s);
+        launch_colsum(dh, m.n_tok, m.Ht, m.Ht, partial, s);
+        launch_reduce_partials(partial, ncs, m.Ht, g->b1, m.Ht, acc, s);
+    }
+    const int n_norm = launch_subsample_norm_bwd_wgrad(dun, v, stats, w->n_g, dv, region[at_norm], (int)(room[at_norm] / norm_row),
+                                                       m.n_tok, m.n_tiles, m.g, m.Hv, s);
+    sums.add(region[at_norm], n_norm, 2 * m.W, g->n_g, m.W);
+    sums.add(region[at_norm] + m.W, n_norm, 2 * m.W, g->n_b, m.W);
+    if ((rc = launch_reduce_batch(sums, acc, s))) return rc;
     return check_launch(who);
 }

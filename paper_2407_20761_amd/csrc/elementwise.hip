@@ -469,9 +469,10 @@ __global__ __launch_bounds__(REDUCE_THREADS) void reduce_batch_kernel(ReduceBatc
     reduce_columns(j.partial, j.n_part, j.stride, (__bf16 *)j.out, j.C, accumulate);
 }
 
-// partial[blockIdx.y][c] = sum over the rows blockIdx.y, +gridDim.y, ... of in[row][c]
-__global__ __launch_bounds__(256) void colsum_kernel(const __bf16 *__restrict__ in, int T, int C,
+// partial[blockIdx.z][blockIdx.y][c] = sum over the rows blockIdx.y, +gridDim.y, ... of in[row][c], in = in0 or in1
+__global__ __launch_bounds__(256) void colsum_kernel(const __bf16 *__restrict__ in0, const __bf16 *__restrict__ in1, int T, int C,
                                                      int ld, float *__restrict__ partial) {
+    const __bf16 *in = blockIdx.z ? in1 : in0;
     const int c8 = blockIdx.x * 256 + threadIdx.x;  // 8-column vector index
     if (c8 * 8 >= C) return;
     float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -493,7 +494,7 @@ __global__ __launch_bounds__(256) void colsum_kernel(const __bf16 *__restrict__ 
 #pragma unroll
         for (int e = 0; e < 8; ++e) s[e] += (float)t[e];
     }
-    float *dst = partial + (size_t)blockIdx.y * C + c8 * 8;
+    float *dst = partial + ((size_t)blockIdx.z * g + blockIdx.y) * C + c8 * 8;
     *(f32x4 *)dst = f32x4{s[0], s[1], s[2], s[3]};
     *(f32x4 *)(dst + 4) = f32x4{s[4], s[5], s[6], s[7]};
 }
@@ -788,7 +789,13 @@ int colsum_partials(int T) { return T < 256 ? T : 256; }
 void launch_colsum(const void *in, int T, int C, int ld, float *partial, hipStream_t s) {
     ProfScope prof(K_COLSUM, s, 2.0 * T * C);
     dim3 grid((C / 8 + 255) / 256, colsum_partials(T));
-    hipLaunchKernelGGL(colsum_kernel, grid, dim3(256), 0, s, (const __bf16 *)in, T, C, ld, partial);
+    hipLaunchKernelGGL(colsum_kernel, grid, dim3(256), 0, s, (const __bf16 *)in, (const __bf16 *)nullptr, T, C, ld, partial);
+}
+
+void launch_colsum_pair(const void *in0, const void *in1, int T, int C, int n_part, float *partial, hipStream_t s) {
+    ProfScope prof(K_COLSUM, s, 4.0 * T * C);
+    dim3 grid((C / 8 + 255) / 256, n_part, 2);
+    hipLaunchKernelGGL(colsum_kernel, grid, dim3(256), 0, s, (const __bf16 *)in0, (const __bf16 *)in1, T, C, C, partial);
 }
 
 void launch_rotary(void *qkv, int ld, int T, int n_heads_rot, int d, const int32_t *cu_dev, int n_seg,

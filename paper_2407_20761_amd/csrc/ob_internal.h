@@ -79,6 +79,8 @@ struct ReduceBatch {
 int launch_reduce_batch(const ReduceBatch &b, int accumulate, hipStream_t s);
 int colsum_partials(int T);
 void launch_colsum(const void *in, int T, int C, int ld, float *partial, hipStream_t s);
+// partial [2][n_part][C]: the column sums of in0 and of in1, dense rows of C elements
+void launch_colsum_pair(const void *in0, const void *in1, int T, int C, int n_part, float *partial, hipStream_t s);
 void launch_rotary(void *qkv, int ld, int T, int n_heads_rot, int d, const int32_t *cu_dev,
                    int n_seg, float base, float sign, hipStream_t s);
 void launch_act_fwd(int mlp, const void *up, void *act, int T, int F, hipStream_t s);
@@ -91,13 +93,11 @@ void launch_mask(const int32_t *cu_dev, int n_seg, int T, int mask, uint8_t *out
 int subsample_max_width();
 void launch_subsample_norm_fwd(const void *v, const void *gamma, const void *beta, void *un, float *stats,
                                int n_tok, int g, int Hv, float eps, hipStream_t s);
-// writes every row of dv [n_tiles (g^2 + 1), Hv] (class rows: zeros)
-void launch_subsample_norm_bwd(const void *dun, const void *v, const float *stats, const void *gamma, void *dv,
-                               int n_tok, int n_tiles, int g, int Hv, hipStream_t s);
-// partial [subsample_wgrad_partials(n_tok)][2][4 Hv] fp32: gain sums, then beta sums
-int subsample_wgrad_partials(int n_tok);
-void launch_subsample_norm_wgrad(const void *dun, const void *v, const float *stats, float *partial, int n_tok,
-                                 int g, int Hv, hipStream_t s);
+// writes every row of dv [n_tiles (g^2 + 1), Hv] (class rows: zeros) and partial [n][2][4 Hv] fp32, gain sums then beta
+// sums; returns n <= max_partials
+int launch_subsample_norm_bwd_wgrad(const void *dun, const void *v, const float *stats, const void *gamma, void *dv,
+                                    float *partial, int max_partials, int n_tok, int n_tiles, int g, int Hv, hipStream_t s);
+int subsample_wgrad_partials(int n_tok);   // rows of partial sums that the workspace has a region of its own for
 // big[rows[i]] = small[i]  /  small[i] = big[rows[i]];  rows of H bf16 elements, H % 8 == 0
 void launch_rows_scatter(const void *small, void *big, const int32_t *rows_dev, int n_rows, int H, hipStream_t s);
 void launch_rows_gather(void *small, const void *big, const int32_t *rows_dev, int n_rows, int H, hipStream_t s);

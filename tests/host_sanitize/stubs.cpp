@@ -29,15 +29,16 @@ void launch_reduce_partials(const float *, int, int, void *, int, int, hipStream
 int launch_reduce_batch(const ReduceBatch &, int, hipStream_t) { OB_STUB("launch_reduce_batch"); }
 int colsum_partials(int T) { return T < 256 ? T : 256; }
 void launch_colsum(const void *, int, int, int, float *, hipStream_t) { OB_STUB("launch_colsum"); }
+void launch_colsum_pair(const void *, const void *, int, int, int, float *, hipStream_t) { OB_STUB("launch_colsum_pair"); }
 void launch_rotary(void *, int, int, int, int, const int32_t *, int, float, float, hipStream_t) { OB_STUB("launch_rotary"); }
 void launch_act_fwd(int, const void *, void *, int, int, hipStream_t) { OB_STUB("launch_act_fwd"); }
 void launch_act_bwd(int, const void *, const void *, void *, int, int, hipStream_t) { OB_STUB("launch_act_bwd"); }
 void launch_mask(const int32_t *, int, int, int, uint8_t *, hipStream_t) { OB_STUB("launch_mask"); }
 int subsample_max_width() { return 16384; }
 void launch_subsample_norm_fwd(const void *, const void *, const void *, void *, float *, int, int, int, float, hipStream_t) { OB_STUB("launch_subsample_norm_fwd"); }
-void launch_subsample_norm_bwd(const void *, const void *, const float *, const void *, void *, int, int, int, int, hipStream_t) { OB_STUB("launch_subsample_norm_bwd"); }
+int launch_subsample_norm_bwd_wgrad(const void *, const void *, const float *, const void *, void *, float *, int, int, int, int,
+                                    int, hipStream_t) { OB_STUB("launch_subsample_norm_bwd_wgrad"); }
 int subsample_wgrad_partials(int n_tok) { return n_tok < 256 ? n_tok : 256; }
-void launch_subsample_norm_wgrad(const void *, const void *, const float *, float *, int, int, int, hipStream_t) { OB_STUB("launch_subsample_norm_wgrad"); }
 void launch_rows_scatter(const void *, void *, const int32_t *, int, int, hipStream_t) { OB_STUB("launch_rows_scatter"); }
 void launch_rows_gather(void *, const void *, const int32_t *, int, int, hipStream_t) { OB_STUB("launch_rows_gather"); }
 void launch_attn_fwd(const void *, const void *, const void *, void *, float *, int, int, int, const ob_segments *, int,

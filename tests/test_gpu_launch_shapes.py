@@ -8,6 +8,7 @@ import paper_2407_20761_amd as ob
 import synth_inputs as si
 from gpu_util import bytes_buf, to_dev, to_np
 from oracle import block as orc
+from oracle import connector as orc_conn
 
 pytestmark = pytest.mark.gpu
 
@@ -95,3 +96,32 @@ def test_gemm_fine_tiles(layout, M, N, K):
         C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
         ob.ob_gemm_bf16(layout, M, N, K, a_dev, b_dev, C, None, to_dev(R), ws)
         assert np.abs(to_np(C) - ref).max() <= 2.0 ** -8 * np.abs(ref).max(), ws is not None
+
+
+@pytest.mark.parametrize("Hv,Ht,grid,tiles", [(64, 128, 2, 3), (1024, 64, 32, 1), (1088, 128, 16, 5), (2048, 64, 16, 4), (2112, 64, 32, 2),
+                                              (4096, 64, 18, 3)])
+def test_connector_widths(Hv, Ht, grid, tiles):
+    """The hand-over's row kernels at the widths where their launch shape changes, with token counts that leave groups and
+    workgroups without a token, and few enough (81 and less) or enough for the one launch of all column sums."""
+    print(f"connector widths {Hv} {Ht} {grid} {tiles}", flush=True)
+    rng = np.random.default_rng(Hv + grid)
+    n_tok, rows_v = tiles * (grid // 2) ** 2, tiles * (grid * grid + 1)
+    w = si.connector_weights(Hv, Ht, seed=1)
+    v = si.round_to_bf16(rng.standard_normal((rows_v, Hv), dtype=np.float32))
+    llm = n_tok + 7
+    dst = rng.permutation(llm)[:n_tok].astype(np.int32)
+    dx = si.round_to_bf16(rng.standard_normal((llm, Ht), dtype=np.float32))
+    desc = ob.make_connector_desc(Hv, Ht, grid, 1e-5)
+    wd = {n: to_dev(t) for n, t in w.items()}
+    gd = {n: torch.full_like(t, float("nan")) for n, t in wd.items()}
+    vd, dv, x = to_dev(v), torch.full((rows_v, Hv), float("nan"), dtype=torch.bfloat16, device="cuda"), torch.zeros((llm, Ht), dtype=torch.bfloat16, device="cuda")
+    rows = ob.RowIndex(dst)
+    saved, ws = bytes_buf(ob.ob_connector_saved_bytes(desc, tiles)), bytes_buf(ob.ob_connector_workspace_bytes(desc, tiles))
+    ob.ob_connector_fwd(desc, wd, vd, tiles, rows, x, llm, saved, ws)
+    ob.ob_connector_bwd(desc, wd, gd, 0, vd, to_dev(dx), dv, tiles, rows, llm, saved, ws)
+    x_ref, cache = orc_conn.connector_fwd(w, v, tiles, grid, 1e-5, np.zeros((llm, Ht)), dst)
+    dv_ref, g_ref = orc_conn.connector_bwd(w, cache, dx, tiles, grid, 1e-5, dst)
+    got = {"x": to_np(x), "dv": to_np(dv), **{n: to_np(t) for n, t in gd.items()}}
+    ref = {"x": x_ref, "dv": dv_ref, **g_ref}
+    for n in ref:
+        assert np.abs(got[n] - ref[n]).max() <= TOL * np.abs(ref[n]).max(), n
