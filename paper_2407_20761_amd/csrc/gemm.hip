@@ -90,10 +90,10 @@ struct TailSplit {
 template <int BM, int BN, int WM, int WN>
 struct Cfg {
     static constexpr int NW = WM * WN;
-    static constexpr int T = BM / WM / 16;        // 16x16 MFMA tiles per wave, each way
+    static constexpr int TA = BM / WM / 16, TB = BN / WN / 16;   // 16x16 MFMA tiles per wave, each way
     static constexpr int SLOT = (BM + BN) * ROW_BYTES;
-    static_assert(BM / WM == BN / WN, "square wave tiles");
-    static_assert(BM == BN && BM / 16 / NW * 2 == T, "T / 2 pieces of 1 KB per wave, operand and slot");
+    static_assert(BM / 16 / NW * 2 == TA && BN / 16 / NW * 2 == TB, "TA / 2 and TB / 2 pieces of 1 KB per wave and slot");
+    static_assert(TA == TB || (TA == 6 && TB == 8), "the schedules below");
 };
 
 // One operand's part of the ring; a fragment of the 16x16x32 MFMA is 16 x-values by 32 k, lane l
@@ -262,8 +262,9 @@ __device__ __forceinline__ void wg_barrier() {
 // s_waitcnt operand: at most `vm` vector-memory operations and `lgkm` LDS operations still pending
 constexpr int waitcnt(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) | 0x70 | (lgkm << 8); }
 
-// State of one wave in the K loop.  The contraction advances one ring slot (32 k) at a time: T runs,
-// run g multiplying A fragment g with all T B fragments.  Between its MFMAs a run carries two or
+// State of one wave in the K loop.  The contraction advances one ring slot (32 k) at a time: TA runs,
+// run g multiplying A fragment g with all TB B fragments.  (T below: TA = TB; 192 x 256 tiles, TA = 6 and TB = 8, have
+// the same order of loads, with two in some runs.)  Between its MFMAs a run carries two or
 // three fragment reads for the slot after (the next B fragment g into the other B set, the next A
 // fragment g - 1 into the register run g - 1 has just finished with) and one step of the refill:
 //  * a k-major operand refills, for NS slots ahead, the slot whose last reader has passed the barrier
@@ -277,13 +278,14 @@ constexpr int waitcnt(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) |
 template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS>
 struct KLoop {
     using C = Cfg<BM, BN, WM, WN>;
-    static constexpr int T = C::T;
-    Operand<BM, C::NW, T, AK> opa;
-    Operand<BN, C::NW, T, BKM> opb;
+    static constexpr int TA = C::TA, TB = C::TB;
+    static_assert(TA == TB || !AK, "a rectangular tile's K-major A would need a swizzle of its own");
+    Operand<BM, C::NW, TA, AK> opa;
+    Operand<BN, C::NW, TB, BKM> opb;
     __amdgpu_buffer_rsrc_t ra, rb, ra_n, rb_n;
     int ka_left, kb_left;                        // slots (k-major) / pairs of slots (k-contiguous) not yet described
     int wave;
-    bf16x8 af[T], bfr[2][T];
+    bf16x8 af[TA], bfr[2][TB];
 
     // The descriptors of the next slot (pair), ten steps (five per operand, see Operand::next_step); ra_n
     // and rb_n take over behind run 0 of the slot they are for.
@@ -332,62 +334,68 @@ struct KLoop {
     __device__ __forceinline__ bf16x8 b_frag(const unsigned char OB_LDS *__restrict__ ring, int S, int j) const {
         return opb.frag(ring + (BKM ? S : S & ~1) * B_SLOT, j, S & 1);       // (the operand's offsets start at its region)
     }
-    // Position of run g of slot S among the 2 T runs between the barrier of an odd slot and the barrier
-    // two slots on: the odd slot's runs 1 .. T-1, the even slot's runs, run 0 of the next odd slot.
-    static constexpr int position(int S, int g) { return (S & 1) ? (g == 0 ? 2 * T - 1 : g - 1) : T - 1 + g; }
+    // Position of run g of slot S among the 2 TA runs between the barrier of an odd slot and the barrier
+    // two slots on: the odd slot's runs 1 .. TA-1, the even slot's runs, run 0 of the next odd slot.
+    static constexpr int position(int S, int g) { return (S & 1) ? (g == 0 ? 2 * TA - 1 : g - 1) : TA - 1 + g; }
     // the piece of k-contiguous A that the run at position q loads (-1: none): next to k-contiguous B
-    // the even slot's runs; next to k-major B, whose loads sit in runs 1 .. T/2 of every slot, the
-    // other runs
+    // the even slot's runs; next to k-major B, whose loads sit in runs 1 .. TB/2 of every slot, the
+    // other runs (192 x 256: two of these four runs carry a second piece, see piece_a2)
     static constexpr int piece_a(int q) {
         if (AK) return -1;
-        if (!BKM) return q >= T - 1 && q < 2 * T - 1 ? q - (T - 1) : -1;         // the even slot's runs
-        return q >= T / 2 && q < T ? q - T / 2 : (q >= T + T / 2 ? q - T : -1);
+        if (!BKM) return q >= TA - 1 && q < 2 * TA - 1 ? q - (TA - 1) : -1;      // the even slot's runs
+        if (TA != TB) return q == 4 ? 0 : q == 5 ? 2 : q == 10 ? 3 : q == 11 ? 5 : -1;
+        return q >= TA / 2 && q < TA ? q - TA / 2 : (q >= TA + TA / 2 ? q - TA : -1);
     }
+    static constexpr int piece_a2(int q) { return TA != TB && BKM && (q == 4 || q == 10) ? piece_a(q) + 1 : -1; }
     // (B k-contiguous: A is as well, there is no layout with A alone k-major.)  B's pieces go out in the
-    // odd slot's runs 1 .. T-1, as early as its pair is free, the last one as a second load of run 1
+    // odd slot's runs 1 .. TA-1, as early as its pair is free, the rest as a second load of the first of them
     static constexpr int piece_b(int q) {
         if (BKM) return -1;
-        return q < T - 1 ? q : -1;
+        return q < TA - 1 ? q : -1;
     }
+    static constexpr int piece_b2(int q) { return !BKM && q < TB - (TA - 1) ? TA - 1 + q : -1; }
+    // the B fragments of the slot after that run g >= 1 reads: as many as there are runs, the rest in the first of them
+    static constexpr int read_b(int g) { return TA == TB ? g : g <= 3 ? 2 * g - 2 : g + 2; }
+    static constexpr int read_b2(int g) { return TA == TB ? (g == 1 ? 0 : -1) : g <= 3 ? 2 * g - 1 : -1; }
     // the pair of slots (0: slots 0 and 1; 1: slots 2 and 3) that the runs of slot S refill
     static constexpr int pair_of(int S, int g) { return (S & 1) ? (g == 0 ? ((S + 1) / 2) & 1 : (S - 1) / 2) : ((S / 2) + 1) & 1; }
 
-    // Run g of the slot in ring position S: its T MFMAs and between them, never more than one memory
+    // Run g of the slot in ring position S: its TB MFMAs and between them, never more than one memory
     // instruction between two MFMAs (a 16x16x32 MFMA keeps the pipe busy for four issue slots of a
     // lone wave, and whatever sits between two of them beyond three slots is lost: scalar
     // instructions count).  Run 0 reads its slot's own last A fragment (the register was busy until
     // now) and moves the descriptors on; the others read ahead in the slot after (run 1 one B fragment
     // more, which makes up for run 0).
     template <int S, int g>
-    __device__ __forceinline__ void run(f32x4 (&acc)[T][T], unsigned char OB_LDS *__restrict__ ring) {
-        constexpr int AT_2 = T > 2 ? 2 : 1, AT_RB = 0, AT_RA = 1, AT_RX = T >= 8 ? 2 : 1, AT_DL = T > 2 ? T / 2 + 1 : 1, AT_RQ = T >= 8 ? T / 2 + 2 : T - 1;
-        constexpr int set = S & 1, q = position(S, g), pa = piece_a(q), pb = piece_b(q);
+    __device__ __forceinline__ void run(f32x4 (&acc)[TA][TB], unsigned char OB_LDS *__restrict__ ring) {
+        constexpr int AT_2 = TB > 2 ? 2 : 1, AT_RB = 0, AT_RA = 1, AT_RX = TB >= 8 ? 2 : 1, AT_DL = TB > 2 ? TB / 2 + 1 : 1, AT_RQ = TB >= 8 ? TB / 2 + 2 : TB - 1;
+        constexpr int set = S & 1, q = position(S, g), pa = piece_a(q), pa2 = piece_a2(q), pb = piece_b(q), pb2 = piece_b2(q);
         constexpr int N = (S + 1) % NS, P = (S + NS - 1) % NS, pair = pair_of(S, g);
 #pragma unroll
-        for (int j = 0; j < T; ++j) {
+        for (int j = 0; j < TB; ++j) {
             mfma(acc[g][j], bfr[set][j], af[g]);
             __builtin_amdgcn_sched_barrier(0);
             if (g == 0) {
-                if (j == AT_RA) af[T - 1] = a_frag(ring, S, T - 1, true);
+                if (j == AT_RA) af[TA - 1] = a_frag(ring, S, TA - 1, true);
                 // the last load of the slot before, when both operands go straight to LDS
-                if (AK && BKM && j == AT_2) opb.load(rb, ring + B_BASE + P * B_SLOT, wave, T / 2 - 1);
+                if (AK && BKM && j == AT_2) opb.load(rb, ring + B_BASE + P * B_SLOT, wave, TB / 2 - 1);
                 // (small tiles: the descriptors of this slot's loads are worked out here, see below)
-                if (T < 8 && (AK || (S & 1)) && j == 0) prepare_a();
-                if (T < 8 && (BKM || (S & 1)) && j == AT_2) prepare_b();
+                if (TB < 8 && (AK || (S & 1)) && j == 0) prepare_a();
+                if (TB < 8 && (BKM || (S & 1)) && j == AT_2) prepare_b();
             } else {
-                if (j == AT_RB) bfr[set ^ 1][g] = b_frag(ring, N, g);
+                if (j == AT_RB) bfr[set ^ 1][read_b(g)] = b_frag(ring, N, read_b(g));
                 if (j == AT_RA) af[g - 1] = a_frag(ring, N, g - 1, false);
-                if (j == AT_RX && g == 1) bfr[set ^ 1][0] = b_frag(ring, N, 0);
+                if (read_b2(g) >= 0 && j == AT_RX) bfr[set ^ 1][read_b2(g) >= 0 ? read_b2(g) : 0] = b_frag(ring, N, read_b2(g) >= 0 ? read_b2(g) : 0);
                 if (j == AT_RQ) {
-                    if (AK && g - 1 < T / 2) opa.load(ra, ring + A_BASE + S * A_SLOT, wave, g - 1);
-                    if (BKM && !AK && g - 1 < T / 2) opb.load(rb, ring + B_BASE + S * B_SLOT, wave, g - 1);
-                    if (BKM && AK && g - 1 >= T / 2) opb.load(rb, ring + B_BASE + S * B_SLOT, wave, g - 1 - T / 2);
+                    if (AK && g - 1 < TA / 2) opa.load(ra, ring + A_BASE + S * A_SLOT, wave, g - 1);
+                    if (BKM && !AK && g - 1 < TB / 2) opb.load(rb, ring + B_BASE + S * B_SLOT, wave, g - 1);
+                    if (BKM && AK && g - 1 >= TA / 2) opb.load(rb, ring + B_BASE + S * B_SLOT, wave, g - 1 - TA / 2);
                 }
             }
             // Descriptors: a k-major operand moves on every slot, a k-contiguous one every other, behind run 0.
             // The ten steps of working the next ones out are dealt over the gaps of runs 2 - 4 of the slot
             // before that no memory instruction uses (a wave alone on its SIMD has three issue slots per gap).
-            if (T >= 8 && g >= 2 && g <= 4 && (j == 3 || j == 4 || j == 5 || j == 7)) {
+            if (TB >= 8 && g >= 2 && g <= 4 && (j == 3 || j == 4 || j == 5 || j == 7)) {
                 constexpr int first = (g - 2) * 4;
                 const int step_no = first + (j == 7 ? 3 : j - 3);
                 if (AK || !(S & 1)) {
@@ -407,7 +415,8 @@ struct KLoop {
             }
             if (pa >= 0 && j == AT_RQ) opa.load_pair(ra, ring + A_BASE + a_fill, wave, pa);
             if (pb >= 0 && j == AT_RQ) opb.load_pair(rb, ring + B_BASE + pair * 2 * B_SLOT, wave, pb);
-            if (pb == 0 && j == AT_DL) opb.load_pair(rb, ring + B_BASE + pair * 2 * B_SLOT, wave, T - 1);
+            if (pa2 >= 0 && j == AT_DL) opa.load_pair(ra, ring + A_BASE + a_fill, wave, pa2);
+            if (pb2 >= 0 && j == AT_DL) opb.load_pair(rb, ring + B_BASE + pair * 2 * B_SLOT, wave, pb2);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (g == 0) {
@@ -420,11 +429,11 @@ struct KLoop {
                 a_nxt = a_cur == (A_PAIRS - 1) * 2 * A_SLOT ? 0 : a_cur + 2 * A_SLOT;
             }
         }
-        if (!AK && (S & 1) && g == T - 1) a_cur = a_nxt;
+        if (!AK && (S & 1) && g == TA - 1) a_cur = a_nxt;
     }
     template <int S, int g>
-    __device__ __forceinline__ void runs_from(f32x4 (&acc)[T][T], unsigned char OB_LDS *__restrict__ ring) {
-        if constexpr (g < T) {
+    __device__ __forceinline__ void runs_from(f32x4 (&acc)[TA][TB], unsigned char OB_LDS *__restrict__ ring) {
+        if constexpr (g < TA) {
             run<S, g>(acc, ring);
             runs_from<S, g + 1>(acc, ring);
         }
@@ -432,11 +441,11 @@ struct KLoop {
     // the loads of at most this many slots, the newest, may still be on their way at a barrier
     // (both operands k-contiguous: at the barrier of an odd slot, behind which B's pair filled two slots
     // before is read, the T loads of A since; at that of an even slot nothing new is read)
-    static constexpr int vm_pending(int S) { return AK || BKM ? T * (NS - 2) : (S & 1) ? T * (NS - 3) : 63; }
+    static constexpr int vm_pending(int S) { return AK || BKM ? (TA + TB) / 2 * (NS - 2) : (S & 1) ? TA * (NS / 2 - 1) + TB * (NS / 2 - 2) : 63; }
     // The slot in ring position S.  On entry bfr[S & 1] and af[0 .. T-2] hold its fragments; on return
     // those of the slot after.
     template <int S>
-    __device__ __forceinline__ void slot(f32x4 (&acc)[T][T], unsigned char OB_LDS *__restrict__ ring) {
+    __device__ __forceinline__ void slot(f32x4 (&acc)[TA][TB], unsigned char OB_LDS *__restrict__ ring) {
         run<S, 0>(acc, ring);
         // own reads of this slot and own writes to LDS landed, own loads to the slot after in LDS (every
         // run issues one load, and the last one to the slot after went out NS - 2 slots ago or earlier),
@@ -451,23 +460,23 @@ struct KLoop {
     // in front of the loop's first would have asked for (positions 0 .. T-2).
     // prologue_later(): the number of loads it issues after the last one that the first slot needs.
     static constexpr int prologue_later() {
-        if (!AK && !BKM) return (NS - 2) * T;
+        if (!AK && !BKM) return (NS / 2 - 1) * (TA + TB);
         int n = 0;
-        for (int q = 0; q < T - 1; ++q) n += piece_a(q) >= 0 ? 1 : 0;
-        n += AK ? (NS - 1) * T / 2 : (NS / 2 - 1) * T;
-        n += (NS - 1) * T / 2 - (AK ? 1 : 0);
+        for (int q = 0; q < TA - 1; ++q) n += (piece_a(q) >= 0 ? 1 : 0) + (piece_a2(q) >= 0 ? 1 : 0);
+        n += AK ? (NS - 1) * TA / 2 : (NS / 2 - 1) * TA;
+        n += (NS - 1) * TB / 2 - (AK ? 1 : 0);
         return n;
     }
     __device__ __forceinline__ void prologue(unsigned char OB_LDS *__restrict__ ring) {
         next_a();
 #pragma unroll
-        for (int p = 0; p < (AK ? T / 2 : T); ++p) {
+        for (int p = 0; p < (AK ? TA / 2 : TA); ++p) {
             if (AK) opa.load(ra, ring + A_BASE, wave, p);
             else opa.load_pair(ra, ring + A_BASE, wave, p);
         }
         next_b();
 #pragma unroll
-        for (int p = 0; p < (BKM ? T / 2 : T); ++p) {
+        for (int p = 0; p < (BKM ? TB / 2 : TB); ++p) {
             if (BKM) opb.load(rb, ring + B_BASE, wave, p);
             else opb.load_pair(rb, ring + B_BASE, wave, p);
         }
@@ -478,37 +487,39 @@ struct KLoop {
             if (AK) {
                 next_a();
 #pragma unroll
-                for (int p = 0; p < T / 2; ++p) opa.load(ra, ring + A_BASE + sl * A_SLOT, wave, p);
+                for (int p = 0; p < TA / 2; ++p) opa.load(ra, ring + A_BASE + sl * A_SLOT, wave, p);
             }
             if (BKM) {
                 next_b();
 #pragma unroll
-                for (int p = 0; p < T / 2; ++p)
-                    if (!(AK && sl == NS - 1 && p == T / 2 - 1)) opb.load(rb, ring + B_BASE + sl * B_SLOT, wave, p);
+                for (int p = 0; p < TB / 2; ++p)
+                    if (!(AK && sl == NS - 1 && p == TB / 2 - 1)) opb.load(rb, ring + B_BASE + sl * B_SLOT, wave, p);
             }
             if (!BKM && (sl & 1) && sl < NS - 1) {
                 next_b();
 #pragma unroll
-                for (int p = 0; p < T; ++p) opb.load_pair(rb, ring + B_BASE + (sl + 1) * B_SLOT, wave, p);
+                for (int p = 0; p < TB; ++p) opb.load_pair(rb, ring + B_BASE + (sl + 1) * B_SLOT, wave, p);
             }
             if (!AK && (sl & 1) && sl < NS - 1) {
                 next_a();
 #pragma unroll
-                for (int p = 0; p < T; ++p) opa.load_pair(ra, ring + A_BASE + (sl + 1) * A_SLOT, wave, p);
+                for (int p = 0; p < TA; ++p) opa.load_pair(ra, ring + A_BASE + (sl + 1) * A_SLOT, wave, p);
             }
             if (!AK && sl == NS - 1) {
                 next_a();
 #pragma unroll
-                for (int q = 0; q < T - 1; ++q)
+                for (int q = 0; q < TA - 1; ++q) {
                     if (piece_a(q) >= 0) opa.load_pair(ra, ring + A_BASE + NS * A_SLOT, wave, piece_a(q));
+                    if (piece_a2(q) >= 0) opa.load_pair(ra, ring + A_BASE + NS * A_SLOT, wave, piece_a2(q));
+                }
                 a_cur = a_nxt = 0;
                 a_fill = NS * A_SLOT;
             }
         }
         // what runs 2 - 4 of the slot before the first would have left: the descriptors that take over
         // behind run 0 of the first slot
-        if (T >= 8 && AK) prepare_a();
-        if (T >= 8 && BKM) prepare_b();
+        if (TB >= 8 && AK) prepare_a();
+        if (TB >= 8 && BKM) prepare_b();
     }
 };
 
@@ -520,7 +531,7 @@ __device__ __forceinline__ void gemm_tile(
     int ldb, __bf16 *__restrict__ Cm, int ldc, const __bf16 *__restrict__ bias,
     const __bf16 *R, int ldr, int tile_m, int tile_n, bool sliced, int kz, int tail_tile, const TailSplit &ts) {
     using C = Cfg<BM, BN, WM, WN>;
-    constexpr int T = C::T;
+    constexpr int TA = C::TA, TB = C::TB;
     __shared__ __attribute__((aligned(1024))) unsigned char ring_mem[KLoop<BM, BN, WM, WN, AK, BKM, NS>::RING_BYTES];
     const int m0 = __builtin_amdgcn_readfirstlane(tile_m) * BM;
     const int n0 = __builtin_amdgcn_readfirstlane(tile_n) * BN;
@@ -533,7 +544,7 @@ __device__ __forceinline__ void gemm_tile(
     lp.opa.init(A, lda, m0, (AK ? (long)K : (long)M) * lda * 2, wave, lane, wm * (BM / WM), lp.A_BASE);
     lp.opb.init(B, ldb, n0, (BKM ? (long)K : (long)N) * ldb * 2, wave, lane, wn * (BN / WN), lp.B_BASE);
 
-    f32x4 acc[T][T];
+    f32x4 acc[TA][TB];
     unsigned char OB_LDS *ring = (unsigned char OB_LDS *)ring_mem;
     // a slice covers K steps [k_first, k_first + nk); two ring slots to the K step
     const int k_first = kz * ts.k_chunk;
@@ -546,9 +557,9 @@ __device__ __forceinline__ void gemm_tile(
     // the accumulators are cleared while the first loads are on their way (the empty statement pins the 256
     // moves here: left alone they sink behind the wait for those loads)
 #pragma unroll
-    for (int i = 0; i < T; ++i)
+    for (int i = 0; i < TA; ++i)
 #pragma unroll
-        for (int j = 0; j < T; ++j) {
+        for (int j = 0; j < TB; ++j) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
             asm volatile("" : "+a"(acc[i][j]));
@@ -557,9 +568,9 @@ __device__ __forceinline__ void gemm_tile(
     __builtin_amdgcn_s_waitcnt(waitcnt(later < 63 ? later : 63, 0));
     wg_barrier();
 #pragma unroll
-    for (int j = 0; j < T; ++j) lp.bfr[0][j] = lp.b_frag(ring, 0, j);
+    for (int j = 0; j < TB; ++j) lp.bfr[0][j] = lp.b_frag(ring, 0, j);
 #pragma unroll
-    for (int i = 0; i < T - 1; ++i) lp.af[i] = lp.a_frag(ring, 0, i, true);
+    for (int i = 0; i < TA - 1; ++i) lp.af[i] = lp.a_frag(ring, 0, i, true);
 
     // once round the ring per trip: a single straight path with immediate LDS addresses.  There is no
     // separate tail (several ways into the epilogue make the register allocator move the
@@ -613,7 +624,7 @@ __device__ __forceinline__ void gemm_tile(
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int j = 0; j < T; ++j)
+            for (int j = 0; j < TB; ++j)
                 *(f32x4 OB_LDS *)(slab + (16 * h + lx) * RSTR + (j * 16 + lq * 4) * 4) = acc[2 * ii + h][j];
     };
     // One straight path per kind of output (MODE 0: bf16; 1: bf16 with the residual added; 2: the fp32 sums
@@ -628,7 +639,7 @@ __device__ __forceinline__ void gemm_tile(
         constexpr int NR = 32 / RPI;
         put(0);
 #pragma unroll
-        for (int ii = 0; ii < T / 2; ++ii) {
+        for (int ii = 0; ii < TA / 2; ++ii) {
             f32x4 lo[NR], hi[NR];
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
@@ -636,7 +647,7 @@ __device__ __forceinline__ void gemm_tile(
                 lo[r] = *(const f32x4 OB_LDS *)(slab + row * RSTR + (lane % LPR) * 32);
                 hi[r] = *(const f32x4 OB_LDS *)(slab + row * RSTR + (lane % LPR) * 32 + 16);
             }
-            if (ii + 1 < T / 2) put(ii + 1);
+            if (ii + 1 < TA / 2) put(ii + 1);
             const int m_first = m0 + wm * (BM / WM) + ii * 32 + lane / LPR;
             bf16x8 r8[NR];
             if (MODE == 1) {
@@ -738,6 +749,8 @@ template __global__ void gemm_group_kernel<64, 64, 2, 2, true, true, 8>(GemmGrou
 OB_GEMM_INSTANCE(256, 256, false, false, 4)
 OB_GEMM_INSTANCE(128, 128, false, false, 4)
 OB_GEMM_INSTANCE(128, 128, false, false, 8)
+OB_GEMM_INSTANCE(192, 256, false, false, 4)
+OB_GEMM_INSTANCE(192, 256, false, true, 4)
 OB_GEMM_INSTANCE(64, 64, false, false, 8)
 OB_GEMM_INSTANCE(64, 64, false, true, 8)
 OB_GEMM_INSTANCE(64, 64, true, true, 8)
@@ -821,13 +834,14 @@ __global__ __launch_bounds__(256) void tail_sum_group_kernel(TailSplit ts, GemmG
 }
 
 // How a GEMM is cut into workgroups: the kind of tile, and which tiles have their contraction split.
-// 256 x 256 | 128 x 128, two to a CU | 128 x 128 over a ring of eight slots | 64 x 64, eight slots, two to a CU
-enum TileKind { BIG = 0, SMALL = 1, DEEP = 2, FINE = 3 };
-constexpr int tile_edge(TileKind kind) { return kind == BIG ? 256 : kind == FINE ? 64 : 128; }
+// 256 x 256 | 128 x 128, two to a CU | 128 x 128 over a ring of eight slots | 64 x 64, eight slots, two to a CU | 192 x 256
+enum TileKind { BIG = 0, SMALL = 1, DEEP = 2, FINE = 3, MID = 4 };
+constexpr int tile_rows(TileKind kind) { return kind == BIG ? 256 : kind == MID ? 192 : kind == FINE ? 64 : 128; }
+constexpr int tile_cols(TileKind kind) { return kind == MID ? 256 : tile_rows(kind); }
 struct Plan {
     TileKind kind;
     int n_full, n_tail, splits, k_chunk;   // splits == 1: every tile whole
-    size_t part_bytes() const { return splits > 1 ? (size_t)splits * n_tail * tile_edge(kind) * tile_edge(kind) * 4 : 0; }
+    size_t part_bytes() const { return splits > 1 ? (size_t)splits * n_tail * tile_rows(kind) * tile_cols(kind) * 4 : 0; }
 };
 
 // compute units of the current device, asked once (256 on MI355X, also when no device answers: the
@@ -844,8 +858,7 @@ int compute_units() {
     return cus;
 }
 int tiles_of(TileKind kind, int M, int N) {
-    const int t = tile_edge(kind);
-    return ((M + t - 1) / t) * ((N + t - 1) / t);
+    return ((M + tile_rows(kind) - 1) / tile_rows(kind)) * ((N + tile_cols(kind) - 1) / tile_cols(kind));
 }
 int slots_of(TileKind kind) { return (kind == SMALL || kind == FINE ? 2 : 1) * compute_units(); }   // workgroups the chip holds at a time
 // The tail of `tiles` tiles cut into at most z slices of whole trips of the two-step loop; false: that cuts nothing.
@@ -863,6 +876,9 @@ bool cut(TileKind kind, int tiles, int nk, int z, Plan &p) {
 //  * big tiles come in rounds of one per CU, and the tiles of an incomplete last round take as long as a full one; a K
 //    step takes 1.23 on a full chip, 1.1 while half the chip or less is at work (the clock is higher), prologue and
 //    epilogue as much as 4.67 more (nothing else runs on the CU meanwhile);
+//  * a 192 x 256 tile takes 0.82 of a big one's time for 0.75 of its work: for rows that fit it better, or a round that
+//    it fills and big tiles do not (3072 x 4096 x 4096, 256 tiles instead of 192: 85 -> 76; 3075 x 3200 x 12800, 221
+//    instead of 169: 235 -> 208);
 //  * a small tile with a CU to itself is bound by what the CU takes in from beyond the L2 (50 - 75 bytes per ns, also
 //    with a ring twice as deep, with eight waves, or with lines fetched ahead by another wave: 0.5 per K step of 32 KB).
 //    Two to a CU take 0.94 each, and, out of step as they are, hide each other's epilogues and fill the last round
@@ -880,7 +896,7 @@ double estimate_us(int layout, TileKind kind, int nk, const Plan &p) {
     const bool sliced = p.splits > 1;
     const double whole = sliced ? p.n_full : 0, tail = sliced ? (double)p.n_tail * p.splits : p.n_full + p.n_tail;
     const int k_tail = sliced ? p.k_chunk : nk;
-    const double sums = sliced ? tail * tile_edge(kind) * tile_edge(kind) * 4 / 3.38e6 + 2.94 : 0.0;
+    const double sums = sliced ? tail * tile_rows(kind) * tile_cols(kind) * 4 / 3.38e6 + 2.94 : 0.0;
     const bool alone = whole == 0 && tail <= cus;
     auto paired = [&](double step, double edge, double last, double least) {   // tiles that share a CU in twos
         if (sliced) return (whole / (2 * cus) * (nk + edge) + ceil(tail / (2 * cus)) * (k_tail + edge)) * step;
@@ -888,9 +904,11 @@ double estimate_us(int layout, TileKind kind, int nk, const Plan &p) {
     };
     double t = 0;
     switch (kind) {
+    case MID:
     case BIG: {
         const double rounds = ceil(tail / cus), fill = (whole + tail) / (rounds * cus + whole);
-        t = (whole / cus * (nk + 4.67) + rounds * (k_tail + 4.67)) * (1.1 + 0.13 * fmax(0.0, 2 * fill - 1));
+        const double edge = kind == MID ? 5.2 : 4.67, step = (1.1 + 0.13 * fmax(0.0, 2 * fill - 1)) * (kind == MID ? 0.82 : 1.0);
+        t = (whole / cus * (nk + edge) + rounds * (k_tail + edge)) * step;
         break;
     }
     case SMALL: t = alone ? (k_tail + 2.86) * (layout == 0 ? 0.566 : 0.521) : paired(0.939, 1.17, 0.3, 0); break;
@@ -935,8 +953,8 @@ Plan make_plan(int layout, int M, int N, int K, size_t scratch) {
     const int nk = (K + KSTEP - 1) / KSTEP;
     Plan best{BIG, 0, 0, 1, 0}, p;
     double t_best = -1;
-    for (TileKind kind : {BIG, SMALL, DEEP, FINE}) {
-        if (kind == DEEP && layout != 0) continue;
+    for (TileKind kind : {BIG, SMALL, DEEP, FINE, MID}) {
+        if ((kind == DEEP && layout != 0) || (kind == MID && layout == 2)) continue;
         const int tiles = tiles_of(kind, M, N);
         p = Plan{kind, tiles, 0, 1, 0};
         const double t = estimate_us(layout, kind, nk, p);
@@ -971,7 +989,9 @@ void launch_layout(int layout, int M, int N, int K, const void *A, int lda, cons
     if (p.kind == BIG) launch_tile<256, 256, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
     else if (p.kind == SMALL) launch_tile<128, 128, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
     else if (p.kind == FINE) launch_tile<64, 64, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
-    else if constexpr (!AK && !BKM) launch_tile<128, 128, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
+    else if (p.kind == MID) {
+        if constexpr (!AK) launch_tile<192, 256, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
+    } else if constexpr (!AK && !BKM) launch_tile<128, 128, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
 }
 
 // The scratch of a group of "TN" GEMMs over one K: 256 x 256 tiles, the slices of the combined list's tail.
@@ -1038,7 +1058,7 @@ int gemm_tn_group(int count, const GemmTN *g, int K, void *ws, size_t ws_bytes, 
     grp.n = count;
     int first = 0;
     for (int i = 0; i < count; ++i) {
-        const int t = tile_edge(p.kind);
+        const int t = tile_rows(p.kind);
         grp.first[i] = first;
         grp.M[i] = g[i].M; grp.N[i] = g[i].N;
         grp.A[i] = (const __bf16 *)g[i].A; grp.lda[i] = g[i].M;

@@ -125,3 +125,23 @@ def test_connector_widths(Hv, Ht, grid, tiles):
     ref = {"x": x_ref, "dv": dv_ref, **g_ref}
     for n in ref:
         assert np.abs(got[n] - ref[n]).max() <= TOL * np.abs(ref[n]).max(), n
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(2050, 4032, 896), (2050, 4096, 960), (2112, 4096, 1024), (1921, 4096, 1088), (3072, 4096, 2048)])
+def test_gemm_rectangular_tiles(layout, M, N, K):
+    """Launches that 192 x 256 tiles are chosen for: ragged and whole rows and columns, every remainder of the trip's two
+    K steps, sampled rows against fp64."""
+    print(f"rectangular tiles layout={layout} {M} {N} {K}", flush=True)
+    rng = np.random.default_rng(M + N + K + layout)
+    A = si.round_to_bf16(rng.standard_normal((M, K), dtype=np.float32))
+    B = si.round_to_bf16(rng.standard_normal((N, K), dtype=np.float32))
+    bias = si.round_to_bf16(rng.standard_normal((N,), dtype=np.float32))
+    R = si.round_to_bf16(rng.standard_normal((M, N), dtype=np.float32) * 4)
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ob.ob_gemm_bf16(layout, M, N, K, to_dev(A), to_dev(B if layout == 0 else np.ascontiguousarray(B.T)), C, to_dev(bias), to_dev(R), None)
+    rows = np.unique(np.concatenate([np.arange(0, M, 37), [95, 96, 191, 192, 287, 288, M - 2, M - 1]]))
+    ref = A[rows].astype(np.float64) @ B.astype(np.float64).T + bias + R[rows]
+    got = to_np(C)
+    assert np.isfinite(got).all()
+    assert np.abs(got[rows] - ref).max() <= 2.0 ** -8 * np.abs(ref).max()
