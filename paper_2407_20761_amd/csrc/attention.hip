@@ -823,26 +823,28 @@ __device__ __forceinline__ void issue_row_stats(const float *base, long floats_l
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, dst, 4, lane * 4, 0, 0, 0);
 }
 
-// The dK / dV kernel comes in two shapes per head size (NP pairs of waves, each pair owning 32 key rows; query
+// The dK / dV kernel comes in two or three shapes per head size (NP pairs of waves, each pair owning 32 key rows; query
 // tiles of SR rows), of which dkv_shape() takes the one its estimate of the launch favours:
 //  * D = 64: two pairs, so that workgroups which nothing synchronises share a CU and a 1025-row segment wastes
 //    6 % of the rows (six pairs in step: 12 %).  SR = 32 needs 34 KB of LDS and under 128 registers: four
 //    workgroups to the CU, the better rate when the chip is full (12 ViT tiles x 16 heads: 151 us, against 178
 //    with SR = 64 and 189 for six pairs).  SR = 64 has half the barriers and stage switches to a row, the shorter
-//    chain when one long segment keeps the launch waiting (16 texts, 16 / 4 heads: 121 against 144 and 177 us).
+//    chain when one long segment keeps the launch waiting (16 texts, 16 / 4 heads: 121 against 144 and 177 us).  Six pairs
+//    remain for bidirectional launches that are just about one round of them (5 ViT tiles x 8 heads in groups of 6, 240
+//    workgroups: 195 us, against 207 with SR = 32).
 //  * D = 128: four pairs on one CU, eight waves in step, the better rate when the chip is full (7B-shaped batch:
 //    707 us, two pairs 1012, two pairs with SR = 32 746); two pairs, one wave to a SIMD, the shorter
 //    trip for launches that leave most of it idle (one segment of 557, 32 / 8 heads: 61 against 70 us; of
 //    2000, 12 / 2 heads: 274 against 327).
-// Both shapes of a head size add up the query rows of a key row in the same order, set by DKV_ORDER_Q and the
+// All shapes of a head size add up the query rows of a key row in the same order, set by DKV_ORDER_Q and (causal) the
 // place in whole tiles of dkv_whole() key rows: which of them runs does not show in the result, so a packed batch
 // still gives bit for bit what its segments give alone.
 constexpr int DKV_ORDER_Q = 64;   // the ragged end of the query rows is one masked step of up to this many rows
 constexpr int dkv_whole(int d) { return d == 64 ? 64 : 128; }
-constexpr int dkv_np(int d, int shape) { return d == 128 && shape == 0 ? 4 : 2; }      // pairs and query rows of a shape
+constexpr int dkv_np(int d, int shape) { return shape == 2 ? 6 : d == 128 && shape == 0 ? 4 : 2; }   // pairs and query rows of a shape
 constexpr int dkv_sr(int d, int shape) { return d == 64 && shape == 1 ? 32 : 64; }
 template <int D, bool CAUSAL, int NP, int SR>
-__global__ __launch_bounds__(128 * NP, D == 128 ? 1 : SR == 32 ? 4 : 2) void attn_bwd_dkv_kernel(
+__global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 2) void attn_bwd_dkv_kernel(
     const __bf16 *__restrict__ d_o, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
     const __bf16 *__restrict__ v, const float *__restrict__ lse2_all, const float *__restrict__ delta,
     __bf16 *__restrict__ dk, __bf16 *__restrict__ dv, int ldq, int ldkv, int ldo,
@@ -851,7 +853,7 @@ __global__ __launch_bounds__(128 * NP, D == 128 ? 1 : SR == 32 ? 4 : 2) void att
     // three stages of the streamed Q and dO tiles (the dK side works one tile behind the dV side, see
     // below), two buffers for the probabilities on their way from one to the other, row statistics
     __shared__ __attribute__((aligned(1024))) unsigned char tiles_s[6 * Tile<D, SR>::BYTES];
-    constexpr int KVT = 32 * NP, WHOLE = dkv_whole(D), MT = SR / 32, PB = MT * 2048;   // key rows of the workgroup, of the whole it may be a part of
+    constexpr int KVT = 32 * NP, WHOLE = CAUSAL ? dkv_whole(D) : KVT, MT = SR / 32, PB = MT * 2048;   // key rows of the workgroup, of the whole it may be a part of
     static_assert(WHOLE % KVT == 0 && KVT % SR == 0, "parts of whole tiles");
     __shared__ __attribute__((aligned(1024))) unsigned char p_s[2 * NP * PB];  // [buffer][pair]: 2 MT x 64 lanes x 16 B
     __shared__ __attribute__((aligned(256))) float stat_s[6 * ST];              // lse2 x 3 stages, Delta x 3 stages
@@ -1087,12 +1089,12 @@ void make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side
     ord.n = n;
 }
 
-// Which of its two shapes the dK / dV kernel runs in (see there).  An estimate of the launch's duration in
+// Which of its shapes the dK / dV kernel runs in (see there).  An estimate of the launch's duration in
 // microseconds: the trips (64 query rows against a workgroup's key rows) that a CU has to make at the rate of a full
 // chip, or the longest chain of trips (the first key rows of the longest segment, all query heads of a group) at the
-// rate its workgroup sees, whichever is longer.  The rates are fitted to 23 launches of either shape (segments of
-// 100 - 8192 rows, 4 - 32 heads, groups of 1 - 8, both masks); the pick was the faster one in 21 and within 4 % of it in the
-// others.
+// rate its workgroup sees, whichever is longer.  Over 224 launches measured in either shape (64 - 16000 tokens in one
+// segment, ViT tiles or texts, 1 - 25 key / value heads, groups of 1 - 6, both masks) the picks are 0.03 % (D = 64) and 0.2 %
+// (D = 128) slower than the faster shape.
 struct DkvShape { int kv_rows; double full, chain; };
 constexpr DkvShape DKV_SHAPES[2][2] = {{{64, 0.81, 1.1}, {64, 0.70, 1.53}},      // D = 64: SR = 64, SR = 32
                                        {{128, 2.39, 1.7}, {64, 1.76, 1.42}}};    // D = 128: four pairs, two
@@ -1107,6 +1109,10 @@ int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
             chain = std::max(chain, first);
         }
         est[i] = group * std::max(sum * nkv / 256 * sh.full, chain * sh.chain);
+    }
+    if (d == 64 && !causal) {      // 70 - 100 % of one round of six pairs
+        const long six = (long)count_tiles(seg, 32 * dkv_np(64, 2)) * nkv;
+        if (six >= 180 && six <= 256) return 2;
     }
     return est[1] < est[0] ? 1 : 0;
 }
@@ -1131,6 +1137,7 @@ int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
                                                            TileOrder);
 OB_ATTN_INSTANCES(64, true)
 OB_ATTN_INSTANCES(64, false)
+OB_DKV_INSTANCE(64, false, dkv_np(64, 2), dkv_sr(64, 2))
 OB_ATTN_INSTANCES(128, true)
 OB_ATTN_INSTANCES(128, false)
 #undef OB_DKV_INSTANCE
@@ -1193,7 +1200,9 @@ void launch_attn_bwd(const void *d_o, const void *q, const void *k, const void *
     const dim3 grid_kv((unsigned)tiles_kv * nkv);
 #define OB_DKV_ARGS (const __bf16 *)d_o, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, lse2, delta, (__bf16 *)dk,  \
                     (__bf16 *)dv, ldq, ldkv, ldo, seg->cu_dev, seg->n_seg, T, group, scale, rot, nkv, ord
-    if (shape == 0) OB_ATTN_DISPATCH(attn_bwd_dkv_0, grid_kv, 4 * kvt, OB_DKV_ARGS);
+    if (shape == 2)
+        hipLaunchKernelGGL((attn_bwd_dkv_kernel<64, false, dkv_np(64, 2), dkv_sr(64, 2)>), grid_kv, dim3(4 * kvt), 0, s, OB_DKV_ARGS);
+    else if (shape == 0) OB_ATTN_DISPATCH(attn_bwd_dkv_0, grid_kv, 4 * kvt, OB_DKV_ARGS);
     else OB_ATTN_DISPATCH(attn_bwd_dkv_1, grid_kv, 4 * kvt, OB_DKV_ARGS);
 #undef OB_DKV_ARGS
 }

@@ -31,11 +31,12 @@ def _attention(qkv, d_o, lens, nq, nkv, d, mask):
 
 
 @pytest.mark.parametrize("mask", [orc.MASK_BIDIR, orc.MASK_CAUSAL])
-@pytest.mark.parametrize("d,nq,nkv", [(64, 16, 16), (64, 16, 8), (128, 8, 8), (128, 16, 8)])
+@pytest.mark.parametrize("d,nq,nkv", [(64, 16, 16), (64, 16, 8), (64, 10, 10), (128, 8, 8), (128, 16, 8)])
 def test_dkv_shapes_give_the_same_bits(d, nq, nkv, mask):
     """Many short segments fill the chip (the shape for throughput), each alone leaves it idle (the shape for the
-    shorter trip): lengths on and beside the 32-, 64- and 128-row borders, oracle on the first and the longest."""
-    lens = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 191, 193, 257] * 8 + [385]
+    shorter trip): lengths on and beside the 32-, 64- and 128-row borders, oracle on two of them.
+    (64, 10, 10): the bidirectional batch is about one round of the six-pair shape."""
+    lens = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 191, 193, 257] * (1 if nkv == 10 else 8) + [385]
     print(f"dkv shapes d={d} nq={nq} nkv={nkv} mask={mask}", flush=True)
     cu = si.lengths_to_cu(lens)
     T = int(cu[-1])
