@@ -384,7 +384,7 @@ extern "C" int ob_block_bwd(const ob_block_desc *desc, const ob_block_weights *w
     unsigned char *d_o = at(ws, wk.d_o), *dqkv = at(ws, wk.dqkv), *gws = at(ws, wk.gemm);
     float *delta = (float *)at(ws, wk.delta);
     const float scale = 1.0f / sqrtf((float)m.d);
-    const int ncs = colsum_partials(m.T), nnb = norm_bwd_partials(m.T, m.H);
+    const int ncs = colsum_partials(m.T), nnb = norm_bwd_workgroups(m.T, m.H);
     int rc;
     ReduceBatch sums;      // the column reductions' second halves, launched together at the end
     auto bias_grad = [&](const void *src, int C, size_t region, void *out) {

@@ -175,121 +175,119 @@ __global__ __launch_bounds__(256) void norm_fwd_wave_kernel(
 // CSUM: the kernel also leaves the column sums of dres and of its output dx (as stored, after rounding) in
 // csum[blockIdx.x][2][H]: the bias gradients of the two linears around the norm, which would otherwise
 // each take a pass of their own over a [T, H] tensor the kernel has in registers anyway.
+// Bound: HBM.  Two vectors of 8 per thread and as many threads as the row needs (H <= 512 * 16), so that several
+// workgroups share a CU; a row's loads are issued one row ahead, its two sums take one barrier (the LDS words alternate).
 template <bool LAYERNORM, bool CSUM>
-__global__ __launch_bounds__(NORM_THREADS) void norm_bwd_kernel(
+__global__ __launch_bounds__(512) void norm_bwd_kernel(
     const __bf16 *__restrict__ dh, const __bf16 *__restrict__ x, const float *__restrict__ stats,
     const __bf16 *__restrict__ gamma, const __bf16 *__restrict__ dres, __bf16 *__restrict__ dx,
     float *__restrict__ partial, float *__restrict__ csum, int T, int H) {
-    __shared__ float red[NORM_THREADS / 64];
-    const int nvec = H / 8;
-    float g[MAX_VEC][8], dg[MAX_VEC][8], db[MAX_VEC][8];
-    float sr[CSUM ? MAX_VEC : 1][8], sx[CSUM ? MAX_VEC : 1][8];
+    constexpr int NV = 2;
+    __shared__ float2 red[2][8];
+    const int nvec = H / 8, nt = blockDim.x, waves = nt >> 6;
+    bf16x8 g[NV], nx[NV], nd[NV], nr[NV];
+    float dg[NV][8], db[NV][8], sr[CSUM ? NV : 1][8], sx[CSUM ? NV : 1][8];
 #pragma unroll
-    for (int i = 0; i < (CSUM ? MAX_VEC : 1); ++i)
+    for (int i = 0; i < NV; ++i) {
+        const int c = threadIdx.x + i * nt;
+        g[i] = c < nvec ? *(const bf16x8 *)(gamma + c * 8) : bf16x8{};
+        nx[i] = nd[i] = nr[i] = bf16x8{};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sr[i][e] = sx[i][e] = 0.f;
+        for (int e = 0; e < 8; ++e) dg[i][e] = db[i][e] = 0.f;
+        if (CSUM) {
 #pragma unroll
-    for (int i = 0; i < MAX_VEC; ++i) {
-        const int c = threadIdx.x + i * NORM_THREADS;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dg[i][e] = db[i][e] = g[i][e] = 0.f;
-        if (c < nvec) {
-            const bf16x8 t = *(const bf16x8 *)(gamma + c * 8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) g[i][e] = (float)t[e];
+            for (int e = 0; e < 8; ++e) sr[i][e] = sx[i][e] = 0.f;
         }
     }
-    // the loads of a row are issued one row ahead (x, dh) or in front of the row's two reductions
-    // (dres), so that the barriers of the reductions never leave the memory pipe empty
-    bf16x8 nx[MAX_VEC], nd[MAX_VEC];
     float nmean = 0.f, nrstd = 0.f;
     auto fetch = [&](int row) {
         nmean = stats[2 * (size_t)row];
         nrstd = stats[2 * (size_t)row + 1];
 #pragma unroll
-        for (int i = 0; i < MAX_VEC; ++i) {
-            const int c = threadIdx.x + i * NORM_THREADS;
+        for (int i = 0; i < NV; ++i) {
+            const int c = threadIdx.x + i * nt;
             if (c < nvec) {
                 nx[i] = *(const bf16x8 *)(x + (size_t)row * H + c * 8);
                 nd[i] = *(const bf16x8 *)(dh + (size_t)row * H + c * 8);
+                nr[i] = *(const bf16x8 *)(dres + (size_t)row * H + c * 8);
             }
         }
     };
+    int half = 0;
     if ((int)blockIdx.x < T) fetch(blockIdx.x);
     for (int row = blockIdx.x; row < T; row += gridDim.x) {
         const float mean = nmean, rstd = nrstd;
-        float xh[MAX_VEC][8], dxh[MAX_VEC][8];
-        bf16x8 tr[MAX_VEC];
+        bf16x8 cx[NV], cd[NV], cr[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) { cx[i] = nx[i]; cd[i] = nd[i]; cr[i] = nr[i]; }
+        if (row + (int)gridDim.x < T) fetch(row + gridDim.x);
         float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-        for (int i = 0; i < MAX_VEC; ++i) {
-            const int c = threadIdx.x + i * NORM_THREADS;
-            if (c < nvec) {
-                const bf16x8 tx = nx[i], td = nd[i];
-                tr[i] = *(const bf16x8 *)(dres + (size_t)row * H + c * 8);
+        for (int i = 0; i < NV; ++i) {
+            if ((int)threadIdx.x + i * nt < nvec) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float d = (float)td[e];
-                    xh[i][e] = ((float)tx[e] - mean) * rstd;
-                    dxh[i][e] = d * g[i][e];
-                    dg[i][e] += d * xh[i][e];
+                    const float d = (float)cd[i][e], xh = ((float)cx[i][e] - mean) * rstd, dxh = d * (float)g[i][e];
+                    dg[i][e] += d * xh;
                     db[i][e] += d;
-                    s1 += dxh[i][e];
-                    s2 += dxh[i][e] * xh[i][e];
+                    s1 += dxh;
+                    s2 += dxh * xh;
                 }
             }
         }
-        if (row + (int)gridDim.x < T) fetch(row + gridDim.x);
-        s2 = block_sum(s2, red) / H;
-        s1 = LAYERNORM ? block_sum(s1, red) / H : 0.f;
+        s1 = LAYERNORM ? wave_sum(s1) : 0.f;
+        s2 = wave_sum(s2);
+        if ((threadIdx.x & 63) == 0) red[half][threadIdx.x >> 6] = make_float2(s1, s2);
+        __syncthreads();
+        s1 = s2 = 0.f;
+        for (int w = 0; w < waves; ++w) { s1 += red[half][w].x; s2 += red[half][w].y; }
+        half ^= 1;
+        s1 /= H;
+        s2 /= H;
 #pragma unroll
-        for (int i = 0; i < MAX_VEC; ++i) {
-            const int c = threadIdx.x + i * NORM_THREADS;
+        for (int i = 0; i < NV; ++i) {
+            const int c = threadIdx.x + i * nt;
             if (c < nvec) {
                 bf16x8 o;
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    o[e] = (__bf16)((float)tr[i][e] + rstd * (dxh[i][e] - s1 - xh[i][e] * s2));
+                for (int e = 0; e < 8; ++e) {
+                    const float xh = ((float)cx[i][e] - mean) * rstd, dxh = (float)cd[i][e] * (float)g[i][e];
+                    o[e] = (__bf16)((float)cr[i][e] + rstd * (dxh - s1 - xh * s2));
+                }
                 *(bf16x8 *)(dx + (size_t)row * H + c * 8) = o;
                 if (CSUM) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        sr[i][e] += (float)tr[i][e];
+                        sr[i][e] += (float)cr[i][e];
                         sx[i][e] += (float)o[e];
                     }
                 }
             }
         }
     }
-    float *pg = partial + (size_t)blockIdx.x * 2 * H, *pb = pg + H;
+    auto write = [&](const float (&a)[8], float *__restrict__ dst) {
+        *(f32x4 *)dst = f32x4{a[0], a[1], a[2], a[3]};
+        *(f32x4 *)(dst + 4) = f32x4{a[4], a[5], a[6], a[7]};
+    };
+    const size_t base = (size_t)blockIdx.x * 2 * H;
 #pragma unroll
-    for (int i = 0; i < MAX_VEC; ++i) {
-        const int c = threadIdx.x + i * NORM_THREADS;
+    for (int i = 0; i < NV; ++i) {
+        const int c = threadIdx.x + i * nt;
         if (c < nvec) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                pg[c * 8 + e] = dg[i][e];
-                pb[c * 8 + e] = db[i][e];
-            }
+            write(dg[i], partial + base + c * 8);
+            write(db[i], partial + base + H + c * 8);
             if (CSUM) {
-                float *cr = csum + (size_t)blockIdx.x * 2 * H, *cx = cr + H;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    cr[c * 8 + e] = sr[i][e];
-                    cx[c * 8 + e] = sx[i][e];
-                }
+                write(sr[CSUM ? i : 0], csum + base + c * 8);
+                write(sx[CSUM ? i : 0], csum + base + H + c * 8);
             }
         }
     }
 }
 
-// The same backward with one wavefront per row (H <= 64 * 8 * NV): no workgroup barrier in the walk, the
+// The same backward for many narrow rows (H <= 1024), one wavefront per row: no workgroup barrier in the walk, the
 // row sums are wave reductions, and the next row's loads are in flight while the current row is
-// worked on (24 KB per wave in flight at H = 4096).  Every wave keeps its own column sums.  W = 4: every
-// wave writes its own partial, partial[(blockIdx.x * 4 + wave)][2][H].  W = 8 (narrow rows, where four
-// waves per CU have too few bytes in flight to fill the memory pipes): the workgroup's eight waves add
-// their column sums in LDS, in wave order, and leave ONE partial, partial[blockIdx.x][2][H]: twice the
-// rows in flight for a quarter of the partial sums written here and read again by the final reduction.
+// worked on.  The workgroup's eight waves add their column sums in LDS, in wave order, and leave one partial,
+// partial[blockIdx.x][2][H].
 template <bool LAYERNORM, int NV, bool CSUM, int W>
 __global__ __launch_bounds__(64 * W) void norm_bwd_wave_kernel(
     const __bf16 *__restrict__ dh, const __bf16 *__restrict__ x, const float *__restrict__ stats,
@@ -373,56 +371,33 @@ __global__ __launch_bounds__(64 * W) void norm_bwd_wave_kernel(
             }
         }
     }
-    if constexpr (W == 4) {
-        float *pg = partial + (size_t)slot * 2 * H, *pb = pg + H;
+    constexpr int HMAX = 64 * 8 * NV;
+    __shared__ float red[W][2][HMAX];
+    const int wave = threadIdx.x >> 6;
+    auto fold = [&](const float (&a)[NV][8], const float (&b)[NV][8], float *__restrict__ out) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int c = lane + 64 * i;
             if (c < nvec) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    pg[c * 8 + e] = dg[i][e];
-                    pb[c * 8 + e] = db[i][e];
-                }
-                if (CSUM) {
-                    float *pr = csum + (size_t)slot * 2 * H, *px = pr + H;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        pr[c * 8 + e] = sr[i][e];
-                        px[c * 8 + e] = sx[i][e];
-                    }
+                    red[wave][0][c * 8 + e] = a[i][e];
+                    red[wave][1][c * 8 + e] = b[i][e];
                 }
             }
         }
-    } else {
-        constexpr int HMAX = 64 * 8 * NV;
-        __shared__ float red[W][2][HMAX];
-        const int wave = threadIdx.x >> 6;
-        auto fold = [&](const float (&a)[NV][8], const float (&b)[NV][8], float *__restrict__ out) {
+        __syncthreads();
+        for (int c = threadIdx.x; c < 2 * H; c += 64 * W) {
+            const int which = c >= H ? 1 : 0, col = c - which * H;
+            float sum = red[0][which][col];
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                const int c = lane + 64 * i;
-                if (c < nvec) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        red[wave][0][c * 8 + e] = a[i][e];
-                        red[wave][1][c * 8 + e] = b[i][e];
-                    }
-                }
-            }
-            __syncthreads();
-            for (int c = threadIdx.x; c < 2 * H; c += 64 * W) {
-                const int which = c >= H ? 1 : 0, col = c - which * H;
-                float sum = red[0][which][col];
-#pragma unroll
-                for (int w = 1; w < W; ++w) sum += red[w][which][col];
-                out[c] = sum;   // [2][H]
-            }
-            __syncthreads();
-        };
-        fold(dg, db, partial + (size_t)blockIdx.x * 2 * H);
-        if constexpr (CSUM) fold(sr, sx, csum + (size_t)blockIdx.x * 2 * H);
-    }
+            for (int w = 1; w < W; ++w) sum += red[w][which][col];
+            out[c] = sum;   // [2][H]
+        }
+        __syncthreads();
+    };
+    fold(dg, db, partial + (size_t)blockIdx.x * 2 * H);
+    if constexpr (CSUM) fold(sr, sx, csum + (size_t)blockIdx.x * 2 * H);
 }
 
 // out[c] = (accumulate ? out[c] : 0) + sum_p partial[p * stride + c]; fixed summation order.
@@ -721,8 +696,17 @@ void launch_norm_fwd(int norm, const void *x, const void *gamma, const void *bet
                            (const __bf16 *)gamma, (const __bf16 *)nullptr, (__bf16 *)h, stats, T, H, eps);
 }
 
-// rows of H <= 1024 elements, enough of them: 256 workgroups of eight row-walking waves, one partial each
+// rows of H <= 1024 elements, enough of them: 256 workgroups of eight row-walking waves (12300 x 1024: 22 us, a row per
+// workgroup 61)
 static bool norm_bwd_folds(int T, int H) { return H <= 1024 && T >= 2048; }
+// Otherwise a row per workgroup at a time, two workgroups of up to four waves to a CU or one of five to eight: 16327 x 4096
+// 97 us (1024 workgroups 108, 256 99; a row per wave with a partial each 117), 16400 x 3200 75 (89, 96; 96),
+// 1500 x 4096 16 (36), 32741 x 6144 276 (1024 workgroups 300; 256 threads with four vectors each 384).
+int norm_bwd_workgroups(int T, int H) {
+    const int n = norm_bwd_folds(T, H) || H > 4096 ? 256 : 512;
+    return T < n ? T : n;
+}
+// rows of partial sums that the workspace has room for (at least as many as workgroups)
 int norm_bwd_partials(int T, int H) { return norm_bwd_folds(T, H) ? 256 : T < 1024 ? T : 1024; }
 
 template <int NV, int W>
@@ -738,24 +722,17 @@ static void launch_norm_bwd_wave(int norm, const void *dh, const void *x, const 
 #undef OB_NBW
 }
 
-// csum (may be null): [norm_bwd_partials(T, H)][2][H] fp32, column sums of dres and of dx per partial
+// csum (may be null): [norm_bwd_workgroups(T, H)][2][H] fp32, column sums of dres and of dx per partial
 void launch_norm_bwd(int norm, const void *dh, const void *x, const float *stats, const void *gamma,
                      const void *dres, void *dx, float *partial, int T, int H, hipStream_t s, float *csum) {
     ProfScope prof(K_NORM_BWD, s, 8.0 * T * H);
-    const int nb = norm_bwd_partials(T, H);
+    const int nb = norm_bwd_workgroups(T, H);
     if (norm_bwd_folds(T, H)) {
         launch_norm_bwd_wave<2, 8>(norm, dh, x, stats, gamma, dres, dx, partial, csum, T, H, nb, s);
         return;
     }
-    // a wave per row while a row fits 8 vectors per lane and there are whole workgroups of rows
-    if (H <= 4096 && nb % 4 == 0) {
-        if (H <= 1024) launch_norm_bwd_wave<2, 4>(norm, dh, x, stats, gamma, dres, dx, partial, csum, T, H, nb / 4, s);
-        else if (H <= 2048) launch_norm_bwd_wave<4, 4>(norm, dh, x, stats, gamma, dres, dx, partial, csum, T, H, nb / 4, s);
-        else launch_norm_bwd_wave<8, 4>(norm, dh, x, stats, gamma, dres, dx, partial, csum, T, H, nb / 4, s);
-        return;
-    }
 #define OB_NB(LN, CS)                                                                                          \
-    hipLaunchKernelGGL((norm_bwd_kernel<LN, CS>), dim3(nb), dim3(NORM_THREADS), 0, s, (const __bf16 *)dh,       \
+    hipLaunchKernelGGL((norm_bwd_kernel<LN, CS>), dim3(nb), dim3((H / 16 + 63) / 64 * 64), 0, s, (const __bf16 *)dh, \
                        (const __bf16 *)x, stats, (const __bf16 *)gamma, (const __bf16 *)dres, (__bf16 *)dx,    \
                        partial, csum, T, H)
     if (norm == OB_LAYERNORM) { if (csum) OB_NB(true, true); else OB_NB(true, false); }

@@ -53,9 +53,11 @@ int gemm_tn_group(int count, const GemmTN *g, int K, void *ws, size_t ws_bytes, 
 // stats: LayerNorm [T,2] = (mean, rstd); RMSNorm [T,2] = (unused, rstd)
 void launch_norm_fwd(int norm, const void *x, const void *gamma, const void *beta, void *h,
                      float *stats, int T, int H, float eps, hipStream_t s);
-// dx = dres + norm_bwd(dh); partial [n_part, 2, H] fp32 sums of dgamma / dbeta
+// dx = dres + norm_bwd(dh); partial [norm_bwd_workgroups(T, H)][2][H] fp32 sums of dgamma / dbeta, in a region of
+// norm_bwd_partials(T, H) such rows
+int norm_bwd_workgroups(int T, int H);
 int norm_bwd_partials(int T, int H);
-// csum (may be null): [norm_bwd_partials(T, H)][2][H] fp32 column sums of dres and of dx (the bias gradients
+// csum (may be null): [norm_bwd_workgroups(T, H)][2][H] fp32 column sums of dres and of dx (the bias gradients
 // of the linears on either side of the norm), formed in the same pass
 void launch_norm_bwd(int norm, const void *dh, const void *x, const float *stats, const void *gamma,
                      const void *dres, void *dx, float *partial, int T, int H, hipStream_t s,

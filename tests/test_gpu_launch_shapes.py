@@ -6,7 +6,7 @@ import torch
 
 import paper_2407_20761_amd as ob
 import synth_inputs as si
-from gpu_util import bytes_buf, to_dev, to_np
+from gpu_util import bytes_buf, run_block, to_dev, to_np
 from oracle import block as orc
 from oracle import connector as orc_conn
 
@@ -146,3 +146,25 @@ def test_gemm_rectangular_tiles(layout, M, N, K):
     got = to_np(C)
     assert np.isfinite(got).all()
     assert np.abs(got[rows] - ref).max() <= 2.0 ** -8 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("hidden,T", [(64, 1), (64, 2051), (1024, 2047), (1088, 3), (2112, 700), (4096, 513), (4160, 257), (6144, 40),
+                                      (8192, 300)])
+@pytest.mark.parametrize("norm", [si.NORM_LAYERNORM, si.NORM_RMSNORM])
+def test_norm_bwd_widths(hidden, T, norm):
+    """The norm's backward at the widths and row counts where its launch shape changes (folded waves; one to eight waves to a
+    row; fewer rows than workgroups, one more), through a block whose other sizes are the smallest: input and gain / beta /
+    bias gradients against the oracle."""
+    print(f"norm bwd hidden={hidden} T={T} norm={norm}", flush=True)
+    ln = norm == si.NORM_LAYERNORM
+    shape = si.small_shape(hidden=hidden, n_q_heads=1, n_kv_heads=1, head_dim=64, mlp_dim=64, norm=norm, mlp=si.MLP_GELU,
+                           mask=si.MASK_BIDIR, has_bias=ln, norm_eps=1e-5)
+    lens = [T] if T < 64 else [T - 33, 33]
+    cu = si.lengths_to_cu(lens)
+    w = si.block_weights(shape, seed=2)
+    x, dy = si.activations(T, hidden, seed=3, std=1.0)
+    _, y, dx, g = run_block(shape, w, x, dy, cu)
+    y_ref, cache = orc.block_fwd(shape, w, x, cu)
+    dx_ref, g_ref, _ = orc.block_bwd(shape, w, cache, dy, cu)
+    for n, got, ref in [("y", y, y_ref), ("dx", dx, dx_ref)] + [(n, g[n], g_ref[n]) for n in g]:
+        assert np.abs(got - ref).max() <= TOL * np.abs(ref).max(), n
