@@ -224,15 +224,11 @@ __global__ __launch_bounds__(WG) void subsample_norm_bwd_kernel(
     write(db, partial + (size_t)blockIdx.x * 2 * W + W);
 }
 
-// SCATTER: big[rows[i]] = small[i];  otherwise small[i] = big[rows[i]].  One workgroup per row.
-template <bool SCATTER>
-__global__ __launch_bounds__(THREADS) void rows_copy_kernel(__bf16 *__restrict__ small, __bf16 *__restrict__ big,
-                                                            const int32_t *__restrict__ rows, int H) {
+// small[i] = big[rows[i]].  One workgroup per row.
+__global__ __launch_bounds__(THREADS) void rows_gather_kernel(__bf16 *__restrict__ small, const __bf16 *__restrict__ big,
+                                                              const int32_t *__restrict__ rows, int H) {
     const size_t i = blockIdx.x, r = (size_t)rows[i];
-    for (int c8 = threadIdx.x; c8 < H / 8; c8 += THREADS) {
-        if (SCATTER) *(bf16x8 *)(big + r * H + c8 * 8) = *(const bf16x8 *)(small + i * H + c8 * 8);
-        else *(bf16x8 *)(small + i * H + c8 * 8) = *(const bf16x8 *)(big + r * H + c8 * 8);
-    }
+    for (int c8 = threadIdx.x; c8 < H / 8; c8 += THREADS) *(bf16x8 *)(small + i * H + c8 * 8) = *(const bf16x8 *)(big + r * H + c8 * 8);
 }
 
 }  // namespace
@@ -270,16 +266,9 @@ int launch_subsample_norm_bwd_wgrad(const void *dun, const void *v, const float 
 }
 #undef OB_BY_WIDTH
 
-void launch_rows_scatter(const void *small, void *big, const int32_t *rows_dev, int n_rows, int H, hipStream_t s) {
-    ProfScope prof(K_ROWS, s, 4.0 * n_rows * H);
-    hipLaunchKernelGGL(rows_copy_kernel<true>, dim3(n_rows), dim3(THREADS), 0, s, (__bf16 *)small, (__bf16 *)big,
-                       rows_dev, H);
-}
-
 void launch_rows_gather(void *small, const void *big, const int32_t *rows_dev, int n_rows, int H, hipStream_t s) {
     ProfScope prof(K_ROWS, s, 4.0 * n_rows * H);
-    hipLaunchKernelGGL(rows_copy_kernel<false>, dim3(n_rows), dim3(THREADS), 0, s, (__bf16 *)small, (__bf16 *)big,
-                       rows_dev, H);
+    hipLaunchKernelGGL(rows_gather_kernel, dim3(n_rows), dim3(THREADS), 0, s, (__bf16 *)small, (const __bf16 *)big, rows_dev, H);
 }
 
 }  // namespace ob

@@ -27,7 +27,7 @@ CSaved saved_layout(const CDims &m) {
 }
 CWork work_layout(const CDims &m) {
     Bump L; CWork w; const size_t n = m.n_tok;
-    w.z = L.take(n * m.Ht * 2);      // z in the forward, dz in the backward
+    w.z = L.take(n * m.Ht * 2);      // dz
     w.da_bytes = n * m.Ht * 2;
     w.da = L.take(w.da_bytes); w.dh = L.take(n * m.Ht * 2); w.dun = L.take(n * m.W * 2);
     const size_t p_norm = (size_t)subsample_wgrad_partials(m.n_tok) * 2 * m.W * 4;
@@ -119,13 +119,13 @@ extern "C" int ob_connector_fwd(const ob_connector_desc *desc, const ob_connecto
     if (!saved || saved_bytes < sv.total) return fail(OB_EWORKSPACE, "%s: saved buffer too small (%zu bytes given)", who, saved_bytes);
     if (!ws || ws_bytes < wk.total) return fail(OB_EWORKSPACE, "%s: workspace too small (%zu bytes given)", who, ws_bytes);
     hipStream_t s = (hipStream_t)hip_stream;
-    unsigned char *un = at(saved, sv.un), *h = at(saved, sv.h), *a = at(saved, sv.a), *z = at(ws, wk.z);
+    unsigned char *un = at(saved, sv.un), *h = at(saved, sv.h), *a = at(saved, sv.a);
     launch_subsample_norm_fwd(v, w->n_g, w->n_b, un, (float *)at(saved, sv.stats), m.n_tok, m.g, m.Hv, desc->norm_eps, s);
     void *gws = wk.gemm_bytes ? at(ws, wk.gemm) : nullptr;
     launch_gemm_nt(m.n_tok, m.Ht, m.W, un, m.W, w->w1, m.W, h, m.Ht, w->b1, nullptr, 0, s, 0, gws);
     launch_act_fwd(OB_GELU, h, a, m.n_tok, m.Ht, s);
-    launch_gemm_nt(m.n_tok, m.Ht, m.Ht, a, m.Ht, w->w2, m.Ht, z, m.Ht, w->b2, nullptr, 0, s, 0, gws);
-    launch_rows_scatter(z, x_llm, dst_rows_dev, m.n_tok, m.Ht, s);
+    // z = a W2^T + b2, its rows straight onto the visual rows of the LLM batch
+    launch_gemm_nt_rows(m.n_tok, m.Ht, m.Ht, a, m.Ht, w->w2, m.Ht, x_llm, m.Ht, w->b2, dst_rows_dev, s, gws);
     return check_launch(who);
 }
 

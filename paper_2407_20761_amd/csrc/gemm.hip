@@ -525,11 +525,13 @@ struct KLoop {
 
 // One workgroup's work: tile (tile_m, tile_n) of C, whole, or (sliced) K steps [kz k_chunk, ...) of it with
 // the fp32 sums left at part[kz][tail_tile].
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS>
+// ROWS: row m of the result is row rows[m] of C (no residual).
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS, bool ROWS = false>
 __device__ __forceinline__ void gemm_tile(
     int M, int N, int K, const __bf16 *__restrict__ A, int lda, const __bf16 *__restrict__ B,
     int ldb, __bf16 *__restrict__ Cm, int ldc, const __bf16 *__restrict__ bias,
-    const __bf16 *R, int ldr, int tile_m, int tile_n, bool sliced, int kz, int tail_tile, const TailSplit &ts) {
+    const __bf16 *R, int ldr, int tile_m, int tile_n, bool sliced, int kz, int tail_tile, const TailSplit &ts,
+    const int32_t *__restrict__ rows = nullptr) {
     using C = Cfg<BM, BN, WM, WN>;
     constexpr int TA = C::TA, TB = C::TB;
     __shared__ __attribute__((aligned(1024))) unsigned char ring_mem[KLoop<BM, BN, WM, WN, AK, BKM, NS>::RING_BYTES];
@@ -674,7 +676,7 @@ __device__ __forceinline__ void gemm_tile(
                     bf16x8 o;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) o[e] = (__bf16)o8[e];
-                    __builtin_nontemporal_store(o, (bf16x8 *)(Cm + (size_t)m * ldc + n_out));
+                    __builtin_nontemporal_store(o, (bf16x8 *)(Cm + (size_t)(ROWS ? rows[m] : m) * ldc + n_out));
                 }
             }
         }
@@ -688,11 +690,11 @@ __device__ __forceinline__ void gemm_tile(
     else out(integral_constant<int, 0>{}, integral_constant<bool, true>{});
 }
 
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS, bool ROWS = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
     int M, int N, int K, const __bf16 *__restrict__ A, int lda, const __bf16 *__restrict__ B,
     int ldb, __bf16 *__restrict__ Cm, int ldc, const __bf16 *__restrict__ bias,
-    const __bf16 *R, int ldr, int tiles_m, int tiles_n, TailSplit ts) {
+    const __bf16 *R, int ldr, int tiles_m, int tiles_n, TailSplit ts, const int32_t *__restrict__ rows) {
     // workgroups [0, n_full): whole tiles; then slice after slice of the tail tiles
     const int pid = blockIdx.x, n_whole = ts.part ? ts.n_full : (int)gridDim.x;
     const bool sliced = pid >= n_whole;
@@ -701,8 +703,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
     const int tail_tile = sliced ? xcd_chunk((pid - n_whole) % ts.n_tail, ts.n_tail, interleave) : 0;
     int tile_m, tile_n;
     tile_of_id(sliced ? n_whole + tail_tile : xcd_chunk(pid, n_whole, interleave), tiles_m, tiles_n, tile_m, tile_n);
-    gemm_tile<BM, BN, WM, WN, AK, BKM, NS>(M, N, K, A, lda, B, ldb, Cm, ldc, bias, R, ldr, tile_m, tile_n, sliced, kz,
-                                       tail_tile, ts);
+    gemm_tile<BM, BN, WM, WN, AK, BKM, NS, ROWS>(M, N, K, A, lda, B, ldb, Cm, ldc, bias, R, ldr, tile_m, tile_n, sliced, kz,
+                                       tail_tile, ts, rows);
 }
 
 // Several GEMMs of one layout over the same contraction length K in ONE launch (the weight gradients of a
@@ -742,10 +744,10 @@ template __global__ void gemm_group_kernel<256, 256, 2, 2, true, true, 4>(GemmGr
 template __global__ void gemm_group_kernel<128, 128, 2, 2, true, true, 4>(GemmGroup, int, TailSplit);
 template __global__ void gemm_group_kernel<64, 64, 2, 2, true, true, 8>(GemmGroup, int, TailSplit);
 
-#define OB_GEMM_INSTANCE(BM, BN, AK, BKM, NS)                                                        \
-    template __global__ void gemm_kernel<BM, BN, 2, 2, AK, BKM, NS>(                              \
+#define OB_GEMM_INSTANCE(BM, BN, AK, BKM, NS, ...)                                                        \
+    template __global__ void gemm_kernel<BM, BN, 2, 2, AK, BKM, NS __VA_OPT__(,) __VA_ARGS__>(                              \
         int, int, int, const __bf16 *, int, const __bf16 *, int, __bf16 *, int, const __bf16 *,    \
-        const __bf16 *, int, int, int, TailSplit);
+        const __bf16 *, int, int, int, TailSplit, const int32_t *);
 OB_GEMM_INSTANCE(256, 256, false, false, 4)
 OB_GEMM_INSTANCE(128, 128, false, false, 4)
 OB_GEMM_INSTANCE(128, 128, false, false, 8)
@@ -758,6 +760,11 @@ OB_GEMM_INSTANCE(256, 256, false, true, 4)
 OB_GEMM_INSTANCE(128, 128, false, true, 4)
 OB_GEMM_INSTANCE(256, 256, true, true, 4)
 OB_GEMM_INSTANCE(128, 128, true, true, 4)
+OB_GEMM_INSTANCE(256, 256, false, false, 4, true)
+OB_GEMM_INSTANCE(128, 128, false, false, 4, true)
+OB_GEMM_INSTANCE(128, 128, false, false, 8, true)
+OB_GEMM_INSTANCE(192, 256, false, false, 4, true)
+OB_GEMM_INSTANCE(64, 64, false, false, 8, true)
 #undef OB_GEMM_INSTANCE
 
 // C = sum over the slices of the tail tiles' fp32 sums (+ bias) (+ R); 8 outputs per lane, slices
@@ -765,7 +772,7 @@ OB_GEMM_INSTANCE(128, 128, true, true, 4)
 template <int BM, int BN>
 __global__ __launch_bounds__(256) void tail_sum_kernel(TailSplit ts, int M, int N, int tiles_m, int tiles_n,
                                                        const __bf16 *__restrict__ bias, const __bf16 *R, int ldr,
-                                                       __bf16 *__restrict__ Cm, int ldc) {
+                                                       __bf16 *__restrict__ Cm, int ldc, const int32_t *__restrict__ rows) {
     constexpr int PER_TILE = BM * BN / 8 / 256;      // workgroups per tile
     const int t = blockIdx.x / PER_TILE;
     const int e = ((blockIdx.x % PER_TILE) * 256 + threadIdx.x) * 8;
@@ -796,7 +803,7 @@ __global__ __launch_bounds__(256) void tail_sum_kernel(TailSplit ts, int M, int 
     bf16x8 o;
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = (__bf16)o8[i];
-    *(bf16x8 *)(Cm + (size_t)m * ldc + n) = o;
+    *(bf16x8 *)(Cm + (size_t)(rows ? rows[m] : m) * ldc + n) = o;
 }
 
 // the same for the tail tiles of a group of GEMMs
@@ -970,28 +977,34 @@ Plan make_plan(int layout, int M, int N, int K, size_t scratch) {
 
 template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS>
 void launch_tile(int M, int N, int K, const void *A, int lda, const void *B, int ldb, void *C, int ldc,
-                 const void *bias, const void *R, int ldr, float *part, const Plan &p, hipStream_t s) {
+                 const void *bias, const void *R, int ldr, float *part, const Plan &p, const int32_t *rows, hipStream_t s) {
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const TailSplit ts{p.splits > 1 ? part : nullptr, p.n_full, p.n_tail, p.splits, p.k_chunk};
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM, NS>), dim3(p.n_full + p.n_tail * p.splits),
-                       dim3(WM * WN * 64), 0, s, M, N, K, (const __bf16 *)A, lda, (const __bf16 *)B, ldb,
-                       (__bf16 *)C, ldc, (const __bf16 *)bias, (const __bf16 *)R, ldr, tiles_m, tiles_n, ts);
+    const dim3 grid(p.n_full + p.n_tail * p.splits), block(WM * WN * 64);
+#define OB_GEMM_ARGS M, N, K, (const __bf16 *)A, lda, (const __bf16 *)B, ldb, (__bf16 *)C, ldc, (const __bf16 *)bias,     \
+                     (const __bf16 *)R, ldr, tiles_m, tiles_n, ts, rows
+    if constexpr (!AK && !BKM) {
+        if (rows) hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM, NS, true>), grid, block, 0, s, OB_GEMM_ARGS);
+        else hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM, NS>), grid, block, 0, s, OB_GEMM_ARGS);
+    } else
+        hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM, NS>), grid, block, 0, s, OB_GEMM_ARGS);
+#undef OB_GEMM_ARGS
     if (p.splits > 1)
         hipLaunchKernelGGL((tail_sum_kernel<BM, BN>), dim3(p.n_tail * (BM * BN / 8 / 256)), dim3(256), 0, s, ts, M, N,
-                           tiles_m, tiles_n, (const __bf16 *)bias, (const __bf16 *)R, ldr, (__bf16 *)C, ldc);
+                           tiles_m, tiles_n, (const __bf16 *)bias, (const __bf16 *)R, ldr, (__bf16 *)C, ldc, rows);
 }
 
 // `part` (may be null: nothing is split) has room for scratch_bytes()
 template <bool AK, bool BKM>
 void launch_layout(int layout, int M, int N, int K, const void *A, int lda, const void *B, int ldb, void *C, int ldc,
-                   const void *bias, const void *R, int ldr, float *part, hipStream_t s) {
+                   const void *bias, const void *R, int ldr, float *part, hipStream_t s, const int32_t *rows = nullptr) {
     const Plan p = make_plan(layout, M, N, K, part ? scratch_bytes(M, N, K) : 0);
-    if (p.kind == BIG) launch_tile<256, 256, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
-    else if (p.kind == SMALL) launch_tile<128, 128, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
-    else if (p.kind == FINE) launch_tile<64, 64, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
+    if (p.kind == BIG) launch_tile<256, 256, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, rows, s);
+    else if (p.kind == SMALL) launch_tile<128, 128, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, rows, s);
+    else if (p.kind == FINE) launch_tile<64, 64, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, rows, s);
     else if (p.kind == MID) {
-        if constexpr (!AK) launch_tile<192, 256, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
-    } else if constexpr (!AK && !BKM) launch_tile<128, 128, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, s);
+        if constexpr (!AK) launch_tile<192, 256, 2, 2, AK, BKM, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, rows, s);
+    } else if constexpr (!AK && !BKM) launch_tile<128, 128, 2, 2, AK, BKM, 8>(M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, part, p, rows, s);
 }
 
 // The scratch of a group of "TN" GEMMs over one K: 256 x 256 tiles, the slices of the combined list's tail.
@@ -1010,6 +1023,12 @@ void launch_gemm_nt(int M, int N, int K, const void *A, int lda, const void *B, 
                     int ldc, const void *bias, const void *R, int ldr, hipStream_t s, int k_algo, void *ws) {
     ProfScope prof(K_GEMM, s, 2.0 * M * N * (k_algo > 0 ? k_algo : K));
     launch_layout<false, false>(0, M, N, K, A, lda, B, ldb, C, ldc, bias, R, ldr, (float *)ws, s);
+}
+// the same with row m of the result stored as row rows[m] of C
+void launch_gemm_nt_rows(int M, int N, int K, const void *A, int lda, const void *B, int ldb, void *C, int ldc,
+                         const void *bias, const int32_t *rows, hipStream_t s, void *ws) {
+    ProfScope prof(K_GEMM, s, 2.0 * M * N * K);
+    launch_layout<false, false>(0, M, N, K, A, lda, B, ldb, C, ldc, bias, nullptr, 0, (float *)ws, s, rows);
 }
 
 // The weight gradients of a block in one launch: C_p[M_p, N_p] = A_p[K, M_p]^T B_p[K, N_p] (+ R_p), p < count

@@ -39,6 +39,9 @@ struct ProfScope {
 void launch_gemm_nt(int M, int N, int K, const void *A, int lda, const void *B, int ldb, void *C,
                     int ldc, const void *bias, const void *R, int ldr, hipStream_t s,
                     int k_algo = 0, void *ws = nullptr);
+// row m of the product is stored as row rows[m] of C (rows: device memory, distinct entries)
+void launch_gemm_nt_rows(int M, int N, int K, const void *A, int lda, const void *B, int ldb, void *C, int ldc,
+                         const void *bias, const int32_t *rows, hipStream_t s, void *ws);
 size_t gemm_workspace_bytes(int layout, int M, int N, int K);
 int gemm_any(int layout, int M, int N, int K, const void *A, const void *B, void *C,
              const void *bias, const void *R, void *ws, size_t ws_bytes, hipStream_t s);
@@ -100,8 +103,7 @@ void launch_subsample_norm_fwd(const void *v, const void *gamma, const void *bet
 int launch_subsample_norm_bwd_wgrad(const void *dun, const void *v, const float *stats, const void *gamma, void *dv,
                                     float *partial, int max_partials, int n_tok, int n_tiles, int g, int Hv, hipStream_t s);
 int subsample_wgrad_partials(int n_tok);   // rows of partial sums that the workspace has a region of its own for
-// big[rows[i]] = small[i]  /  small[i] = big[rows[i]];  rows of H bf16 elements, H % 8 == 0
-void launch_rows_scatter(const void *small, void *big, const int32_t *rows_dev, int n_rows, int H, hipStream_t s);
+// small[i] = big[rows[i]];  rows of H bf16 elements, H % 8 == 0
 void launch_rows_gather(void *small, const void *big, const int32_t *rows_dev, int n_rows, int H, hipStream_t s);
 
 // ---- attention (attention.hip) ---------------------------------------------------------------

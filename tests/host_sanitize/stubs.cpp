@@ -16,6 +16,8 @@ namespace ob {
 
 void launch_gemm_nt(int, int, int, const void *, int, const void *, int, void *, int, const void *, const void *, int,
                     hipStream_t, int, void *) { OB_STUB("launch_gemm_nt"); }
+void launch_gemm_nt_rows(int, int, int, const void *, int, const void *, int, void *, int, const void *, const int32_t *,
+                         hipStream_t, void *) { OB_STUB("launch_gemm_nt_rows"); }
 size_t gemm_workspace_bytes(int, int, int, int) { return 0; }
 size_t gemm_tn_group_workspace_bytes(int, const GemmTN *, int) { return 0; }
 int gemm_tn_group(int, const GemmTN *, int, void *, size_t, hipStream_t) { OB_STUB("gemm_tn_group"); }
@@ -40,7 +42,6 @@ void launch_subsample_norm_fwd(const void *, const void *, const void *, void *,
 int launch_subsample_norm_bwd_wgrad(const void *, const void *, const float *, const void *, void *, float *, int, int, int, int,
                                     int, hipStream_t) { OB_STUB("launch_subsample_norm_bwd_wgrad"); }
 int subsample_wgrad_partials(int n_tok) { return n_tok < 256 ? n_tok : 256; }
-void launch_rows_scatter(const void *, void *, const int32_t *, int, int, hipStream_t) { OB_STUB("launch_rows_scatter"); }
 void launch_rows_gather(void *, const void *, const int32_t *, int, int, hipStream_t) { OB_STUB("launch_rows_gather"); }
 void launch_attn_fwd(const void *, const void *, const void *, void *, float *, int, int, int, const ob_segments *, int,
                      int, int, float, int, hipStream_t) { OB_STUB("launch_attn_fwd"); }
