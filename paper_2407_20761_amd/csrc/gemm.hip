@@ -4,7 +4,9 @@
 //   "NT" A[M,K] B[N,K] (forward)   "NN" A[M,K] B[K,N] (dgrad)   "TN" A[K,M] B[K,N] (wgrad, K = tokens)
 //
 // One workgroup (4 wavefronts, each a 128x128 block of 8x8 MFMA 16x16x32 tiles, 256 accumulator
-// registers) owns a 256x256 tile of C and walks K in steps of 32 over a ring of four LDS slots.  The
+// registers) owns a 256x256 tile of C and walks K in steps of 32 over a ring of four LDS slots; launches
+// that such tiles would leave partly idle take 192x256, 128x128 or 64x64 ones, the last two also over
+// a ring of eight slots (which one, and why: estimate_us below).  The
 // 16x16x32 shape reads and writes half the accumulator registers per FLOP of the 32x32x16 one; under
 // sustained load the chip is power-limited, and a register-fed loop of it sustains 2010 against
 // 1725-1790 TFLOP/s on random data.
@@ -878,7 +880,7 @@ bool cut(TileKind kind, int tiles, int nk, int z, Plan &p) {
 
 // Duration of a launch in microseconds.  Fitted to 1344 GEMMs (64 - 16400 rows on either side, the linears of seven
 // models, the three layouts; cold operands, N(0, 1) data), each measured with every kind of tile, whole and with
-// its tail in 2, 3, 4, 6, 8 slices: 8 % off in the mean, and the choices made by it are 0.8 % slower than the best
+// its tail in 2, 3, 4, 6, 8 slices: 8 % off in the mean, and the choices made by it are 1.1 % slower than the best
 // ones measured (the estimate before it, with big and small tiles alone: 8 %).
 //  * big tiles come in rounds of one per CU, and the tiles of an incomplete last round take as long as a full one; a K
 //    step takes 1.23 on a full chip, 1.1 while half the chip or less is at work (the clock is higher), prologue and
@@ -918,7 +920,7 @@ double estimate_us(int layout, TileKind kind, int nk, const Plan &p) {
         t = (whole / cus * (nk + edge) + rounds * (k_tail + edge)) * step;
         break;
     }
-    case SMALL: t = alone ? (k_tail + 2.86) * (layout == 0 ? 0.566 : 0.521) : paired(0.939, 1.17, 0.3, 0); break;
+    case SMALL: t = alone ? (k_tail + 2.86) * (layout == 0 ? 0.566 : 0.521) : paired(0.939, 1.17, 0.25, 0); break;
     case DEEP: t = whole / cus * (nk + 3.82) * 0.536 + ceil(tail / cus) * (k_tail + 3.82) * (alone ? 0.51 : 0.536); break;
     case FINE: t = alone ? (k_tail + 5.82) * 0.236 : paired(0.453, 3.0, 0.365, 0.955); break;
     }
