@@ -168,3 +168,48 @@ def test_norm_bwd_widths(hidden, T, norm):
     dx_ref, g_ref, _ = orc.block_bwd(shape, w, cache, dy, cu)
     for n, got, ref in [("y", y, y_ref), ("dx", dx, dx_ref)] + [(n, g[n], g_ref[n]) for n in g]:
         assert np.abs(got - ref).max() <= TOL * np.abs(ref).max(), n
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(2049, 8192, 1024), (1030, 16384, 768), (4444, 4096, 2048), (2500, 14336, 1024)])
+def test_gemm_row_cut(layout, M, N, K):
+    """Launches whose last rows go out on their own, behind whole rounds of tiles: one row, a few, more than a tile; with
+    bias, residual and slice sums allowed.  Rows on both sides of every possible cut against fp64; a row's values do not
+    depend on what is launched with it, up to the rounding of sums in another order where a contraction is split."""
+    print(f"row cut layout={layout} {M} {N} {K}", flush=True)
+    rng = np.random.default_rng(M + N + K + layout)
+    A = si.round_to_bf16(rng.standard_normal((M, K), dtype=np.float32))
+    B = si.round_to_bf16(rng.standard_normal((N, K), dtype=np.float32))
+    bias = si.round_to_bf16(rng.standard_normal((N,), dtype=np.float32))
+    R = si.round_to_bf16(rng.standard_normal((M, N), dtype=np.float32) * 4)
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = bytes_buf(max(ob.ob_gemm_workspace_bytes(layout, M, N, K), 16))
+    ob.ob_gemm_bf16(layout, M, N, K, to_dev(A), to_dev(B if layout == 0 else np.ascontiguousarray(B.T)), C, to_dev(bias), to_dev(R), ws)
+    edges = np.concatenate([np.arange(t, M, t) for t in (192, 256)])
+    rows = np.unique(np.concatenate([edges - 1, edges, [0, M - 2, M - 1]]))
+    ref = A[rows].astype(np.float64) @ B.astype(np.float64).T + bias + R[rows]
+    got = to_np(C)
+    assert np.isfinite(got).all()
+    assert np.abs(got[rows] - ref).max() <= 2.0 ** -8 * np.abs(ref).max()
+
+
+def test_connector_row_cut():
+    """The hand-over's GEMMs cut by rows (4352 tokens, 4096 wide): both launches of the last store through the row list.  The first
+    and the last tile of the batch against the oracle on those tiles alone; rows that no token has stay as they were."""
+    Hv, Ht, grid, tiles = 64, 4096, 32, 17
+    print(f"connector row cut {Hv} {Ht} {grid} {tiles}", flush=True)
+    rng = np.random.default_rng(11)
+    per, n_tok, rows_v = 256, tiles * 256, grid * grid + 1
+    w = si.connector_weights(Hv, Ht, seed=1)
+    v = si.round_to_bf16(rng.standard_normal((tiles * rows_v, Hv), dtype=np.float32))
+    llm = n_tok + 5
+    dst = rng.permutation(llm)[:n_tok].astype(np.int32)
+    desc = ob.make_connector_desc(Hv, Ht, grid, 1e-5)
+    x = torch.full((llm, Ht), 3.0, dtype=torch.bfloat16, device="cuda")
+    saved, ws = bytes_buf(ob.ob_connector_saved_bytes(desc, tiles)), bytes_buf(ob.ob_connector_workspace_bytes(desc, tiles))
+    ob.ob_connector_fwd(desc, {n: to_dev(t) for n, t in w.items()}, to_dev(v), tiles, ob.RowIndex(dst), x, llm, saved, ws)
+    got = to_np(x)
+    assert (np.delete(got, dst, axis=0) == 3.0).all()
+    for t in (0, tiles - 1):
+        ref, _ = orc_conn.connector_fwd(w, v[t * rows_v:(t + 1) * rows_v], 1, grid, 1e-5, np.zeros((per, Ht)), np.arange(per))
+        assert np.abs(got[dst[t * per:(t + 1) * per]] - ref).max() <= TOL * np.abs(ref).max()
