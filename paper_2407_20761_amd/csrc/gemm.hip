@@ -891,7 +891,8 @@ bool cut(TileKind kind, int tiles, int nk, int z, Plan &p) {
 //  * a small tile with a CU to itself is bound by what the CU takes in from beyond the L2 (50 - 75 bytes per ns, also
 //    with a ring twice as deep, with eight waves, or with lines fetched ahead by another wave: 0.5 per K step of 32 KB).
 //    Two to a CU take 0.94 each, and, out of step as they are, hide each other's epilogues and fill the last round
-//    gradually;
+//    gradually, but a launch that gives any CU two lasts as long as two (300 tiles over K = 7175 106, 93 big ones in two
+//    slices 91);
 //  * a deep one has the CU to itself as well, with four instead of two K steps on their way.  Only "NT" has it: there
 //    B's loads have a slot and a half to land in the shallow ring, too little when the weights come from HBM
 //    (557 x 4096 x 4096: 50 -> 36 us; 557 x 6144 x 4096: 51 -> 38), and it keeps its rate when tiles are many enough for
@@ -920,7 +921,7 @@ double estimate_us(int layout, TileKind kind, int nk, const Plan &p) {
         t = (whole / cus * (nk + edge) + rounds * (k_tail + edge)) * step;
         break;
     }
-    case SMALL: t = alone ? (k_tail + 2.86) * (layout == 0 ? 0.566 : 0.521) : paired(0.939, 1.17, 0.25, 0); break;
+    case SMALL: t = alone ? (k_tail + 2.86) * (layout == 0 ? 0.566 : 0.521) : paired(0.939, 1.17, 0.25, 0.95); break;
     case DEEP: t = whole / cus * (nk + 3.82) * 0.536 + ceil(tail / cus) * (k_tail + 3.82) * (alone ? 0.51 : 0.536); break;
     case FINE: t = alone ? (k_tail + 5.82) * 0.236 : paired(0.453, 3.0, 0.365, 0.955); break;
     }
