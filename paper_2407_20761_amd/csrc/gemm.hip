@@ -885,7 +885,8 @@ bool cut(TileKind kind, int tiles, int nk, int z, Plan &p) {
 //  * big tiles come in rounds of one per CU, and the tiles of an incomplete last round take as long as a full one; a K
 //    step takes 1.23 on a full chip, 1.1 while half the chip or less is at work (the clock is higher), prologue and
 //    epilogue as much as 4.67 more (nothing else runs on the CU meanwhile);
-//  * a 192 x 256 tile takes 0.82 of a big one's time for 0.75 of its work: for rows that fit it better, or a round that
+//  * a 192 x 256 tile takes 0.82 of a big one's time (0.86 in the long contractions whose big tiles are dealt to the XCDs
+//    by patches: 11275 x 3200 x 12800, 767 tiles 715 us, 512 big ones and 73 in three slices 664) for 0.75 of its work: for rows that fit it better, or a round that
 //    it fills and big tiles do not (3072 x 4096 x 4096, 256 tiles instead of 192: 85 -> 76; 3075 x 3200 x 12800, 221
 //    instead of 169: 235 -> 208);
 //  * a small tile with a CU to itself is bound by what the CU takes in from beyond the L2 (50 - 75 bytes per ns, also
@@ -917,7 +918,7 @@ double estimate_us(int layout, TileKind kind, int nk, const Plan &p) {
     case MID:
     case BIG: {
         const double rounds = ceil(tail / cus), fill = (whole + tail) / (rounds * cus + whole);
-        const double edge = kind == MID ? 5.2 : 4.67, step = (1.1 + 0.13 * fmax(0.0, 2 * fill - 1)) * (kind == MID ? 0.82 : 1.0);
+        const double edge = kind == MID ? 5.2 : 4.67, step = (1.1 + 0.13 * fmax(0.0, 2 * fill - 1)) * (kind != MID ? 1.0 : nk * KSTEP < INTERLEAVE_MIN_K ? 0.82 : 0.86);
         t = (whole / cus * (nk + edge) + rounds * (k_tail + edge)) * step;
         break;
     }
@@ -958,13 +959,17 @@ size_t scratch_bytes(int M, int N, int K) {
     return scratch_plan(t_big <= t_small ? BIG : SMALL, fmin(t_big, t_small), big, small, nk).part_bytes();
 }
 
+// 192 x 256 tiles where they fill at least seven eighths of their columns (11275 x 640 x 2560, five sixths, inside a step:
+// "NT" 63, "NN" 47 us, small tiles 47 and 39; 12300 x 768 x 2112, all: 43 and 54)
+bool mid_fits(int layout, int N) { return layout != 2 && 8L * N >= 7L * 256 * ((N + 255) / 256); }
+
 // `scratch`: bytes for slice sums; t (may be null): the estimated duration
 Plan make_plan(int layout, int M, int N, int K, size_t scratch, double *t_out = nullptr) {
     const int nk = (K + KSTEP - 1) / KSTEP;
     Plan best{BIG, 0, 0, 1, 0}, p;
     double t_best = -1;
     for (TileKind kind : {BIG, SMALL, DEEP, FINE, MID}) {
-        if ((kind == DEEP && layout != 0) || (kind == MID && layout == 2)) continue;
+        if ((kind == DEEP && layout != 0) || (kind == MID && !mid_fits(layout, N))) continue;
         const int tiles = tiles_of(kind, M, N);
         p = Plan{kind, tiles, 0, 1, 0};
         const double t = estimate_us(layout, kind, nk, p);
@@ -1000,7 +1005,7 @@ RowCut make_row_cut(int layout, int M, int N, int K, size_t scratch) {
     const int nk = (K + KSTEP - 1) / KSTEP, cus = compute_units();
     for (TileKind kind : {BIG, MID}) {
         const int tn = tiles_of(kind, 1, N), tiles = tiles_of(kind, M, N);
-        if (tiles <= cus) continue;
+        if (tiles <= cus || (kind == MID && !mid_fits(layout, N))) continue;
         const int m = (int)((long)(tiles / cus) * cus / tn) * tile_rows(kind);
         if (m == 0 || m >= M) continue;
         const Plan head{kind, tiles_of(kind, m, N), 0, 1, 0};
@@ -1087,8 +1092,8 @@ void launch_gemm_nt_rows(int M, int N, int K, const void *A, int lda, const void
 // the last tiles of one GEMM (with their read of R) hide behind the next one's: for up to 8K tokens it is
 // the faster way wherever the estimate does not promise the opposite (backward of a block, us, one by one -> grouped: 300M
 // ViT 1025 tokens 250 -> 226, 12300 1042 -> 940; 6B ViT 3075 1808 -> 1709; 7B model 557 770 -> 744, 4000 3091 -> 3007).
-// Longer contractions keep their own launch order over the XCDs (see INTERLEAVE_MIN_K) unless it promises 10 % (6B ViT
-// 16400 tokens, promised 5 %: 7550 -> 7600; 7B model 16327, 1 %: 11664 -> 11693).
+// Longer contractions keep their own launch order over the XCDs (see INTERLEAVE_MIN_K) unless it promises 7 % (the four
+// gradients of the 6B ViT over 11275 tokens, promised 9 %: 2242 -> 2077; its backward over 16400, promised 5 %: 7550 -> 7600; 7B model 16327, 1 %: 11664 -> 11693).
 size_t gemm_tn_group_workspace_bytes(int count, const GemmTN *g, int K) {
     int total = 0;
     size_t single = 0;
@@ -1119,7 +1124,7 @@ int gemm_tn_group(int count, const GemmTN *g, int K, void *ws, size_t ws_bytes, 
         const double t = estimate_us(2, kind, nk, q);
         if (t < t_group) { t_group = t; p = q; }
     }
-    if (count == 1 || !ws || ws_bytes < p.part_bytes() || t_group > (K < INTERLEAVE_MIN_K ? 1.0 : 0.9) * t_single) {
+    if (count == 1 || !ws || ws_bytes < p.part_bytes() || t_group > (K < INTERLEAVE_MIN_K ? 1.0 : 0.93) * t_single) {
         for (int i = 0; i < count; ++i)
             if (int rc = gemm_any(2, g[i].M, g[i].N, K, g[i].A, g[i].B, g[i].C, nullptr, g[i].R, ws, ws_bytes, s)) return rc;
         return OB_OK;
