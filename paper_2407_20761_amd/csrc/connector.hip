@@ -233,8 +233,6 @@ __global__ __launch_bounds__(THREADS) void rows_gather_kernel(__bf16 *__restrict
 
 }  // namespace
 
-int subsample_max_width() { return 16384; }
-
 // workgroups that there are tokens for
 static int token_groups(int n_tok, int Hv) { return Hv <= 1024 ? (n_tok + 3) / 4 : Hv <= 2048 ? (n_tok + 1) / 2 : n_tok; }
 #define OB_BY_WIDTH(KERNEL, GRID, ...)                                                                          \
@@ -251,8 +249,6 @@ void launch_subsample_norm_fwd(const void *v, const void *gamma, const void *bet
     OB_BY_WIDTH(subsample_norm_fwd_kernel, dim3(wgs < 512 ? wgs : 512), (const __bf16 *)v, (const __bf16 *)gamma,
                 (const __bf16 *)beta, (__bf16 *)un, stats, n_tok, g, Hv, eps);
 }
-
-int subsample_wgrad_partials(int n_tok) { return n_tok < 64 ? n_tok : 64; }
 
 int launch_subsample_norm_bwd_wgrad(const void *dun, const void *v, const float *stats, const void *gamma, void *dv,
                                     float *partial, int max_partials, int n_tok, int n_tiles, int g, int Hv, hipStream_t s) {

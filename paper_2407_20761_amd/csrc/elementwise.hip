@@ -696,19 +696,6 @@ void launch_norm_fwd(int norm, const void *x, const void *gamma, const void *bet
                            (const __bf16 *)gamma, (const __bf16 *)nullptr, (__bf16 *)h, stats, T, H, eps);
 }
 
-// rows of H <= 1024 elements, enough of them: 256 workgroups of eight row-walking waves (12300 x 1024: 22 us, a row per
-// workgroup 61)
-static bool norm_bwd_folds(int T, int H) { return H <= 1024 && T >= 2048; }
-// Otherwise a row per workgroup at a time, two workgroups of up to four waves to a CU or one of five to eight: 16327 x 4096
-// 97 us (1024 workgroups 108, 256 99; a row per wave with a partial each 117), 16400 x 3200 75 (89, 96; 96),
-// 1500 x 4096 16 (36), 32741 x 6144 276 (1024 workgroups 300; 256 threads with four vectors each 384).
-int norm_bwd_workgroups(int T, int H) {
-    const int n = norm_bwd_folds(T, H) || H > 4096 ? 256 : 512;
-    return T < n ? T : n;
-}
-// rows of partial sums that the workspace has room for (at least as many as workgroups)
-int norm_bwd_partials(int T, int H) { return norm_bwd_folds(T, H) ? 256 : T < 1024 ? T : 1024; }
-
 template <int NV, int W>
 static void launch_norm_bwd_wave(int norm, const void *dh, const void *x, const float *stats, const void *gamma,
                                  const void *dres, void *dx, float *partial, float *csum, int T, int H, int wgs,
@@ -761,7 +748,6 @@ int launch_reduce_batch(const ReduceBatch &b, int accumulate, hipStream_t s) {
     return OB_OK;
 }
 
-int colsum_partials(int T) { return T < 256 ? T : 256; }
 
 void launch_colsum(const void *in, int T, int C, int ld, float *partial, hipStream_t s) {
     ProfScope prof(K_COLSUM, s, 2.0 * T * C);

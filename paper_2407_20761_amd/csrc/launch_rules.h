@@ -1,0 +1,29 @@
+// How many workgroups, and rows of partial sums, the row kernels and column reductions take for a size: shared by the
+// kernels' launchers, the buffer layouts, and a host-only build.
+#pragma once
+
+namespace ob {
+
+// Norm backward.
+// rows of H <= 1024 elements, enough of them: 256 workgroups of eight row-walking waves (12300 x 1024: 22 us, a row per
+// workgroup 61)
+inline bool norm_bwd_folds(int T, int H) { return H <= 1024 && T >= 2048; }
+// Otherwise a row per workgroup at a time, two workgroups of up to four waves to a CU or one of five to eight: 16327 x 4096
+// 97 us (1024 workgroups 108, 256 99; a row per wave with a partial each 117), 16400 x 3200 75 (89, 96; 96),
+// 1500 x 4096 16 (36), 32741 x 6144 276 (1024 workgroups 300; 256 threads with four vectors each 384).
+inline int norm_bwd_workgroups(int T, int H) {
+    const int n = norm_bwd_folds(T, H) || H > 4096 ? 256 : 512;
+    return T < n ? T : n;
+}
+// Rows of partial sums that the workspace has room for: at least as many as workgroups.  (Twice as many from 1024 rows on:
+// programs size buffers by what the size queries report, so the region stays as it is while the launch takes half.)
+inline int norm_bwd_partials(int T, int H) { return norm_bwd_folds(T, H) ? 256 : T < 1024 ? T : 1024; }
+
+// column sums of a [T, C] tensor
+inline int colsum_partials(int T) { return T < 256 ? T : 256; }
+
+// Hand-over: the widest row of its norm, and the rows of partial sums that the workspace has a region of its own for.
+inline int subsample_max_width() { return 16384; }
+inline int subsample_wgrad_partials(int n_tok) { return n_tok < 64 ? n_tok : 64; }
+
+}  // namespace ob

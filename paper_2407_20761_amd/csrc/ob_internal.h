@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/omnibal.h"
+#include "launch_rules.h"
 
 namespace ob {
 
@@ -58,8 +59,6 @@ void launch_norm_fwd(int norm, const void *x, const void *gamma, const void *bet
                      float *stats, int T, int H, float eps, hipStream_t s);
 // dx = dres + norm_bwd(dh); partial [norm_bwd_workgroups(T, H)][2][H] fp32 sums of dgamma / dbeta, in a region of
 // norm_bwd_partials(T, H) such rows
-int norm_bwd_workgroups(int T, int H);
-int norm_bwd_partials(int T, int H);
 // csum (may be null): [norm_bwd_workgroups(T, H)][2][H] fp32 column sums of dres and of dx (the bias gradients
 // of the linears on either side of the norm), formed in the same pass
 void launch_norm_bwd(int norm, const void *dh, const void *x, const float *stats, const void *gamma,
@@ -82,7 +81,6 @@ struct ReduceBatch {
 };
 // OB_EINVAL (nothing launched) when a job was dropped by add()
 int launch_reduce_batch(const ReduceBatch &b, int accumulate, hipStream_t s);
-int colsum_partials(int T);
 void launch_colsum(const void *in, int T, int C, int ld, float *partial, hipStream_t s);
 // partial [2][n_part][C]: the column sums of in0 and of in1, dense rows of C elements
 void launch_colsum_pair(const void *in0, const void *in1, int T, int C, int n_part, float *partial, hipStream_t s);
@@ -95,14 +93,12 @@ void launch_mask(const int32_t *cu_dev, int n_seg, int T, int mask, uint8_t *out
 
 // ---- ViT -> LLM hand-over (connector.hip) ------------------------------------------------------
 // n_tok = n_tiles * (g/2)^2 sub-sampled tokens of 4 Hv channels; stats [n_tok, 2] = (mean, rstd)
-int subsample_max_width();
 void launch_subsample_norm_fwd(const void *v, const void *gamma, const void *beta, void *un, float *stats,
                                int n_tok, int g, int Hv, float eps, hipStream_t s);
 // writes every row of dv [n_tiles (g^2 + 1), Hv] (class rows: zeros) and partial [n][2][4 Hv] fp32, gain sums then beta
 // sums; returns n <= max_partials
 int launch_subsample_norm_bwd_wgrad(const void *dun, const void *v, const float *stats, const void *gamma, void *dv,
                                     float *partial, int max_partials, int n_tok, int n_tiles, int g, int Hv, hipStream_t s);
-int subsample_wgrad_partials(int n_tok);   // rows of partial sums that the workspace has a region of its own for
 // small[i] = big[rows[i]];  rows of H bf16 elements, H % 8 == 0
 void launch_rows_gather(void *small, const void *big, const int32_t *rows_dev, int n_rows, int H, hipStream_t s);
 

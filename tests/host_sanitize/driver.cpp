@@ -195,7 +195,23 @@ static void validation_cases() {
     CHECK(ob_prof_num_classes() > 0 && ob_prof_class_name(0)[0] != 0 && ob_prof_class_name(-1)[0] == 0);
 }
 
+// the buffer sizes of a few blocks and hand-overs, one line each, for comparison with the shipped library's
+static void print_sizes() {
+    const int shapes[4][5] = {{256, 4, 4, 64, 1024}, {1024, 16, 16, 64, 4096}, {4096, 32, 8, 128, 14336}, {6144, 48, 8, 128, 16384}};
+    for (const auto &q : shapes)
+        for (int T : {9, 557, 964, 1500, 2049, 12300, 16327}) {
+            ob_block_desc d{q[0], q[1], q[2], q[3], q[4], OB_LAYERNORM, OB_GELU, OB_MASK_SEG_CAUSAL, OB_BF16, 0, 10000.f, 1e-5f, 1};
+            std::printf("block %d %d %d %d %d %d %zu %zu\n", q[0], q[1], q[2], q[3], q[4], T, ob_block_saved_bytes(&d, T), ob_block_workspace_bytes(&d, T));
+        }
+    for (int Hv : {64, 1024, 3200})
+        for (int tiles : {1, 5, 42}) {
+            ob_connector_desc d{Hv, 4096, 32, OB_BF16, 1e-5f};
+            std::printf("connector %d %d %zu %zu\n", Hv, tiles, ob_connector_saved_bytes(&d, tiles), ob_connector_workspace_bytes(&d, tiles));
+        }
+}
+
 int main() {
+    print_sizes();
     packer_cases();
     planner_cases();
     validation_cases();

@@ -1,6 +1,7 @@
-// Stand-ins for the device half of the library, for the host-only sanitizer build: the size helpers
-// return plain values, and every launcher aborts -- the driver only exercises calls that must be
-// refused by validation before anything is launched.
+// Stand-ins for the device half of the library, for the host-only sanitizer build: every
+// launcher aborts -- the driver only exercises calls that must be refused by validation before
+// anything is launched.  (What sizes depend on is the library's own host code; the fp32 debug path's
+// layouts alone are stand-ins.)
 #include <cstdio>
 #include <cstdlib>
 
@@ -18,30 +19,23 @@ void launch_gemm_nt(int, int, int, const void *, int, const void *, int, void *,
                     hipStream_t, int, void *) { OB_STUB("launch_gemm_nt"); }
 void launch_gemm_nt_rows(int, int, int, const void *, int, const void *, int, void *, int, const void *, const int32_t *,
                          hipStream_t, void *) { OB_STUB("launch_gemm_nt_rows"); }
-size_t gemm_workspace_bytes(int, int, int, int) { return 0; }
-size_t gemm_tn_group_workspace_bytes(int, const GemmTN *, int) { return 0; }
 int gemm_tn_group(int, const GemmTN *, int, void *, size_t, hipStream_t) { OB_STUB("gemm_tn_group"); }
 int gemm_any(int, int, int, int, const void *, const void *, void *, const void *, const void *, void *, size_t,
              hipStream_t) { OB_STUB("gemm_any"); }
 void launch_norm_fwd(int, const void *, const void *, const void *, void *, float *, int, int, float, hipStream_t) { OB_STUB("launch_norm_fwd"); }
-int norm_bwd_workgroups(int T, int H) { return H <= 1024 || H > 4096 ? (T < 256 ? T : 256) : T < 512 ? T : 512; }
-int norm_bwd_partials(int T, int H) { return (H <= 1024 && T >= 2048) ? 256 : T < 1024 ? T : 1024; }
 void launch_norm_bwd(int, const void *, const void *, const float *, const void *, const void *, void *, float *, int,
                      int, hipStream_t, float *) { OB_STUB("launch_norm_bwd"); }
 void launch_reduce_partials(const float *, int, int, void *, int, int, hipStream_t) { OB_STUB("launch_reduce_partials"); }
 int launch_reduce_batch(const ReduceBatch &, int, hipStream_t) { OB_STUB("launch_reduce_batch"); }
-int colsum_partials(int T) { return T < 256 ? T : 256; }
 void launch_colsum(const void *, int, int, int, float *, hipStream_t) { OB_STUB("launch_colsum"); }
 void launch_colsum_pair(const void *, const void *, int, int, int, float *, hipStream_t) { OB_STUB("launch_colsum_pair"); }
 void launch_rotary(void *, int, int, int, int, const int32_t *, int, float, float, hipStream_t) { OB_STUB("launch_rotary"); }
 void launch_act_fwd(int, const void *, void *, int, int, hipStream_t) { OB_STUB("launch_act_fwd"); }
 void launch_act_bwd(int, const void *, const void *, void *, int, int, hipStream_t) { OB_STUB("launch_act_bwd"); }
 void launch_mask(const int32_t *, int, int, int, uint8_t *, hipStream_t) { OB_STUB("launch_mask"); }
-int subsample_max_width() { return 16384; }
 void launch_subsample_norm_fwd(const void *, const void *, const void *, void *, float *, int, int, int, float, hipStream_t) { OB_STUB("launch_subsample_norm_fwd"); }
 int launch_subsample_norm_bwd_wgrad(const void *, const void *, const float *, const void *, void *, float *, int, int, int, int,
                                     int, hipStream_t) { OB_STUB("launch_subsample_norm_bwd_wgrad"); }
-int subsample_wgrad_partials(int n_tok) { return n_tok < 256 ? n_tok : 256; }
 void launch_rows_gather(void *, const void *, const int32_t *, int, int, hipStream_t) { OB_STUB("launch_rows_gather"); }
 void launch_attn_fwd(const void *, const void *, const void *, void *, float *, int, int, int, const ob_segments *, int,
                      int, int, float, int, hipStream_t) { OB_STUB("launch_attn_fwd"); }
