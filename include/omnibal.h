@@ -168,12 +168,41 @@ size_t ob_block_saved_offset(const ob_block_desc *desc, int total_tokens, const 
  * All three layouts run natively (a K-major operand is transposed by the LDS read).
  * The output tiles of an incomplete last round of the chip (all tiles, for the weight gradients of
  * a narrow model) may have their contraction split along K: the slices leave fp32 sums in `ws`
- * (device memory, ob_gemm_workspace_bytes() bytes: 0 for a GEMM that is not split, never more than
- * 510 MiB) and a second kernel adds them, bias and R in a fixed order.  ws == NULL: the GEMM runs
+ * (device memory, ob_gemm_workspace_bytes() bytes, the most that a split of this GEMM may take: 0 for
+ * one that is never split, never more than 510 MiB) and a second kernel adds them, bias and R in a fixed order.  ws == NULL: the GEMM runs
  * unsplit, whatever its shape; a non-NULL ws of fewer bytes than that is OB_EWORKSPACE. */
 size_t ob_gemm_workspace_bytes(int layout, int M, int N, int K);
 int ob_gemm_bf16(int layout, int M, int N, int K, const void *A, const void *B, void *C,
                  const void *bias, const void *R, void *ws, size_t ws_bytes, void *hip_stream);
+
+/* How a call is cut into launches: host only, nothing is launched or read from the device (without
+ * one, 256 compute units are assumed).  For tests, which have to know which kernel they reach.
+ * ob_gemm_plan: the launches of ob_gemm_bf16 with (scratch != 0) or without ws; *n_launches 1 or 2, the
+ * second covering the rows from row0 on.  ob_gemm_group_plan: the one launch of the `count` (<= 4)
+ * weight gradients [M_i, N_i] over K tokens of a block's backward with scratch of ws_bytes, or *n_launches
+ * = 0 when each is launched on its own (as layout 2 of ob_gemm_plan). */
+typedef struct {
+    int row0, rows;                /* rows of C that the launch covers                                  */
+    int tile_rows, tile_cols;      /* of a workgroup's tile                                             */
+    int ring_slots;                /* 32-k slots of the K loop's LDS ring                               */
+    int whole_tiles;               /* tiles that a workgroup walks all of K for                         */
+    int split_tiles, slices;       /* tiles whose K is cut into `slices` (1: none)                      */
+    int slice_k;                   /* k per slice, the last one's rest                                  */
+} ob_gemm_launch;
+int ob_gemm_plan(int layout, int M, int N, int K, int scratch, ob_gemm_launch launches[2], int *n_launches);
+int ob_gemm_group_plan(int count, const int *M, const int *N, int K, size_t ws_bytes, ob_gemm_launch *launch,
+                       int *n_launches);
+/* The dK / dV launch of ob_varlen_attn_bwd (bf16): its shape, and in first_rows[0 .. workgroups) (may be NULL;
+ * n_first_rows entries given) the first key row of the tile that each place of the launch works on, per key/value
+ * head, in the order they are handed out (-1: a place without a tile). */
+typedef struct {
+    int key_rows, query_rows;      /* of a workgroup's tile, of a streamed tile                         */
+    int workgroups;                /* places per key/value head                                         */
+    int order_rows;                /* key rows per entry of the table that orders the work, heaviest    */
+                                   /* first; 0: the batch does not fit the table, natural order         */
+} ob_attn_bwd_launch;
+int ob_varlen_attn_bwd_plan(const ob_segments *seg, int nq, int nkv, int d, int mask, ob_attn_bwd_launch *launch,
+                            int32_t *first_rows, int n_first_rows);
 
 /* ---- ViT -> LLM hand-over of a mixed stage (App. A; the "token sub-sampling" of Sec. 5.4) ------
  * The paper names the step but fixes neither it nor the connector; what runs here is

@@ -51,6 +51,15 @@ class ob_segments(C.Structure):
                 ("total_tokens", C.c_int), ("max_seqlen", C.c_int)]
 
 
+class ob_gemm_launch(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("row0", "rows", "tile_rows", "tile_cols", "ring_slots", "whole_tiles", "split_tiles",
+                                       "slices", "slice_k")]
+
+
+class ob_attn_bwd_launch(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("key_rows", "query_rows", "workgroups", "order_rows")]
+
+
 CONNECTOR_FIELDS = ("n_g", "n_b", "w1", "b1", "w2", "b2")
 
 
@@ -102,6 +111,10 @@ _SIGNATURES = {
                           _P, _P, _Z, _SEG, _P, _Z, _P]),
     "ob_gemm_workspace_bytes": (_Z, [_I, _I, _I, _I]),
     "ob_gemm_bf16": (_I, [_I, _I, _I, _I, _P, _P, _P, _P, _P, _P, _Z, _P]),
+    "ob_gemm_plan": (_I, [_I, _I, _I, _I, _I, C.POINTER(ob_gemm_launch), C.POINTER(C.c_int)]),
+    "ob_gemm_group_plan": (_I, [_I, C.POINTER(C.c_int), C.POINTER(C.c_int), _I, _Z, C.POINTER(ob_gemm_launch),
+                                C.POINTER(C.c_int)]),
+    "ob_varlen_attn_bwd_plan": (_I, [_SEG, _I, _I, _I, _I, C.POINTER(ob_attn_bwd_launch), _i32p, _I]),
     "ob_debug_materialize_mask": (_I, [_SEG, _I, _P, _P]),
     "ob_connector_saved_bytes": (_Z, [C.POINTER(ob_connector_desc), _I]),
     "ob_connector_workspace_bytes": (_Z, [C.POINTER(ob_connector_desc), _I]),
@@ -264,6 +277,30 @@ def ob_gemm_bf16(layout, M, N, K, A, B, Cout, bias=None, R=None, ws=None, stream
     _check(lib.ob_gemm_bf16(layout, M, N, K, _ptr(A), _ptr(B), _ptr(Cout), _ptr(bias), _ptr(R),
                             _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(),
                             _stream(stream)))
+
+
+def ob_gemm_plan(layout, M, N, K, scratch=True) -> list:
+    """the launches (one or two ob_gemm_launch) of a GEMM with or without slice-sum scratch"""
+    out, n = (ob_gemm_launch * 2)(), C.c_int()
+    _check(lib.ob_gemm_plan(layout, M, N, K, int(bool(scratch)), out, C.byref(n)))
+    return [out[i] for i in range(n.value)]
+
+
+def ob_gemm_group_plan(sizes, K, ws_bytes):
+    """the one launch of the weight gradients [(M, N), ...] over K tokens, None when they go out one by one"""
+    M, N = ((C.c_int * len(sizes))(*(q[i] for q in sizes)) for i in (0, 1))
+    out, n = ob_gemm_launch(), C.c_int()
+    _check(lib.ob_gemm_group_plan(len(sizes), M, N, K, ws_bytes, C.byref(out), C.byref(n)))
+    return out if n.value else None
+
+
+def ob_varlen_attn_bwd_plan(seg, nq, nkv, d, mask):
+    """(ob_attn_bwd_launch, first key row of each place of the dK / dV launch)"""
+    out = ob_attn_bwd_launch()
+    _check(lib.ob_varlen_attn_bwd_plan(C.byref(seg.c), nq, nkv, d, int(mask), C.byref(out), None, 0))
+    rows = np.empty(out.workgroups, dtype=np.int32)
+    _check(lib.ob_varlen_attn_bwd_plan(C.byref(seg.c), nq, nkv, d, int(mask), C.byref(out), rows.ctypes.data_as(_i32p), rows.size))
+    return out, rows
 
 
 class RowIndex:

@@ -6,6 +6,8 @@
 #include <cstring>
 #include <vector>
 
+#include "attention_plan.h"
+#include "gemm_plan.h"
 #include "ob_internal.h"
 
 namespace ob {
@@ -455,6 +457,61 @@ extern "C" int ob_gemm_bf16(int layout, int M, int N, int K, const void *A, cons
     const size_t need = gemm_workspace_bytes(layout, M, N, K);
     if (need && ws && ws_bytes < need) return fail(OB_EWORKSPACE, "ob_gemm_bf16: workspace too small (%zu < %zu)", ws_bytes, need);
     return gemm_any(layout, M, N, K, A, B, C, bias, R, ws, ws_bytes, (hipStream_t)hip_stream);
+}
+
+static ob_gemm_launch describe(const Plan &p, int row0, int rows) {
+    const bool split = p.splits > 1;
+    return ob_gemm_launch{row0, rows, tile_rows(p.kind), tile_cols(p.kind), p.kind == DEEP || p.kind == FINE ? 8 : 4,
+                          split ? p.n_full : p.n_full + p.n_tail, split ? p.n_tail : 0, p.splits, split ? p.k_chunk * KSTEP : 0};
+}
+
+extern "C" int ob_gemm_plan(int layout, int M, int N, int K, int scratch, ob_gemm_launch launches[2], int *n_launches) {
+    if (!launches || !n_launches) return fail(OB_EINVAL, "ob_gemm_plan: null output");
+    if (layout < 0 || layout > 2 || M < 1 || N < 1 || K < 1) return fail(OB_EINVAL, "ob_gemm_plan: bad layout or size");
+    const RowCut c = make_row_cut(layout, M, N, K, scratch ? scratch_bytes(M, N, K) : 0);
+    *n_launches = 0;
+    if (c.m) launches[(*n_launches)++] = describe(c.head, 0, c.m);
+    launches[(*n_launches)++] = describe(c.rest, c.m, M - c.m);
+    return OB_OK;
+}
+
+extern "C" int ob_gemm_group_plan(int count, const int *M, const int *N, int K, size_t ws_bytes, ob_gemm_launch *launch,
+                                  int *n_launches) {
+    if (!M || !N || !launch || !n_launches) return fail(OB_EINVAL, "ob_gemm_group_plan: null pointer");
+    if (count < 1 || count > GEMM_GROUP_MAX || K < 1) return fail(OB_EINVAL, "ob_gemm_group_plan: bad count or size");
+    int rows = 0;
+    for (int i = 0; i < count; ++i) {
+        if (M[i] < 1 || N[i] < 1) return fail(OB_EINVAL, "ob_gemm_group_plan: bad count or size");
+        rows += M[i];
+    }
+    Plan p;
+    *n_launches = make_group_plan(count, M, N, K, true, ws_bytes, p) ? 1 : 0;
+    if (*n_launches) *launch = describe(p, 0, rows);
+    return OB_OK;
+}
+
+extern "C" int ob_varlen_attn_bwd_plan(const ob_segments *seg, int nq, int nkv, int d, int mask, ob_attn_bwd_launch *launch,
+                                       int32_t *first_rows, int n_first_rows) {
+    if (!launch) return fail(OB_EINVAL, "ob_varlen_attn_bwd_plan: null output");
+    if (int rc = validate_attn(seg, nq, nkv, d, nq * d, nkv * d, nq * d, mask, OB_BF16, "ob_varlen_attn_bwd_plan")) return rc;
+    const bool causal = mask == OB_MASK_SEG_CAUSAL;
+    const int shape = dkv_shape(seg, nkv, nq / nkv, d, causal), key_rows = 32 * dkv_np(d, shape);
+    TileOrder ord;
+    const int places = make_order(seg, key_rows, causal, true, ord);
+    *launch = ob_attn_bwd_launch{key_rows, dkv_sr(d, shape), places, ord.n ? key_rows << ord.unit_log2 : 0};
+    if (!first_rows) return OB_OK;
+    if (n_first_rows < places) return fail(OB_EINVAL, "ob_varlen_attn_bwd_plan: room for %d of %d places", n_first_rows, places);
+    if (ord.n == 0) {
+        for (int j = 0, i = 0; j < seg->n_seg; ++j)
+            for (int r = seg->cu_host[j]; r < seg->cu_host[j + 1]; r += key_rows) first_rows[i++] = r;
+        return OB_OK;
+    }
+    for (int i = 0; i < places; ++i) {
+        const uint32_t e = ord.e[i >> ord.unit_log2];
+        const int r = seg->cu_host[e >> 16] + tile_of_rank(ord, e, i) * key_rows;
+        first_rows[i] = r < seg->cu_host[(e >> 16) + 1] ? r : -1;
+    }
+    return OB_OK;
 }
 
 extern "C" int ob_debug_materialize_mask(const ob_segments *seg, int mask, uint8_t *mask_dev, void *hip_stream) {

@@ -20,10 +20,10 @@
 // read 16-byte fragments; products that contract over the streamed rows read the same tile with
 // the transposing LDS read (ds_read_b64_tr_b16), so no tile is ever stored twice.  16-byte chunks
 // are XOR-swizzled by the row so that both kinds of read are free of bank conflicts.
-#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
+#include "attention_plan.h"
 #include "ob_internal.h"
 
 namespace ob {
@@ -42,7 +42,6 @@ constexpr float LN2 = 0.6931471805599453f;
 constexpr float NEG_BIG = -1.0e30f;
 constexpr float RESCALE_LOG2 = 8.0f;  // the forward's reference maximum may lag the row maximum by this much (base-2 log)
 constexpr int QT = 128;  // rows owned by a workgroup (4 waves x 32)
-constexpr int ST = 64;   // rows of a streamed tile
 constexpr int WAIT_VM0 = 0x0F70;  // s_waitcnt vmcnt(0) only
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -195,20 +194,6 @@ __device__ __forceinline__ int head_of_slot(int hs, int heads) {
     return (heads & 7) == 0 ? (hs & 7) * (heads >> 3) + (hs >> 3) : hs;
 }
 
-// Order of the tiles: heaviest first.  The work of a tile is the number of streamed tiles it walks;
-// in a causal batch that differs by an order of magnitude between the first and the last tile of a
-// long segment, and a launch that hands out the tiles segment by segment ends with a few workgroups
-// on the heaviest tiles of the last segment while the rest of the chip idles (simulated on the
-// benchmark's batches: 20 % of the forward's and 40 % of the dK/dV kernel's duration).  The host
-// sorts the tiles by work (ties: natural order) and passes the order as a kernel argument:
-// entry = segment << 16 | tile in segment.  n == 0 (more tiles than the table holds, or a segment or
-// tile number beyond 16 bits): natural order, found by find_tile.
-struct TileOrder {
-    static constexpr int CAP = 896;
-    int n;
-    uint32_t e[CAP];
-};
-
 // Which segment-aligned tile (of `tile_rows` rows) has number `tile` when tiles are numbered segment
 // by segment.  Thread j looks at segment j (256 segments per round), an inclusive scan over the
 // workgroup gives each segment's first tile number, and the thread whose range holds `tile`
@@ -255,16 +240,19 @@ __device__ __forceinline__ TileInfo find_tile(const int32_t *__restrict__ cu, in
     return t;
 }
 
-// tile number `rank` in the order of work
+// the tile of place `rank` in the order of work; UNITS (dK / dV): the table may hold units of several tiles, and row0 < 0:
+// that place of its unit lies past the segment's end
+template <bool UNITS>
 __device__ __forceinline__ TileInfo pick_tile(const TileOrder &ord, int rank, const int32_t *__restrict__ cu,
                                               int n_seg, int tile_rows, int *sh) {
     if (ord.n == 0) return find_tile(cu, n_seg, tile_rows, sh, rank);
-    const uint32_t e = ord.e[rank];
+    const uint32_t e = ord.e[UNITS ? rank >> ord.unit_log2 : rank];
     const int seg = (int)(e >> 16);
     TileInfo t;
     t.seg_start = __builtin_amdgcn_readfirstlane(cu[seg]);
     t.seg_end = __builtin_amdgcn_readfirstlane(cu[seg + 1]);
-    t.row0 = t.seg_start + (int)(e & 0xFFFFu) * tile_rows;
+    t.row0 = t.seg_start + (UNITS ? tile_of_rank(ord, e, rank) : (int)(e & 0xFFFFu)) * tile_rows;
+    if (UNITS && t.row0 >= t.seg_end) t.row0 = -1;
     return t;
 }
 
@@ -411,7 +399,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void attn_fwd_kernel(
     __shared__ __attribute__((aligned(1024))) unsigned char v_s1[Tile<D>::BYTES];
     __shared__ int sh[8];
     const int rank = blockIdx.x / heads;
-    const TileInfo ti = pick_tile(ord, rank, cu, n_seg, QT, sh);
+    const TileInfo ti = pick_tile<false>(ord, rank, cu, n_seg, QT, sh);
     if (ti.row0 < 0) return;
     const int head = head_of_slot(blockIdx.x - rank * heads, heads), kvh = head / group;
     const int lane = threadIdx.x & 63, lx = lane & 31, lh = lane >> 5;
@@ -600,7 +588,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(
     __shared__ __attribute__((aligned(1024))) unsigned char v_s1[Tile<D>::BYTES];
     __shared__ int sh[8];
     const int rank = blockIdx.x / heads;
-    const TileInfo ti = pick_tile(ord, rank, cu, n_seg, QT, sh);
+    const TileInfo ti = pick_tile<false>(ord, rank, cu, n_seg, QT, sh);
     if (ti.row0 < 0) return;
     const int head = head_of_slot(blockIdx.x - rank * heads, heads), kvh = head / group;
     const int lane = threadIdx.x & 63, lx = lane & 31, lh = lane >> 5;
@@ -848,8 +836,6 @@ __device__ __forceinline__ void issue_row_stats(const float *base, long floats_l
 // still gives bit for bit what its segments give alone.
 constexpr int DKV_ORDER_Q = 64;   // the ragged end of the query rows is one masked step of up to this many rows
 constexpr int dkv_whole(int d) { return d == 64 ? 64 : 128; }
-constexpr int dkv_np(int d, int shape) { return shape == 2 ? 6 : d == 128 && shape == 0 ? 4 : 2; }   // pairs and query rows of a shape
-constexpr int dkv_sr(int d, int shape) { return d == 64 && shape == 1 ? 32 : 64; }
 template <int D, bool CAUSAL, int NP, int SR>
 __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 2) void attn_bwd_dkv_kernel(
     const __bf16 *__restrict__ d_o, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
@@ -866,7 +852,7 @@ __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 
     __shared__ __attribute__((aligned(256))) float stat_s[6 * ST];              // lse2 x 3 stages, Delta x 3 stages
     __shared__ int sh[8];
     const int rank = blockIdx.x / heads;
-    const TileInfo ti = pick_tile(ord, rank, cu, n_seg, KVT, sh);
+    const TileInfo ti = pick_tile<true>(ord, rank, cu, n_seg, KVT, sh);
     if (ti.row0 < 0) return;
     // one workgroup per key/value head: the group's query heads run one after another
     const int kvh = head_of_slot(blockIdx.x - rank * heads, heads);
@@ -1061,69 +1047,6 @@ double attn_flops(const ob_segments *seg, int nq, int d, bool causal) {
     return 4.0 * nq * d * area;
 }
 
-int count_tiles(const ob_segments *seg, int tile_rows) {
-    long n = 0;
-    for (int j = 0; j < seg->n_seg; ++j)
-        n += (seg->cu_host[j + 1] - seg->cu_host[j] + tile_rows - 1) / tile_rows;
-    return (int)n;
-}
-
-// Order of work of a launch whose workgroups own `tile_rows` rows of a segment and stream 64-row
-// tiles of the other side: descending number of streamed tiles, ties in natural order.  `kv_side`:
-// the workgroup owns key rows and streams query tiles (from its diagonal on when causal); otherwise
-// it owns query rows and streams key tiles (up to its diagonal when causal).  No heap memory.
-void make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side, int n_tiles, TileOrder &ord) {
-    ord.n = 0;
-    if (n_tiles > TileOrder::CAP || seg->n_seg > 0xFFFF) return;
-    uint64_t key[TileOrder::CAP];
-    int n = 0;
-    for (int j = 0; j < seg->n_seg; ++j) {
-        const int a = seg->cu_host[j], len = seg->cu_host[j + 1] - a;
-        const int nt = (len + tile_rows - 1) / tile_rows;
-        if (nt > 0xFFFF) return;
-        for (int t = 0; t < nt; ++t) {
-            int rows = len;                                            // streamed rows
-            if (causal && kv_side) rows = len - (t * tile_rows) / ST * ST;
-            else if (causal) rows = std::min(len, (t + 1) * tile_rows);
-            const uint32_t w = (uint32_t)((rows + ST - 1) / ST);
-            // ascending sort of (~work, natural index); the entry rides in the low half
-            key[n] = ((uint64_t)(0xFFFFFu - w) << 44) | ((uint64_t)n << 32) | ((uint32_t)j << 16) | (uint32_t)t;
-            ++n;
-        }
-    }
-    std::sort(key, key + n);
-    for (int i = 0; i < n; ++i) ord.e[i] = (uint32_t)key[i];
-    ord.n = n;
-}
-
-// Which of its shapes the dK / dV kernel runs in (see there).  An estimate of the launch's duration in
-// microseconds: the trips (64 query rows against a workgroup's key rows) that a CU has to make at the rate of a full
-// chip, or the longest chain of trips (the first key rows of the longest segment, all query heads of a group) at the
-// rate its workgroup sees, whichever is longer.  Over 224 launches measured in either shape (64 - 16000 tokens in one
-// segment, ViT tiles or texts, 1 - 25 key / value heads, groups of 1 - 6, both masks) the picks are 0.03 % (D = 64) and 0.2 %
-// (D = 128) slower than the faster shape.
-struct DkvShape { int kv_rows; double full, chain; };
-constexpr DkvShape DKV_SHAPES[2][2] = {{{64, 0.81, 1.1}, {64, 0.70, 1.53}},      // D = 64: SR = 64, SR = 32
-                                       {{128, 2.39, 1.7}, {64, 1.76, 1.42}}};    // D = 128: four pairs, two
-int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
-    double est[2];
-    for (int i = 0; i < 2; ++i) {
-        const DkvShape &sh = DKV_SHAPES[d == 128][i];
-        double sum = 0, chain = 0;
-        for (int j = 0; j < seg->n_seg; ++j) {
-            const double len = seg->cu_host[j + 1] - seg->cu_host[j], tiles = ceil(len / sh.kv_rows), first = ceil(len / 64);
-            sum += tiles * first - (causal ? 0.5 * tiles * (tiles - 1) * sh.kv_rows / 64 : 0.0);
-            chain = std::max(chain, first);
-        }
-        est[i] = group * std::max(sum * nkv / 256 * sh.full, chain * sh.chain);
-    }
-    if (d == 64 && !causal) {      // 70 - 100 % of one round of six pairs
-        const long six = (long)count_tiles(seg, 32 * dkv_np(64, 2)) * nkv;
-        if (six >= 180 && six <= 256) return 2;
-    }
-    return est[1] < est[0] ? 1 : 0;
-}
-
 // explicit instantiations (the host pass otherwise drops launch stubs of kernels reached only
 // through the dispatch macro below)
 #define OB_ATTN_INSTANCES(D, C)                                                                               \
@@ -1172,11 +1095,10 @@ void launch_attn_fwd(const void *q, const void *k, const void *v, void *o, float
                      int mask, hipStream_t s) {
     const bool causal = mask == OB_MASK_SEG_CAUSAL;
     ProfScope prof(K_ATTN_FWD, s, attn_flops(seg, nq, d, causal));
-    const int tiles = count_tiles(seg, QT);
     TileOrder ord;
-    make_order(seg, QT, causal, false, tiles, ord);
+    const int tiles = make_order(seg, QT, causal, false, ord);
     const dim3 grid((unsigned)tiles * nq);
-OB_ATTN_DISPATCH(attn_fwd_kernel, grid, 256, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v,
+    OB_ATTN_DISPATCH(attn_fwd_kernel, grid, 256, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v,
                      (__bf16 *)o, lse, ldq, ldkv, ldo, seg->cu_dev, seg->n_seg, seg->total_tokens,
                      nq / nkv, scale, nq, ord);
 }
@@ -1186,14 +1108,13 @@ void launch_attn_bwd(const void *d_o, const void *q, const void *k, const void *
                      const ob_segments *seg, int nq, int nkv, int d, float scale, int mask, float rotary_base,
                      hipStream_t s) {
     const bool causal = mask == OB_MASK_SEG_CAUSAL;
-    const int tiles = count_tiles(seg, QT);
     const int T = seg->total_tokens, group = nq / nkv;
     const float rot = rotary_base > 1.f ? log2f(rotary_base) : 0.f;
     {
         // dQ = dS K: 1 of the 4 backward products; the kernel also forms Delta and the base-2 log-sum-exp
         ProfScope prof(K_ATTN_BWD_DQ, s, 0.5 * attn_flops(seg, nq, d, causal));
         TileOrder ord;
-        make_order(seg, QT, causal, false, tiles, ord);
+        const int tiles = make_order(seg, QT, causal, false, ord);
         const dim3 grid_q((unsigned)tiles * nq);
         OB_ATTN_DISPATCH(attn_bwd_dq_kernel, grid_q, 256, (const __bf16 *)d_o, (const __bf16 *)q,
                          (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)o, lse, lse2, delta, (__bf16 *)dq, ldq,
@@ -1202,9 +1123,8 @@ void launch_attn_bwd(const void *d_o, const void *q, const void *k, const void *
     ProfScope prof(K_ATTN_BWD_DKV, s, 1.5 * attn_flops(seg, nq, d, causal));  // dV, dP, dK
     TileOrder ord;
     const int shape = dkv_shape(seg, nkv, group, d, causal);
-    const int kvt = 32 * dkv_np(d, shape), tiles_kv = count_tiles(seg, kvt);
-    make_order(seg, kvt, causal, true, tiles_kv, ord);
-    const dim3 grid_kv((unsigned)tiles_kv * nkv);
+    const int kvt = 32 * dkv_np(d, shape), places = make_order(seg, kvt, causal, true, ord);
+    const dim3 grid_kv((unsigned)places * nkv);
 #define OB_DKV_ARGS (const __bf16 *)d_o, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, lse2, delta, (__bf16 *)dk,  \
                     (__bf16 *)dv, ldq, ldkv, ldo, seg->cu_dev, seg->n_seg, T, group, scale, rot, nkv, ord
     if (shape == 2)

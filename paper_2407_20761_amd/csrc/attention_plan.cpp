@@ -1,0 +1,87 @@
+// Order of work and launch shapes of the attention kernels.
+#include "attention_plan.h"
+
+#include <algorithm>
+#include <cmath>
+
+#include "ob_internal.h"
+
+namespace ob {
+
+namespace {
+
+int count_tiles(const ob_segments *seg, int tile_rows) {
+    long n = 0;
+    for (int j = 0; j < seg->n_seg; ++j)
+        n += (seg->cu_host[j + 1] - seg->cu_host[j] + tile_rows - 1) / tile_rows;
+    return (int)n;
+}
+
+}  // namespace
+
+// Order of work of a launch whose workgroups own `tile_rows` rows of a segment and stream 64-row
+// tiles of the other side: descending number of streamed tiles, ties in natural order.  `kv_side`:
+// the workgroup owns key rows and streams query tiles (from its diagonal on when causal); otherwise
+// it owns query rows and streams key tiles (up to its diagonal when causal).  A unit counts as its first
+// tile, on the key side the heaviest of them.  No heap memory.
+int make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side, TileOrder &ord) {
+    ord.n = ord.unit_log2 = 0;
+    const int n_tiles = count_tiles(seg, tile_rows), max_log2 = kv_side && tile_rows == 64 ? 2 : 0;
+    int log2 = 0, n_units = n_tiles;
+    while (n_units > TileOrder::CAP && log2 < max_log2) n_units = count_tiles(seg, tile_rows << ++log2);
+    if (n_units > TileOrder::CAP || seg->n_seg > 0xFFFF) return n_tiles;
+    const int unit_rows = tile_rows << log2;
+    uint64_t key[TileOrder::CAP];
+    int n = 0;
+    for (int j = 0; j < seg->n_seg; ++j) {
+        const int a = seg->cu_host[j], len = seg->cu_host[j + 1] - a;
+        const int nt = (len + unit_rows - 1) / unit_rows;
+        if (nt > 0xFFFF) return n_tiles;
+        for (int t = 0; t < nt; ++t) {
+            int rows = len;                                            // streamed rows
+            if (causal && kv_side) rows = len - (t * unit_rows) / ST * ST;
+            else if (causal) rows = std::min(len, (t + 1) * unit_rows);
+            const uint32_t w = (uint32_t)((rows + ST - 1) / ST);
+            // ascending sort of (~work, natural index); the entry rides in the low half
+            key[n] = ((uint64_t)(0xFFFFFu - w) << 44) | ((uint64_t)n << 32) | ((uint32_t)j << 16) | (uint32_t)t;
+            ++n;
+        }
+    }
+    std::sort(key, key + n);
+    for (int i = 0; i < n; ++i) ord.e[i] = (uint32_t)key[i];
+    ord.n = n;
+    ord.unit_log2 = log2;
+    return n << log2;
+}
+
+// Which of its shapes the dK / dV kernel runs in (see there).  An estimate of the launch's duration in
+// microseconds: the trips (64 query rows against a workgroup's key rows) that a CU has to make at the rate of a full
+// chip, or the longest chain of trips (the first key rows of the longest segment, all query heads of a group) at the
+// rate its workgroup sees, whichever is longer.  Over 224 launches measured in either shape (64 - 16000 tokens in one
+// segment, ViT tiles or texts, 1 - 25 key / value heads, groups of 1 - 6, both masks) the picks are 0.03 % (D = 64) and 0.2 %
+// (D = 128) slower than the faster shape.
+namespace {
+struct DkvShape { int kv_rows; double full, chain; };
+constexpr DkvShape DKV_SHAPES[2][2] = {{{64, 0.81, 1.1}, {64, 0.70, 1.53}},      // D = 64: SR = 64, SR = 32
+                                       {{128, 2.39, 1.7}, {64, 1.76, 1.42}}};    // D = 128: four pairs, two
+}  // namespace
+int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
+    double est[2];
+    for (int i = 0; i < 2; ++i) {
+        const DkvShape &sh = DKV_SHAPES[d == 128][i];
+        double sum = 0, chain = 0;
+        for (int j = 0; j < seg->n_seg; ++j) {
+            const double len = seg->cu_host[j + 1] - seg->cu_host[j], tiles = ceil(len / sh.kv_rows), first = ceil(len / 64);
+            sum += tiles * first - (causal ? 0.5 * tiles * (tiles - 1) * sh.kv_rows / 64 : 0.0);
+            chain = std::max(chain, first);
+        }
+        est[i] = group * std::max(sum * nkv / 256 * sh.full, chain * sh.chain);
+    }
+    if (d == 64 && !causal) {      // 70 - 100 % of one round of six pairs
+        const long six = (long)count_tiles(seg, 32 * dkv_np(64, 2)) * nkv;
+        if (six >= 180 && six <= 256) return 2;
+    }
+    return est[1] < est[0] ? 1 : 0;
+}
+
+}  // namespace ob

@@ -56,6 +56,33 @@ def test_dkv_shapes_give_the_same_bits(d, nq, nkv, mask):
                 assert np.abs(got - r).max() <= TOL * np.abs(r).max(), (name, j)
 
 
+@pytest.mark.parametrize("mask", [orc.MASK_BIDIR, orc.MASK_CAUSAL])
+@pytest.mark.parametrize("d,unit", [(64, 128), (64, 256), (128, 128)])
+def test_dkv_order_in_units_of_tiles(d, unit, mask):
+    """Batches with more 64-row key tiles than the order table holds: the table's entries are two or four tiles, the last of a
+    segment's places have none.  Segments on and beside the borders of tiles and units give the bits they give alone."""
+    edges = [1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 255, 256, 257, 700, 1987]
+    total = 59000 if unit == 128 else 117000
+    rest = [12000] + [300] * 150 if d == 128 else [3000] * ((total - sum(edges)) // 3000)      # (d = 128: one long walk)
+    lens = edges + rest
+    print(f"dkv order in units d={d} unit={unit} mask={mask}", flush=True)
+    nq, nkv = 2, 1
+    cu = si.lengths_to_cu(lens)
+    plan, _ = ob.ob_varlen_attn_bwd_plan(ob.Segments(cu), nq, nkv, d, mask)
+    assert plan.key_rows == 64 and plan.order_rows == unit
+    gen = torch.Generator(device="cuda").manual_seed(d + unit)
+    T = int(cu[-1])
+    qkv = torch.randn((T, (nq + 2 * nkv) * d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    d_o = torch.randn((T, nq * d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    packed = _attention(qkv, d_o, lens, nq, nkv, d, mask)
+    assert all(torch.isfinite(t.float()).all() for t in packed)
+    for j in list(range(len(edges) + 1)) + [len(lens) - 1]:
+        a, b = int(cu[j]), int(cu[j + 1])
+        alone = _attention(qkv[a:b].contiguous(), d_o[a:b].contiguous(), [b - a], nq, nkv, d, mask)
+        for name, x, y in zip(("o", "dq", "dk", "dv"), packed, alone):
+            assert torch.equal(x[a:b].view(torch.int16), y.view(torch.int16)), (name, j, b - a)
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 64, 640), (127, 192, 704), (129, 320, 768), (300, 4160, 832), (557, 1088, 1088),
                                    (257, 256, 4096), (300, 4096, 4096), (200, 768, 4224)])
 def test_gemm_deep_ring(M, N, K):

@@ -20,7 +20,7 @@ HERE = os.path.join(ROOT, "tests", "host_sanitize")
 def test_host_code_is_clean_under_asan_and_ubsan(tmp_path):
     exe = str(tmp_path / "host_sanitize")
     srcs = [os.path.join(HERE, "driver.cpp"), os.path.join(HERE, "stubs.cpp")] + \
-           [os.path.join(CSRC, f) for f in ("packer.cpp", "planner.cpp", "gemm_plan.cpp", "api.cpp", "connector_api.cpp")]
+           [os.path.join(CSRC, f) for f in ("packer.cpp", "planner.cpp", "gemm_plan.cpp", "attention_plan.cpp", "api.cpp", "connector_api.cpp")]
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
            "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", *srcs, "-L/opt/rocm/lib", "-lamdhip64",
            "-Wl,-rpath,/opt/rocm/lib", "-o", exe]
