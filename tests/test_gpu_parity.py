@@ -1,7 +1,7 @@
 """GPU parity: the HIP path (through the C ABI) against the CPU oracle on the same seeded inputs.
 
 Tolerance: max|err| / max|ref| <= 2e-2 per tensor for the bf16 path (the benchmark contract's
-bound; bf16 has 8 mantissa bits, every stored intermediate costs up to 2^-9 relative) and <= 1e-4
+bound; bf16 has 8 significant bits, every stored intermediate costs up to 2^-8 relative) and <= 1e-4
 for the fp32 debug path.  Segment offsets and masks are compared bit for bit.
 """
 import numpy as np
