@@ -13,7 +13,7 @@ namespace ob {
 int fail(int status, const char *fmt, ...);
 int check_launch(const char *what);
 
-inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+constexpr size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // host-side checks shared by the attention entry points (api.cpp); OB_OK or a status with the text set
 int validate_attn(const ob_segments *seg, int nq, int nkv, int d, int ldq, int ldkv, int ldo,
