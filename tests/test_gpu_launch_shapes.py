@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+import gemm_launches
 import paper_2407_20761_amd as ob
 import synth_inputs as si
 from gpu_util import bytes_buf, run_block, saved_view, to_dev, to_np
@@ -85,11 +86,46 @@ def test_dkv_order_in_units_of_tiles(d, unit, mask):
             assert torch.equal(x[a:b].view(torch.int16), y.view(torch.int16)), (name, j, b - a)
 
 
+def _normal_gemm(layout, M, N, K, seed):
+    """operands of N(0, 1) as the library takes them, bias, residual, and A, B as [M, K], [N, K] views"""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    new = lambda *size: torch.randn(size, generator=gen, device="cuda", dtype=torch.bfloat16)
+    A, B = new(K, M) if layout == 2 else new(M, K), new(N, K) if layout == 0 else new(K, N)
+    return A, B, new(N), new(M, N) * 4, A.T if layout == 2 else A, B if layout == 0 else B.T
+
+
+@pytest.mark.parametrize("layout,M,N,K,want", gemm_launches.FORMS + [(0, *c, None) for c in gemm_launches.DEEP])
+def test_gemm_forms(layout, M, N, K, want):
+    """Every kind of tile in every layout that has it, whole, in slices and whole beside sliced, and launches cut by rows in two:
+    the rows on and beside every border of a tile, whole, against fp64; plain, and with bias and residual in place of the result.
+    Scratch and result hold garbage before."""
+    print(f"gemm forms layout={layout} {M} {N} {K} {want}", flush=True)
+    assert want is None or gemm_launches.named(gemm_launches.forms(layout, M, N, K)) == want
+    A, B, bias, R, a, b = _normal_gemm(layout, M, N, K, seed=M + N + K + layout)
+    edges = np.concatenate([np.arange(t, M, t) for t in (64, 192)] + [[0, M - 1]])
+    rows = torch.from_numpy(np.unique(np.concatenate([edges - 1, edges, [min(M - 1, 33)]]).clip(0))).cuda()
+    ref = a[rows].double() @ b.double().T
+    ws = bytes_buf(ob.ob_gemm_workspace_bytes(layout, M, N, K))
+    for plain in (True, False):
+        ws.fill_(0x7F)
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda") if plain else R.clone()
+        ob.ob_gemm_bf16(layout, M, N, K, A, B, C, None if plain else bias, None if plain else C, ws)
+        want_rows = ref if plain else ref + bias.double() + R[rows].double()
+        assert torch.isfinite(C).all()
+        # one rounding to bf16 (8 significant bits: 2^-8 of the value at most) behind fp32 sums
+        assert (C[rows].double() - want_rows).abs().max() <= 2.0 ** -8 * want_rows.abs().max(), plain
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 64, 640), (127, 192, 704), (129, 320, 768), (300, 4160, 832), (557, 1088, 1088),
-                                   (257, 256, 4096), (300, 4096, 4096), (200, 768, 4224)])
+                                   (257, 256, 4096), (300, 4096, 4096), (200, 768, 4224)] + gemm_launches.DEEP[:5])
 def test_gemm_deep_ring(M, N, K):
-    """"NT" launches of few tiles walk K over a ring of eight slots and may leave it in the middle (K of 10 - 66 steps of
-    64, every remainder modulo the four steps of a trip), whole or in slices, on ragged edges; with bias and residual."""
+    """"NT" launches of few rows walk K over a ring of eight slots and may leave it in the middle, in 64 x 64 tiles (the first
+    eight but one) and 128 x 128 ones (K steps of every remainder modulo the four of a trip), whole or in slices, on ragged edges;
+    with bias and residual."""
+    for scratch in (False, True):
+        plan = ob.ob_gemm_plan(0, M, N, K, scratch)
+        assert all(p.ring_slots == 8 for p in plan)
+        assert (M, N, K) not in gemm_launches.DEEP or plan[0].tile_rows == 128
     print(f"deep ring {M} {N} {K}", flush=True)
     rng = np.random.default_rng(M + N + K)
     A = si.round_to_bf16(rng.standard_normal((M, K), dtype=np.float32))
@@ -110,10 +146,11 @@ def test_gemm_deep_ring(M, N, K):
 @pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1, 64, 128), (65, 128, 192), (130, 192, 640), (200, 768, 768), (63, 448, 1088),
                                    (1025, 768, 832), (64, 4096, 4224)])
 def test_gemm_fine_tiles(layout, M, N, K):
-    """Launches that 64 x 64 tiles are chosen for (and their neighbours), all layouts: ragged rows and columns, every
-    remainder of the eight-slot ring, token counts that are no multiple of 32."""
+    """Launches that 64 x 64 tiles are chosen for, all layouts: ragged rows and columns, every remainder of the eight-slot
+    ring, token counts that are no multiple of 32."""
     if layout == 2:
         M, K = (M + 63) // 64 * 64, K + 37
+    assert all(k == "fine" for scratch in (False, True) for k, _ in gemm_launches.forms(layout, M, N, K, scratch))
     print(f"fine tiles layout={layout} {M} {N} {K}", flush=True)
     rng = np.random.default_rng(M + N + K + layout)
     A = si.round_to_bf16(rng.standard_normal((M, K), dtype=np.float32))
@@ -158,11 +195,12 @@ def test_connector_widths(Hv, Ht, grid, tiles):
 
 
 @pytest.mark.parametrize("layout", [0, 1])
-@pytest.mark.parametrize("M,N,K", [(2050, 4032, 896), (2050, 4096, 960), (2112, 4096, 1024), (1921, 4096, 1088), (3072, 4096, 2048)])
+@pytest.mark.parametrize("M,N,K", [(2050, 4032, 896), (2050, 4096, 960), (2112, 4096, 1024), (2881, 4096, 1088), (3072, 4096, 2048)])
 def test_gemm_rectangular_tiles(layout, M, N, K):
     """Launches that 192 x 256 tiles are chosen for: ragged and whole rows and columns, every remainder of the trip's two
     K steps, sampled rows against fp64."""
     print(f"rectangular tiles layout={layout} {M} {N} {K}", flush=True)
+    assert gemm_launches.forms(layout, M, N, K, False) == [("mid", "whole")]
     rng = np.random.default_rng(M + N + K + layout)
     A = si.round_to_bf16(rng.standard_normal((M, K), dtype=np.float32))
     B = si.round_to_bf16(rng.standard_normal((N, K), dtype=np.float32))
@@ -199,13 +237,16 @@ def test_norm_bwd_widths(hidden, T, norm):
         assert np.abs(got - ref).max() <= TOL * np.abs(ref).max(), n
 
 
-@pytest.mark.parametrize("layout", [0, 1])
-@pytest.mark.parametrize("M,N,K", [(2049, 8192, 1024), (1030, 16384, 768), (4444, 4096, 2048), (2500, 14336, 1024)])
+@pytest.mark.parametrize("layout,M,N,K", [(0, 2049, 8192, 1024), (0, 1030, 16384, 768), (0, 4444, 4096, 2048), (0, 2500, 14336, 1024),
+                                          (0, 6012, 3072, 2560), (1, 2049, 8192, 1024), (1, 2500, 14336, 1024), (1, 4494, 4096, 2496)])
 def test_gemm_row_cut(layout, M, N, K):
-    """Launches whose last rows go out on their own, behind whole rounds of tiles: one row, a few, more than a tile; with
-    bias, residual and slice sums allowed.  Rows on both sides of every possible cut against fp64; a row's values do not
+    """Launches whose last rows go out on their own, behind whole rounds of tiles: one row, a few, more than a tile, some
+    of them in slices; with bias and residual.  Rows on both sides of every possible cut against fp64; a row's values do not
     depend on what is launched with it, up to the rounding of sums in another order where a contraction is split."""
     print(f"row cut layout={layout} {M} {N} {K}", flush=True)
+    head, rest = ob.ob_gemm_plan(layout, M, N, K)
+    assert head.rows + rest.rows == M and rest.row0 == head.rows
+    assert (rest.slices > 1) == (K > 2400)
     rng = np.random.default_rng(M + N + K + layout)
     A = si.round_to_bf16(rng.standard_normal((M, K), dtype=np.float32))
     B = si.round_to_bf16(rng.standard_normal((N, K), dtype=np.float32))
@@ -222,13 +263,17 @@ def test_gemm_row_cut(layout, M, N, K):
     assert np.abs(got[rows] - ref).max() <= 2.0 ** -8 * np.abs(ref).max()
 
 
-def test_connector_row_cut():
-    """The hand-over's GEMMs cut by rows (4352 tokens, 4096 wide): both launches of the last store through the row list.  The first
-    and the last tile of the batch against the oracle on those tiles alone; rows that no token has stay as they were."""
-    Hv, Ht, grid, tiles = 64, 4096, 32, 17
-    print(f"connector row cut {Hv} {Ht} {grid} {tiles}", flush=True)
+@pytest.mark.parametrize("Ht,grid,tiles,want", gemm_launches.ROW_LIST)
+def test_connector_row_list(Ht, grid, tiles, want):
+    """The hand-over's last GEMM stores through the row list from every kind of tile, whole and in slices, and from both launches
+    of one cut by rows.  The first, the middle and the last tile of the batch against the oracle on those tiles alone; rows that no token
+    has stay as they were."""
+    Hv = 64
+    print(f"connector row list {Ht} {grid} {tiles} {want}", flush=True)
     rng = np.random.default_rng(11)
-    per, n_tok, rows_v = 256, tiles * 256, grid * grid + 1
+    per, rows_v = (grid // 2) ** 2, grid * grid + 1
+    n_tok = tiles * per
+    assert gemm_launches.named(gemm_launches.forms(0, n_tok, Ht, Ht)) == want
     w = si.connector_weights(Hv, Ht, seed=1)
     v = si.round_to_bf16(rng.standard_normal((tiles * rows_v, Hv), dtype=np.float32))
     llm = n_tok + 5
@@ -236,12 +281,39 @@ def test_connector_row_cut():
     desc = ob.make_connector_desc(Hv, Ht, grid, 1e-5)
     x = torch.full((llm, Ht), 3.0, dtype=torch.bfloat16, device="cuda")
     saved, ws = bytes_buf(ob.ob_connector_saved_bytes(desc, tiles)), bytes_buf(ob.ob_connector_workspace_bytes(desc, tiles))
+    ws.fill_(0x7F)
     ob.ob_connector_fwd(desc, {n: to_dev(t) for n, t in w.items()}, to_dev(v), tiles, ob.RowIndex(dst), x, llm, saved, ws)
     got = to_np(x)
-    assert (np.delete(got, dst, axis=0) == 3.0).all()
-    for t in (0, tiles - 1):
+    assert np.isfinite(got).all() and (np.delete(got, dst, axis=0) == 3.0).all()
+    for t in (0, tiles // 2, tiles - 1):
         ref, _ = orc_conn.connector_fwd(w, v[t * rows_v:(t + 1) * rows_v], 1, grid, 1e-5, np.zeros((per, Ht)), np.arange(per))
         assert np.abs(got[dst[t * per:(t + 1) * per]] - ref).max() <= TOL * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("hidden,mlp,T,want", [(256, 1024, 200, ("fine", "whole")), (640, 2560, 300, ("small", "whole")),
+                                               (1024, 4096, 557, ("big", "whole")), (256, 1024, 12300, ("big", "split"))])
+def test_grouped_weight_gradients_by_tile(hidden, mlp, T, want):
+    """A block's four weight gradients in one launch, in each kind of tile that the group takes, whole and in slices: against the
+    oracle, and accumulated onto themselves."""
+    print(f"grouped weight gradients {hidden} {mlp} T={T}", flush=True)
+    shape = si.small_shape(hidden=hidden, n_q_heads=hidden // 64, n_kv_heads=hidden // 64, head_dim=64, mlp_dim=mlp,
+                           norm=si.NORM_LAYERNORM, mlp=si.MLP_GELU, mask=si.MASK_BIDIR, has_bias=True, norm_eps=1e-5)
+    lens = [100] * (T // 100) + ([T % 100] if T % 100 else [])
+    cu = si.lengths_to_cu(lens)
+    w = si.block_weights(shape, seed=2)
+    x, dy = si.activations(T, hidden, seed=3, std=1.0)
+    run, y, dx, g = run_block(shape, w, x, dy, cu)
+    sizes = [(3 * hidden, hidden), (hidden, hidden), (mlp, hidden), (hidden, mlp)]
+    launch = ob.ob_gemm_group_plan(sizes, T, ob.ob_block_workspace_bytes(run.desc, T))
+    assert launch and gemm_launches.form(launch) == want
+    y_ref, cache = orc.block_fwd(shape, w, x, cu)
+    dx_ref, g_ref, _ = orc.block_bwd(shape, w, cache, dy, cu)
+    for n, got, ref in [("y", y, y_ref), ("dx", dx, dx_ref)] + [(n, g[n], g_ref[n]) for n in g]:
+        assert np.abs(got - ref).max() <= TOL * np.abs(ref).max(), n
+    once = {n: t.clone() for n, t in run.g.items()}
+    run.bwd(to_dev(x), to_dev(dy), ob.Segments(cu), accumulate=True)
+    for n in once:
+        assert torch.equal((2 * once[n].float()).to(torch.bfloat16).view(torch.int16), run.g[n].view(torch.int16)), n
 
 
 def test_gelu_and_derivative_element_by_element():

@@ -56,15 +56,17 @@ def test_gemm_against_fp64_matmul(layout, M, N, K):
 
 
 @pytest.mark.parametrize("layout,M,N,K", [(2, 1024, 1024, 12300), (2, 2048, 1024, 12300), (2, 512, 1024, 8219),
-                                          (2, 64, 64, 1000), (0, 257, 256, 4096), (1, 700, 512, 2112),
-                                          (2, 4096, 5120, 4100), (0, 4100, 4992, 4096), (1, 2500, 8192, 4160)])
+                                          (2, 64, 256, 4203), (0, 257, 256, 4160), (1, 700, 512, 4160),
+                                          (2, 4096, 5120, 4100), (0, 4608, 4096, 4160), (1, 652, 24576, 2624)])
 def test_gemm_split_contraction(layout, M, N, K):
     """The tiles of an incomplete last round (all tiles, for the small weight gradients of config 2) have
     their contraction cut into slices whose fp32 sums a second kernel adds; the last slice is shorter
     than the rest, and the last three cases keep whole tiles beside the split ones."""
     _say(f"gemm split layout={layout} M={M} N={N} K={K}")
     need = ob.ob_gemm_workspace_bytes(layout, M, N, K)
-    assert need > 0                                                  # this case does split
+    (launch,) = ob.ob_gemm_plan(layout, M, N, K)
+    assert launch.slices > 1 and K < launch.slices * launch.slice_k   # it does split, the last slice shorter
+    assert (launch.whole_tiles > 0) == (M * N > 4e6)
     rng = np.random.default_rng(M + N + K + layout)
     A = si.round_to_bf16(rng.standard_normal((M, K), dtype=np.float32))
     B = si.round_to_bf16(rng.standard_normal((N, K), dtype=np.float32))
@@ -120,7 +122,7 @@ def test_gemm_random_shapes():
         ob.ob_gemm_bf16(layout, M, N, K, a_dev, b_dev, c2, None, None, None)
         assert rel_err(to_np(c2), ref) < 5e-3
         done += 1
-        split += need > 0
+        split += any(p.slices > 1 for p in ob.ob_gemm_plan(layout, M, N, K))
     assert split >= 10          # the sweep does reach the split path
 
 

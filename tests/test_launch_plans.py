@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+import gemm_launches
 import paper_2407_20761_amd as ob
 import synth_inputs as si
 from oracle import block as orc
@@ -41,3 +42,37 @@ def test_dkv_order_covers_every_tile_heaviest_first(d, nq, nkv, mask, total):
         first = -(-work[::per] // 64)                       # of the heaviest tile of each unit
         assert (rows[::per] >= 0).all() and (np.diff(first) <= 0).all()
         assert len(rows) % per == 0 and (rows < 0).sum() < per * len(lens)
+
+
+def test_gpu_cases_reach_the_kernels_they_name():
+    for layout, M, N, K, want in gemm_launches.FORMS:
+        assert gemm_launches.named(gemm_launches.forms(layout, M, N, K)) == want, (layout, M, N, K)
+    for Ht, grid, tiles, want in gemm_launches.ROW_LIST:
+        assert gemm_launches.named(gemm_launches.forms(0, tiles * (grid // 2) ** 2, Ht, Ht)) == want, (Ht, grid, tiles)
+    left = {"whole": set(), "split": set()}      # K steps modulo the trip's four that a deep tile walks
+    for M, N, K in gemm_launches.DEEP:
+        (launch,) = ob.ob_gemm_plan(0, M, N, K)
+        kind, how = gemm_launches.form(launch)
+        assert kind == "deep"
+        left[how].add(gemm_launches.steps(launch, K)[-1] % 4)
+    assert left == {"whole": {0, 1, 2, 3}, "split": {0, 1, 2, 3}}
+
+
+def test_every_gemm_form_has_a_gpu_case():
+    """Whatever the plan takes over sizes of every magnitude, the GPU tests run: each kind of tile, whole, split and mixed, per
+    layout, and each pair of launches a GEMM is cut into, by the kind of the first and of the second and whether that is split."""
+    def seen(layout, forms):
+        out = {(layout, *f) for f in forms}
+        if len(forms) == 2:
+            out |= {(layout, "head", forms[0][0]), (layout, "rest", forms[1][0], forms[1][1] != "whole")}
+        return out
+
+    covered = set().union(*(seen(layout, gemm_launches.forms(layout, M, N, K)) for layout, M, N, K, _ in gemm_launches.FORMS))
+    rng = np.random.default_rng(5)
+    dims = [256, 512, 640, 768, 1024, 1088, 2048, 2112, 2560, 3072, 3200, 4096, 5120, 6144, 9600, 12288, 12800, 14336, 16384, 28672]
+    for i in range(30000):
+        a, b = (int(rng.choice(dims)) if rng.random() < 0.8 else 64 * int(rng.integers(1, 400)) for _ in range(2))
+        T, layout = int(2 ** rng.uniform(0, 15)), i % 3
+        M, N, K = (a, b, T) if layout == 2 else (T, a, b)
+        missing = seen(layout, gemm_launches.forms(layout, M, N, K, i % 5 != 0)) - covered
+        assert not missing, (layout, M, N, K, missing)
