@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "gemm_plan.h"
 #include "ob_internal.h"
 
 namespace ob {
@@ -75,11 +76,11 @@ int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
             sum += tiles * first - (causal ? 0.5 * tiles * (tiles - 1) * sh.kv_rows / 64 : 0.0);
             chain = std::max(chain, first);
         }
-        est[i] = group * std::max(sum * nkv / 256 * sh.full, chain * sh.chain);
+        est[i] = group * std::max(sum * nkv / compute_units() * sh.full, chain * sh.chain);
     }
     if (d == 64 && !causal) {      // 70 - 100 % of one round of six pairs
         const long six = (long)count_tiles(seg, 32 * dkv_np(64, 2)) * nkv;
-        if (six >= 180 && six <= 256) return 2;
+        if (10 * six >= 7 * compute_units() && six <= compute_units()) return 2;
     }
     return est[1] < est[0] ? 1 : 0;
 }

@@ -288,11 +288,13 @@ __global__ __launch_bounds__(512) void norm_bwd_kernel(
 // row sums are wave reductions, and the next row's loads are in flight while the current row is
 // worked on.  The workgroup's eight waves add their column sums in LDS, in wave order, and leave one partial,
 // partial[blockIdx.x][2][H].
-template <bool LAYERNORM, int NV, bool CSUM, int W>
-__global__ __launch_bounds__(64 * W) void norm_bwd_wave_kernel(
+constexpr int FOLD_WAVES = 8;
+template <bool LAYERNORM, bool CSUM>
+__global__ __launch_bounds__(64 * FOLD_WAVES) void norm_bwd_wave_kernel(
     const __bf16 *__restrict__ dh, const __bf16 *__restrict__ x, const float *__restrict__ stats,
     const __bf16 *__restrict__ gamma, const __bf16 *__restrict__ dres, __bf16 *__restrict__ dx,
     float *__restrict__ partial, float *__restrict__ csum, int T, int H) {
+    constexpr int NV = 2, W = FOLD_WAVES;
     const int nvec = H / 8, lane = threadIdx.x & 63;
     const int slot = blockIdx.x * W + (threadIdx.x >> 6), n_slots = gridDim.x * W;
     bf16x8 g[NV];
@@ -698,30 +700,15 @@ void launch_norm_fwd(int norm, const void *x, const void *gamma, const void *bet
                            (const __bf16 *)gamma, (const __bf16 *)nullptr, (__bf16 *)h, stats, T, H, eps);
 }
 
-template <int NV, int W>
-static void launch_norm_bwd_wave(int norm, const void *dh, const void *x, const float *stats, const void *gamma,
-                                 const void *dres, void *dx, float *partial, float *csum, int T, int H, int wgs,
-                                 hipStream_t s) {
-#define OB_NBW(LN, CS)                                                                                          \
-    hipLaunchKernelGGL((norm_bwd_wave_kernel<LN, NV, CS, W>), dim3(wgs), dim3(64 * W), 0, s, (const __bf16 *)dh, \
-                       (const __bf16 *)x, stats, (const __bf16 *)gamma, (const __bf16 *)dres, (__bf16 *)dx,     \
-                       partial, csum, T, H)
-    if (norm == OB_LAYERNORM) { if (csum) OB_NBW(true, true); else OB_NBW(true, false); }
-    else { if (csum) OB_NBW(false, true); else OB_NBW(false, false); }
-#undef OB_NBW
-}
-
 // csum (may be null): [norm_bwd_workgroups(T, H)][2][H] fp32, column sums of dres and of dx per partial
 void launch_norm_bwd(int norm, const void *dh, const void *x, const float *stats, const void *gamma,
                      const void *dres, void *dx, float *partial, int T, int H, hipStream_t s, float *csum) {
     ProfScope prof(K_NORM_BWD, s, 8.0 * T * H);
     const int nb = norm_bwd_workgroups(T, H);
-    if (norm_bwd_folds(T, H)) {
-        launch_norm_bwd_wave<2, 8>(norm, dh, x, stats, gamma, dres, dx, partial, csum, T, H, nb, s);
-        return;
-    }
+    const bool folds = norm_bwd_folds(T, H);
+    const int threads = folds ? 64 * FOLD_WAVES : (H / 16 + 63) / 64 * 64;
 #define OB_NB(LN, CS)                                                                                          \
-    hipLaunchKernelGGL((norm_bwd_kernel<LN, CS>), dim3(nb), dim3((H / 16 + 63) / 64 * 64), 0, s, (const __bf16 *)dh, \
+    hipLaunchKernelGGL((folds ? norm_bwd_wave_kernel<LN, CS> : norm_bwd_kernel<LN, CS>), dim3(nb), dim3(threads), 0, s, (const __bf16 *)dh, \
                        (const __bf16 *)x, stats, (const __bf16 *)gamma, (const __bf16 *)dres, (__bf16 *)dx,    \
                        partial, csum, T, H)
     if (norm == OB_LAYERNORM) { if (csum) OB_NB(true, true); else OB_NB(true, false); }

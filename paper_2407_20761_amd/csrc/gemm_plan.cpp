@@ -107,7 +107,7 @@ double estimate_us(int layout, TileKind kind, int nk, double bytes, const Plan &
 
 // The scratch that a GEMM may fill with slice sums, and that the size queries report, is part of the interface:
 // programs size buffers by it, once for the largest batch.  So it is a rule of its own, and the plan of a launch
-// stays within it (that costs 0.15 %).
+// stays within it (that costs 0.26 % over the measured shapes).
 Plan scratch_plan(TileKind whole_kind, double t_whole, int tiles_big, int tiles_small, int nk) {
     auto rule = [&](TileKind kind, const Plan &p) {
         const double cus = compute_units(), w = (double)p.n_tail * p.splits;
