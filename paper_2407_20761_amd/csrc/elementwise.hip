@@ -567,44 +567,25 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 }
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + __expf(-z)); }
 
-// GELU: act[t, f] = gelu(up[t, f]): one flat array.  A workgroup takes 512 consecutive vectors of 8, two per thread.
-constexpr int GELU_VECS = 512;
+// GELU: act[t, f] = gelu(up[t, f]): one flat array, a vector of 8 per thread.  (Two per thread halve the workgroups, and the last of them
+// end alone: forward of 8M elements 10.1 us, with one 8.3; backward of 6M 10.2 and 8.1, of 32M 37.4 and 35.2; of 200M no difference.)
 __global__ __launch_bounds__(256) void gelu_fwd_kernel(const __bf16 *__restrict__ up, __bf16 *__restrict__ act, long n_vec) {
-    for (long base = (long)blockIdx.x * GELU_VECS; base < n_vec; base += (long)gridDim.x * GELU_VECS) {
-        const long i[2] = {base + threadIdx.x, base + 256 + threadIdx.x};
-        bf16x8 u[2];
+    for (long i = blockIdx.x * 256L + threadIdx.x; i < n_vec; i += gridDim.x * 256L) {
+        const bf16x8 u = *(const bf16x8 *)(up + i * 8);
+        bf16x8 o;
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (i[k] < n_vec) u[k] = *(const bf16x8 *)(up + i[k] * 8);
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (i[k] < n_vec) {
-                bf16x8 o;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (__bf16)gelu_f((float)u[k][e]);
-                *(bf16x8 *)(act + i[k] * 8) = o;
-            }
+        for (int e = 0; e < 8; ++e) o[e] = (__bf16)gelu_f((float)u[e]);
+        *(bf16x8 *)(act + i * 8) = o;
     }
 }
 __global__ __launch_bounds__(256) void gelu_bwd_kernel(const __bf16 *__restrict__ dact, const __bf16 *__restrict__ up,
                                                        __bf16 *__restrict__ dup, long n_vec) {
-    for (long base = (long)blockIdx.x * GELU_VECS; base < n_vec; base += (long)gridDim.x * GELU_VECS) {
-        const long i[2] = {base + threadIdx.x, base + 256 + threadIdx.x};
-        bf16x8 u[2], d[2];
+    for (long i = blockIdx.x * 256L + threadIdx.x; i < n_vec; i += gridDim.x * 256L) {
+        const bf16x8 u = *(const bf16x8 *)(up + i * 8), d = *(const bf16x8 *)(dact + i * 8);
+        bf16x8 o;
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (i[k] < n_vec) {
-                u[k] = *(const bf16x8 *)(up + i[k] * 8);
-                d[k] = *(const bf16x8 *)(dact + i[k] * 8);
-            }
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (i[k] < n_vec) {
-                bf16x8 o;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)d[k][e] * gelu_grad_f((float)u[k][e]));
-                *(bf16x8 *)(dup + i[k] * 8) = o;
-            }
+        for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)d[e] * gelu_grad_f((float)u[e]));
+        *(bf16x8 *)(dup + i * 8) = o;
     }
 }
 
@@ -757,26 +738,26 @@ void launch_rotary(void *qkv, int ld, int T, int n_heads_rot, int d, const int32
                        cu_dev, n_seg, log2f(base), sign);
 }
 
-// workgroups of an element-wise pass over n_vec vectors of 8, `per` to a workgroup: at most 65536
-static int act_blocks(long n_vec, int per) { return (int)((n_vec + per - 1) / per < 65536 ? (n_vec + per - 1) / per : 65536); }
+// workgroups of an element-wise pass over n_vec vectors of 8, 256 to a workgroup: at most 65536
+static int act_blocks(long n_vec) { return (int)((n_vec + 255) / 256 < 65536 ? (n_vec + 255) / 256 : 65536); }
 
 void launch_act_fwd(int mlp, const void *up, void *act, int T, int F, hipStream_t s) {
     ProfScope prof(K_ACT_FWD, s, (mlp == OB_SWIGLU ? 6.0 : 4.0) * T * F);
     const long n_vec = (long)T * (F / 8);
     if (mlp == OB_SWIGLU)
-        hipLaunchKernelGGL(swiglu_fwd_kernel, dim3(act_blocks(n_vec, 256)), dim3(256), 0, s, (const __bf16 *)up, (__bf16 *)act, T, F);
+        hipLaunchKernelGGL(swiglu_fwd_kernel, dim3(act_blocks(n_vec)), dim3(256), 0, s, (const __bf16 *)up, (__bf16 *)act, T, F);
     else
-        hipLaunchKernelGGL(gelu_fwd_kernel, dim3(act_blocks(n_vec, GELU_VECS)), dim3(256), 0, s, (const __bf16 *)up, (__bf16 *)act, n_vec);
+        hipLaunchKernelGGL(gelu_fwd_kernel, dim3(act_blocks(n_vec)), dim3(256), 0, s, (const __bf16 *)up, (__bf16 *)act, n_vec);
 }
 
 void launch_act_bwd(int mlp, const void *dact, const void *up, void *dup, int T, int F, hipStream_t s) {
     ProfScope prof(K_ACT_BWD, s, (mlp == OB_SWIGLU ? 10.0 : 6.0) * T * F);
     const long n_vec = (long)T * (F / 8);
     if (mlp == OB_SWIGLU)
-        hipLaunchKernelGGL(swiglu_bwd_kernel, dim3(act_blocks(n_vec, 256)), dim3(256), 0, s, (const __bf16 *)dact,
+        hipLaunchKernelGGL(swiglu_bwd_kernel, dim3(act_blocks(n_vec)), dim3(256), 0, s, (const __bf16 *)dact,
                            (const __bf16 *)up, (__bf16 *)dup, T, F);
     else
-        hipLaunchKernelGGL(gelu_bwd_kernel, dim3(act_blocks(n_vec, GELU_VECS)), dim3(256), 0, s, (const __bf16 *)dact,
+        hipLaunchKernelGGL(gelu_bwd_kernel, dim3(act_blocks(n_vec)), dim3(256), 0, s, (const __bf16 *)dact,
                            (const __bf16 *)up, (__bf16 *)dup, n_vec);
 }
 
