@@ -10,13 +10,16 @@ namespace ob {
 inline bool norm_bwd_folds(int T, int H) { return H <= 1024 && T >= 2048; }
 // Otherwise a row per workgroup at a time, two workgroups of up to four waves to a CU or one of five to eight: 16327 x 4096
 // 97 us (1024 workgroups 108, 256 99; a row per wave with a partial each 117), 16400 x 3200 75 (89, 96; 96),
-// 1500 x 4096 16 (36), 32741 x 6144 276 (1024 workgroups 300; 256 threads with four vectors each 384).
+// 1500 x 4096 16 (36), 32741 x 6144 276 (1024 workgroups 300; 256 threads with four vectors each 384).  Rows of one or two waves have
+// too few bytes in flight in two workgroups: four from 4096 rows on, where the reduction of twice the partials costs less than that
+// gains (with it, 16400 x 1088 55 -> 38, x 1536 58 -> 42, x 2048 62 -> 52, 4100 x 1088 17.7 -> 16.3; 2047 x 1088 13.2 -> 15.0).
 inline int norm_bwd_workgroups(int T, int H) {
-    const int n = norm_bwd_folds(T, H) || H > 4096 ? 256 : 512;
+    const int n = norm_bwd_folds(T, H) || H > 4096 ? 256 : H <= 2048 && T >= 4096 ? 1024 : 512;
     return T < n ? T : n;
 }
-// Rows of partial sums that the workspace has room for: at least as many as workgroups.  (Twice as many from 1024 rows on:
-// programs size buffers by what the size queries report, so the region stays as it is while the launch takes half.)
+// Rows of partial sums that the workspace has room for: at least as many as workgroups.  (Up to twice as
+// many from 1024 rows on: programs size buffers by what the size queries report, so the region stays as it is while most launches take
+// half.)
 inline int norm_bwd_partials(int T, int H) { return norm_bwd_folds(T, H) ? 256 : T < 1024 ? T : 1024; }
 
 // column sums of a [T, C] tensor

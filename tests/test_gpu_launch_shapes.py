@@ -215,7 +215,7 @@ def test_gemm_rectangular_tiles(layout, M, N, K):
     assert np.abs(got[rows] - ref).max() <= 2.0 ** -8 * np.abs(ref).max()
 
 
-@pytest.mark.parametrize("hidden,T", [(64, 1), (64, 2051), (1024, 2047), (1088, 3), (2112, 700), (4096, 513), (4160, 257), (6144, 40),
+@pytest.mark.parametrize("hidden,T", [(64, 1), (64, 2051), (1024, 2047), (1088, 3), (1088, 4095), (1088, 4096), (2048, 4097), (2112, 4097), (2112, 700), (4096, 513), (4160, 257), (6144, 40),
                                       (8192, 300)])
 @pytest.mark.parametrize("norm", [si.NORM_LAYERNORM, si.NORM_RMSNORM])
 def test_norm_bwd_widths(hidden, T, norm):
