@@ -41,9 +41,13 @@ __device__ __forceinline__ size_t gather_offset(long row0, int c8, int g, int Hv
 // The row kernels below: persistent workgroups of WG threads, split into G groups of S threads that each own a token
 // at a time, NV vectors of 8 channels per thread.  A token's loads are issued one token ahead, so that the barriers of
 // the row sums (one per sum: the LDS words alternate) never leave the memory pipe empty.
-// (WG, S, NV): (1024, 256, 2) for rows of up to 4096 channels; wider ones take four vectors per thread and 512 threads,
-// (512, 256, 4) to 8192 and (512, 512, 4) to 16384, so that the backward's column sums fit 256 registers (with 1024
+// Backward, (WG, S, NV): (1024, 256, 2) for rows of up to 4096 channels; wider ones take four vectors per thread and 512 threads,
+// (512, 256, 4) to 8192 and (512, 512, 4) to 16384, so that the column sums fit 256 registers (with 1024
 // threads and two vectors it spilled 60: 463 us for 10752 x 12800).
+// Forward, no sums to keep: a token per workgroup, (256, 256, 2), (256, 256, 4) and (1024, 1024, 2) at the same widths, as many
+// workgroups as have tokens up to what the chip holds well (launch_subsample_norm_fwd).  In the backward's shapes few tokens meet
+// few CUs and barriers of 16 waves: 1280 tokens of 4096 channels 10.4 us, so 7.0; 768 of 4352 8.7 and 5.8; 6144 of
+// 4096 25.4 and 21.3; 1280 of 12800 18.1 and 16.2.
 
 // sums of a (and b) over the S threads of the caller's group; `red` alternates between two halves
 template <int WG, int S>
@@ -74,8 +78,6 @@ __global__ __launch_bounds__(WG) void subsample_norm_fwd_kernel(
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         const int c8 = lane + k * S;
-        gm[k] = c8 < nvec ? *(const bf16x8 *)(gamma + c8 * 8) : bf16x8{};
-        bt[k] = c8 < nvec ? *(const bf16x8 *)(beta + c8 * 8) : bf16x8{};
         src[k] = c8 < nvec ? (int)gather_offset(0, c8, g, Hv) : -1;
         nx[k] = bf16x8{};
     }
@@ -87,6 +89,12 @@ __global__ __launch_bounds__(WG) void subsample_norm_fwd_kernel(
     };
     int half = 0, i = blockIdx.x * G + threadIdx.x / S;
     if (i < n_tok) fetch(i);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {          // (behind the first token's loads, which the first sum waits for)
+        const int c8 = lane + k * S;
+        gm[k] = c8 < nvec ? *(const bf16x8 *)(gamma + c8 * 8) : bf16x8{};
+        bt[k] = c8 < nvec ? *(const bf16x8 *)(beta + c8 * 8) : bf16x8{};
+    }
     for (int first = blockIdx.x * G; first < n_tok; first += stride, i += stride) {   // (same trip count for every thread)
         float x[NV][8], s = 0.f, q = 0.f;
 #pragma unroll
@@ -233,22 +241,29 @@ __global__ __launch_bounds__(THREADS) void rows_gather_kernel(__bf16 *__restrict
 
 }  // namespace
 
-// workgroups that there are tokens for
-static int token_groups(int n_tok, int Hv) { return Hv <= 1024 ? (n_tok + 3) / 4 : Hv <= 2048 ? (n_tok + 1) / 2 : n_tok; }
-#define OB_BY_WIDTH(KERNEL, GRID, ...)                                                                          \
-    do {                                                                                                        \
-        if (Hv <= 1024) hipLaunchKernelGGL((KERNEL<1024, 256, 2>), GRID, dim3(1024), 0, s, __VA_ARGS__);         \
-        else if (Hv <= 2048) hipLaunchKernelGGL((KERNEL<512, 256, 4>), GRID, dim3(512), 0, s, __VA_ARGS__);      \
-        else hipLaunchKernelGGL((KERNEL<512, 512, 4>), GRID, dim3(512), 0, s, __VA_ARGS__);                      \
-    } while (0)
+// Workgroups (of a token at a time) of the forward: one per token while the chip holds them, then as few trips of equal length as
+// keep `most` of them at work.  Of 4352 channels 768 tokens in 768 workgroups 5.8 us, in 512 7.1, 1024 tokens in 1024 8.3, in 512 7.7;
+// of 4096 1280 in 1280 7.0, in 640 7.8, 2048 in 1024 9.2, in 512 10.4.  Wide rows have a CU to themselves.
+static int fwd_workgroups(int n_tok, int Hv) {
+    const int whole = Hv <= 1024 ? 1536 : Hv <= 2048 ? 768 : 256, most = Hv <= 1024 ? 1024 : Hv <= 2048 ? 512 : 256;
+    if (n_tok <= whole) return n_tok;
+    const int trips = (n_tok + most - 1) / most;
+    return (n_tok + trips - 1) / trips;
+}
 
 void launch_subsample_norm_fwd(const void *v, const void *gamma, const void *beta, void *un, float *stats,
                                int n_tok, int g, int Hv, float eps, hipStream_t s) {
     ProfScope prof(K_CONN_FWD, s, 16.0 * n_tok * Hv);   // 4 Hv bf16 in, 4 Hv bf16 out
-    const int wgs = token_groups(n_tok, Hv);
-    OB_BY_WIDTH(subsample_norm_fwd_kernel, dim3(wgs < 512 ? wgs : 512), (const __bf16 *)v, (const __bf16 *)gamma,
-                (const __bf16 *)beta, (__bf16 *)un, stats, n_tok, g, Hv, eps);
+    const dim3 grid(fwd_workgroups(n_tok, Hv));
+#define OB_ARGS (const __bf16 *)v, (const __bf16 *)gamma, (const __bf16 *)beta, (__bf16 *)un, stats, n_tok, g, Hv, eps
+    if (Hv <= 1024) hipLaunchKernelGGL((subsample_norm_fwd_kernel<256, 256, 2>), grid, dim3(256), 0, s, OB_ARGS);
+    else if (Hv <= 2048) hipLaunchKernelGGL((subsample_norm_fwd_kernel<256, 256, 4>), grid, dim3(256), 0, s, OB_ARGS);
+    else hipLaunchKernelGGL((subsample_norm_fwd_kernel<1024, 1024, 2>), grid, dim3(1024), 0, s, OB_ARGS);
+#undef OB_ARGS
 }
+
+// workgroups of the backward that there are tokens for
+static int token_groups(int n_tok, int Hv) { return Hv <= 1024 ? (n_tok + 3) / 4 : Hv <= 2048 ? (n_tok + 1) / 2 : n_tok; }
 
 int launch_subsample_norm_bwd_wgrad(const void *dun, const void *v, const float *stats, const void *gamma, void *dv,
                                     float *partial, int max_partials, int n_tok, int n_tiles, int g, int Hv, hipStream_t s) {
@@ -256,11 +271,13 @@ int launch_subsample_norm_bwd_wgrad(const void *dun, const void *v, const float 
     int wgs = token_groups(n_tok, Hv);
     if (wgs > 256) wgs = 256;
     if (wgs > max_partials) wgs = max_partials;
-    OB_BY_WIDTH(subsample_norm_bwd_kernel, dim3(wgs), (const __bf16 *)dun, (const __bf16 *)v, stats, (const __bf16 *)gamma,
-                (__bf16 *)dv, partial, n_tok, n_tiles, g, Hv);
+#define OB_ARGS (const __bf16 *)dun, (const __bf16 *)v, stats, (const __bf16 *)gamma, (__bf16 *)dv, partial, n_tok, n_tiles, g, Hv
+    if (Hv <= 1024) hipLaunchKernelGGL((subsample_norm_bwd_kernel<1024, 256, 2>), dim3(wgs), dim3(1024), 0, s, OB_ARGS);
+    else if (Hv <= 2048) hipLaunchKernelGGL((subsample_norm_bwd_kernel<512, 256, 4>), dim3(wgs), dim3(512), 0, s, OB_ARGS);
+    else hipLaunchKernelGGL((subsample_norm_bwd_kernel<512, 512, 4>), dim3(wgs), dim3(512), 0, s, OB_ARGS);
+#undef OB_ARGS
     return wgs;
 }
-#undef OB_BY_WIDTH
 
 void launch_rows_gather(void *small, const void *big, const int32_t *rows_dev, int n_rows, int H, hipStream_t s) {
     ProfScope prof(K_ROWS, s, 4.0 * n_rows * H);
