@@ -822,15 +822,15 @@ __device__ __forceinline__ void issue_row_stats(const float *base, long floats_l
 // tiles of SR rows), of which dkv_shape() takes the one its estimate of the launch favours:
 //  * D = 64: two pairs, so that workgroups which nothing synchronises share a CU and a 1025-row segment wastes
 //    6 % of the rows (six pairs in step: 12 %).  SR = 32 needs 34 KB of LDS and under 128 registers: four
-//    workgroups to the CU, the better rate when the chip is full (12 ViT tiles x 16 heads: 151 us, against 178
-//    with SR = 64 and 189 for six pairs).  SR = 64 has half the barriers and stage switches to a row, the shorter
-//    chain when one long segment keeps the launch waiting (16 texts, 16 / 4 heads: 121 against 144 and 177 us).  Six pairs
-//    remain for bidirectional launches that are just about one round of them (5 ViT tiles x 8 heads in groups of 6, 240
-//    workgroups: 195 us, against 207 with SR = 32).
+//    workgroups to the CU, the better rate when the chip is full (12 ViT tiles x 16 heads: 134 us, against 149
+//    with SR = 64 and 159 for six pairs).  SR = 64 has half the barriers and stage switches to a row, the shorter
+//    chain when one long segment keeps the launch waiting (texts of 8187 tokens in all, 16 / 4 heads: 110 against 140 us).  Six
+//    pairs remain for bidirectional launches that two pairs would need a second round for (one segment of 4097, 8 heads in
+//    groups of 6: 549 us, against 670 with SR = 32).
 //  * D = 128: four pairs on one CU, eight waves in step, the better rate when the chip is full (7B-shaped batch:
 //    707 us, two pairs 1012, two pairs with SR = 32 746); two pairs, one wave to a SIMD, the shorter
-//    trip for launches that leave most of it idle (one segment of 557, 32 / 8 heads: 61 against 70 us; of
-//    2000, 12 / 2 heads: 274 against 327).
+//    trip for launches that leave most of it idle (one segment of 557, 32 / 8 heads: 60 against 69 us; of
+//    2000, 12 / 2 heads: 271 against 310).
 // All shapes of a head size add up the query rows of a key row in the same order, set by DKV_ORDER_Q and (causal) the
 // place in whole tiles of dkv_whole() key rows: which of them runs does not show in the result, so a packed batch
 // still gives bit for bit what its segments give alone.

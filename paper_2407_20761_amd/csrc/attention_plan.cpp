@@ -58,9 +58,9 @@ int make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side,
 // Which of its shapes the dK / dV kernel runs in (see there).  An estimate of the launch's duration in
 // microseconds: the trips (64 query rows against a workgroup's key rows) that a CU has to make at the rate of a full
 // chip, or the longest chain of trips (the first key rows of the longest segment, all query heads of a group) at the
-// rate its workgroup sees, whichever is longer.  Over 224 launches measured in either shape (64 - 16000 tokens in one
-// segment, ViT tiles or texts, 1 - 25 key / value heads, groups of 1 - 6, both masks) the picks are 0.03 % (D = 64) and 0.2 %
-// (D = 128) slower than the faster shape.
+// rate its workgroup sees, whichever is longer.  Over 448 launches measured in every shape (profiles/dkv_shape_choice.csv: 64 - 16400
+// tokens in one segment, ViT tiles or texts, 1 - 25 key / value heads, groups of 1 - 6, both masks) the picks are 0.1 - 0.2 %
+// slower in the mean than the fastest shape; nine more than 3 %, the worst 16 % (one segment of 2000, 8 heads of 128: 62 us, two pairs 53).
 namespace {
 struct DkvShape { int kv_rows; double full, chain; };
 constexpr DkvShape DKV_SHAPES[2][2] = {{{64, 0.81, 1.1}, {64, 0.70, 1.53}},      // D = 64: SR = 64, SR = 32
@@ -78,10 +78,12 @@ int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
         }
         est[i] = group * std::max(sum * nkv / compute_units() * sh.full, chain * sh.chain);
     }
-    if (d == 64 && !causal) {      // 70 - 100 % of one round of six pairs
-        const long six = (long)count_tiles(seg, 32 * dkv_np(64, 2)) * nkv;
-        if (10 * six >= 7 * compute_units() && six <= compute_units()) return 2;
-    }
+    // six pairs where two would need a second round (of two workgroups to a CU) and they do not: 520 or 176 workgroups, one segment
+    // of 4097, 48 / 8 heads: 670 us with SR = 32, 760 with 64, 549; ten ViT tiles x 4 heads in groups of 4, 680 or 240: 125, 142,
+    // 114; but three tiles x 10 heads, 510 or 180: 32, 29, 34
+    if (d == 64 && !causal && (long)count_tiles(seg, 64) * nkv > 2 * compute_units() &&
+        (long)count_tiles(seg, 32 * dkv_np(64, 2)) * nkv <= compute_units())
+        return 2;
     return est[1] < est[0] ? 1 : 0;
 }
 

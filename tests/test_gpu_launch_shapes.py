@@ -38,8 +38,12 @@ def _attention(qkv, d_o, lens, nq, nkv, d, mask):
 def test_dkv_shapes_give_the_same_bits(d, nq, nkv, mask):
     """Many short segments fill the chip (the shape for throughput), each alone leaves it idle (the shape for the
     shorter trip): lengths on and beside the 32-, 64- and 128-row borders, oracle on two of them.
-    (64, 10, 10): the bidirectional batch is about one round of the six-pair shape."""
-    lens = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 191, 193, 257] * (1 if nkv == 10 else 8) + [385]
+    (64, 10, 10): two pairs would need a second round for the bidirectional batch, six do not."""
+    lens = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 191, 193, 257] * 8 + [385]
+    if nkv == 10:
+        lens = [1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 257, 513, 1025, 385]
+    plan, _ = ob.ob_varlen_attn_bwd_plan(ob.Segments(si.lengths_to_cu(lens)), nq, nkv, d, mask)
+    assert (plan.key_rows, plan.query_rows) == ((128, 64) if d == 128 else (64, 32) if nkv != 10 else (64, 64) if mask else (192, 64))
     print(f"dkv shapes d={d} nq={nq} nkv={nkv} mask={mask}", flush=True)
     cu = si.lengths_to_cu(lens)
     T = int(cu[-1])
@@ -47,8 +51,10 @@ def test_dkv_shapes_give_the_same_bits(d, nq, nkv, mask):
     qkv = to_dev(np.concatenate([q.reshape(T, -1), k.reshape(T, -1), v.reshape(T, -1)], axis=1))
     d_o = to_dev(d_o_np.reshape(T, -1))
     packed = _attention(qkv, d_o, lens, nq, nkv, d, mask)
-    for j in list(range(17)) + [len(lens) - 1]:
+    for j in list(range(min(17, len(lens) - 1))) + [len(lens) - 1]:
         a, b = int(cu[j]), int(cu[j + 1])
+        plan, _ = ob.ob_varlen_attn_bwd_plan(ob.Segments(si.lengths_to_cu([b - a])), nq, nkv, d, mask)
+        assert (plan.key_rows, plan.query_rows) == (64, 64)
         alone = _attention(qkv[a:b].contiguous(), d_o[a:b].contiguous(), [b - a], nq, nkv, d, mask)
         for name, x, y in zip(("o", "dq", "dk", "dv"), packed, alone):
             assert torch.equal(x[a:b].view(torch.int16), y.view(torch.int16)), (name, j, b - a)

@@ -76,3 +76,11 @@ def test_every_gemm_form_has_a_gpu_case():
         M, N, K = (a, b, T) if layout == 2 else (T, a, b)
         missing = seen(layout, gemm_launches.forms(layout, M, N, K, i % 5 != 0)) - covered
         assert not missing, (layout, M, N, K, missing)
+
+
+# bidirectional, heads of 64: six pairs where two need a second round of two workgroups to a CU and they do not (256 CUs)
+@pytest.mark.parametrize("nkv,lens,six", [(10, [1025] * 3, False), (8, [1025] * 4, True), (8, [4097], True), (8, [1025] * 6, False), (16, [2000], False),
+                                          (4, [1025] * 7, False), (4, [1025] * 8, True)])
+def test_dkv_six_pairs_save_a_round(nkv, lens, six):
+    plan, _ = ob.ob_varlen_attn_bwd_plan(_segments(lens), nkv, nkv, 64, orc.MASK_BIDIR)
+    assert (plan.key_rows == 192) == six
