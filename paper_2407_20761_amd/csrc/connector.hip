@@ -45,7 +45,8 @@ __device__ __forceinline__ size_t gather_offset(long row0, int c8, int g, int Hv
 // (512, 256, 4) to 8192 and (512, 512, 4) to 16384, so that the column sums fit 256 registers (with 1024
 // threads and two vectors it spilled 60: 463 us for 10752 x 12800).
 // Forward, no sums to keep: a token per workgroup, (256, 256, 2), (256, 256, 4) and (1024, 1024, 2) at the same widths, as many
-// workgroups as have tokens up to what the chip holds well (launch_subsample_norm_fwd).  In the backward's shapes few tokens meet
+// workgroups as have tokens up to what the chip holds well (fwd_workgroups); for more than 3072 tokens of the widest rows
+// (512, 512, 4), two to a CU (of 12800 channels 2048 24.7 us, with 1024 threads 24.0, 4096 41.6 and 42.6, 6144 60.8 and 61.8).  In the backward's shapes few tokens meet
 // few CUs and barriers of 16 waves: 1280 tokens of 4096 channels 10.4 us, so 7.0; 768 of 4352 8.7 and 5.8; 6144 of
 // 4096 25.4 and 21.3; 1280 of 12800 18.1 and 16.2.
 
@@ -243,9 +244,9 @@ __global__ __launch_bounds__(THREADS) void rows_gather_kernel(__bf16 *__restrict
 
 // Workgroups (of a token at a time) of the forward: one per token while the chip holds them, then as few trips of equal length as
 // keep `most` of them at work.  Of 4352 channels 768 tokens in 768 workgroups 5.8 us, in 512 7.1, 1024 tokens in 1024 8.3, in 512 7.7;
-// of 4096 1280 in 1280 7.0, in 640 7.8, 2048 in 1024 9.2, in 512 10.4.  Wide rows have a CU to themselves.
+// of 4096 1280 in 1280 7.0, in 640 7.8, 2048 in 1024 9.2, in 512 10.4.  The widest rows have a CU to themselves, or share it in twos.
 static int fwd_workgroups(int n_tok, int Hv) {
-    const int whole = Hv <= 1024 ? 1536 : Hv <= 2048 ? 768 : 256, most = Hv <= 1024 ? 1024 : Hv <= 2048 ? 512 : 256;
+    const int whole = Hv <= 1024 ? 1536 : Hv <= 2048 ? 768 : 256, most = Hv <= 1024 ? 1024 : Hv <= 2048 || n_tok > 3072 ? 512 : 256;
     if (n_tok <= whole) return n_tok;
     const int trips = (n_tok + most - 1) / most;
     return (n_tok + trips - 1) / trips;
@@ -258,7 +259,8 @@ void launch_subsample_norm_fwd(const void *v, const void *gamma, const void *bet
 #define OB_ARGS (const __bf16 *)v, (const __bf16 *)gamma, (const __bf16 *)beta, (__bf16 *)un, stats, n_tok, g, Hv, eps
     if (Hv <= 1024) hipLaunchKernelGGL((subsample_norm_fwd_kernel<256, 256, 2>), grid, dim3(256), 0, s, OB_ARGS);
     else if (Hv <= 2048) hipLaunchKernelGGL((subsample_norm_fwd_kernel<256, 256, 4>), grid, dim3(256), 0, s, OB_ARGS);
-    else hipLaunchKernelGGL((subsample_norm_fwd_kernel<1024, 1024, 2>), grid, dim3(1024), 0, s, OB_ARGS);
+    else if (n_tok <= 3072) hipLaunchKernelGGL((subsample_norm_fwd_kernel<1024, 1024, 2>), grid, dim3(1024), 0, s, OB_ARGS);
+    else hipLaunchKernelGGL((subsample_norm_fwd_kernel<512, 512, 4>), grid, dim3(512), 0, s, OB_ARGS);
 #undef OB_ARGS
 }
 

@@ -173,7 +173,7 @@ def test_gemm_fine_tiles(layout, M, N, K):
 
 @pytest.mark.parametrize("Hv,Ht,grid,tiles", [(64, 128, 2, 3), (1024, 64, 32, 1), (1088, 128, 16, 5), (2048, 64, 16, 4), (2112, 64, 32, 2),
                                               (4096, 64, 18, 3), (64, 64, 2, 1536), (64, 64, 2, 1537), (1088, 64, 2, 768),
-                                              (1088, 64, 2, 769), (2112, 64, 2, 256), (2112, 64, 2, 257)])
+                                              (1088, 64, 2, 769), (2112, 64, 2, 256), (2112, 64, 2, 257), (2112, 64, 16, 48), (2112, 64, 16, 49)])
 def test_connector_widths(Hv, Ht, grid, tiles):
     """The hand-over's row kernels at the widths where their launch shape changes, with token counts that leave groups and
     workgroups without a token, and few enough (81 and less) or enough for the one launch of all column sums."""
