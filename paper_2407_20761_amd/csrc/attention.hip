@@ -701,8 +701,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(
 // "row-fragment tile x held rows -> 32x32 scores" and "transposed tile x packed scores -> output";
 // role G does the second one tile late (see the kernel), so that it never waits for its partner.
 // A wave raises its priority for its matrix products: of two waves on a SIMD the one with MFMAs to issue goes first and
-// the other one's element-wise work fills the gaps (7B-shaped batch 714 -> 702 us, 6B ViT tiles 668 -> 656, one segment of
-// 7168 888 -> 862; a fixed priority for either role loses, the forward and dQ gain nothing).
+// the other one's element-wise work fills the gaps (7B-shaped batch and 6B ViT tiles 1.7 %, one segment
+// of 7168 2.9 %, both builds in turn; a fixed priority for either role loses, the forward and dQ gain nothing).
 // ------------------------------------------------------------------------------------------------
 // scores of a streamed tile of 32 MT rows against the 32 held rows: acc[mt] = rows 32 mt .. of the tile
 template <int D, int MT>
@@ -827,8 +827,8 @@ __device__ __forceinline__ void issue_row_stats(const float *base, long floats_l
 //    chain when one long segment keeps the launch waiting (texts of 8187 tokens in all, 16 / 4 heads: 110 against 140 us).  Six
 //    pairs remain for bidirectional launches that two pairs would need a second round for (one segment of 4097, 8 heads in
 //    groups of 6: 549 us, against 670 with SR = 32).
-//  * D = 128: four pairs on one CU, eight waves in step, the better rate when the chip is full (7B-shaped batch:
-//    707 us, two pairs 1012, two pairs with SR = 32 746); two pairs, one wave to a SIMD, the shorter
+//  * D = 128: four pairs on one CU, eight waves in step, the better rate when the chip is full (texts of
+//    16384 tokens, 32 / 8 heads: 269 us, two pairs 423; two pairs with SR = 32 5 % behind); two pairs, one wave to a SIMD, the shorter
 //    trip for launches that leave most of it idle (one segment of 557, 32 / 8 heads: 60 against 69 us; of
 //    2000, 12 / 2 heads: 271 against 310).
 // All shapes of a head size add up the query rows of a key row in the same order, set by DKV_ORDER_Q and (causal) the
