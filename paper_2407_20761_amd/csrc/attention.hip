@@ -32,6 +32,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 namespace {
 
@@ -79,6 +80,61 @@ __device__ __forceinline__ int swz(int r) {
     return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
 }
 
+// One wave-level load global -> LDS of WORDS dwords per lane, lane i to byte 4 WORDS i from dst (lanes past the descriptor's
+// range deliver zeros).  As an instruction: the compiler counts the builtin among the accesses that a later LDS read may have to wait
+// for, and where stages are parts of one array it waits for the loads just issued in front of the first read of every trip.
+// What has to have landed is said by the s_waitcnt in front of each barrier.  A descriptor that has just been put
+// together goes through fresh() first (five wait states between a vector instruction's scalar result and a memory
+// instruction that reads it).
+__device__ __forceinline__ void fresh(u32x4 &rsrc) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_nop 4" : "+s"(rsrc));
+#endif
+}
+template <int WORDS>
+__device__ __forceinline__ void load_lds(u32x4 rsrc, unsigned char OB_LDS *dst, uint32_t voff) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+    if constexpr (WORDS == 4)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(at), "v"(voff), "s"(rsrc) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" : : "s"(at), "v"(voff), "s"(rsrc) : "memory");
+#endif
+}
+// descriptor of the `bytes_left` bytes from `base` on (clamped to [0, 2^32 - 1], in scalar instructions: the compiler's
+// own 64-bit compares go through the vector unit)
+__device__ __forceinline__ u32x4 make_rsrc(const void *base, long bytes_left) {
+    const uint64_t b = (uint64_t)base;
+    u32x4 r = {(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)), 0u, 0x00020000u};
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint32_t num;
+    asm("s_cmp_eq_u32 %2, 0\n\ts_cselect_b32 %0, %1, -1\n\ts_cmp_lt_i32 %2, 0\n\ts_cselect_b32 %0, 0, %0"
+        : "=&s"(num)
+        : "s"(__builtin_amdgcn_readfirstlane((uint32_t)bytes_left)),
+          "s"(__builtin_amdgcn_readfirstlane((int32_t)(bytes_left >> 32)))
+        : "scc");
+    r[2] = num;
+#endif
+    fresh(r);
+    return r;
+}
+
+// 16 bytes of LDS per lane (a restrict argument says that no load to LDS in flight touches them: without it the compiler waits
+// for all of those first)
+template <class V>
+__device__ __forceinline__ V lds16(const unsigned char OB_LDS *__restrict__ p) { return *(const V OB_LDS *)p; }
+
+// s_waitcnt operand: at most `vm` vector-memory operations pending, no LDS operation
+constexpr int wait_vm_lds0(int vm) { return (vm & 15) | ((vm >> 4) << 14) | 0x70; }
+
+// The barrier instruction alone: what has to be complete in front of it is said by an s_waitcnt (__syncthreads() waits for every
+// load in flight); the empty statements keep the compiler from moving LDS accesses across.
+__device__ __forceinline__ void bare_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Per-lane addressing of one streamed [ROWS][D] tile family.
 template <int D, int ROWS = ST>
 struct Tile {
@@ -101,15 +157,16 @@ struct Tile {
         const int x = lane & 31, h = lane >> 5;
 #pragma unroll
         for (int t = 0; t < D / 16; ++t) rr[t] = x * RB + (((2 * t + h) ^ swz<D>(x)) * 16);
-        const int b = lane >> 4, q = lane & 15, kq = q >> 2, c = q & 3, hb = b >> 1;
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int dt = 0; dt < D / 32; ++dt) {
-                const int row = 8 * s + 4 * hb + kq;  // + 16 u
-                const int chunk = 4 * dt + 2 * (b & 1) + (c >> 1);
-                tro[s][dt] = row * RB + ((chunk ^ swz<D>(row)) * 16) + (c & 1) * 8;
-            }
+            for (int dt = 0; dt < D / 32; ++dt) tro[s][dt] = tr_offset(lane, s, dt);
+    }
+    static __device__ __forceinline__ int tr_offset(int lane, int s, int dt) {
+        const int b = lane >> 4, q = lane & 15, kq = q >> 2, c = q & 3, hb = b >> 1;
+        const int row = 8 * s + 4 * hb + kq;  // + 16 u
+        const int chunk = 4 * dt + 2 * (b & 1) + (c >> 1);
+        return row * RB + ((chunk ^ swz<D>(row)) * 16) + (c & 1) * 8;
     }
     // asynchronous copy of rows [row0, row0 + ROWS) of a [*, ld] matrix (column offset folded into
     // `base`); rows past the end of the matrix arrive as zeros
@@ -140,11 +197,14 @@ struct Tile {
     }
     // lane l: column 32 dt + l % 32, rows 16 u + 8 (e / 4) + 4 (l / 32) + e % 4 for e = 0..7
     __device__ __forceinline__ bf16x8 frag_tr(const unsigned char OB_LDS *__restrict__ tile, int dt, int u) const {
+        return frag_at(tile, tro[0][dt], tro[1][dt], u);
+    }
+    static __device__ __forceinline__ bf16x8 frag_at(const unsigned char OB_LDS *__restrict__ tile, int off0, int off1, int u) {
 #if defined(__HIP_DEVICE_COMPILE__)  // gfx950-only builtin, hidden from the host pass
         typedef __attribute__((ext_vector_type(4))) short s16x4;
         typedef __attribute__((ext_vector_type(8))) short s16x8;
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 OB_LDS *)(tile + tro[0][dt] + u * 16 * RB));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 OB_LDS *)(tile + tro[1][dt] + u * 16 * RB));
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 OB_LDS *)(tile + off0 + u * 16 * RB));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 OB_LDS *)(tile + off1 + u * 16 * RB));
         return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 #else
         return bf16x8{};
@@ -167,22 +227,25 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int base) {
 // Sine and cosine come from the hardware's functions of the angle in revolutions, reduced to [0, 1)
 // first: an absolute error of a few 1e-4 rad at positions in the thousands, an order of magnitude
 // below the bf16 rounding of the result.
+// x1: accumulator tile dt, x2: dt + D/64.
+template <int D>
+__device__ __forceinline__ void rotary_bwd_pair(f32x16 &x1, f32x16 &x2, int dt, int pos, float log2_base, int lh) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int i = 32 * dt + 8 * (r >> 2) + 4 * lh + (r & 3);
+        const float theta = __builtin_amdgcn_exp2f(-2.0f * (float)i / (float)D * log2_base);
+        float rev = (float)pos * theta * 0.15915494309189535f;
+        rev -= floorf(rev);
+        const float sn = __builtin_amdgcn_sinf(rev), cs = __builtin_amdgcn_cosf(rev);
+        const float a = x1[r], b = x2[r];
+        x1[r] = a * cs + b * sn;
+        x2[r] = b * cs - a * sn;
+    }
+}
 template <int D>
 __device__ __forceinline__ void rotary_bwd_row(f32x16 (&acc)[D / 32], int pos, float log2_base, int lh) {
-    constexpr int H = D / 64;   // accumulator tiles per half of the head dimension
 #pragma unroll
-    for (int dt = 0; dt < H; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = 32 * dt + 8 * (r >> 2) + 4 * lh + (r & 3);
-            const float theta = __builtin_amdgcn_exp2f(-2.0f * (float)i / (float)D * log2_base);
-            float rev = (float)pos * theta * 0.15915494309189535f;
-            rev -= floorf(rev);
-            const float sn = __builtin_amdgcn_sinf(rev), cs = __builtin_amdgcn_cosf(rev);
-            const float x1 = acc[dt][r], x2 = acc[dt + H][r];
-            acc[dt][r] = x1 * cs + x2 * sn;
-            acc[dt + H][r] = x2 * cs - x1 * sn;
-        }
+    for (int dt = 0; dt < D / 64; ++dt) rotary_bwd_pair<D>(acc[dt], acc[dt + D / 64], dt, pos, log2_base, lh);
 }
 
 // Which workgroup does which tile.  The launch is one-dimensional: workgroup b works on tile
@@ -736,7 +799,7 @@ __device__ __forceinline__ void dkv_scores(const unsigned char OB_LDS *__restric
 // role P: probabilities of the 32 MT x 32 score tile, packed as the second operands of the 2 MT
 // 16-row contraction steps (pk[mt][h] serves step 2 mt + h)
 template <bool CAUSAL, bool MASK, int MT>
-__device__ __forceinline__ void dkv_probs(const f32x16 (&s)[MT], const float OB_LDS *__restrict__ lse2_s,
+__device__ __forceinline__ void dkv_probs(const f32x16 (&s)[MT], const unsigned char OB_LDS *__restrict__ lse2_s,
                                           int q0, int seg_end, int kv_row, float sl2, bf16x8 (&pk)[MT][2]) {
     const int lh = (threadIdx.x & 63) >> 5;
 #pragma unroll
@@ -744,7 +807,7 @@ __device__ __forceinline__ void dkv_probs(const f32x16 (&s)[MT], const float OB_
         f32x16 p;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const f32x4 l4 = *(const f32x4 OB_LDS *)(lse2_s + mt * 32 + 8 * g + 4 * lh);
+            const f32x4 l4 = lds16<f32x4>(lse2_s + (mt * 32 + 8 * g + 4 * lh) * 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 bool ok = true;
@@ -752,7 +815,8 @@ __device__ __forceinline__ void dkv_probs(const f32x16 (&s)[MT], const float OB_
                     const int qr = q0 + mt * 32 + 8 * g + 4 * lh + e;
                     ok = qr < seg_end && (!CAUSAL || kv_row <= qr);
                 }
-                p[4 * g + e] = ok ? fast_exp2(s[mt][4 * g + e] * sl2 - l4[e]) : 0.f;
+                const float pe = fast_exp2(s[mt][4 * g + e] * sl2 - l4[e]);
+                p[4 * g + e] = ok ? pe : 0.f;
             }
         }
         pk[mt][0] = pack8(p, 0);
@@ -762,7 +826,7 @@ __device__ __forceinline__ void dkv_probs(const f32x16 (&s)[MT], const float OB_
 
 // role G: dS = P (dP - Delta), in place of the packed probabilities
 template <int MT>
-__device__ __forceinline__ void dkv_dscores(const f32x16 (&dp)[MT], const float OB_LDS *__restrict__ dlt_s,
+__device__ __forceinline__ void dkv_dscores(const f32x16 (&dp)[MT], const unsigned char OB_LDS *__restrict__ dlt_s,
                                             bf16x8 (&pk)[MT][2]) {
     const int lh = (threadIdx.x & 63) >> 5;
 #pragma unroll
@@ -770,7 +834,7 @@ __device__ __forceinline__ void dkv_dscores(const f32x16 (&dp)[MT], const float 
         f32x16 ds;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const f32x4 d4 = *(const f32x4 OB_LDS *)(dlt_s + mt * 32 + 8 * g + 4 * lh);
+            const f32x4 d4 = lds16<f32x4>(dlt_s + (mt * 32 + 8 * g + 4 * lh) * 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int r = 4 * g + e;
@@ -806,36 +870,200 @@ __device__ __forceinline__ void dkv_outputs(const unsigned char OB_LDS *__restri
     __builtin_amdgcn_s_setprio(0);
 }
 
-// one wave-level load of 64 consecutive floats into LDS (lanes past the end deliver zeros)
-__device__ __forceinline__ void issue_row_stats(const float *base, long floats_left,
-                                                float OB_LDS *__restrict__ dst, int lane) {
-    const uint64_t b = (uint64_t)base;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-    const long cl = floats_left < 0 ? 0 : floats_left * 4;
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(((uint64_t)hi << 32) | lo), 0, (int)__builtin_amdgcn_readfirstlane((uint32_t)cl), 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, dst, 4, lane * 4, 0, 0, 0);
+// role P: the products of dkv_outputs (probabilities pk of the tile before), the probabilities of the tile at hand between them:
+// two products, their operands read two products ahead, to 16 / D x 16 values per lane
+template <int D, int MT>
+__device__ __forceinline__ void dkv_outputs_probs(const unsigned char OB_LDS *__restrict__ tile, const Tile<D, 32 * MT> &tl,
+                                                  const bf16x8 (&pk)[MT][2], f32x16 (&acc_out)[D / 32], const f32x16 (&s)[MT],
+                                                  const unsigned char OB_LDS *__restrict__ lse2_s, float sl2, bf16x8 (&pn)[MT][2]) {
+    constexpr int DT = D / 32, PER = DT / 2, NB = 2 * MT * PER, EL = 8 / PER;      // batches of two products; values per lane and batch
+    const int lh = (threadIdx.x & 63) >> 5;
+    bf16x8 tf[2][2];
+    f32x4 l4[2][EL / 4];
+    auto read = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) tf[b & 1][i] = tl.frag_tr(tile, 2 * (b % PER) + i, b / PER);
+#pragma unroll
+        for (int g = 0; g < EL / 4; ++g) l4[b & 1][g] = lds16<f32x4>(lse2_s + (2 * EL * b + 8 * g + 4 * lh) * 4);
+    };
+    read(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int u = b / PER, e0 = (b % PER) * EL;
+        if (b + 1 < NB) read(b + 1);
+#pragma unroll
+        for (int e = 0; e < EL; ++e)
+            pn[u >> 1][u & 1][e0 + e] = (__bf16)fast_exp2(s[u >> 1][8 * (u & 1) + e0 + e] * sl2 - l4[b & 1][e >> 2][e & 3]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int dt = 2 * (b % PER) + i;
+            acc_out[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf[b & 1][i], pk[u >> 1][u & 1], acc_out[dt], 0, 0, 0);
+        }
+        if (b + 1 < NB) __builtin_amdgcn_sched_group_barrier(0x100, 4 + EL / 4, 0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, EL * 5 / 4, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
-// The dK / dV kernel comes in two or three shapes per head size (NP pairs of waves, each pair owning 32 key rows; query
-// tiles of SR rows), of which dkv_shape() takes the one its estimate of the launch favours:
+// role G: the products of dkv_scores, dS = P (dP - Delta) of the tile before, in place of its probabilities pk, between them
+template <int D, int MT>
+__device__ __forceinline__ void dkv_scores_dscores(const unsigned char OB_LDS *__restrict__ tile, const Tile<D, 32 * MT> &tl,
+                                                   const bf16x8 (&held)[D / 16], f32x16 (&acc)[MT], const f32x16 (&dp)[MT],
+                                                   const unsigned char OB_LDS *__restrict__ dlt_s, bf16x8 (&pk)[MT][2]) {
+    constexpr int KT = D / 16, PER = KT / 2, NB = MT * PER, EL = 16 * MT / NB;       // batches of two products; values per lane and batch
+    const int lh = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+    bf16x8 fr[2][2];
+    f32x4 d4[2][EL / 4];
+    auto read = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) fr[b & 1][i] = tl.frag_row(tile, b / PER, 2 * (b % PER) + i);
+#pragma unroll
+        for (int g = 0; g < EL / 4; ++g) d4[b & 1][g] = lds16<f32x4>(dlt_s + (2 * EL * b + 8 * g + 4 * lh) * 4);
+    };
+    read(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if (b + 1 < NB) read(b + 1);
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+            const int r = EL * b + e, mt = r >> 4;                          // accumulator register r % 16 of row tile mt
+            const float p = (float)pk[mt][(r >> 3) & 1][r & 7];
+            pk[mt][(r >> 3) & 1][r & 7] = (__bf16)(p * (dp[mt][r & 15] - d4[b & 1][e >> 2][e & 3]));
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            acc[b / PER] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[b & 1][i], held[2 * (b % PER) + i], acc[b / PER], 0, 0, 0);
+        if (b + 1 < NB) __builtin_amdgcn_sched_group_barrier(0x100, 2 + EL / 4, 0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, EL * 7 / 4, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// dK / dV comes in three shapes per head size (NP pairs of waves, each pair owning 32 key rows, query tiles of SR rows; or blocks, a
+// kernel of its own further down), of which dkv_shape() takes the one its estimate of the launch favours:
 //  * D = 64: two pairs, so that workgroups which nothing synchronises share a CU and a 1025-row segment wastes
 //    6 % of the rows (six pairs in step: 12 %).  SR = 32 needs 34 KB of LDS and under 128 registers: four
-//    workgroups to the CU, the better rate when the chip is full (12 ViT tiles x 16 heads: 134 us, against 149
-//    with SR = 64 and 159 for six pairs).  SR = 64 has half the barriers and stage switches to a row, the shorter
-//    chain when one long segment keeps the launch waiting (texts of 8187 tokens in all, 16 / 4 heads: 110 against 140 us).  Six
-//    pairs remain for bidirectional launches that two pairs would need a second round for (one segment of 4097, 8 heads in
-//    groups of 6: 549 us, against 670 with SR = 32).
+//    workgroups to the CU, the better rate when the chip is full (12 ViT tiles x 16 heads: 138 us, against 166
+//    with SR = 64).  SR = 64 has half the barriers and stage switches to a row, and as a wave has its SIMD nearly to
+//    itself its element-wise work goes between its own products: the shorter
+//    chain when one long segment keeps the launch waiting (texts of 8187 tokens in all, 16 / 4 heads: 96 us, one after the other 110,
+//    SR = 32 126).  Six pairs remain for bidirectional launches that two pairs would need a second round for (one segment of 4097, 8 heads in
+//    groups of 6: 560 us, against 661 with SR = 32).
 //  * D = 128: four pairs on one CU, eight waves in step, the better rate when the chip is full (texts of
-//    16384 tokens, 32 / 8 heads: 269 us, two pairs 423; two pairs with SR = 32 5 % behind); two pairs, one wave to a SIMD, the shorter
-//    trip for launches that leave most of it idle (one segment of 557, 32 / 8 heads: 60 against 69 us; of
-//    2000, 12 / 2 heads: 271 against 310).
+//    16384 tokens, 32 / 8 heads, and other batches of its size: 612 us, blocks 776); blocks for launches that wait for their longest walk; two pairs,
+//    one trip less from scores to results, for walks of a tile or two (one segment of 64, 8 heads: 9.8 us, blocks 10.1).
 // All shapes of a head size add up the query rows of a key row in the same order, set by DKV_ORDER_Q and (causal) the
 // place in whole tiles of dkv_whole() key rows: which of them runs does not show in the result, so a packed batch
 // still gives bit for bit what its segments give alone.
 constexpr int DKV_ORDER_Q = 64;   // the ragged end of the query rows is one masked step of up to this many rows
 constexpr int dkv_whole(int d) { return d == 64 ? 64 : 128; }
+
+// The query tiles that a workgroup of dK / dV walks, in the order of work: the masked ones (causal: on the diagonal; either way the
+// ragged end) of every query head of the group, then the mask-free ones of every head -- the sums do not care, and one loop per kind keeps
+// the accumulators in place.  `dead`: causal query rows before the whole's first key row see none of its keys; a part's dead tiles lie
+// before its own first key row and are left out.
+template <int D, bool CAUSAL, int KVT, int SR>
+struct DkvWalk {
+    static constexpr int WHOLE = CAUSAL ? dkv_whole(D) : KVT;    // key rows of the whole that the workgroup's may be a part of
+    static_assert(WHOLE % KVT == 0 && KVT % SR == 0, "parts of whole tiles");
+    int q_begin, dead, n_head, n_diag, n_end, n_mid, n_masked, n_all;
+    __device__ __forceinline__ DkvWalk(const TileInfo &ti, int group) {
+        const int whole_row0 = ti.row0 - (ti.row0 - ti.seg_start) % WHOLE;
+        q_begin = CAUSAL ? whole_row0 : ti.seg_start;
+        dead = CAUSAL ? (ti.row0 - whole_row0) / SR : 0;
+        const int n_iter = (ti.seg_end - q_begin + SR - 1) / SR;
+        // causal: only the first WHOLE / SR query tiles touch some key's diagonal; either way only the last
+        // tile can be ragged.  The tiles in between need no mask.
+        n_head = CAUSAL ? min(WHOLE / SR, n_iter) : 0;
+        const int n_mid_end = max(n_head, (ti.seg_end - q_begin) / DKV_ORDER_Q * (DKV_ORDER_Q / SR));
+        n_diag = n_head - dead;
+        n_end = n_iter - n_mid_end;
+        n_mid = n_mid_end - n_head;
+        n_masked = group * (n_diag + n_end);
+        n_all = n_masked + group * n_mid;
+    }
+    // first query row of masked tile j of a head
+    __device__ __forceinline__ int masked_row(int j) const {
+        const int diag = dead + j, end = n_head + n_mid + j - n_diag;
+        return q_begin + (j < n_diag ? diag : end) * SR;
+    }
+};
+
+// One wave's requests for them: LD pieces of each tile (1 KB apiece) and, global -> LDS as well, the tile's row statistics.  The order of
+// work is runs of consecutive tiles: per head the diagonal and the ragged end, then per head what lies between.  A descriptor serves
+// a run (or RUN tiles of it: the offsets inside stay far below 2^32) and a lane's offsets advance, a handful of instructions per
+// tile where making descriptors anew took a hundred, as long as four products, in front of every tile's first one (7B-shaped batch 667 -> 616 us,
+// 16 tiles of the 6B ViT 636 -> 590, 12 of the 300M ViT 148 -> 140).
+template <int D, bool CAUSAL, int KVT, int SR, int LD>
+struct DkvRequests {
+    static constexpr int RUN = 64;
+    const DkvWalk<D, CAUSAL, KVT, SR> &w;
+    const unsigned char *base;
+    const float *stat_base;
+    long ld2;                     // bytes from row to row
+    int T, head0, group;
+    uint32_t (&first)[LD], voff[LD], stat_voff;
+    int n_issued, run_left, part_left, part_row, part_head, next_part, next_head;
+    u32x4 rsrc, stat_rsrc;
+    __device__ __forceinline__ DkvRequests(const DkvWalk<D, CAUSAL, KVT, SR> &walk, const void *base_, long ld2_, const float *stat_, int T_,
+                                           int head0_, int group_, uint32_t (&first_)[LD])
+        : w(walk), base((const unsigned char *)base_), stat_base(stat_), ld2(ld2_), T(T_), head0(head0_), group(group_), first(first_),
+          stat_voff(0), n_issued(0), run_left(0), part_left(0), part_row(0), part_head(0),
+          next_part(walk.n_masked == 0 ? 2 : walk.n_diag > 0 ? 0 : 1), next_head(0),
+          rsrc{0, 0, 0, 0}, stat_rsrc{0, 0, 0, 0} {}
+    __device__ __forceinline__ void next_run(int lane) {
+        if (part_left == 0) {                          // (only called while there are tiles left)
+            const int f0 = w.dead, f1 = w.n_head + w.n_mid, f2 = w.n_head, c0 = w.n_diag, c1 = w.n_end, c2 = w.n_mid;
+            const int part = next_part;
+            part_row = w.q_begin + (part == 0 ? f0 : part == 1 ? f1 : f2) * SR;
+            part_left = part == 0 ? c0 : part == 1 ? c1 : c2;
+            part_head = head0 + next_head;
+            const bool same = part == 0 && c1 > 0, last = next_head + 1 == group;
+            next_part = same ? 1 : part == 2 || last ? 2 : c0 > 0 ? 0 : 1;
+            next_head = same ? next_head : last ? 0 : next_head + 1;
+        }
+        run_left = min(part_left, RUN);
+        const long off = (long)part_row * ld2 + (long)part_head * D * 2;
+        rsrc = make_rsrc(base + off, (long)T * ld2 - off);
+        stat_rsrc = make_rsrc(stat_base + (size_t)part_head * T + part_row, (long)(T - part_row) * 4);
+#pragma unroll
+        for (int p = 0; p < LD; ++p) voff[p] = first[p];
+        stat_voff = lane * 4;
+        part_left -= run_left;
+        part_row += run_left * SR;
+    }
+    // the next tile: piece p of it to tile + piece[p], if `copies`; its statistics to stat, if `stats`
+    __device__ __forceinline__ void issue(unsigned char OB_LDS *tile, const int (&piece)[LD], bool copies, unsigned char OB_LDS *stat, bool stats, int lane) {
+        if (n_issued >= w.n_all) return;
+        if (run_left == 0) next_run(lane);
+        if (copies) {
+#pragma unroll
+            for (int p = 0; p < LD; ++p) {
+                load_lds<4>(rsrc, tile + piece[p], voff[p]);
+                voff[p] += (uint32_t)(SR * ld2);
+            }
+        }
+        if (stats) load_lds<1>(stat_rsrc, stat, stat_voff);
+        stat_voff += SR * 4;
+        --run_left;
+        ++n_issued;
+    }
+};
+
 template <int D, bool CAUSAL, int NP, int SR>
 __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 2) void attn_bwd_dkv_kernel(
     const __bf16 *__restrict__ d_o, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
@@ -843,13 +1071,12 @@ __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 
     __bf16 *__restrict__ dk, __bf16 *__restrict__ dv, int ldq, int ldkv, int ldo,
     const int32_t *__restrict__ cu, int n_seg, int T, int group, float scale, float rot_log2_base, int heads,
     TileOrder ord) {
-    // three stages of the streamed Q and dO tiles (the dK side works one tile behind the dV side, see
-    // below), two buffers for the probabilities on their way from one to the other, row statistics
+    // three stages of the streamed Q and dO tiles (the results are formed one tile behind the scores, see
+    // below), two buffers for the probabilities on their way from one role to the other, row statistics
     __shared__ __attribute__((aligned(1024))) unsigned char tiles_s[6 * Tile<D, SR>::BYTES];
-    constexpr int KVT = 32 * NP, WHOLE = CAUSAL ? dkv_whole(D) : KVT, MT = SR / 32, PB = MT * 2048;   // key rows of the workgroup, of the whole it may be a part of
-    static_assert(WHOLE % KVT == 0 && KVT % SR == 0, "parts of whole tiles");
+    constexpr int KVT = 32 * NP, MT = SR / 32, PB = MT * 2048;
     __shared__ __attribute__((aligned(1024))) unsigned char p_s[2 * NP * PB];  // [buffer][pair]: 2 MT x 64 lanes x 16 B
-    __shared__ __attribute__((aligned(256))) float stat_s[6 * ST];              // lse2 x 3 stages, Delta x 3 stages
+    __shared__ __attribute__((aligned(256))) unsigned char stat_s[6 * 256];    // lse2 x 3 stages, Delta x 3 stages
     __shared__ int sh[8];
     const int rank = blockIdx.x / heads;
     const TileInfo ti = pick_tile<true>(ord, rank, cu, n_seg, KVT, sh);
@@ -865,21 +1092,11 @@ __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 
     const int pair_kv_first = ti.row0 + pair * 32;
     const float sl2 = scale * LOG2E;
     constexpr int KT = D / 16, DT = D / 32;
+    constexpr bool FUSE = NP == 2 && SR == 64;      // one or two waves to a SIMD: element-wise work between the wave's own products
 
     // the wave copies the tile it reads row fragments from: Q (role P) or dO (role G)
     Tile<D, SR> tl;
     tl.init(role_g ? ldo : ldq, pair, lane);
-    const unsigned char *const own_base = role_g ? (const unsigned char *)d_o : (const unsigned char *)q;
-    const long own_ld2 = (role_g ? (long)ldo : (long)ldq) * 2;
-    const long own_total = (long)T * own_ld2;
-
-    // held rows: K (role P) or V (role G)
-    bf16x8 kvf[KT];
-    {
-        const __bf16 *src = (role_g ? v : k) + (size_t)kv_row * ldkv + kvh * D + 8 * lh;
-#pragma unroll
-        for (int t = 0; t < KT; ++t) kvf[t] = *(const bf16x8 *)(src + 16 * t);
-    }
     f32x16 acc_out[DT];  // dV^T (role P) or dK^T (role G)
 #pragma unroll
     for (int i = 0; i < DT; ++i)
@@ -887,140 +1104,137 @@ __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 
         for (int r = 0; r < 16; ++r) acc_out[i][r] = 0.f;
 
     constexpr int BYTES = Tile<D, SR>::BYTES;
-    unsigned char OB_LDS *const tiles = (unsigned char OB_LDS *)tiles_s;
-    float OB_LDS *const stats = (float OB_LDS *)stat_s;
-#define OB_QS(S) (tiles + (S) * BYTES)
-#define OB_DOS(S) (tiles + (3 + (S)) * BYTES)
-#define OB_LSES(S) (stats + (S) * ST)
-#define OB_DLTS(S) (stats + (3 + (S)) * ST)
-    unsigned char OB_LDS *const p_mine = (unsigned char OB_LDS *)p_s + pair * PB + lane * 16;
 
-    // causal: query rows before the whole's first key row see none of its keys; a part's `dead` tiles lie
-    // before its own first key row and are left out
-    const int whole_row0 = ti.row0 - (ti.row0 - ti.seg_start) % WHOLE;
-    const int q_begin = CAUSAL ? whole_row0 : ti.seg_start;
-    const int dead = CAUSAL ? (ti.row0 - whole_row0) / SR : 0;
-    const int n_iter = (ti.seg_end - q_begin + SR - 1) / SR;
-#define OB_ISSUE_DKV(hq_, it_, S)                                                                             \
-    do {                                                                                                      \
-        const int head_ = kvh * group + (hq_);                                                                \
-        const int q0_ = q_begin + (it_) * SR;                                                                 \
-        const long off_ = (long)q0_ * own_ld2 + (long)head_ * D * 2;                                          \
-        /* four waves of each role copy a tile, or two half of it each */                                    \
-        if (pair < 4) tl.issue(own_base + off_, own_total - off_, role_g ? OB_DOS(S) : OB_QS(S), pair);       \
-        if (NP == 2) tl.issue(own_base + off_ + SR / 2 * own_ld2, own_total - off_ - SR / 2 * own_ld2,                \
-                              (role_g ? OB_DOS(S) : OB_QS(S)) + SR / 2 * Tile<D, SR>::RB, pair);                      \
-        if (wave == 0) issue_row_stats(lse2_all + (size_t)head_ * T + q0_, (long)T - q0_, OB_LSES(S), lane);  \
-        if (wave == NP) issue_row_stats(delta + (size_t)head_ * T + q0_, (long)T - q0_, OB_DLTS(S), lane);    \
-    } while (0)
-    // causal: only the first WHOLE / SR query tiles touch some pair's diagonal; either way only the last
-    // tile can be ragged.  The tiles in between need no mask.
-    const int n_head = CAUSAL ? min(WHOLE / SR, n_iter) : 0;
-    const int n_mid_end = max(n_head, (ti.seg_end - q_begin) / DKV_ORDER_Q * (DKV_ORDER_Q / SR));
-    // Order of work: first the masked tiles of every query head of the group (phase 0), then the
-    // mask-free ones of every head (phase 1) in one single-path loop -- the sums do not care, and one
-    // loop nest per phase keeps the accumulators in place (a loop over the heads around the per-head
-    // loops made the register allocator spill them).  A cursor names a tile: (phase, head in group, j).
-    const int n_diag = n_head - dead;
-    const int cnt0 = n_diag + (n_iter - n_mid_end), cnt1 = n_mid_end - n_head;
-    struct Cursor { int phase, hq, j; };
-    auto tile_of = [&](const Cursor &c) { return c.phase ? n_head + c.j : (c.j < n_diag ? dead + c.j : n_mid_end + c.j - n_diag); };
-    auto step = [&](Cursor &c) {   // to the next tile in the order of work; phase 2 = past the end
-        const int cnt = c.phase ? cnt1 : cnt0;
-        if (c.j + 1 < cnt) { ++c.j; return; }
-        c.j = 0;
-        if (c.hq + 1 < group) { ++c.hq; return; }
-        c.hq = 0;
-        ++c.phase;
-        if (c.phase == 1 && cnt1 == 0) c.phase = 2;
-    };
-    // the whole walk once per role, chosen outside the loops: each role's loop then carries only its own
-    // registers (role G keeps dP across trips, role P does not)
-    auto walk = [&](auto role_tag) {
+    const DkvWalk<D, CAUSAL, KVT, SR> w(ti, group);
+
+    // the whole walk once per role, chosen outside the loops: each role's loop then carries only its own registers
+    auto walk = [&](auto role_tag) __attribute__((always_inline)) {
     constexpr bool RG = decltype(role_tag)::value;
-    Cursor cur = {0, 0, 0};
-    if (cnt0 == 0) cur.phase = cnt1 ? 1 : 2;
-    Cursor nxt = cur;
-    step(nxt);
-    OB_ISSUE_DKV(cur.hq, tile_of(cur), 0);
+    unsigned char OB_LDS *const tiles = (unsigned char OB_LDS *)tiles_s;
+    // (where in the array a role's two rings start is part of every lane's offsets: what is added per stage and row tile fits an
+    // instruction's 16-bit offset)
+    constexpr int OWN_AT = RG ? 3 * BYTES : 0, OTHER_AT = RG ? 0 : 3 * BYTES;
+#pragma unroll
+    for (int t = 0; t < KT; ++t) tl.rr[t] += OWN_AT;
+#pragma unroll
+    for (int i = 0; i < 2 * DT; ++i) tl.tro[i / DT][i % DT] += OTHER_AT;
+    unsigned char OB_LDS *const stat = (unsigned char OB_LDS *)stat_s + (RG ? 3 * 256 : 0);
+    unsigned char OB_LDS *const p_mine = (unsigned char OB_LDS *)p_s + pair * PB + lane * 16;
+    // four waves of a role copy a tile, or two half of it each
+    constexpr int TLD = Tile<D, SR>::LD, LDW = NP == 2 ? 2 * TLD : TLD;
+    const long ld2 = (RG ? (long)ldo : (long)ldq) * 2;
+    uint32_t first[LDW];
+    int piece[LDW];
+#pragma unroll
+    for (int p = 0; p < LDW; ++p) {
+        first[p] = tl.voff[p % TLD] + (p < TLD ? 0u : (uint32_t)(SR / 2 * ld2));
+        piece[p] = OWN_AT + ((p < TLD ? pair : pair + 2) * TLD + p % TLD) * 1024;
+    }
+    DkvRequests<D, CAUSAL, KVT, SR, LDW> req(w, RG ? d_o : q, ld2, RG ? delta : lse2_all, T, kvh * group, group, first);
+    auto request = [&](int stage) __attribute__((always_inline)) {
+        req.issue(tiles + stage * BYTES, piece, pair < 4, stat + stage * 256, pair == 0, lane);
+    };
+    request(0);
+    bf16x8 kvf[KT];     // held rows: K (role P) or V (role G)
+    {
+        const __bf16 *src = (RG ? v : k) + (size_t)kv_row * ldkv + kvh * D + 8 * lh;
+#pragma unroll
+        for (int t = 0; t < KT; ++t) kvf[t] = *(const bf16x8 *)(src + 16 * t);
+    }
+#pragma unroll
+    for (int t = 0; t < KT; ++t) asm volatile("" : "+v"(kvf[t]));      // have landed: no wait for them inside the loops
+
     // The dK side runs one tile behind: in the trip of tile n the role-P wave does S, P, dV of tile n
     // and leaves P in buffer n % 2, while the role-G wave first finishes tile n - 1 (dS from the P it
     // finds in buffer (n - 1) % 2 and the dP it kept in registers, then dK) and then forms dP of tile
-    // n.  One barrier per tile instead of two, the role-G wave never waits for its partner inside a
+    // n.  One barrier per tile, the role-G wave never waits for its partner inside a
     // trip, and the two waves of a SIMD start a trip in different kinds of work (MFMAs / element-wise).
+    // FUSE: over the mask-free tiles dV runs one tile behind as well, P of tile n between its products, and dS of tile n - 1 goes between
+    // those of dP of tile n.
     // Stage n % 3 holds tile n: the load of tile n + 1 overwrites tile n - 2, which nobody needs any more.
-    int gi = 0, st = 0;        // tiles done; stage of the current tile
-    int left1 = group * cnt1;  // mask-free tiles not yet done
-    bool live_prev = false;    // role G: tile n - 1 took part
-    f32x16 dp_keep[MT];         // role G: dP of tile n - 1
-#define OB_DKV_ITER(MASKED, S, PREV, NEXT)                                                                   \
-    {                                                                                                       \
-        const int q0 = q_begin + tile_of(cur) * SR;                                                         \
-        __builtin_amdgcn_s_waitcnt(WAIT_VM0);                                                               \
-        __syncthreads();                                                                                    \
-        if (nxt.phase < 2) OB_ISSUE_DKV(nxt.hq, tile_of(nxt), NEXT);                                        \
-        /* a masked tile entirely before this pair's keys contributes nothing */                            \
-        const bool live = !((MASKED) && CAUSAL && q0 + SR - 1 < pair_kv_first);                             \
-        if constexpr (!RG) {                                                                                \
-            if (live) {                                                                                     \
-                f32x16 acc_x[MT];                                                                            \
-                bf16x8 pk[MT][2];                                                                            \
-                dkv_scores<D, MT>(OB_QS(S), tl, kvf, acc_x);                                                    \
-                dkv_probs<CAUSAL, MASKED, MT>(acc_x, OB_LSES(S), q0, ti.seg_end, kv_row, sl2, pk);              \
-                _Pragma("unroll") for (int i_ = 0; i_ < 2 * MT; ++i_)                                            \
-                    *(bf16x8 OB_LDS *)(p_mine + (gi & 1) * (NP * PB) + i_ * 1024) = pk[i_ >> 1][i_ & 1];        \
-                dkv_outputs<D, MT>(OB_DOS(S), tl, pk, acc_out);                                                 \
-            }                                                                                               \
-        } else {                                                                                            \
-            if (live_prev) {                                                                                \
-                bf16x8 pk[MT][2];                                                                            \
-                _Pragma("unroll") for (int i_ = 0; i_ < 2 * MT; ++i_)                                            \
-                    pk[i_ >> 1][i_ & 1] = *(const bf16x8 OB_LDS *)(p_mine + ((gi - 1) & 1) * (NP * PB) + i_ * 1024); \
-                dkv_dscores<MT>(dp_keep, OB_DLTS(PREV), pk);                                                    \
-                dkv_outputs<D, MT>(OB_QS(PREV), tl, pk, acc_out);                                               \
-            }                                                                                               \
-            if (live) dkv_scores<D, MT>(OB_DOS(S), tl, kvf, dp_keep);                                           \
-            live_prev = live;                                                                               \
-        }                                                                                                   \
-        if (cur.phase == 1) --left1;                                                                        \
-        cur = nxt;                                                                                          \
-        step(nxt);                                                                                          \
-        ++gi;                                                                                               \
-        st = (NEXT);                                                                                        \
-    }
-#define OB_DKV_ANY(MASKED)                                                                                   \
-    {                                                                                                       \
-        const int s_ = st, p_ = st == 0 ? 2 : st - 1, n_ = st == 2 ? 0 : st + 1;                            \
-        OB_DKV_ITER(MASKED, s_, p_, n_)                                                                     \
-    }
-    while (cur.phase == 0) OB_DKV_ANY(true)
-    while (st != 0 && cur.phase == 1) OB_DKV_ANY(false)   // the three-tile loop below starts on stage 0
-    while (left1 >= 3) {  // three tiles per trip: constant stage addresses, a single straight path
-        OB_DKV_ITER(false, 0, 2, 1)
-        OB_DKV_ITER(false, 1, 0, 2)
-        OB_DKV_ITER(false, 2, 1, 0)
-    }
-    while (cur.phase == 1) OB_DKV_ANY(false)
-    // the dK side still owes the last tile
-    __syncthreads();
-    if (RG && live_prev) {
-        const int p_ = st == 0 ? 2 : st - 1;
-        bf16x8 pk[MT][2];
+    int n = 0, q0 = 0, m_j = 0;
+    bool live_prev = false, owed = false;      // tile n - 1 took part; (role P) its dV is still to come
+    bf16x8 pk[MT][2];            // role P: P of tile n - 1
+    f32x16 dp_keep[MT];          // role G: dP of tile n - 1
+    auto trip = [&](auto general_tag, auto masked_tag, int S, int PREV, int NEXT, bool owe) __attribute__((always_inline)) {
+        constexpr bool GEN = decltype(general_tag)::value, MASK = decltype(masked_tag)::value;
+        __builtin_amdgcn_s_waitcnt(wait_vm_lds0(0));
+        bare_barrier();
+        if (GEN) request(NEXT);      // (the masked tiles' trips are short and each takes a descriptor of its own)
+        // (GEN: one after the other, each step behind a test)  a masked tile entirely before this pair's keys contributes nothing
+        const bool live = !GEN || (n < w.n_all && !(MASK && CAUSAL && q0 + SR - 1 < pair_kv_first));
+        unsigned char OB_LDS *const p_new = p_mine + (n & 1) * (NP * PB), *const p_old = p_mine + ((n & 1) ^ 1) * (NP * PB);
+        const bool late = !GEN || (RG ? live_prev : owed);
+        if constexpr (!RG) {
+            f32x16 acc_x[MT];
+            if (live) dkv_scores<D, MT>(tiles + S * BYTES, tl, kvf, acc_x);
+            if (!GEN) request(NEXT);
+            if constexpr (FUSE && !GEN) {
+                bf16x8 pn[MT][2];
+                dkv_outputs_probs<D, MT>(tiles + PREV * BYTES, tl, pk, acc_out, acc_x, stat + S * 256, sl2, pn);
 #pragma unroll
-        for (int i_ = 0; i_ < 2 * MT; ++i_)
-            pk[i_ >> 1][i_ & 1] = *(const bf16x8 OB_LDS *)(p_mine + ((gi - 1) & 1) * (NP * PB) + i_ * 1024);
-        dkv_dscores<MT>(dp_keep, OB_DLTS(p_), pk);
-        dkv_outputs<D, MT>(OB_QS(p_), tl, pk, acc_out);
+                for (int i = 0; i < 2 * MT; ++i) pk[i >> 1][i & 1] = pn[i >> 1][i & 1];
+            } else {
+                if (FUSE && late) dkv_outputs<D, MT>(tiles + PREV * BYTES, tl, pk, acc_out);
+                if (live) dkv_probs<CAUSAL, MASK, MT>(acc_x, stat + S * 256, q0, ti.seg_end, kv_row, sl2, pk);
+            }
+            if (live) {
+#pragma unroll
+                for (int i = 0; i < 2 * MT; ++i) *(bf16x8 OB_LDS *)(p_new + i * 1024) = pk[i >> 1][i & 1];
+                if (GEN || !FUSE) {
+                    if (!owe) dkv_outputs<D, MT>(tiles + S * BYTES, tl, pk, acc_out);
+                }
+            }
+            owed = owe && live;
+        } else {
+            bf16x8 pn[MT][2];
+            if (late) {
+#pragma unroll
+                for (int i = 0; i < 2 * MT; ++i) pn[i >> 1][i & 1] = lds16<bf16x8>(p_old + i * 1024);
+            }
+            if constexpr (FUSE && !GEN) {
+                f32x16 acc_x[MT];
+                dkv_scores_dscores<D, MT>(tiles + S * BYTES, tl, kvf, acc_x, dp_keep, stat + PREV * 256, pn);
+                request(NEXT);
+                dkv_outputs<D, MT>(tiles + PREV * BYTES, tl, pn, acc_out);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) dp_keep[mt] = acc_x[mt];
+            } else {
+                if (late) {
+                    dkv_dscores<MT>(dp_keep, stat + PREV * 256, pn);
+                    dkv_outputs<D, MT>(tiles + PREV * BYTES, tl, pn, acc_out);
+                }
+                if (!GEN) request(NEXT);
+                if (live) dkv_scores<D, MT>(tiles + S * BYTES, tl, kvf, dp_keep);
+            }
+        }
+        live_prev = live;
+        ++n;
+    };
+    int st = 0;
+    auto slow = [&](auto masked_tag, bool owe) __attribute__((always_inline)) {
+        const int s_ = st, p_ = st == 0 ? 2 : st - 1, n_ = st == 2 ? 0 : st + 1;
+        trip(std::true_type{}, masked_tag, s_, p_, n_, owe);
+        st = n_;
+    };
+    while (n < w.n_masked) {
+        q0 = w.masked_row(m_j);
+        if (++m_j == w.n_diag + w.n_end) m_j = 0;
+        slow(std::true_type{}, false);
     }
+    // The mask-free tiles: three to a trip, constant stage addresses, a single straight path, from a tile on stage 0 on; where the
+    // products of dV lag behind, the tile in front of them leaves its own to the first of them.
+    const int lead = !FUSE && live_prev && n % 3 == 0 ? n : n + 3 - n % 3;      // the first tile of the first three (never the very first)
+    const bool threes = lead + 3 <= w.n_all;
+    while (threes && n < lead) slow(std::false_type{}, FUSE && n + 1 == lead);
+    while (threes && n + 3 <= w.n_all) {
+        trip(std::false_type{}, std::false_type{}, 0, 2, 1, FUSE);
+        trip(std::false_type{}, std::false_type{}, 1, 0, 2, FUSE);
+        trip(std::false_type{}, std::false_type{}, 2, 1, 0, FUSE);
+    }
+    while (n <= w.n_all) slow(std::false_type{}, false);
     };
     if (role_g) walk(std::true_type{}); else walk(std::false_type{});
-#undef OB_DKV_ANY
-#undef OB_DKV_ITER
-#undef OB_ISSUE_DKV
-#undef OB_DLTS
-#undef OB_LSES
-#undef OB_DOS
-#undef OB_QS
     if (!kv_live) return;
     // dV^T / dK^T of the whole group of query heads sit in the accumulators: one rounding to bf16
     const float out_scale = role_g ? scale : 1.0f;
@@ -1034,6 +1248,217 @@ __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 
 #pragma unroll
             for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(acc_out[dt][4 * g + e] * out_scale);
             *(bf16x4 *)(dst + (size_t)kv_row * ldkv + kvh * D + dt * 32 + g * 8 + lh * 4) = ov;
+        }
+}
+
+// ------------------------------------------------------------------------------------------------
+// dK / dV of 64 key rows of a head of 128 by eight waves, for launches whose longest walk keeps everything waiting.  A
+// trip (one query tile of 64 rows) is half the work of a trip of four pairs, and all of it is dealt to the eight waves in 32 x 32 blocks:
+// query half a and key half b of S (four waves of role P) and of dP (four of role G), columns 32 a and 32 a + 64 of key half b of dV (P)
+// and of dK (G).  Nothing in a trip waits for anything of the same trip but a wave's own scores:
+//   role P: S of tile n;  P of tile n between the products of dV of tile n - 1
+//   role G: dP of tile n;  dS of tile n - 1 between the products of dK of tile n - 2
+// P and dS go through LDS in the packed operand layout, two buffers each; Q has four stages and dO three.  What bounds a
+// trip is the LDS: reads at 256 bytes per clock, writes at 79, 1500 clocks of a trip's 2500 (its products take 1024 of a SIMD's).
+// Against two pairs (four waves that took both blocks of a key half): one segment of 557, 32 / 8 heads 61 -> 48 us, of 2000 187 -> 140, of
+// 2000, 12 / 2 heads 271 -> 189; a full chip is better off with four pairs (16384 tokens, 32 / 8 heads 616 us, here 776).
+// The sums are those of the other shapes, in their order.
+// ------------------------------------------------------------------------------------------------
+struct DkvBlocks {
+    static constexpr int D = 128, SR = 64, KVT = 64, Q_STAGES = 4, DO_STAGES = 3, LSE_STAGES = 2, DLT_STAGES = 3;
+    static constexpr int BYTES = Tile<D, SR>::BYTES, BLK = 2048, BUF = 4 * BLK;      // a packed 32 x 32 block, the four of a tile
+    static constexpr int Q_AT = 0, DO_AT = Q_STAGES * BYTES, P_AT = DO_AT + DO_STAGES * BYTES, DS_AT = P_AT + 2 * BUF,
+                         LSE_AT = DS_AT + 2 * BUF, DLT_AT = LSE_AT + LSE_STAGES * 256, TOTAL = DLT_AT + DLT_STAGES * 256;
+    static_assert(TOTAL + 64 <= 160 * 1024, "LDS");
+};
+template <bool CAUSAL>
+__global__ __launch_bounds__(512, 2) void attn_bwd_dkv_blocks_kernel(
+    const __bf16 *__restrict__ d_o, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
+    const __bf16 *__restrict__ v, const float *__restrict__ lse2_all, const float *__restrict__ delta,
+    __bf16 *__restrict__ dk, __bf16 *__restrict__ dv, int ldq, int ldkv, int ldo,
+    const int32_t *__restrict__ cu, int n_seg, int T, int group, float scale, float rot_log2_base, int heads,
+    TileOrder ord) {
+    using B = DkvBlocks;
+    constexpr int D = B::D, SR = B::SR, KT = D / 16, BUF = B::BUF, LD = Tile<D, SR>::LD;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_s[B::TOTAL];
+    __shared__ int sh[8];
+    unsigned char OB_LDS *const lds = (unsigned char OB_LDS *)lds_s;
+    const int rank = blockIdx.x / heads;
+    const TileInfo ti = pick_tile<true>(ord, rank, cu, n_seg, B::KVT, sh);
+    if (ti.row0 < 0) return;
+    const int kvh = head_of_slot(blockIdx.x - rank * heads, heads);
+    const int lane = threadIdx.x & 63, lx = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool role_g = wave >= 4;
+    const int w4 = wave & 3, a = w4 & 1, b = w4 >> 1;
+    const int kv_row = min(ti.row0 + b * 32 + lx, ti.seg_end - 1);
+    const bool kv_live = ti.row0 + b * 32 + lx < ti.seg_end;
+    const float sl2 = scale * LOG2E;
+
+    Tile<D, SR> tl;
+    tl.init(role_g ? ldo : ldq, w4, lane);
+    int tro[2][2], rr[KT], piece[LD];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) tro[s][i] = Tile<D, SR>::tr_offset(lane, s, a + 2 * i);
+#pragma unroll
+    for (int t = 0; t < KT; ++t) rr[t] = tl.rr[t] + a * 32 * Tile<D, SR>::RB;
+#pragma unroll
+    for (int p = 0; p < LD; ++p) piece[p] = (w4 * LD + p) * 1024;
+    f32x16 acc_out[2];     // columns 32 (a + 2 i) .. of dV^T (role P) or dK^T (role G)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc_out[i][r] = 0.f;
+    const DkvWalk<D, CAUSAL, B::KVT, SR> w(ti, group);
+
+    auto walk = [&](auto role_tag) __attribute__((always_inline)) {
+    constexpr bool RG = decltype(role_tag)::value;
+    constexpr int OWN_STAGES = RG ? B::DO_STAGES : B::Q_STAGES, OTHER_STAGES = RG ? B::Q_STAGES : B::DO_STAGES;
+    constexpr int STAT_STAGES = RG ? B::DLT_STAGES : B::LSE_STAGES;
+    unsigned char OB_LDS *const own = lds + (RG ? B::DO_AT : B::Q_AT);         // operand of the scores: dO (G), Q (P)
+    unsigned char OB_LDS *const other = lds + (RG ? B::Q_AT : B::DO_AT);       // operand of the result
+    unsigned char OB_LDS *const stat = lds + (RG ? B::DLT_AT : B::LSE_AT);
+    unsigned char OB_LDS *const p_blk = lds + B::P_AT + (b * 2 + a) * B::BLK + lane * 16;       // own block of the scores
+    unsigned char OB_LDS *const ds_blk = lds + B::DS_AT + (b * 2 + a) * B::BLK + lane * 16;
+    unsigned char OB_LDS *const out_blk = lds + (RG ? B::DS_AT : B::P_AT) + b * 2 * B::BLK + lane * 16;   // the four steps of a result
+    DkvRequests<D, CAUSAL, B::KVT, SR, LD> req(w, RG ? d_o : q, (RG ? (long)ldo : (long)ldq) * 2, RG ? delta : lse2_all, T, kvh * group, group,
+                                              tl.voff);
+    auto next = [](int stage, int stages) __attribute__((always_inline)) { return stage + 1 == stages ? 0 : stage + 1; };
+    int st_issue = 0, st_stat_issue = 0;                                       // stages of the tile to request next
+    auto request = [&]() __attribute__((always_inline)) {
+        req.issue(own + st_issue * B::BYTES, piece, true, stat + st_stat_issue * 256, true, lane);
+        st_issue = next(st_issue, OWN_STAGES);
+        st_stat_issue = next(st_stat_issue, STAT_STAGES);
+    };
+    request();
+    bf16x8 kvf[KT];     // held rows: K (role P) or V (role G)
+    {
+        const __bf16 *src = (RG ? v : k) + (size_t)kv_row * ldkv + kvh * D + 8 * lh;
+#pragma unroll
+        for (int t = 0; t < KT; ++t) kvf[t] = *(const bf16x8 *)(src + 16 * t);
+    }
+#pragma unroll
+    for (int t = 0; t < KT; ++t) asm volatile("" : "+v"(kvf[t]));      // have landed: no wait for them inside the loops
+    // stages: of the tile whose scores are formed, of its row statistics (G: of the tile before), of the tile whose share of the
+    // result is formed
+    int st_own = 0, st_stat = 0, st_other = 0;
+    f32x16 dp_keep;     // role G: dP of tile n - 1
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dp_keep[r] = 0.f;
+    int n = 0, q0 = 0, m_j = 0;
+    // GEN: each step behind a test (the first trips, in which there is nothing to finish yet, and the last)
+    auto trip = [&](auto general_tag, auto masked_tag) __attribute__((always_inline)) {
+        constexpr bool GEN = decltype(general_tag)::value, MASK = decltype(masked_tag)::value;
+        __builtin_amdgcn_s_waitcnt(wait_vm_lds0(0));
+        bare_barrier();
+        if (GEN) request();
+        const bool has_score = !GEN || n < w.n_all;
+        const bool has_late = !GEN || (n >= 1 && n <= w.n_all);                       // dV, dS of tile n - 1
+        const bool has_out = RG ? !GEN || (n >= 2 && n <= w.n_all + 1) : has_late, has_elem = RG ? has_late : has_score;
+        const unsigned char OB_LDS *const sc = own + st_own * B::BYTES, *const ot = other + st_other * B::BYTES;
+        const int buf = n & 1;
+        bf16x8 fr[KT], of[4], tf[4][2], pk[2];
+        f32x4 row4[4];                                                                // lse2 (P), Delta (G)
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        if (has_score) {
+#pragma unroll
+            for (int t = 0; t < KT; ++t) fr[t] = lds16<bf16x8>(sc + rr[t]);
+        }
+        if (!GEN) __builtin_amdgcn_sched_barrier(0);
+        if (has_elem) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) row4[g] = lds16<f32x4>(stat + st_stat * 256 + (a * 32 + 8 * g + 4 * lh) * 4);
+        }
+        if (RG && has_late) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) pk[i] = lds16<bf16x8>(p_blk + (buf ^ 1) * BUF + i * 1024);
+        }
+        if (has_out) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                of[u] = lds16<bf16x8>(out_blk + (RG ? buf : buf ^ 1) * BUF + u * 1024);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) tf[u][i] = Tile<D, SR>::frag_at(ot, tro[0][i], tro[1][i], u);
+            }
+        }
+        if (has_score) {
+#pragma unroll
+            for (int t = 0; t < KT; ++t) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[t], kvf[t], s, 0, 0, 0);
+        }
+        if (!GEN) {
+            __builtin_amdgcn_sched_barrier(0);
+            request();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (has_elem) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int r = 8 * h + e, g = r >> 2;
+                    if constexpr (RG) {
+                        pk[h][e] = (__bf16)((float)pk[h][e] * (dp_keep[r] - row4[g][r & 3]));
+                    } else {
+                        const int qr = q0 + a * 32 + 8 * g + 4 * lh + (r & 3);
+                        const bool ok = !MASK || (qr < ti.seg_end && (!CAUSAL || kv_row <= qr));
+                        const float p = fast_exp2(s[r] * sl2 - row4[g][r & 3]);
+                        pk[h][e] = (__bf16)(ok ? p : 0.f);
+                    }
+                }
+            }
+            if (has_out) {
+#pragma unroll
+                for (int u = 2 * h; u < 2 * h + 2; ++u)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc_out[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf[u][i], of[u], acc_out[i], 0, 0, 0);
+            }
+            if (!GEN) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, RG ? 8 : 6, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (has_elem) {
+            unsigned char OB_LDS *const dst = RG ? ds_blk + (buf ^ 1) * BUF : p_blk + buf * BUF;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) *(bf16x8 OB_LDS *)(dst + i * 1024) = pk[i];
+        }
+        if (RG && has_score) dp_keep = s;
+        st_own = next(st_own, OWN_STAGES);
+        if (has_out) st_other = next(st_other, OTHER_STAGES);
+        if (has_elem) st_stat = next(st_stat, STAT_STAGES);
+        ++n;
+    };
+    while (n < w.n_masked) {
+        q0 = w.masked_row(m_j);
+        if (++m_j == w.n_diag + w.n_end) m_j = 0;
+        trip(std::true_type{}, std::true_type{});
+    }
+    while (n < 2) trip(std::true_type{}, std::false_type{});
+    while (n < w.n_all) trip(std::false_type{}, std::false_type{});
+    while (n < w.n_all + 2) trip(std::true_type{}, std::false_type{});
+    };
+    if (role_g) walk(std::true_type{}); else walk(std::false_type{});
+    if (!kv_live) return;
+    const float out_scale = role_g ? scale : 1.0f;
+    __bf16 *const dst = role_g ? dk : dv;
+    if (role_g && rot_log2_base > 0.f) rotary_bwd_pair<D>(acc_out[0], acc_out[1], a, kv_row - ti.seg_start, rot_log2_base, lh);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            bf16x4 ov;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(acc_out[i][4 * g + e] * out_scale);
+            *(bf16x4 *)(dst + (size_t)kv_row * ldkv + kvh * D + (a + 2 * i) * 32 + g * 8 + lh * 4) = ov;
         }
 }
 
@@ -1057,8 +1482,7 @@ double attn_flops(const ob_segments *seg, int nq, int d, bool causal) {
                                                       const __bf16 *, const __bf16 *, const float *, float *, \
                                                       float *, __bf16 *, int, int, int, const int32_t *, int, \
                                                       int, int, float, float, int, TileOrder);                \
-    OB_DKV_INSTANCE(D, C, dkv_np(D, 0), dkv_sr(D, 0))                                                         \
-    OB_DKV_INSTANCE(D, C, dkv_np(D, 1), dkv_sr(D, 1))
+    OB_DKV_INSTANCE(D, C, dkv_np(D, 0), dkv_sr(D, 0))
 #define OB_DKV_INSTANCE(D, C, NP, SR)                                                                             \
     template __global__ void attn_bwd_dkv_kernel<D, C, NP, SR>(const __bf16 *, const __bf16 *, const __bf16 *,    \
                                                            const __bf16 *, const float *, const float *,      \
@@ -1067,14 +1491,31 @@ double attn_flops(const ob_segments *seg, int nq, int d, bool causal) {
                                                            TileOrder);
 OB_ATTN_INSTANCES(64, true)
 OB_ATTN_INSTANCES(64, false)
+OB_DKV_INSTANCE(64, true, dkv_np(64, 1), dkv_sr(64, 1))
+OB_DKV_INSTANCE(64, false, dkv_np(64, 1), dkv_sr(64, 1))
 OB_DKV_INSTANCE(64, false, dkv_np(64, 2), dkv_sr(64, 2))
+OB_DKV_INSTANCE(128, true, dkv_np(128, 2), dkv_sr(128, 2))
+OB_DKV_INSTANCE(128, false, dkv_np(128, 2), dkv_sr(128, 2))
 OB_ATTN_INSTANCES(128, true)
 OB_ATTN_INSTANCES(128, false)
+#define OB_BLOCKS_INSTANCE(C)                                                                                     \
+    template __global__ void attn_bwd_dkv_blocks_kernel<C>(const __bf16 *, const __bf16 *, const __bf16 *,         \
+                                                           const __bf16 *, const float *, const float *,      \
+                                                           __bf16 *, __bf16 *, int, int, int,                 \
+                                                           const int32_t *, int, int, int, float, float, int, \
+                                                           TileOrder);
+OB_BLOCKS_INSTANCE(true)
+OB_BLOCKS_INSTANCE(false)
+#undef OB_BLOCKS_INSTANCE
 #undef OB_DKV_INSTANCE
 #undef OB_ATTN_INSTANCES
 
-template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_0 = attn_bwd_dkv_kernel<D, CAUSAL, dkv_np(D, 0), dkv_sr(D, 0)>;
-template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_1 = attn_bwd_dkv_kernel<D, CAUSAL, dkv_np(D, 1), dkv_sr(D, 1)>;
+// the kernel of each shape
+template <int D, bool CAUSAL, int SHAPE> constexpr auto attn_bwd_dkv = attn_bwd_dkv_kernel<D, CAUSAL, dkv_np(D, SHAPE), dkv_sr(D, SHAPE)>;
+template <bool CAUSAL> constexpr auto attn_bwd_dkv<128, CAUSAL, 1> = attn_bwd_dkv_blocks_kernel<CAUSAL>;
+template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_0 = attn_bwd_dkv<D, CAUSAL, 0>;
+template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_1 = attn_bwd_dkv<D, CAUSAL, 1>;
+template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_2 = attn_bwd_dkv<D, CAUSAL && D == 128, 2>;      // (heads of 64: bidirectional only)
 
 }  // namespace
 
@@ -1127,10 +1568,10 @@ void launch_attn_bwd(const void *d_o, const void *q, const void *k, const void *
     const dim3 grid_kv((unsigned)places * nkv);
 #define OB_DKV_ARGS (const __bf16 *)d_o, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, lse2, delta, (__bf16 *)dk,  \
                     (__bf16 *)dv, ldq, ldkv, ldo, seg->cu_dev, seg->n_seg, T, group, scale, rot, nkv, ord
-    if (shape == 2)
-        hipLaunchKernelGGL((attn_bwd_dkv_kernel<64, false, dkv_np(64, 2), dkv_sr(64, 2)>), grid_kv, dim3(4 * kvt), 0, s, OB_DKV_ARGS);
-    else if (shape == 0) OB_ATTN_DISPATCH(attn_bwd_dkv_0, grid_kv, 4 * kvt, OB_DKV_ARGS);
-    else OB_ATTN_DISPATCH(attn_bwd_dkv_1, grid_kv, 4 * kvt, OB_DKV_ARGS);
+    const int threads = dkv_threads(d, shape);
+    if (shape == 0) OB_ATTN_DISPATCH(attn_bwd_dkv_0, grid_kv, threads, OB_DKV_ARGS);
+    else if (shape == 1) OB_ATTN_DISPATCH(attn_bwd_dkv_1, grid_kv, threads, OB_DKV_ARGS);
+    else OB_ATTN_DISPATCH(attn_bwd_dkv_2, grid_kv, threads, OB_DKV_ARGS);
 #undef OB_DKV_ARGS
 }
 

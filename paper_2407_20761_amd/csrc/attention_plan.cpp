@@ -55,20 +55,22 @@ int make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side,
     return n << log2;
 }
 
-// Which of its shapes the dK / dV kernel runs in (see there).  An estimate of the launch's duration in
-// microseconds: the trips (64 query rows against a workgroup's key rows) that a CU has to make at the rate of a full
-// chip, or the longest chain of trips (the first key rows of the longest segment, all query heads of a group) at the
-// rate its workgroup sees, whichever is longer.  Over 448 launches measured in every shape (profiles/dkv_shape_choice.csv: 64 - 16400
-// tokens in one segment, ViT tiles or texts, 1 - 25 key / value heads, groups of 1 - 6, both masks) the picks are 0.1 - 0.2 %
-// slower in the mean than the fastest shape; nine more than 3 %, the worst 16 % (one segment of 2000, 8 heads of 128: 62 us, two pairs 53).
+// Which of its shapes dK / dV runs in (see the kernels).  An estimate of each shape's duration, about a microsecond to the unit: the trips (64
+// query rows against a workgroup's key rows) that a CU has to make at the rate of a full chip, or the longest chain of
+// trips (the first key rows of the longest segment, all query heads of a group) at the rate its workgroup sees, whichever is longer, and what the
+// blocks take to finish two trips behind their scores.  Over 544 launches measured in every shape (profiles/dkv_shape_choice.csv: 64 - 16400
+// tokens in one segment, ViT tiles or texts, 1 - 48 key / value heads, groups of 1 - 6, both masks) the picks are 0.2 %
+// slower in the mean than the fastest shape; eleven more than 3 %, the worst 7.6 % (one segment of 7168, 10 heads of 64: 166 us, with tiles of 64 154).
 namespace {
-struct DkvShape { int kv_rows; double full, chain; };
-constexpr DkvShape DKV_SHAPES[2][2] = {{{64, 0.81, 1.1}, {64, 0.70, 1.53}},      // D = 64: SR = 64, SR = 32
-                                       {{128, 2.39, 1.7}, {64, 1.76, 1.42}}};    // D = 128: four pairs, two
+struct DkvShape { int kv_rows; double full, chain, ends; };
+constexpr DkvShape DKV_SHAPES[2][3] = {
+    {{64, 0.81, 1.1, 0}, {64, 0.70, 1.53, 0}, {0, 0, 0, 0}},               // D = 64: SR = 64, SR = 32 (six pairs: below)
+    {{128, 1.69, 2.5, 0}, {64, 2.4, 0.85, 1.5}, {64, 2.8, 1.25, 0}}};      // D = 128: four pairs, blocks, two pairs
 }  // namespace
 int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
-    double est[2];
-    for (int i = 0; i < 2; ++i) {
+    int best = 0;
+    double t_best = 0;
+    for (int i = 0; i < (d == 128 ? 3 : 2); ++i) {
         const DkvShape &sh = DKV_SHAPES[d == 128][i];
         double sum = 0, chain = 0;
         for (int j = 0; j < seg->n_seg; ++j) {
@@ -76,7 +78,8 @@ int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
             sum += tiles * first - (causal ? 0.5 * tiles * (tiles - 1) * sh.kv_rows / 64 : 0.0);
             chain = std::max(chain, first);
         }
-        est[i] = group * std::max(sum * nkv / compute_units() * sh.full, chain * sh.chain);
+        const double t = group * std::max(sum * nkv / compute_units() * sh.full, chain * sh.chain) + sh.ends;
+        if (i == 0 || t < t_best) { t_best = t; best = i; }
     }
     // six pairs where two would need a second round (of two workgroups to a CU) and they do not: 520 or 176 workgroups, one segment
     // of 4097, 48 / 8 heads: 670 us with SR = 32, 760 with 64, 549; ten ViT tiles x 4 heads in groups of 4, 680 or 240: 125, 142,
@@ -84,7 +87,7 @@ int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
     if (d == 64 && !causal && (long)count_tiles(seg, 64) * nkv > 2 * compute_units() &&
         (long)count_tiles(seg, 32 * dkv_np(64, 2)) * nkv <= compute_units())
         return 2;
-    return est[1] < est[0] ? 1 : 0;
+    return best;
 }
 
 }  // namespace ob

@@ -31,9 +31,11 @@ __host__ __device__ __forceinline__ int tile_of_rank(const TileOrder &ord, uint3
     return (int)((e & 0xFFFFu) << ord.unit_log2) | (rank & ((1 << ord.unit_log2) - 1));
 }
 
-// shapes of dK / dV: pairs of waves, query rows of a streamed tile
-constexpr int dkv_np(int d, int shape) { return shape == 2 ? 6 : d == 128 && shape == 0 ? 4 : 2; }
+// shapes of dK / dV: pairs of 32 key rows, query rows of a streamed tile, threads.  Heads of 64: two pairs, two pairs with tiles of 32,
+// six pairs (bidirectional); heads of 128: four pairs, two as 32 x 32 blocks on eight waves, two pairs.
+constexpr int dkv_np(int d, int shape) { return d == 64 && shape == 2 ? 6 : d == 128 && shape == 0 ? 4 : 2; }
 constexpr int dkv_sr(int d, int shape) { return d == 64 && shape == 1 ? 32 : 64; }
+constexpr int dkv_threads(int d, int shape) { return d == 128 && shape == 1 ? 512 : 128 * dkv_np(d, shape); }
 
 // the order of a launch; returns its places (workgroups per head): as many as tiles, or whole units of them
 int make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side, TileOrder &ord);

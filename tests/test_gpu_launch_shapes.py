@@ -92,6 +92,37 @@ def test_dkv_order_in_units_of_tiles(d, unit, mask):
             assert torch.equal(x[a:b].view(torch.int16), y.view(torch.int16)), (name, j, b - a)
 
 
+@pytest.mark.parametrize("mask", [orc.MASK_BIDIR, orc.MASK_CAUSAL])
+@pytest.mark.parametrize("d,nq,nkv,lens", [(64, 2, 1, [4097]), (64, 2, 1, [8192 + 65]), (128, 2, 1, [4097 + 64]), (128, 2, 1, [8192 + 65]),
+                                           (128, 1, 1, [33, 64, 127, 128]), (128, 3, 1, [65, 129, 193, 321]),
+                                           (128, 32, 8, [4161, 4224] * 2)])
+def test_dkv_walks(d, nq, nkv, lens, mask):
+    """Walks of more query tiles than one descriptor of the requests serves (64), of a tile or two, and of odd and even numbers of them:
+    dK, dV of the first and the last segment against float32 products on the device (their own error is below 1e-5)."""
+    print(f"dkv walks d={d} nq={nq} nkv={nkv} mask={mask} {lens}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(d + nq + len(lens))
+    cu = si.lengths_to_cu(lens)
+    T, group = int(cu[-1]), nq // nkv
+    qkv = torch.randn((T, (nq + 2 * nkv) * d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    d_o = torch.randn((T, nq * d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    _, _, dk, dv = _attention(qkv, d_o, lens, nq, nkv, d, mask)
+    for a, b in ((int(cu[0]), int(cu[1])), (int(cu[-2]), int(cu[-1]))):
+        q, k, v = (x.float() for x in qkv[a:b].split([nq * d, nkv * d, nkv * d], 1))
+        hidden = torch.ones((b - a, b - a), dtype=torch.bool, device="cuda").triu_(1) if mask == orc.MASK_CAUSAL else None
+        for h in (0, nkv - 1):
+            c = slice(h * d, (h + 1) * d)
+            want_k, want_v = torch.zeros_like(k[:, c]), torch.zeros_like(v[:, c])
+            for g in range(h * group, (h + 1) * group):
+                qh, go = q[:, g * d:(g + 1) * d], d_o[a:b, g * d:(g + 1) * d].float()
+                S = (qh @ k[:, c].t()) * d ** -0.5
+                P = (S if hidden is None else S.masked_fill_(hidden, -math.inf)).softmax(1)
+                dP = go @ v[:, c].t()
+                want_v += P.t() @ go
+                want_k += (P * (dP - (P * dP).sum(1, keepdim=True))).t() @ qh * d ** -0.5
+            for name, got, want in (("dk", dk[a:b, c], want_k), ("dv", dv[a:b, c], want_v)):
+                assert (got.float() - want).abs().max() <= TOL * want.abs().max(), (name, a, h)
+
+
 def _normal_gemm(layout, M, N, K, seed):
     """operands of N(0, 1) as the library takes them, bias, residual, and A, B as [M, K], [N, K] views"""
     gen = torch.Generator(device="cuda").manual_seed(seed)
