@@ -336,8 +336,12 @@ static void block_fwd_bf16(const ob_block_desc *desc, const ob_block_weights *w,
                     m.Dqkv, m.HD, seg, m.nq, m.nkv, m.d, scale, desc->mask, s);
     launch_gemm_nt(m.T, m.H, m.HD, o, m.HD, w->w_o, m.HD, x1, m.H, bias ? w->b_o : nullptr, x, m.H, s, 0, gws);
     launch_norm_fwd(desc->norm, x1, w->n2_g, beta ? w->n2_b : nullptr, h2, (float *)at(saved, sv.stat2), m.T, m.H, desc->norm_eps, s);
-    launch_gemm_nt(m.T, m.upF, m.H, h2, m.H, w->w_up, m.H, up, m.upF, bias ? w->b_up : nullptr, nullptr, 0, s, 0, gws);
-    launch_act_fwd(desc->mlp, up, act, m.T, m.F, s);
+    if (desc->mlp == OB_GELU && gemm_act_fuses(GEMM_NT_GELU, m.T, m.F, m.H, gws != nullptr))
+        (void)gemm_any(GEMM_NT_GELU, m.T, m.F, m.H, h2, w->w_up, up, bias ? w->b_up : nullptr, act, gws, sv.gemm_bytes, s);
+    else {
+        launch_gemm_nt(m.T, m.upF, m.H, h2, m.H, w->w_up, m.H, up, m.upF, bias ? w->b_up : nullptr, nullptr, 0, s, 0, gws);
+        launch_act_fwd(desc->mlp, up, act, m.T, m.F, s);
+    }
     if (y) launch_gemm_nt(m.T, m.H, m.F, act, m.F, w->w_down, m.F, y, m.H, bias ? w->b_down : nullptr, x1, m.H, s, 0, gws);
 }
 
@@ -401,9 +405,20 @@ extern "C" int ob_block_bwd(const ob_block_desc *desc, const ob_block_weights *w
     };
 
     // y = x1 + act W_down^T + b_down
-    if ((rc = gemm_any(1, m.T, m.F, m.H, dy, w->w_down, dact, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
-    launch_act_bwd(desc->mlp, dact, up, dup, m.T, m.F, s);
-    if (bias) bias_grad(dup, m.upF, wk.p_up, g->b_up);
+    const int act_layout = desc->mlp == OB_GELU ? GEMM_NN_GELU_BWD : GEMM_NN_SWIGLU_BWD;
+    Plan act_plan;
+    if (gemm_act_fuses(act_layout, m.T, m.F, m.H, true, &act_plan)) {
+        // (d act never stored; with biases the column sums of dup come with it where their region has the rows for them)
+        const int rows = gemm_act_colsums(act_plan, m.T);
+        float *partial = bias && rows <= ncs ? (float *)at(ws, wk.p_up) : nullptr;
+        if ((rc = gemm_any(act_layout, m.T, m.F, m.H, dy, w->w_down, dup, partial, up, gws, wk.gemm_bytes, s))) return rc;
+        if (partial) sums.add(partial, rows, m.upF, g->b_up, m.upF);
+        else if (bias) bias_grad(dup, m.upF, wk.p_up, g->b_up);
+    } else {
+        if ((rc = gemm_any(1, m.T, m.F, m.H, dy, w->w_down, dact, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
+        launch_act_bwd(desc->mlp, dact, up, dup, m.T, m.F, s);
+        if (bias) bias_grad(dup, m.upF, wk.p_up, g->b_up);
+    }
     if ((rc = gemm_any(1, m.T, m.H, m.upF, dup, w->w_up, dh, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
     // dx1 = dy + norm2_bwd(dh2)
     // (with biases the same pass leaves the column sums of dy and of dx1: the gradients of b_down and b_o)

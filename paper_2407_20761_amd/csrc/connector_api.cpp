@@ -2,6 +2,7 @@
 // of the row-wise kernels in connector.hip, the GEMM, the GELU and the column-sum kernels.
 #include <vector>
 
+#include "gemm_plan.h"
 #include "ob_internal.h"
 
 using namespace ob;
@@ -122,8 +123,12 @@ extern "C" int ob_connector_fwd(const ob_connector_desc *desc, const ob_connecto
     unsigned char *un = at(saved, sv.un), *h = at(saved, sv.h), *a = at(saved, sv.a);
     launch_subsample_norm_fwd(v, w->n_g, w->n_b, un, (float *)at(saved, sv.stats), m.n_tok, m.g, m.Hv, desc->norm_eps, s);
     void *gws = wk.gemm_bytes ? at(ws, wk.gemm) : nullptr;
-    launch_gemm_nt(m.n_tok, m.Ht, m.W, un, m.W, w->w1, m.W, h, m.Ht, w->b1, nullptr, 0, s, 0, gws);
-    launch_act_fwd(OB_GELU, h, a, m.n_tok, m.Ht, s);
+    if (gemm_act_fuses(GEMM_NT_GELU, m.n_tok, m.Ht, m.W, gws != nullptr)) {
+        if (int rc = gemm_any(GEMM_NT_GELU, m.n_tok, m.Ht, m.W, un, w->w1, h, w->b1, a, gws, wk.gemm_bytes, s)) return rc;
+    } else {
+        launch_gemm_nt(m.n_tok, m.Ht, m.W, un, m.W, w->w1, m.W, h, m.Ht, w->b1, nullptr, 0, s, 0, gws);
+        launch_act_fwd(OB_GELU, h, a, m.n_tok, m.Ht, s);
+    }
     // z = a W2^T + b2, its rows straight onto the visual rows of the LLM batch
     launch_gemm_nt_rows(m.n_tok, m.Ht, m.Ht, a, m.Ht, w->w2, m.Ht, x_llm, m.Ht, w->b2, dst_rows_dev, s, gws);
     return check_launch(who);
@@ -167,9 +172,13 @@ extern "C" int ob_connector_bwd(const ob_connector_desc *desc, const ob_connecto
     launch_rows_gather(dz, dx_llm, dst_rows_dev, m.n_tok, m.Ht, s);
     // z = a W2^T + b2
     if ((rc = gemm_any(2, m.Ht, m.Ht, m.n_tok, dz, a, g->w2, nullptr, acc ? g->w2 : nullptr, gws, wk.gemm_bytes, s))) return rc;
-    if ((rc = gemm_any(1, m.n_tok, m.Ht, m.Ht, dz, w->w2, da, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
     // a = GELU(h), h = un W1^T + b1
-    launch_act_bwd(OB_GELU, da, h, dh, m.n_tok, m.Ht, s);
+    if (gemm_act_fuses(GEMM_NN_GELU_BWD, m.n_tok, m.Ht, m.Ht, true)) {
+        if ((rc = gemm_any(GEMM_NN_GELU_BWD, m.n_tok, m.Ht, m.Ht, dz, w->w2, dh, nullptr, h, gws, wk.gemm_bytes, s))) return rc;
+    } else {
+        if ((rc = gemm_any(1, m.n_tok, m.Ht, m.Ht, dz, w->w2, da, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
+        launch_act_bwd(OB_GELU, da, h, dh, m.n_tok, m.Ht, s);
+    }
     if ((rc = gemm_any(2, m.Ht, m.W, m.n_tok, dh, un, g->w1, nullptr, acc ? g->w1 : nullptr, gws, wk.gemm_bytes, s))) return rc;
     if ((rc = gemm_any(1, m.n_tok, m.W, m.Ht, dh, w->w1, dun, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
     // un = LayerNorm(gather(v)), and the column reductions: b2 and b1 over dz and dh, gain and beta by the norm's backward.

@@ -2,6 +2,7 @@
 // backward counterparts b1, b3, b6, b8, bias-gradient column sums).
 // bf16 in / out, fp32 arithmetic, 16-byte loads and stores; one workgroup per token row for the
 // row-wise ones so every byte is read once and written once.
+#include "act.h"
 #include "ob_internal.h"
 
 namespace ob {
@@ -535,38 +536,6 @@ __global__ __launch_bounds__(256) void rotary_kernel(__bf16 *__restrict__ qkv, i
     }
 }
 
-// GELU through h = Phi(-|z|) = erfc(|z| / sqrt 2) / 2 = t Q(t) e^(-z^2 / 2), t = 1 / (1 + 0.43 |z| / sqrt 2), Q the degree-7
-// polynomial that is closest in the relative sense to erfc(x) e^(x^2) / t over x <= 9.5 (a Lawson fit to 8000 Chebyshev
-// nodes; 1.5e-7 with its coefficients in fp32): an exponential, a reciprocal and 8 FMAs, where erff() takes twice that and
-// 1 + erf(z) cancels for negative z.  Over bf16 arguments h is within 8.2e-7 of its value for |z| <= 4, 2.2e-6 to 6 and 1.2e-5
-// to 13 (the rounding of z^2 in the exponent), relative; so is GELU.  The derivative takes h as it is for negative z too
-// (0.5 - (0.5 - h) cancels: 3 % at z = -6) and the same exponential for the density: within 1.2e-5 for z <= -1,
-// 7e-8 absolute around its zero at -0.75.  (These kernels were bound by the vector unit, not by HBM.)
-struct HalfTail { float h, e; };   // Phi(-|z|), e^(-z^2 / 2)
-__device__ __forceinline__ HalfTail half_tail(float z) {
-    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(fabsf(z), 0.30405592f, 1.0f));
-    const float y = z * 0.84932180f;             // e^(-z^2 / 2) = 2^(-y^2)
-    const float e = __builtin_amdgcn_exp2f(-y * y);
-    float q = 0.036854025f;
-    q = __builtin_fmaf(q, t, -0.15518695f);
-    q = __builtin_fmaf(q, t, 0.19185331f);
-    q = __builtin_fmaf(q, t, -0.042863335f);
-    q = __builtin_fmaf(q, t, 0.12342247f);
-    q = __builtin_fmaf(q, t, 0.10247547f);
-    q = __builtin_fmaf(q, t, 0.12218773f);
-    q = __builtin_fmaf(q, t, 0.12125731f);
-    return HalfTail{q * t * e, e};
-}
-__device__ __forceinline__ float gelu_f(float z) {
-    const float h = half_tail(z).h;
-    return z * (z < 0.0f ? h : 1.0f - h);
-}
-__device__ __forceinline__ float gelu_grad_f(float z) {
-    const HalfTail k = half_tail(z);
-    return __builtin_fmaf(z * k.e, 0.3989422804014327f, z < 0.0f ? k.h : 1.0f - k.h);
-}
-__device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + __expf(-z)); }
-
 // GELU: act[t, f] = gelu(up[t, f]): one flat array, a vector of 8 per thread.  (Two per thread halve the workgroups, and the last of them
 // end alone: forward of 8M elements 10.1 us, with one 8.3; backward of 6M 10.2 and 8.1, of 32M 37.4 and 35.2; of 200M no difference.)
 __global__ __launch_bounds__(256) void gelu_fwd_kernel(const __bf16 *__restrict__ up, __bf16 *__restrict__ act, long n_vec) {
@@ -633,9 +602,9 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const __bf16 *__restric
         bf16x8 og, ou;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float gz = (float)g[e], sg = sigmoid_f(gz), d = (float)da[e];
-            og[e] = (__bf16)(d * (float)u[e] * sg * (1.0f + gz * (1.0f - sg)));
-            ou[e] = (__bf16)(d * gz * sg);
+            const SwigluGrad r = swiglu_grad_f((float)da[e], (float)g[e], (float)u[e]);
+            og[e] = (__bf16)r.gate;
+            ou[e] = (__bf16)r.up;
         }
         *(bf16x8 *)(dup + t * 2 * F + c) = og;
         *(bf16x8 *)(dup + t * 2 * F + F + c) = ou;

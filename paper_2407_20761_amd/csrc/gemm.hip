@@ -37,6 +37,7 @@
 // consecutive output columns; the epilogue transposes them through LDS into full-row stores.
 #include <type_traits>
 
+#include "act.h"
 #include "gemm_plan.h"
 #include "ob_internal.h"
 
@@ -522,13 +523,21 @@ struct KLoop {
 
 // One workgroup's work: tile (tile_m, tile_n) of C, whole, or (sliced) K steps [kz k_chunk, ...) of it with
 // the fp32 sums left at part[kz][tail_tile].
-// ROWS: row m of the result is row rows[m] of C (no residual).
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS, bool ROWS = false>
+// What becomes of the tile on its way out.  EPI_ROWS: row m of the result is row rows[m] of C (no residual).  The others apply an
+// activation to the rounded result x, for launches of one pass over small tiles (gemm_act_fuses(), where the rule stands):
+//   EPI_GELU        C = x (+ bias), act[m, n] = GELU(C), act in place of R
+//   EPI_GELU_BWD    C = x GELU'(up), up in place of R
+//   EPI_SWIGLU_BWD  C[m, n], C[m, N + n]: the gradients of gate and up for x, that of their product; up [M, 2 N] in place of R
+// The last two leave the fp32 sums of each half tile's columns of C at colsum[2 tile_m + wave row][C's columns] (may be null: in place of the bias).
+enum { EPI_PLAIN = 0, EPI_ROWS, EPI_GELU, EPI_GELU_BWD, EPI_SWIGLU_BWD };
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS, int EPI = EPI_PLAIN>
 __device__ __forceinline__ void gemm_tile(
     int M, int N, int K, const __bf16 *__restrict__ A, int lda, const __bf16 *__restrict__ B,
     int ldb, __bf16 *__restrict__ Cm, int ldc, const __bf16 *__restrict__ bias,
     const __bf16 *R, int ldr, int tile_m, int tile_n, bool sliced, int kz, int tail_tile, const TailSplit &ts,
-    const int32_t *__restrict__ rows = nullptr) {
+    const void *__restrict__ side = nullptr) {       // rows, act or up
+    constexpr bool ROWS = EPI == EPI_ROWS;
+    const int32_t *__restrict__ rows = (const int32_t *)side;
     using C = Cfg<BM, BN, WM, WN>;
     constexpr int TA = C::TA, TB = C::TB;
     __shared__ __attribute__((aligned(1024))) unsigned char ring_mem[KLoop<BM, BN, WM, WN, AK, BKM, NS>::RING_BYTES];
@@ -614,7 +623,7 @@ __device__ __forceinline__ void gemm_tile(
     float bv[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) bv[e] = 0.f;
-    if (bias && n_out < N) {
+    if (EPI < EPI_GELU_BWD && bias && n_out < N) {
         const bf16x8 b8 = *(const bf16x8 *)(bias + n_out);
 #pragma unroll
         for (int e = 0; e < 8; ++e) bv[e] = (float)b8[e];
@@ -626,6 +635,9 @@ __device__ __forceinline__ void gemm_tile(
             for (int j = 0; j < TB; ++j)
                 *(f32x4 OB_LDS *)(slab + (16 * h + lx) * RSTR + (j * 16 + lq * 4) * 4) = acc[2 * ii + h][j];
     };
+    float cs[2][8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cs[0][e] = cs[1][e] = 0.f;
     // One straight path per kind of output (MODE 0: bf16; 1: bf16 with the residual added; 2: the fp32 sums
     // of a slice, the whole tile: sums beyond M and N are never read by tail_sum_kernel) and per kind of
     // tile (CHECK: some rows or columns lie past M or N): with the choices inside the loop every row read
@@ -648,7 +660,16 @@ __device__ __forceinline__ void gemm_tile(
             }
             if (ii + 1 < TA / 2) put(ii + 1);
             const int m_first = m0 + wm * (BM / WM) + ii * 32 + lane / LPR;
-            bf16x8 r8[NR];
+            bf16x8 r8[NR], g8[NR];
+            if (EPI >= EPI_GELU_BWD) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (!CHECK || (m_first + r * RPI < M && n_out < N)) {
+                        const __bf16 *up = (const __bf16 *)side + (size_t)(m_first + r * RPI) * ldc + n_out;
+                        r8[r] = *(const bf16x8 *)up;
+                        if (EPI == EPI_SWIGLU_BWD) g8[r] = *(const bf16x8 *)(up + N);
+                    }
+            }
             if (MODE == 1) {
 #pragma unroll
                 for (int r = 0; r < NR; ++r)
@@ -673,13 +694,63 @@ __device__ __forceinline__ void gemm_tile(
                     bf16x8 o;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) o[e] = (__bf16)o8[e];
-                    __builtin_nontemporal_store(o, (bf16x8 *)(Cm + (size_t)(ROWS ? rows[m] : m) * ldc + n_out));
+                    if constexpr (EPI == EPI_GELU) {
+                        bf16x8 act;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) act[e] = (__bf16)gelu_f((float)o[e]);
+                        *(bf16x8 *)((__bf16 *)side + (size_t)m * ldc + n_out) = act;
+                    }
+                    if constexpr (EPI == EPI_GELU_BWD) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            o[e] = (__bf16)((float)o[e] * gelu_grad_f((float)r8[r][e]));
+                            cs[0][e] += (float)o[e];
+                        }
+                    }
+                    if constexpr (EPI == EPI_SWIGLU_BWD) {
+                        bf16x8 ou;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const SwigluGrad w = swiglu_grad_f((float)o[e], (float)r8[r][e], (float)g8[r][e]);
+                            o[e] = (__bf16)w.gate;
+                            ou[e] = (__bf16)w.up;
+                            cs[0][e] += (float)o[e];
+                            cs[1][e] += (float)ou[e];
+                        }
+                        *(bf16x8 *)(Cm + (size_t)m * ldc + N + n_out) = ou;
+                    }
+                    if constexpr (EPI >= EPI_GELU_BWD) *(bf16x8 *)(Cm + (size_t)m * ldc + n_out) = o;
+                    else __builtin_nontemporal_store(o, (bf16x8 *)(Cm + (size_t)(ROWS ? rows[m] : m) * ldc + n_out));
                 }
             }
         }
     };
     using std::integral_constant;
     const bool inside = m0 + BM <= M && n0 + BN <= N;
+    if constexpr (EPI >= EPI_GELU) {
+        if (inside) out(integral_constant<int, 0>{}, integral_constant<bool, false>{});
+        else out(integral_constant<int, 0>{}, integral_constant<bool, true>{});
+        if constexpr (EPI >= EPI_GELU_BWD) {
+            if (!bias) return;
+            // a lane's columns are the same in every row it has: over the lanes of the same columns, then one row of sums per wave row
+            constexpr int HALVES = EPI == EPI_SWIGLU_BWD ? 2 : 1;
+#pragma unroll
+            for (int half = 0; half < HALVES; ++half)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int d = LPR; d < 64; d <<= 1) cs[half][e] += __shfl_xor(cs[half][e], d);
+            if (lane < LPR && n_out < N) {
+                float *dst = (float *)bias + (size_t)(2 * tile_m + wm) * ldc + n_out;
+#pragma unroll
+                for (int half = 0; half < HALVES; ++half) {
+                    *(f32x4 *)(dst + half * N) = f32x4{cs[half][0], cs[half][1], cs[half][2], cs[half][3]};
+                    *(f32x4 *)(dst + half * N + 4) = f32x4{cs[half][4], cs[half][5], cs[half][6], cs[half][7]};
+                }
+            }
+        }
+        return;
+    }
     if (sliced) out(integral_constant<int, 2>{}, integral_constant<bool, false>{});
     else if (inside && R) out(integral_constant<int, 1>{}, integral_constant<bool, false>{});
     else if (inside) out(integral_constant<int, 0>{}, integral_constant<bool, false>{});
@@ -687,9 +758,9 @@ __device__ __forceinline__ void gemm_tile(
     else out(integral_constant<int, 0>{}, integral_constant<bool, true>{});
 }
 
-// ROWS: R is the row list (one more argument would make the argument block 128 bytes long, and a launch of that is 0.2 us
+// EPI other than plain: R is the row list, act or up (one more argument would make the argument block 128 bytes long, and a launch of that is 0.2 us
 // slower: 2567 x 768 x 256 6.0 -> 6.2)
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS, bool ROWS = false>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, int NS, int EPI = EPI_PLAIN>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
     int M, int N, int K, const __bf16 *__restrict__ A, int lda, const __bf16 *__restrict__ B,
     int ldb, __bf16 *__restrict__ Cm, int ldc, const __bf16 *__restrict__ bias,
@@ -702,8 +773,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
     const int tail_tile = sliced ? xcd_chunk((pid - n_whole) % ts.n_tail, ts.n_tail, interleave) : 0;
     int tile_m, tile_n;
     tile_of_id(sliced ? n_whole + tail_tile : xcd_chunk(pid, n_whole, interleave), tiles_m, tiles_n, tile_m, tile_n);
-    gemm_tile<BM, BN, WM, WN, AK, BKM, NS, ROWS>(M, N, K, A, lda, B, ldb, Cm, ldc, bias, ROWS ? nullptr : R, ldr, tile_m, tile_n,
-                                                 sliced, kz, tail_tile, ts, (const int32_t *)R);
+    gemm_tile<BM, BN, WM, WN, AK, BKM, NS, EPI>(M, N, K, A, lda, B, ldb, Cm, ldc, bias, EPI == EPI_PLAIN ? R : nullptr, ldr, tile_m, tile_n,
+                                                sliced, kz, tail_tile, ts, R);
 }
 
 // Several GEMMs of one layout over the same contraction length K in ONE launch (the weight gradients of a
@@ -759,11 +830,18 @@ OB_GEMM_INSTANCE(256, 256, false, true, 4)
 OB_GEMM_INSTANCE(128, 128, false, true, 4)
 OB_GEMM_INSTANCE(256, 256, true, true, 4)
 OB_GEMM_INSTANCE(128, 128, true, true, 4)
-OB_GEMM_INSTANCE(256, 256, false, false, 4, true)
-OB_GEMM_INSTANCE(128, 128, false, false, 4, true)
-OB_GEMM_INSTANCE(128, 128, false, false, 8, true)
-OB_GEMM_INSTANCE(192, 256, false, false, 4, true)
-OB_GEMM_INSTANCE(64, 64, false, false, 8, true)
+OB_GEMM_INSTANCE(256, 256, false, false, 4, EPI_ROWS)
+OB_GEMM_INSTANCE(128, 128, false, false, 4, EPI_ROWS)
+OB_GEMM_INSTANCE(128, 128, false, false, 8, EPI_ROWS)
+OB_GEMM_INSTANCE(192, 256, false, false, 4, EPI_ROWS)
+OB_GEMM_INSTANCE(64, 64, false, false, 8, EPI_ROWS)
+OB_GEMM_INSTANCE(128, 128, false, false, 4, EPI_GELU)
+OB_GEMM_INSTANCE(128, 128, false, false, 8, EPI_GELU)
+OB_GEMM_INSTANCE(64, 64, false, false, 8, EPI_GELU)
+OB_GEMM_INSTANCE(128, 128, false, true, 4, EPI_GELU_BWD)
+OB_GEMM_INSTANCE(64, 64, false, true, 8, EPI_GELU_BWD)
+OB_GEMM_INSTANCE(128, 128, false, true, 4, EPI_SWIGLU_BWD)
+OB_GEMM_INSTANCE(64, 64, false, true, 8, EPI_SWIGLU_BWD)
 #undef OB_GEMM_INSTANCE
 template <class... A>
 constexpr size_t arg_bytes(void (*)(A...)) {
@@ -855,7 +933,7 @@ void launch_tile(int M, int N, int K, const void *A, int lda, const void *B, int
 #define OB_GEMM_ARGS M, N, K, (const __bf16 *)A, lda, (const __bf16 *)B, ldb, (__bf16 *)C, ldc, (const __bf16 *)bias,     \
                      (const __bf16 *)(rows ? (const void *)rows : R), ldr, tiles_m, tiles_n, ts
     if constexpr (!AK && !BKM) {
-        if (rows) hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM, NS, true>), grid, block, 0, s, OB_GEMM_ARGS);
+        if (rows) hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM, NS, EPI_ROWS>), grid, block, 0, s, OB_GEMM_ARGS);
         else hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM, NS>), grid, block, 0, s, OB_GEMM_ARGS);
     } else
         hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AK, BKM, NS>), grid, block, 0, s, OB_GEMM_ARGS);
@@ -946,12 +1024,38 @@ int gemm_tn_group(int count, const GemmTN *g, int K, void *ws, size_t ws_bytes, 
     return check_launch("gemm group");
 }
 
+// one launch of small tiles with an activation in its epilogue (Plan p whole, see gemm_act_fuses())
+template <int BM, int NS, bool BKM, int EPI>
+static void launch_act(int M, int N, int K, const void *A, const void *B, void *C, int ldc, const void *bias, const void *side,
+                       const Plan &p, hipStream_t s) {
+    const TailSplit ts{nullptr, 0, 0, 1, 0};
+    hipLaunchKernelGGL((gemm_kernel<BM, BM, 2, 2, false, BKM, NS, EPI>), dim3(p.n_full + p.n_tail), dim3(256), 0, s, M, N, K,
+                       (const __bf16 *)A, K, (const __bf16 *)B, BKM ? N : K, (__bf16 *)C, ldc, (const __bf16 *)bias,
+                       (const __bf16 *)side, ldc, (M + BM - 1) / BM, (N + BM - 1) / BM, ts);
+}
+
 // layout 0 ("NT"): A[M,K] B[N,K]; 1 ("NN"): A[M,K] B[K,N]; 2 ("TN"): A[K,M] B[K,N].  All three
 // run natively: a K-major operand is staged as it lies in memory and transposed by the LDS read.
 // The timed span of a GEMM with split tiles includes the kernel that sums the slices.
 int gemm_any(int layout, int M, int N, int K, const void *A, const void *B, void *C,
              const void *bias, const void *R, void *ws, size_t ws_bytes, hipStream_t s) {
     ProfScope prof(K_GEMM, s, 2.0 * M * N * K);
+    if (layout > 2) {      // GEMM_NT_GELU ...: R is act or up, bias of the last two the column sums
+        Plan p;
+        if (!gemm_act_fuses(layout, M, N, K, ws != nullptr, &p)) return fail(OB_EINVAL, "gemm: activation in a launch that has none");
+        if (layout == GEMM_NT_GELU) {
+            if (p.kind == FINE) launch_act<64, 8, false, EPI_GELU>(M, N, K, A, B, C, N, bias, R, p, s);
+            else if (p.kind == DEEP) launch_act<128, 8, false, EPI_GELU>(M, N, K, A, B, C, N, bias, R, p, s);
+            else launch_act<128, 4, false, EPI_GELU>(M, N, K, A, B, C, N, bias, R, p, s);
+        } else if (layout == GEMM_NN_GELU_BWD) {
+            if (p.kind == FINE) launch_act<64, 8, true, EPI_GELU_BWD>(M, N, K, A, B, C, N, bias, R, p, s);
+            else launch_act<128, 4, true, EPI_GELU_BWD>(M, N, K, A, B, C, N, bias, R, p, s);
+        } else {
+            if (p.kind == FINE) launch_act<64, 8, true, EPI_SWIGLU_BWD>(M, N, K, A, B, C, 2 * N, bias, R, p, s);
+            else launch_act<128, 4, true, EPI_SWIGLU_BWD>(M, N, K, A, B, C, 2 * N, bias, R, p, s);
+        }
+        return check_launch("gemm with activation");
+    }
     float *part = ws && ws_bytes >= gemm_workspace_bytes(layout, M, N, K) ? (float *)ws : nullptr;
     if (layout == 0)
         launch_layout<false, false>(0, M, N, K, A, K, B, K, C, N, bias, R, N, part, s);

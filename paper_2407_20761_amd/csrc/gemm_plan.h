@@ -34,6 +34,12 @@ int tiles_of(TileKind kind, int M, int N);
 size_t scratch_bytes(int M, int N, int K);
 // the launches of a GEMM; layout 0 "NT", 1 "NN", 2 "TN"; `scratch`: bytes for slice sums
 RowCut make_row_cut(int layout, int M, int N, int K, size_t scratch);
+// GEMMs with an activation in the epilogue: layouts of gemm_any() beyond the three (internal).  Whether such a launch is taken instead of two, and its
+// plan; `scratch`: the GEMM alone would have room for slice sums
+enum { GEMM_NT_GELU = 3, GEMM_NN_GELU_BWD = 4, GEMM_NN_SWIGLU_BWD = 5 };
+bool gemm_act_fuses(int layout, int M, int N, int K, bool scratch, Plan *plan = nullptr);
+// rows of column sums that the last two leave: two per row of tiles
+inline int gemm_act_colsums(const Plan &p, int M) { return 2 * ((M + tile_rows(p.kind) - 1) / tile_rows(p.kind)); }
 // the same for a group of up to GEMM_GROUP_MAX "TN" GEMMs over one K: true: one launch, p; false: one by one.  has_ws: there is scratch, of ws_bytes
 bool make_group_plan(int count, const int *M, const int *N, int K, bool has_ws, size_t ws_bytes, Plan &p);
 

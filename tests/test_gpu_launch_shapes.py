@@ -354,6 +354,31 @@ def test_grouped_weight_gradients_by_tile(hidden, mlp, T, want):
         assert torch.equal((2 * once[n].float()).to(torch.bfloat16).view(torch.int16), run.g[n].view(torch.int16)), n
 
 
+@pytest.mark.parametrize("mlp,T,hidden,F,tile", [(si.MLP_GELU, 1, 128, 192, (64, 8)), (si.MLP_GELU, 65, 256, 512, (64, 8)),
+                                                 (si.MLP_GELU, 1025, 640, 2560, (128, 4)), (si.MLP_GELU, 1500, 768, 2112, (128, 8)),
+                                                 (si.MLP_SWIGLU, 129, 256, 1088, (64, 8)), (si.MLP_SWIGLU, 1700, 640, 2560, (128, 4))])
+def test_activations_in_the_epilogue(mlp, T, hidden, F, tile):
+    """Activations applied to a GEMM's result on its way out, forward (GELU) and backward, with the column sums that come with the backward:
+    each kind of tile that takes them, rows and columns on and beside the tiles' borders, against the oracle."""
+    print(f"activation in the epilogue mlp={mlp} T={T} {hidden} {F}", flush=True)
+    shape = si.small_shape(hidden=hidden, n_q_heads=hidden // 64, n_kv_heads=hidden // 64, head_dim=64, mlp_dim=F,
+                           norm=si.NORM_LAYERNORM, mlp=mlp, mask=si.MASK_BIDIR, has_bias=True, norm_eps=1e-5)
+    for layout, ring in ((0, tile[1]), (1, 8 if tile[0] == 64 else 4)):
+        launches = ob.ob_gemm_plan(layout, T, F, hidden, layout == 1)
+        if layout == 1 or mlp == si.MLP_GELU:
+            assert [(g.tile_rows, g.ring_slots, g.slices) for g in launches] == [(tile[0], ring, 1)]
+    lens = [100] * (T // 100) + ([T % 100] if T % 100 else [])
+    cu = si.lengths_to_cu(lens)
+    w = si.block_weights(shape, seed=2)
+    x, dy = si.activations(T, hidden, seed=3, std=1.0)
+    run, y, dx, g = run_block(shape, w, x, dy, cu)
+    y_ref, cache = orc.block_fwd(shape, w, x, cu)
+    dx_ref, g_ref, _ = orc.block_bwd(shape, w, cache, dy, cu)
+    for n, got, ref in [("y", y, y_ref), ("dx", dx, dx_ref)] + [(n, g[n], g_ref[n]) for n in g]:
+        if n != "b_qkv" or T > 1:      # (one token: no gradient through its softmax, and the oracle's rounding as the scale)
+            assert np.abs(got - ref).max() <= TOL * np.abs(ref).max(), n
+
+
 def test_gelu_and_derivative_element_by_element():
     """GELU and its derivative at every bf16 argument of 2^-12 .. 13.1 in size, each against its own value and not the tensor's
     maximum: one rounding to bf16 (8 significant bits: 2^-8 of the value at most) and the functions' own error (1.2e-5 of the value in the tails, 7e-8
