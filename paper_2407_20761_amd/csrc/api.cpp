@@ -416,8 +416,13 @@ extern "C" int ob_block_bwd(const ob_block_desc *desc, const ob_block_weights *w
         else if (bias) bias_grad(dup, m.upF, wk.p_up, g->b_up);
     } else {
         if ((rc = gemm_any(1, m.T, m.F, m.H, dy, w->w_down, dact, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
-        launch_act_bwd(desc->mlp, dact, up, dup, m.T, m.F, s);
-        if (bias) bias_grad(dup, m.upF, wk.p_up, g->b_up);
+        if (bias && desc->mlp == OB_GELU) {
+            float *partial = (float *)at(ws, wk.p_up);
+            sums.add(partial, launch_gelu_bwd_cols(dact, up, dup, m.T, m.F, partial, ncs, s), m.F, g->b_up, m.F);
+        } else {
+            launch_act_bwd(desc->mlp, dact, up, dup, m.T, m.F, s);
+            if (bias) bias_grad(dup, m.upF, wk.p_up, g->b_up);
+        }
     }
     if ((rc = gemm_any(1, m.T, m.H, m.upF, dup, w->w_up, dh, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
     // dx1 = dy + norm2_bwd(dh2)

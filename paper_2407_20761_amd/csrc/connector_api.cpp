@@ -169,32 +169,44 @@ extern "C" int ob_connector_bwd(const ob_connector_desc *desc, const ob_connecto
     void *gws = at(ws, wk.gemm);
     const int ncs = colsum_partials(m.n_tok);
     int rc;
-    launch_rows_gather(dz, dx_llm, dst_rows_dev, m.n_tok, m.Ht, s);
-    // z = a W2^T + b2
-    if ((rc = gemm_any(2, m.Ht, m.Ht, m.n_tok, dz, a, g->w2, nullptr, acc ? g->w2 : nullptr, gws, wk.gemm_bytes, s))) return rc;
-    // a = GELU(h), h = un W1^T + b1
-    if (gemm_act_fuses(GEMM_NN_GELU_BWD, m.n_tok, m.Ht, m.Ht, true)) {
-        if ((rc = gemm_any(GEMM_NN_GELU_BWD, m.n_tok, m.Ht, m.Ht, dz, w->w2, dh, nullptr, h, gws, wk.gemm_bytes, s))) return rc;
-    } else {
-        if ((rc = gemm_any(1, m.n_tok, m.Ht, m.Ht, dz, w->w2, da, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
-        launch_act_bwd(OB_GELU, da, h, dh, m.n_tok, m.Ht, s);
-    }
-    if ((rc = gemm_any(2, m.Ht, m.W, m.n_tok, dh, un, g->w1, nullptr, acc ? g->w1 : nullptr, gws, wk.gemm_bytes, s))) return rc;
-    if ((rc = gemm_any(1, m.n_tok, m.W, m.Ht, dh, w->w1, dun, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
-    // un = LayerNorm(gather(v)), and the column reductions: b2 and b1 over dz and dh, gain and beta by the norm's backward.
-    // Their partial sums lie in the region laid out for them and in that of da, which nothing needs any more: the
-    // norm's, which want up to 256 rows of 2 W, in the roomier one, the bias sums in the other, and one launch
+    // The column reductions: b2 and b1 over dz and dh, gain and beta by the norm's backward.
+    // Their partial sums lie in the region laid out for them and in that of da, which nothing needs any more by the time of the norm's
+    // backward: the norm's, which want up to 256 rows of 2 W, in the roomier one, the bias sums in the other, and one launch
     // adds them all.  Below 256 tokens (a grid of a few patches) neither has room for that: one after the other.
     const size_t room[2] = {wk.da_bytes, wk.partial_bytes}, norm_row = (size_t)2 * m.W * 4;
     float *const region[2] = {(float *)da, partial};
     const int at_norm = m.n_tok >= 256 && room[0] > room[1] ? 0 : 1, at_bias = 1 - at_norm;
+    // Where the bias sums have a region that nothing else uses, the passes that write dz and dh leave them there (half of it each)
+    const int half = (int)(wk.partial_bytes / ((size_t)2 * m.Ht * 4));
+    const bool fuses = gemm_act_fuses(GEMM_NN_GELU_BWD, m.n_tok, m.Ht, m.Ht, true), beside = !fuses && m.n_tok >= 256 && at_bias == 1;
     ReduceBatch sums;
-    if (m.n_tok >= 256) {
+    if (beside)
+        sums.add(partial, launch_rows_gather_cols(dz, dx_llm, dst_rows_dev, m.n_tok, m.Ht, partial, half, s), m.Ht, g->b2, m.Ht);
+    else
+        launch_rows_gather(dz, dx_llm, dst_rows_dev, m.n_tok, m.Ht, s);
+    // z = a W2^T + b2
+    if ((rc = gemm_any(2, m.Ht, m.Ht, m.n_tok, dz, a, g->w2, nullptr, acc ? g->w2 : nullptr, gws, wk.gemm_bytes, s))) return rc;
+    // a = GELU(h), h = un W1^T + b1
+    if (fuses) {
+        if ((rc = gemm_any(GEMM_NN_GELU_BWD, m.n_tok, m.Ht, m.Ht, dz, w->w2, dh, nullptr, h, gws, wk.gemm_bytes, s))) return rc;
+    } else {
+        if ((rc = gemm_any(1, m.n_tok, m.Ht, m.Ht, dz, w->w2, da, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
+        if (beside) {
+            float *const at_b1 = partial + (size_t)half * m.Ht;
+            sums.add(at_b1, launch_gelu_bwd_cols(da, h, dh, m.n_tok, m.Ht, at_b1, half, s), m.Ht, g->b1, m.Ht);
+        } else {
+            launch_act_bwd(OB_GELU, da, h, dh, m.n_tok, m.Ht, s);
+        }
+    }
+    if ((rc = gemm_any(2, m.Ht, m.W, m.n_tok, dh, un, g->w1, nullptr, acc ? g->w1 : nullptr, gws, wk.gemm_bytes, s))) return rc;
+    if ((rc = gemm_any(1, m.n_tok, m.W, m.Ht, dh, w->w1, dun, nullptr, nullptr, gws, wk.gemm_bytes, s))) return rc;
+    // un = LayerNorm(gather(v)), and the column reductions that are still to do
+    if (!beside && m.n_tok >= 256) {
         const int fits = (int)(room[at_bias] / ((size_t)2 * m.Ht * 4)), n = ncs < fits ? ncs : fits;
         launch_colsum_pair(dz, dh, m.n_tok, m.Ht, n, region[at_bias], s);
         sums.add(region[at_bias], n, m.Ht, g->b2, m.Ht);
         sums.add(region[at_bias] + (size_t)n * m.Ht, n, m.Ht, g->b1, m.Ht);
-    } else {
+    } else if (!beside) {
         launch_colsum(dz, m.n_tok, m.Ht, m.Ht, partial, s);
         launch_reduce_partials(partial, ncs, m.Ht, g->b2, m.Ht, acc, s);
         launch_colsum(dh, m.n_tok, m.Ht, m.Ht, partial, s);

@@ -3,6 +3,7 @@
 // bf16 in / out, fp32 arithmetic, 16-byte loads and stores; one workgroup per token row for the
 // row-wise ones so every byte is read once and written once.
 #include "act.h"
+#include "gemm_plan.h"
 #include "ob_internal.h"
 
 namespace ob {
@@ -558,6 +559,69 @@ __global__ __launch_bounds__(256) void gelu_bwd_kernel(const __bf16 *__restrict_
     }
 }
 
+// Passes over a [T, C] tensor that leave its column sums beside it: a workgroup of eight waves owns 512 columns (a vector of 8 per lane)
+// and walks rows 8 blockIdx.y + wave, + 8 gridDim.y, ...; its waves' sums are added in order.  partial[blockIdx.y][c].  Bound by HBM,
+// like the flat passes, without the sums' own reading of the result: 10752 x 6144, GELU's backward, gather and both sums 146 us, here
+// 116; 12300 x 4096, GELU's backward and its sums 66 and 54.  (Four rows' loads at a time were slower by 2 to 10 %,
+// with the next four asked for ahead by a third.)
+constexpr int COLS_WAVES = 8, COLS_BLOCK = 512;
+template <class Pass>
+__device__ __forceinline__ void cols_pass(const Pass &pass, int T, int C, float *__restrict__ partial) {
+    __shared__ float red[COLS_WAVES][COLS_BLOCK];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = blockIdx.x * COLS_BLOCK + lane * 8, step = COLS_WAVES * gridDim.y;
+    float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (c < C) {
+        for (int row = COLS_WAVES * blockIdx.y + wave; row < T; row += step) {
+            const bf16x8 o = pass(row, C, c);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s[e] += (float)o[e];
+        }
+    }
+    *(f32x4 *)&red[wave][lane * 8] = f32x4{s[0], s[1], s[2], s[3]};
+    *(f32x4 *)&red[wave][lane * 8 + 4] = f32x4{s[4], s[5], s[6], s[7]};
+    __syncthreads();
+    const int col = blockIdx.x * COLS_BLOCK + threadIdx.x;
+    if (col >= C) return;
+    float sum = red[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < COLS_WAVES; ++w) sum += red[w][threadIdx.x];
+    partial[(size_t)blockIdx.y * C + col] = sum;
+}
+
+struct GeluBwdPass {
+    const __bf16 *__restrict__ dact, *__restrict__ up;
+    __bf16 *__restrict__ dup;
+    __device__ __forceinline__ bf16x8 operator()(int row, int C, int c) const {
+        const size_t i = (size_t)row * C + c;
+        const bf16x8 u = *(const bf16x8 *)(up + i), d = *(const bf16x8 *)(dact + i);
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)d[e] * gelu_grad_f((float)u[e]));
+        *(bf16x8 *)(dup + i) = o;
+        return o;
+    }
+};
+__global__ __launch_bounds__(64 * COLS_WAVES) void gelu_bwd_cols_kernel(const __bf16 *__restrict__ dact, const __bf16 *__restrict__ up,
+                                                                        __bf16 *__restrict__ dup, int T, int C, float *__restrict__ partial) {
+    cols_pass(GeluBwdPass{dact, up, dup}, T, C, partial);
+}
+
+struct GatherPass {
+    const __bf16 *__restrict__ big;
+    const int32_t *__restrict__ rows;
+    __bf16 *__restrict__ small;
+    __device__ __forceinline__ bf16x8 operator()(int row, int C, int c) const {
+        const bf16x8 x = *(const bf16x8 *)(big + (size_t)rows[row] * C + c);
+        *(bf16x8 *)(small + (size_t)row * C + c) = x;
+        return x;
+    }
+};
+__global__ __launch_bounds__(64 * COLS_WAVES) void rows_gather_cols_kernel(__bf16 *__restrict__ small, const __bf16 *__restrict__ big,
+                                                                           const int32_t *__restrict__ rows, int T, int C, float *__restrict__ partial) {
+    cols_pass(GatherPass{big, rows, small}, T, C, partial);
+}
+
 // SwiGLU: up row = [gate (F) | up (F)], act = silu(gate) * up.  A thread's first row and column by one 32-bit division
 // (the launch has less than 2^32 threads), the next ones by adding the grid's stride.
 struct RowCol {
@@ -728,6 +792,23 @@ void launch_act_bwd(int mlp, const void *dact, const void *up, void *dup, int T,
     else
         hipLaunchKernelGGL(gelu_bwd_kernel, dim3(act_blocks(n_vec)), dim3(256), 0, s, (const __bf16 *)dact,
                            (const __bf16 *)up, (__bf16 *)dup, n_vec);
+}
+
+int launch_gelu_bwd_cols(const void *dact, const void *up, void *dup, int T, int C, float *partial, int max_partials, hipStream_t s) {
+    ProfScope prof(K_ACT_BWD, s, 6.0 * T * C);
+    const int n = cols_pass_partials(T, C, compute_units(), max_partials);
+    hipLaunchKernelGGL(gelu_bwd_cols_kernel, dim3((C + COLS_BLOCK - 1) / COLS_BLOCK, n), dim3(64 * COLS_WAVES), 0, s, (const __bf16 *)dact,
+                       (const __bf16 *)up, (__bf16 *)dup, T, C, partial);
+    return n;
+}
+
+int launch_rows_gather_cols(void *small, const void *big, const int32_t *rows_dev, int n_rows, int H, float *partial, int max_partials,
+                            hipStream_t s) {
+    ProfScope prof(K_ROWS, s, 4.0 * n_rows * H);
+    const int n = cols_pass_partials(n_rows, H, compute_units(), max_partials);
+    hipLaunchKernelGGL(rows_gather_cols_kernel, dim3((H + COLS_BLOCK - 1) / COLS_BLOCK, n), dim3(64 * COLS_WAVES), 0, s, (__bf16 *)small,
+                       (const __bf16 *)big, rows_dev, n_rows, H, partial);
+    return n;
 }
 
 void launch_mask(const int32_t *cu_dev, int n_seg, int T, int mask, uint8_t *out, hipStream_t s) {

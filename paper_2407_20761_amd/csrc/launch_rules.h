@@ -25,6 +25,14 @@ inline int norm_bwd_partials(int T, int H) { return norm_bwd_folds(T, H) ? 256 :
 // column sums of a [T, C] tensor
 inline int colsum_partials(int T) { return T < 256 ? T : 256; }
 
+// The same beside a pass over the tensor, workgroups of eight waves on eight rows x 512 columns: as many as the chip holds at once (four to a CU),
+// none beyond (10752 x 6144: 1020 of them 72 us, 1032 77; 516 86), at most one per eight rows.
+inline int cols_pass_partials(int T, int C, int cus, int max_partials) {
+    const int blocks = (C + 511) / 512, n = 4 * cus / blocks > 1 ? 4 * cus / blocks : 1;
+    const int most = (T + 7) / 8 < max_partials ? (T + 7) / 8 : max_partials;
+    return n < most ? n : most;
+}
+
 // Hand-over: the widest row of its norm, and the rows of partial sums that the workspace has a region of its own for.
 inline int subsample_max_width() { return 16384; }
 inline int subsample_wgrad_partials(int n_tok) { return n_tok < 64 ? n_tok : 64; }

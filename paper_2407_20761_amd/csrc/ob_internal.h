@@ -89,6 +89,11 @@ void launch_rotary(void *qkv, int ld, int T, int n_heads_rot, int d, const int32
 void launch_act_fwd(int mlp, const void *up, void *act, int T, int F, hipStream_t s);
 void launch_act_bwd(int mlp, const void *dact, const void *up, void *dup, int T, int F,
                     hipStream_t s);
+// the backward of GELU over [T, C], and rows gathered (below), with the column sums of what they write: partial [n][C], n <= max_partials
+// returned; C % 8 == 0
+int launch_gelu_bwd_cols(const void *dact, const void *up, void *dup, int T, int C, float *partial, int max_partials, hipStream_t s);
+int launch_rows_gather_cols(void *small, const void *big, const int32_t *rows_dev, int n_rows, int H, float *partial, int max_partials,
+                            hipStream_t s);
 void launch_mask(const int32_t *cu_dev, int n_seg, int T, int mask, uint8_t *out, hipStream_t s);
 
 // ---- ViT -> LLM hand-over (connector.hip) ------------------------------------------------------

@@ -31,6 +31,8 @@ void launch_colsum(const void *, int, int, int, float *, hipStream_t) { OB_STUB(
 void launch_colsum_pair(const void *, const void *, int, int, int, float *, hipStream_t) { OB_STUB("launch_colsum_pair"); }
 void launch_rotary(void *, int, int, int, int, const int32_t *, int, float, float, hipStream_t) { OB_STUB("launch_rotary"); }
 void launch_act_fwd(int, const void *, void *, int, int, hipStream_t) { OB_STUB("launch_act_fwd"); }
+int launch_gelu_bwd_cols(const void *, const void *, void *, int, int, float *, int, hipStream_t) { OB_STUB("launch_gelu_bwd_cols"); }
+int launch_rows_gather_cols(void *, const void *, const int32_t *, int, int, float *, int, hipStream_t) { OB_STUB("launch_rows_gather_cols"); }
 void launch_act_bwd(int, const void *, const void *, void *, int, int, hipStream_t) { OB_STUB("launch_act_bwd"); }
 void launch_mask(const int32_t *, int, int, int, uint8_t *, hipStream_t) { OB_STUB("launch_mask"); }
 void launch_subsample_norm_fwd(const void *, const void *, const void *, void *, float *, int, int, int, float, hipStream_t) { OB_STUB("launch_subsample_norm_fwd"); }

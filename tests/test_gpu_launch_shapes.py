@@ -379,6 +379,27 @@ def test_activations_in_the_epilogue(mlp, T, hidden, F, tile):
             assert np.abs(got - ref).max() <= TOL * np.abs(ref).max(), n
 
 
+@pytest.mark.parametrize("T,F", [(2051, 4160), (4102, 2112)])
+def test_column_sums_beside_the_passes(T, F):
+    """Where the GEMM in front has large tiles, GELU's backward is a pass of its own that leaves the column sums of its result, and so is the
+    hand-over's gather: columns that do not fill the last workgroup, rows that do not fill the last walk.  Against the oracle."""
+    print(f"column sums beside the passes T={T} F={F}", flush=True)
+    assert all(g.tile_rows > 128 for g in ob.ob_gemm_plan(1, T, F, 256, True))
+    shape = si.small_shape(hidden=256, n_q_heads=4, n_kv_heads=4, head_dim=64, mlp_dim=F, norm=si.NORM_LAYERNORM, mlp=si.MLP_GELU,
+                           mask=si.MASK_BIDIR, has_bias=True, norm_eps=1e-5)
+    cu = si.lengths_to_cu([100] * (T // 100) + [T % 100])
+    w = si.block_weights(shape, seed=2)
+    x, dy = si.activations(T, 256, seed=3, std=1.0)
+    _, _, dx, g = run_block(shape, w, x, dy, cu)
+    _, cache = orc.block_fwd(shape, w, x, cu)
+    dx_ref, g_ref, _ = orc.block_bwd(shape, w, cache, dy, cu)
+    for n, got, ref in [("dx", dx, dx_ref)] + [(n, g[n], g_ref[n]) for n in g]:
+        assert np.abs(got - ref).max() <= TOL * np.abs(ref).max(), n
+    if F == 2112:      # the hand-over over as many tokens, a square GEMM in front
+        assert all(g.tile_rows > 128 for g in ob.ob_gemm_plan(1, T, F, F, True))
+        test_connector_widths(64, F, 2, T)
+
+
 def test_gelu_and_derivative_element_by_element():
     """GELU and its derivative at every bf16 argument of 2^-12 .. 13.1 in size, each against its own value and not the tensor's
     maximum: one rounding to bf16 (8 significant bits: 2^-8 of the value at most) and the functions' own error (1.2e-5 of the value in the tails, 7e-8
