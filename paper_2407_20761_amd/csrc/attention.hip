@@ -80,27 +80,42 @@ __device__ __forceinline__ int swz(int r) {
     return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
 }
 
-// One wave-level load global -> LDS of WORDS dwords per lane, lane i to byte 4 WORDS i from dst (lanes past the descriptor's
-// range deliver zeros).  As an instruction: the compiler counts the builtin among the accesses that a later LDS read may have to wait
-// for, and where stages are parts of one array it waits for the loads just issued in front of the first read of every trip.
-// What has to have landed is said by the s_waitcnt in front of each barrier.  A descriptor that has just been put
-// together goes through fresh() first (five wait states between a vector instruction's scalar result and a memory
-// instruction that reads it).
-__device__ __forceinline__ void fresh(u32x4 &rsrc) {
+// Wave-level loads global -> LDS of N pieces, 16 bytes per lane (4 for the second form), lane i to byte 16 i (4 i) of its piece (lanes past the
+// descriptor's range deliver zeros).  A piece is 1 KB behind the one before, piece SKIP 1 + SKIP.  As instructions: the compiler
+// counts the builtin among the accesses that a later LDS read may have to wait for, and where stages are parts of one array it waits for the loads
+// just issued in front of the first read of every trip.  What has to have landed is said by the s_waitcnt in front of each barrier.
+// The compiler does not look inside either, so a block keeps the distances itself, whatever stands in front of it: five wait states from a vector instruction
+// that wrote a part of the descriptor (a v_readlane that brings a spilled one back) to the first load, one from m0 to each.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"      // (m0 is a reserved register, never preserved across a clobber: that is what is meant)
+#define OB_TO_LDS(WIDTH, P) "s_add_i32 m0, %[at], %[d" P "]\n\ts_nop 0\n\tbuffer_load_" WIDTH " %[v" P "], %[rsrc], 0 offen lds\n\t"
+#define OB_PIECE(P) [d##P] "i"((FIRST + P < SKIP ? FIRST + P : FIRST + P + SKIP) * 1024), [v##P] "v"(voff[FIRST + P])
+template <int N, int SKIP = N, int FIRST = 0>
+__device__ __forceinline__ void load_lds16(u32x4 rsrc, unsigned char OB_LDS *dst, const uint32_t *voff) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_nop 4" : "+s"(rsrc));
-#endif
-}
-template <int WORDS>
-__device__ __forceinline__ void load_lds(u32x4 rsrc, unsigned char OB_LDS *dst, uint32_t voff) {
-#if defined(__HIP_DEVICE_COMPILE__)
+    static_assert(N == 1 || N == 2 || N % 4 == 0, "pieces");
     const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
-    if constexpr (WORDS == 4)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(at), "v"(voff), "s"(rsrc) : "memory");
+    if constexpr (N == 1)
+        asm volatile("s_nop 2\n\t" OB_TO_LDS("dwordx4", "0") : : [at] "s"(at), OB_PIECE(0), [rsrc] "s"(rsrc) : "m0", "scc", "memory");
+    else if constexpr (N == 2)
+        asm volatile("s_nop 2\n\t" OB_TO_LDS("dwordx4", "0") OB_TO_LDS("dwordx4", "1")
+                     : : [at] "s"(at), OB_PIECE(0), OB_PIECE(1), [rsrc] "s"(rsrc) : "m0", "scc", "memory");
     else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" : : "s"(at), "v"(voff), "s"(rsrc) : "memory");
+        asm volatile("s_nop 2\n\t" OB_TO_LDS("dwordx4", "0") OB_TO_LDS("dwordx4", "1") OB_TO_LDS("dwordx4", "2") OB_TO_LDS("dwordx4", "3")
+                     : : [at] "s"(at), OB_PIECE(0), OB_PIECE(1), OB_PIECE(2), OB_PIECE(3), [rsrc] "s"(rsrc) : "m0", "scc", "memory");
+    if constexpr (N > 4) load_lds16<N - 4, SKIP, FIRST + 4>(rsrc, dst, voff);
 #endif
 }
+__device__ __forceinline__ void load_lds4(u32x4 rsrc, unsigned char OB_LDS *dst, uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int FIRST = 0, SKIP = 1;
+    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst), voff[1] = {v};
+    asm volatile("s_nop 2\n\t" OB_TO_LDS("dword", "0") : : [at] "s"(at), OB_PIECE(0), [rsrc] "s"(rsrc) : "m0", "scc", "memory");
+#endif
+}
+#undef OB_PIECE
+#undef OB_TO_LDS
+#pragma clang diagnostic pop
 // descriptor of the `bytes_left` bytes from `base` on (clamped to [0, 2^32 - 1], in scalar instructions: the compiler's
 // own 64-bit compares go through the vector unit)
 __device__ __forceinline__ u32x4 make_rsrc(const void *base, long bytes_left) {
@@ -115,7 +130,6 @@ __device__ __forceinline__ u32x4 make_rsrc(const void *base, long bytes_left) {
         : "scc");
     r[2] = num;
 #endif
-    fresh(r);
     return r;
 }
 
@@ -1008,7 +1022,7 @@ struct DkvWalk {
 // a run (or RUN tiles of it: the offsets inside stay far below 2^32) and a lane's offsets advance, a handful of instructions per
 // tile where making descriptors anew took a hundred, as long as four products, in front of every tile's first one (7B-shaped batch 667 -> 616 us,
 // 16 tiles of the 6B ViT 636 -> 590, 12 of the 300M ViT 148 -> 140).
-template <int D, bool CAUSAL, int KVT, int SR, int LD>
+template <int D, bool CAUSAL, int KVT, int SR, int LD, int SKIP = LD>
 struct DkvRequests {
     static constexpr int RUN = 64;
     const DkvWalk<D, CAUSAL, KVT, SR> &w;
@@ -1046,18 +1060,16 @@ struct DkvRequests {
         part_left -= run_left;
         part_row += run_left * SR;
     }
-    // the next tile: piece p of it to tile + piece[p], if `copies`; its statistics to stat, if `stats`
-    __device__ __forceinline__ void issue(unsigned char OB_LDS *tile, const int (&piece)[LD], bool copies, unsigned char OB_LDS *stat, bool stats, int lane) {
+    // the next tile: the wave's pieces of it to `pieces`, if `copies`; its statistics to stat, if `stats`
+    __device__ __forceinline__ void issue(unsigned char OB_LDS *pieces, bool copies, unsigned char OB_LDS *stat, bool stats, int lane) {
         if (n_issued >= w.n_all) return;
         if (run_left == 0) next_run(lane);
         if (copies) {
+            load_lds16<LD, SKIP>(rsrc, pieces, voff);
 #pragma unroll
-            for (int p = 0; p < LD; ++p) {
-                load_lds<4>(rsrc, tile + piece[p], voff[p]);
-                voff[p] += (uint32_t)(SR * ld2);
-            }
+            for (int p = 0; p < LD; ++p) voff[p] += (uint32_t)(SR * ld2);
         }
-        if (stats) load_lds<1>(stat_rsrc, stat, stat_voff);
+        if (stats) load_lds4(stat_rsrc, stat, stat_voff);
         stat_voff += SR * 4;
         --run_left;
         ++n_issued;
@@ -1124,15 +1136,12 @@ __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 
     constexpr int TLD = Tile<D, SR>::LD, LDW = NP == 2 ? 2 * TLD : TLD;
     const long ld2 = (RG ? (long)ldo : (long)ldq) * 2;
     uint32_t first[LDW];
-    int piece[LDW];
 #pragma unroll
-    for (int p = 0; p < LDW; ++p) {
-        first[p] = tl.voff[p % TLD] + (p < TLD ? 0u : (uint32_t)(SR / 2 * ld2));
-        piece[p] = OWN_AT + ((p < TLD ? pair : pair + 2) * TLD + p % TLD) * 1024;
-    }
-    DkvRequests<D, CAUSAL, KVT, SR, LDW> req(w, RG ? d_o : q, ld2, RG ? delta : lse2_all, T, kvh * group, group, first);
+    for (int p = 0; p < LDW; ++p) first[p] = tl.voff[p % TLD] + (p < TLD ? 0u : (uint32_t)(SR / 2 * ld2));
+    unsigned char OB_LDS *const pieces = tiles + OWN_AT + pair * TLD * 1024;
+    DkvRequests<D, CAUSAL, KVT, SR, LDW, TLD> req(w, RG ? d_o : q, ld2, RG ? delta : lse2_all, T, kvh * group, group, first);
     auto request = [&](int stage) __attribute__((always_inline)) {
-        req.issue(tiles + stage * BYTES, piece, pair < 4, stat + stage * 256, pair == 0, lane);
+        req.issue(pieces + stage * BYTES, pair < 4, stat + stage * 256, pair == 0, lane);
     };
     request(0);
     bf16x8 kvf[KT];     // held rows: K (role P) or V (role G)
@@ -1297,15 +1306,13 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkv_blocks_kernel(
 
     Tile<D, SR> tl;
     tl.init(role_g ? ldo : ldq, w4, lane);
-    int tro[2][2], rr[KT], piece[LD];
+    int tro[2][2], rr[KT];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int s = 0; s < 2; ++s) tro[s][i] = Tile<D, SR>::tr_offset(lane, s, a + 2 * i);
 #pragma unroll
     for (int t = 0; t < KT; ++t) rr[t] = tl.rr[t] + a * 32 * Tile<D, SR>::RB;
-#pragma unroll
-    for (int p = 0; p < LD; ++p) piece[p] = (w4 * LD + p) * 1024;
     f32x16 acc_out[2];     // columns 32 (a + 2 i) .. of dV^T (role P) or dK^T (role G)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -1328,7 +1335,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkv_blocks_kernel(
     auto next = [](int stage, int stages) __attribute__((always_inline)) { return stage + 1 == stages ? 0 : stage + 1; };
     int st_issue = 0, st_stat_issue = 0;                                       // stages of the tile to request next
     auto request = [&]() __attribute__((always_inline)) {
-        req.issue(own + st_issue * B::BYTES, piece, true, stat + st_stat_issue * 256, true, lane);
+        req.issue(own + st_issue * B::BYTES + w4 * LD * 1024, true, stat + st_stat_issue * 256, true, lane);
         st_issue = next(st_issue, OWN_STAGES);
         st_stat_issue = next(st_stat_issue, STAT_STAGES);
     };
