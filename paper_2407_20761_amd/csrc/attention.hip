@@ -1019,12 +1019,11 @@ struct DkvWalk {
 
 // One wave's requests for them: LD pieces of each tile (1 KB apiece) and, global -> LDS as well, the tile's row statistics.  The order of
 // work is runs of consecutive tiles: per head the diagonal and the ragged end, then per head what lies between.  A descriptor serves
-// a run (or RUN tiles of it: the offsets inside stay far below 2^32) and a lane's offsets advance, a handful of instructions per
+// a run (or dkv_run() tiles of it, so that the offsets inside stay below 2^32) and a lane's offsets advance, a handful of instructions per
 // tile where making descriptors anew took a hundred, as long as four products, in front of every tile's first one (7B-shaped batch 667 -> 616 us,
 // 16 tiles of the 6B ViT 636 -> 590, 12 of the 300M ViT 148 -> 140).
 template <int D, bool CAUSAL, int KVT, int SR, int LD, int SKIP = LD>
 struct DkvRequests {
-    static constexpr int RUN = 64;
     const DkvWalk<D, CAUSAL, KVT, SR> &w;
     const unsigned char *base;
     const float *stat_base;
@@ -1050,7 +1049,7 @@ struct DkvRequests {
             next_part = same ? 1 : part == 2 || last ? 2 : c0 > 0 ? 0 : 1;
             next_head = same ? next_head : last ? 0 : next_head + 1;
         }
-        run_left = min(part_left, RUN);
+        run_left = min(part_left, dkv_run((uint32_t)ld2, SR));
         const long off = (long)part_row * ld2 + (long)part_head * D * 2;
         rsrc = make_rsrc(base + off, (long)T * ld2 - off);
         stat_rsrc = make_rsrc(stat_base + (size_t)part_head * T + part_row, (long)(T - part_row) * 4);

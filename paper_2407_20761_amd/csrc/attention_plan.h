@@ -37,6 +37,11 @@ constexpr int dkv_np(int d, int shape) { return d == 64 && shape == 2 ? 6 : d ==
 constexpr int dkv_sr(int d, int shape) { return d == 64 && shape == 1 ? 32 : 64; }
 constexpr int dkv_threads(int d, int shape) { return d == 128 && shape == 1 ? 512 : 128 * dkv_np(d, shape); }
 
+// Consecutive query tiles that one descriptor of a dK / dV wave serves: a lane's offset advances by sr rows of ld2 bytes per tile and
+// has 32 bits, in which `run` whole tiles of rows have to fit; a stride that they do not fit at gets a descriptor per tile.
+constexpr int DKV_RUN = 64;
+__host__ __device__ constexpr int dkv_run(uint32_t ld2, int sr) { return ld2 <= UINT32_MAX / (uint32_t)(DKV_RUN * sr) ? DKV_RUN : 1; }
+
 // the order of a launch; returns its places (workgroups per head): as many as tiles, or whole units of them
 int make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side, TileOrder &ord);
 int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal);

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/omnibal.h"
+#include "../../paper_2407_20761_amd/csrc/attention_plan.h"
 
 static int failures = 0;
 #define CHECK(cond)                                                            \
@@ -195,6 +196,21 @@ static void validation_cases() {
     CHECK(ob_prof_num_classes() > 0 && ob_prof_class_name(0)[0] != 0 && ob_prof_class_name(-1)[0] == 0);
 }
 
+// A run of dK / dV's query tiles behind one descriptor: the byte that a lane asks for, its 32-bit offset advanced from tile to
+// tile as the kernels do, is the byte at the tile's row, for every row stride that a tile itself fits in.
+static void dkv_run_cases() {
+    for (int sr : {32, 64})
+        for (uint64_t ld : {64ull, 4096ull, 43008ull, 524280ull, 524288ull, 524296ull, 524416ull, 524424ull, 1048568ull, 1048576ull, 1048584ull,
+                            1050000ull, 4194304ull, 33554424ull}) {
+            const uint64_t ld2 = 2 * ld;
+            const int run = ob::dkv_run((uint32_t)ld2, sr);
+            CHECK(run >= 1 && run <= ob::DKV_RUN);
+            CHECK(run == ob::DKV_RUN || ld2 * (ob::DKV_RUN * sr) > UINT32_MAX);      // (whole runs wherever they fit)
+            uint32_t voff = (uint32_t)((sr - 1) * ld2);                              // the tile's last row
+            for (int tile = 0; tile < run; ++tile, voff += (uint32_t)(sr * ld2)) CHECK(voff == ((uint64_t)tile * sr + sr - 1) * ld2);
+        }
+}
+
 // the buffer sizes of a few blocks and hand-overs, one line each, for comparison with the shipped library's
 static void print_sizes() {
     const int shapes[4][5] = {{256, 4, 4, 64, 1024}, {1024, 16, 16, 64, 4096}, {4096, 32, 8, 128, 14336}, {6144, 48, 8, 128, 16384}};
@@ -215,6 +231,7 @@ int main() {
     packer_cases();
     planner_cases();
     validation_cases();
+    dkv_run_cases();
     if (failures) { std::fprintf(stderr, "%d checks failed\n", failures); return 1; }
     std::puts("host sanitizer driver: all checks passed");
     return 0;

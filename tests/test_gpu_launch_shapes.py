@@ -123,6 +123,35 @@ def test_dkv_walks(d, nq, nkv, lens, mask):
                 assert (got.float() - want).abs().max() <= TOL * want.abs().max(), (name, a, h)
 
 
+@pytest.mark.parametrize("d,nq,nkv,T,ld,mask,rows", [(64, 2, 1, 4160, 530000, orc.MASK_CAUSAL, (64, 64)), (64, 24, 24, 2176, 1060000, orc.MASK_BIDIR, (64, 32)),
+                                                     (64, 8, 8, 4160, 530000, orc.MASK_BIDIR, (192, 64)), (128, 8, 8, 4160, 530000, orc.MASK_BIDIR, (128, 64)),
+                                                     (128, 2, 1, 4160, 530000, orc.MASK_CAUSAL, (64, 64))])
+def test_attention_in_rows_far_apart(d, nq, nkv, T, ld, mask, rows):
+    """Heads in columns of a wide buffer, rows so far apart that the 64 query tiles that a descriptor of dK / dV serves elsewhere span
+    more than 2^32 bytes: the bits of the same heads side by side."""
+    print(f"rows far apart d={d} nq={nq} nkv={nkv} T={T} ld={ld} mask={mask}", flush=True)
+    plan, _ = ob.ob_varlen_attn_bwd_plan(ob.Segments(si.lengths_to_cu([T])), nq, nkv, d, mask)
+    assert (plan.key_rows, plan.query_rows) == rows and 64 * rows[1] * ld * 2 > 2 ** 32
+    gen = torch.Generator(device="cuda").manual_seed(d + nq)
+    qkv = torch.randn((T, (nq + 2 * nkv) * d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    d_o = torch.randn((T, nq * d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    want = _attention(qkv, d_o, [T], nq, nkv, d, mask)
+    buf, at, views = torch.empty((T, ld), device="cuda", dtype=torch.bfloat16), 8, []
+    for n in (nq, nkv, nkv, nq, nq, nq, nkv, nkv):          # q k v d_o o dq dk dv, from the row's second vector on
+        views.append(buf[:, at:at + n * d])
+        at += n * d
+    q, k, v, go, o, dq, dk, dv = views
+    for to, x in zip((q, k, v), qkv.split([nq * d, nkv * d, nkv * d], 1)):
+        to.copy_(x)
+    go.copy_(d_o)
+    seg, lse = ob.Segments(si.lengths_to_cu([T])), torch.empty((nq, T), dtype=torch.float32, device="cuda")
+    ob.ob_varlen_attn_fwd(q, k, v, o, lse, ld, ld, ld, seg, nq, nkv, d, d ** -0.5, mask)
+    ws = bytes_buf(ob.ob_varlen_attn_bwd_workspace_bytes(T, nq, nkv, d))
+    ob.ob_varlen_attn_bwd(go, q, k, v, o, lse, dq, dk, dv, ld, ld, ld, seg, nq, nkv, d, d ** -0.5, mask, ws)
+    for name, got, ref in zip(("o", "dq", "dk", "dv"), (o, dq, dk, dv), want):
+        assert torch.equal(got.contiguous().view(torch.int16), ref.contiguous().view(torch.int16)), name
+
+
 def _normal_gemm(layout, M, N, K, seed):
     """operands of N(0, 1) as the library takes them, bias, residual, and A, B as [M, K], [N, K] views"""
     gen = torch.Generator(device="cuda").manual_seed(seed)
