@@ -315,9 +315,10 @@ static int validate_block(const ob_block_desc *desc, const ob_block_weights *w, 
 }
 
 // forward of one bf16 block into `saved`; y == nullptr: everything but the last GEMM (the replay
-// of the re-computation path, which has no use for the block output)
-static void block_fwd_bf16(const ob_block_desc *desc, const ob_block_weights *w, const void *x, void *y,
-                           void *saved, const ob_segments *seg, hipStream_t s) {
+// of the re-computation path, which has no use for the block output).  A GEMM with an activation checks its launch, which clears the device's
+// last error: its status is this one's; the other launches are left to the caller's check.
+static int block_fwd_bf16(const ob_block_desc *desc, const ob_block_weights *w, const void *x, void *y,
+                          void *saved, const ob_segments *seg, hipStream_t s) {
     const Dims m = dims_of(desc, seg->total_tokens);
     const Saved sv = saved_layout(m);
     const bool bias = desc->has_bias != 0;
@@ -336,13 +337,14 @@ static void block_fwd_bf16(const ob_block_desc *desc, const ob_block_weights *w,
                     m.Dqkv, m.HD, seg, m.nq, m.nkv, m.d, scale, desc->mask, s);
     launch_gemm_nt(m.T, m.H, m.HD, o, m.HD, w->w_o, m.HD, x1, m.H, bias ? w->b_o : nullptr, x, m.H, s, 0, gws);
     launch_norm_fwd(desc->norm, x1, w->n2_g, beta ? w->n2_b : nullptr, h2, (float *)at(saved, sv.stat2), m.T, m.H, desc->norm_eps, s);
-    if (desc->mlp == OB_GELU && gemm_act_fuses(GEMM_NT_GELU, m.T, m.F, m.H, gws != nullptr))
-        (void)gemm_any(GEMM_NT_GELU, m.T, m.F, m.H, h2, w->w_up, up, bias ? w->b_up : nullptr, act, gws, sv.gemm_bytes, s);
-    else {
+    if (desc->mlp == OB_GELU && gemm_act_fuses(GEMM_NT_GELU, m.T, m.F, m.H, gws != nullptr)) {
+        if (int rc = gemm_any(GEMM_NT_GELU, m.T, m.F, m.H, h2, w->w_up, up, bias ? w->b_up : nullptr, act, gws, sv.gemm_bytes, s)) return rc;
+    } else {
         launch_gemm_nt(m.T, m.upF, m.H, h2, m.H, w->w_up, m.H, up, m.upF, bias ? w->b_up : nullptr, nullptr, 0, s, 0, gws);
         launch_act_fwd(desc->mlp, up, act, m.T, m.F, s);
     }
     if (y) launch_gemm_nt(m.T, m.H, m.F, act, m.F, w->w_down, m.F, y, m.H, bias ? w->b_down : nullptr, x1, m.H, s, 0, gws);
+    return OB_OK;
 }
 
 extern "C" int ob_block_fwd(const ob_block_desc *desc, const ob_block_weights *w, const void *x, void *y,
@@ -352,7 +354,7 @@ extern "C" int ob_block_fwd(const ob_block_desc *desc, const ob_block_weights *w
     if (int rc = validate_block(desc, w, seg, saved, saved_bytes, ws, ws_bytes, "ob_block_fwd")) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
     if (desc->dtype == OB_FP32) f32::block_fwd(desc, w, x, y, saved, seg, s);
-    else block_fwd_bf16(desc, w, x, y, saved, seg, s);
+    else if (int rc = block_fwd_bf16(desc, w, x, y, saved, seg, s)) return rc;
     return check_launch("ob_block_fwd");
 }
 
@@ -378,7 +380,8 @@ extern "C" int ob_block_bwd(const ob_block_desc *desc, const ob_block_weights *w
         f32::block_bwd(desc, w, g, accumulate_wgrad ? 1 : 0, x, dy, dx, saved, seg, ws, s);
         return check_launch("ob_block_bwd");
     }
-    if (flags & OB_BWD_RECOMPUTE) block_fwd_bf16(desc, w, x, nullptr, saved, seg, s);
+    if (flags & OB_BWD_RECOMPUTE)
+        if (int rc = block_fwd_bf16(desc, w, x, nullptr, saved, seg, s)) return rc;
     const Dims m = dims_of(desc, seg->total_tokens);
     const Saved sv = saved_layout(m);
     const Work wk = work_layout(m);

@@ -10,6 +10,9 @@
 #include "../../include/omnibal.h"
 #include "../../paper_2407_20761_amd/csrc/attention_plan.h"
 
+extern bool launches_pass;      // the stand-in launchers' (stubs.cpp)
+extern int act_gemm_status, act_gemm_calls;
+
 static int failures = 0;
 #define CHECK(cond)                                                            \
     do {                                                                       \
@@ -196,6 +199,40 @@ static void validation_cases() {
     CHECK(ob_prof_num_classes() > 0 && ob_prof_class_name(0)[0] != 0 && ob_prof_class_name(-1)[0] == 0);
 }
 
+// A failed launch in front of or in a GEMM with an activation in its epilogue: that GEMM's answer, which clears the device's
+// last error, is the call's answer.
+static void failed_launch_cases() {
+    int32_t cu[2] = {0, 65};
+    ob_segments seg{cu, cu, 1, 65, 65};
+    void *p = cu;
+    ob_block_weights w;
+    for (size_t i = 0; i < sizeof(w) / sizeof(void *); ++i) ((void **)&w)[i] = p;
+    ob_block_grads g;
+    for (size_t i = 0; i < sizeof(g) / sizeof(void *); ++i) ((void **)&g)[i] = p;
+    const ob_connector_desc cd{64, 256, 4, OB_BF16, 1e-5f};
+    ob_connector_weights cw{p, p, p, p, p, p};
+    ob_connector_grads cg{p, p, p, p, p, p};
+    int32_t rows[8];
+    for (int i = 0; i < 8; ++i) rows[i] = i;
+    const size_t csb = ob_connector_saved_bytes(&cd, 2), cwb = ob_connector_workspace_bytes(&cd, 2);
+    launches_pass = true;
+    const int status = act_gemm_status = 77;
+    for (int mlp : {OB_GELU, OB_SWIGLU}) {
+        const ob_block_desc d{256, 4, 4, 64, 512, OB_LAYERNORM, mlp, OB_MASK_SEG_CAUSAL, OB_BF16, 0, 10000.f, 1e-5f, 1};
+        const size_t sb = ob_block_saved_bytes(&d, 65), wb = ob_block_workspace_bytes(&d, 65);
+        if (mlp == OB_GELU) CHECK(ob_block_fwd(&d, &w, p, p, p, sb, &seg, p, wb, nullptr) == status);
+        CHECK(ob_block_bwd(&d, &w, &g, 0, p, p, p, p, sb, &seg, p, wb, nullptr) == status);
+    }
+    CHECK(ob_connector_fwd(&cd, &cw, p, 2, rows, rows, p, 8, p, csb, p, cwb, nullptr) == status);
+    CHECK(ob_connector_bwd(&cd, &cw, &cg, 0, p, p, p, 2, rows, rows, 8, p, csb, p, cwb, nullptr) == status);
+    // of the replay alone: the backward's own launches would go on
+    act_gemm_calls = 0;
+    const ob_block_desc d{256, 4, 4, 64, 512, OB_LAYERNORM, OB_GELU, OB_MASK_SEG_CAUSAL, OB_BF16, 0, 10000.f, 1e-5f, 1};
+    CHECK(ob_block_bwd(&d, &w, &g, OB_BWD_RECOMPUTE, p, p, p, p, ob_block_saved_bytes(&d, 65), &seg, p, ob_block_workspace_bytes(&d, 65), nullptr) == status);
+    CHECK(act_gemm_calls == 1);
+    launches_pass = false;
+}
+
 // A run of dK / dV's query tiles behind one descriptor: the byte that a lane asks for, its 32-bit offset advanced from tile to
 // tile as the kernels do, is the byte at the tile's row, for every row stride that a tile itself fits in.
 static void dkv_run_cases() {
@@ -232,6 +269,7 @@ int main() {
     planner_cases();
     validation_cases();
     dkv_run_cases();
+    failed_launch_cases();
     if (failures) { std::fprintf(stderr, "%d checks failed\n", failures); return 1; }
     std::puts("host sanitizer driver: all checks passed");
     return 0;
