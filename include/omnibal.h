@@ -203,6 +203,9 @@ typedef struct {
 } ob_attn_bwd_launch;
 int ob_varlen_attn_bwd_plan(const ob_segments *seg, int nq, int nkv, int d, int mask, ob_attn_bwd_launch *launch,
                             int32_t *first_rows, int n_first_rows);
+/* Threads of a workgroup of that launch: with 64 key rows of heads of 128, 512 in the kernel of 32 x 32 blocks, 256 in that of
+ * two pairs of waves. */
+int ob_varlen_attn_bwd_threads(const ob_segments *seg, int nq, int nkv, int d, int mask, int *threads);
 
 /* ---- ViT -> LLM hand-over of a mixed stage (App. A; the "token sub-sampling" of Sec. 5.4) ------
  * The paper names the step but fixes neither it nor the connector; what runs here is

@@ -115,6 +115,7 @@ _SIGNATURES = {
     "ob_gemm_group_plan": (_I, [_I, C.POINTER(C.c_int), C.POINTER(C.c_int), _I, _Z, C.POINTER(ob_gemm_launch),
                                 C.POINTER(C.c_int)]),
     "ob_varlen_attn_bwd_plan": (_I, [_SEG, _I, _I, _I, _I, C.POINTER(ob_attn_bwd_launch), _i32p, _I]),
+    "ob_varlen_attn_bwd_threads": (_I, [_SEG, _I, _I, _I, _I, C.POINTER(C.c_int)]),
     "ob_debug_materialize_mask": (_I, [_SEG, _I, _P, _P]),
     "ob_connector_saved_bytes": (_Z, [C.POINTER(ob_connector_desc), _I]),
     "ob_connector_workspace_bytes": (_Z, [C.POINTER(ob_connector_desc), _I]),
@@ -301,6 +302,13 @@ def ob_varlen_attn_bwd_plan(seg, nq, nkv, d, mask):
     rows = np.empty(out.workgroups, dtype=np.int32)
     _check(lib.ob_varlen_attn_bwd_plan(C.byref(seg.c), nq, nkv, d, int(mask), C.byref(out), rows.ctypes.data_as(_i32p), rows.size))
     return out, rows
+
+
+def ob_varlen_attn_bwd_threads(seg, nq, nkv, d, mask) -> int:
+    """threads of a workgroup of the dK / dV launch"""
+    out = C.c_int()
+    _check(lib.ob_varlen_attn_bwd_threads(C.byref(seg.c), nq, nkv, d, int(mask), C.byref(out)))
+    return out.value
 
 
 class RowIndex:

@@ -537,6 +537,13 @@ extern "C" int ob_varlen_attn_bwd_plan(const ob_segments *seg, int nq, int nkv, 
     return OB_OK;
 }
 
+extern "C" int ob_varlen_attn_bwd_threads(const ob_segments *seg, int nq, int nkv, int d, int mask, int *threads) {
+    if (!threads) return fail(OB_EINVAL, "ob_varlen_attn_bwd_threads: null output");
+    if (int rc = validate_attn(seg, nq, nkv, d, nq * d, nkv * d, nq * d, mask, OB_BF16, "ob_varlen_attn_bwd_threads")) return rc;
+    *threads = dkv_threads(d, dkv_shape(seg, nkv, nq / nkv, d, mask == OB_MASK_SEG_CAUSAL));
+    return OB_OK;
+}
+
 extern "C" int ob_debug_materialize_mask(const ob_segments *seg, int mask, uint8_t *mask_dev, void *hip_stream) {
     if (!mask_dev) return fail(OB_EINVAL, "ob_debug_materialize_mask: null output");
     if (mask != OB_MASK_SEG_BIDIR && mask != OB_MASK_SEG_CAUSAL) return fail(OB_EINVAL, "ob_debug_materialize_mask: unknown mask kind");

@@ -1,8 +1,9 @@
-"""Which kernel a GEMM reaches, asked of the library on the host, and the cases of the GPU tests by the kernel they are for.
+"""Which kernel a GEMM or dK / dV reaches, asked of the library on the host, and the cases of the GPU tests by the kernel they are for.
 
 A form is (kind of tile, how its tiles are walked): kinds by size, "deep" the 128 x 128 tile over a ring of eight slots;
 "whole", "split" (every tile's contraction in slices) or "mixed" (whole tiles beside split ones)."""
 import paper_2407_20761_amd as ob
+import synth_inputs as si
 
 _KINDS = {(256, 256, 4): "big", (192, 256, 4): "mid", (128, 128, 4): "small", (128, 128, 8): "deep", (64, 64, 8): "fine"}
 
@@ -60,3 +61,21 @@ ROW_LIST = [(64, 4, 16, "fine whole"), (1536, 4, 16, "fine split"), (704, 18, 37
 
 def named(case_forms):
     return " + ".join(f"{k} {h}" for k, h in case_forms)
+
+
+def dkv_kernel(lens, nq, nkv, d, mask):
+    """the dK / dV kernel of a batch: (key rows of a workgroup, query rows of a streamed tile, threads)"""
+    seg = ob.Segments(si.lengths_to_cu(lens), device=None)
+    seg.c.cu_dev = 0x1000      # never read: the plan is host work
+    plan, _ = ob.ob_varlen_attn_bwd_plan(seg, nq, nkv, d, mask)
+    return plan.key_rows, plan.query_rows, ob.ob_varlen_attn_bwd_threads(seg, nq, nkv, d, mask)
+
+
+# walks of dK / dV: head size, query and key / value heads, segments, and the kernel in which they are walked under each mask
+# (bidirectional, causal)
+SR64, SR32, SIX = (64, 64, 256), (64, 32, 256), (192, 64, 768)
+FOUR, BLOCKS, TWO = (128, 64, 512), (64, 64, 512), (64, 64, 256)
+DKV_WALKS = [(64, 2, 1, [4097], SR64, SR64), (64, 2, 1, [8192 + 65], SR64, SR64), (64, 16, 16, [1025] * 3 + [4161], SR32, SR32),
+             (64, 10, 10, [4161], SIX, SR64), (128, 2, 1, [4097 + 64], BLOCKS, BLOCKS), (128, 2, 1, [8192 + 65], BLOCKS, BLOCKS),
+             (128, 1, 1, [33, 64, 127, 128], TWO, TWO), (128, 3, 1, [65, 129, 193, 321], BLOCKS, BLOCKS), (128, 16, 16, [448], TWO, BLOCKS),
+             (128, 32, 8, [4161, 4224] * 2, FOUR, FOUR)]

@@ -34,16 +34,20 @@ def _attention(qkv, d_o, lens, nq, nkv, d, mask):
 
 
 @pytest.mark.parametrize("mask", [orc.MASK_BIDIR, orc.MASK_CAUSAL])
-@pytest.mark.parametrize("d,nq,nkv", [(64, 16, 16), (64, 16, 8), (64, 10, 10), (128, 8, 8), (128, 16, 8)])
+@pytest.mark.parametrize("d,nq,nkv", [(64, 16, 16), (64, 16, 8), (64, 10, 10), (128, 8, 8), (128, 16, 8), (128, 16, 16)])
 def test_dkv_shapes_give_the_same_bits(d, nq, nkv, mask):
-    """Many short segments fill the chip (the shape for throughput), each alone leaves it idle (the shape for the
+    """Many short segments fill the chip (the shape for throughput), each alone leaves it idle (a shape for the
     shorter trip): lengths on and beside the 32-, 64- and 128-row borders, oracle on two of them.
-    (64, 10, 10): two pairs would need a second round for the bidirectional batch, six do not."""
+    (64, 10, 10): two pairs would need a second round for the bidirectional batch, six do not.  (128, 16, 16): two pairs of heads of
+    128 walk seven tiles, three to a trip."""
     lens = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 191, 193, 257] * 8 + [385]
     if nkv == 10:
         lens = [1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 257, 513, 1025, 385]
-    plan, _ = ob.ob_varlen_attn_bwd_plan(ob.Segments(si.lengths_to_cu(lens)), nq, nkv, d, mask)
-    assert (plan.key_rows, plan.query_rows) == ((128, 64) if d == 128 else (64, 32) if nkv != 10 else (64, 64) if mask else (192, 64))
+    if (d, nkv) == (128, 16):
+        lens = [448, 385, 320, 191, 129, 65] * 3 + [385]
+    want = gemm_launches.FOUR if d == 128 else gemm_launches.SR32 if nkv != 10 else gemm_launches.SR64 if mask else gemm_launches.SIX
+    assert gemm_launches.dkv_kernel(lens, nq, nkv, d, mask) == want
+    seen = set()
     print(f"dkv shapes d={d} nq={nq} nkv={nkv} mask={mask}", flush=True)
     cu = si.lengths_to_cu(lens)
     T = int(cu[-1])
@@ -53,8 +57,7 @@ def test_dkv_shapes_give_the_same_bits(d, nq, nkv, mask):
     packed = _attention(qkv, d_o, lens, nq, nkv, d, mask)
     for j in list(range(min(17, len(lens) - 1))) + [len(lens) - 1]:
         a, b = int(cu[j]), int(cu[j + 1])
-        plan, _ = ob.ob_varlen_attn_bwd_plan(ob.Segments(si.lengths_to_cu([b - a])), nq, nkv, d, mask)
-        assert (plan.key_rows, plan.query_rows) == (64, 64)
+        seen.add(gemm_launches.dkv_kernel([b - a], nq, nkv, d, mask))
         alone = _attention(qkv[a:b].contiguous(), d_o[a:b].contiguous(), [b - a], nq, nkv, d, mask)
         for name, x, y in zip(("o", "dq", "dk", "dv"), packed, alone):
             assert torch.equal(x[a:b].view(torch.int16), y.view(torch.int16)), (name, j, b - a)
@@ -63,6 +66,7 @@ def test_dkv_shapes_give_the_same_bits(d, nq, nkv, mask):
             for name, x, r in zip(("dq", "dk", "dv"), packed[1:], ref):
                 got = to_np(x[a:b]).reshape(r.shape)
                 assert np.abs(got - r).max() <= TOL * np.abs(r).max(), (name, j)
+    assert seen == ({gemm_launches.SR64} if d == 64 else {gemm_launches.BLOCKS, gemm_launches.TWO})
 
 
 @pytest.mark.parametrize("mask", [orc.MASK_BIDIR, orc.MASK_CAUSAL])
@@ -93,13 +97,12 @@ def test_dkv_order_in_units_of_tiles(d, unit, mask):
 
 
 @pytest.mark.parametrize("mask", [orc.MASK_BIDIR, orc.MASK_CAUSAL])
-@pytest.mark.parametrize("d,nq,nkv,lens", [(64, 2, 1, [4097]), (64, 2, 1, [8192 + 65]), (128, 2, 1, [4097 + 64]), (128, 2, 1, [8192 + 65]),
-                                           (128, 1, 1, [33, 64, 127, 128]), (128, 3, 1, [65, 129, 193, 321]),
-                                           (128, 32, 8, [4161, 4224] * 2)])
-def test_dkv_walks(d, nq, nkv, lens, mask):
+@pytest.mark.parametrize("d,nq,nkv,lens,bidir,causal", gemm_launches.DKV_WALKS)
+def test_dkv_walks(d, nq, nkv, lens, bidir, causal, mask):
     """Walks of more query tiles than one descriptor of the requests serves (64), of a tile or two, and of odd and even numbers of them:
     dK, dV of the first and the last segment against float32 products on the device (their own error is below 1e-5)."""
     print(f"dkv walks d={d} nq={nq} nkv={nkv} mask={mask} {lens}", flush=True)
+    assert gemm_launches.dkv_kernel(lens, nq, nkv, d, mask) == (causal if mask == orc.MASK_CAUSAL else bidir)
     gen = torch.Generator(device="cuda").manual_seed(d + nq + len(lens))
     cu = si.lengths_to_cu(lens)
     T, group = int(cu[-1]), nq // nkv
@@ -123,15 +126,14 @@ def test_dkv_walks(d, nq, nkv, lens, mask):
                 assert (got.float() - want).abs().max() <= TOL * want.abs().max(), (name, a, h)
 
 
-@pytest.mark.parametrize("d,nq,nkv,T,ld,mask,rows", [(64, 2, 1, 4160, 530000, orc.MASK_CAUSAL, (64, 64)), (64, 24, 24, 2176, 1060000, orc.MASK_BIDIR, (64, 32)),
-                                                     (64, 8, 8, 4160, 530000, orc.MASK_BIDIR, (192, 64)), (128, 8, 8, 4160, 530000, orc.MASK_BIDIR, (128, 64)),
-                                                     (128, 2, 1, 4160, 530000, orc.MASK_CAUSAL, (64, 64))])
-def test_attention_in_rows_far_apart(d, nq, nkv, T, ld, mask, rows):
+@pytest.mark.parametrize("d,nq,nkv,T,ld,mask,kernel", [(64, 2, 1, 4160, 530000, orc.MASK_CAUSAL, gemm_launches.SR64), (64, 24, 24, 2176, 1060000, orc.MASK_BIDIR, gemm_launches.SR32),
+                                                       (64, 8, 8, 4160, 530000, orc.MASK_BIDIR, gemm_launches.SIX), (128, 8, 8, 4160, 530000, orc.MASK_BIDIR, gemm_launches.FOUR),
+                                                       (128, 2, 1, 4160, 530000, orc.MASK_CAUSAL, gemm_launches.BLOCKS)])
+def test_attention_in_rows_far_apart(d, nq, nkv, T, ld, mask, kernel):
     """Heads in columns of a wide buffer, rows so far apart that the 64 query tiles that a descriptor of dK / dV serves elsewhere span
     more than 2^32 bytes: the bits of the same heads side by side."""
     print(f"rows far apart d={d} nq={nq} nkv={nkv} T={T} ld={ld} mask={mask}", flush=True)
-    plan, _ = ob.ob_varlen_attn_bwd_plan(ob.Segments(si.lengths_to_cu([T])), nq, nkv, d, mask)
-    assert (plan.key_rows, plan.query_rows) == rows and 64 * rows[1] * ld * 2 > 2 ** 32
+    assert gemm_launches.dkv_kernel([T], nq, nkv, d, mask) == kernel and 64 * kernel[1] * ld * 2 > 2 ** 32
     gen = torch.Generator(device="cuda").manual_seed(d + nq)
     qkv = torch.randn((T, (nq + 2 * nkv) * d), generator=gen, device="cuda", dtype=torch.bfloat16)
     d_o = torch.randn((T, nq * d), generator=gen, device="cuda", dtype=torch.bfloat16)

@@ -78,6 +78,21 @@ def test_every_gemm_form_has_a_gpu_case():
         assert not missing, (layout, M, N, K, missing)
 
 
+def test_every_dkv_kernel_has_a_gpu_case():
+    """Whichever kernel a batch of any layout takes, the walks of the GPU tests are walked in it, under the same mask."""
+    covered = set()
+    for d, nq, nkv, lens, *want in gemm_launches.DKV_WALKS:
+        for mask, kernel in zip((orc.MASK_BIDIR, orc.MASK_CAUSAL), want):
+            assert gemm_launches.dkv_kernel(lens, nq, nkv, d, mask) == kernel, (d, nq, nkv, lens, mask)
+            covered.add((d, mask, kernel))
+    rng = np.random.default_rng(6)
+    for i in range(4000):
+        d, mask, nkv = (64, 128)[i & 1], (orc.MASK_BIDIR, orc.MASK_CAUSAL)[i >> 1 & 1], int(rng.integers(1, 49))
+        total = int(2 ** rng.uniform(0, 14))
+        lens = [total] if i % 3 == 0 else [1025] * (1 + total // 1025) if i % 3 == 1 else _lengths(total, 300, 4096, i)
+        assert (d, mask, gemm_launches.dkv_kernel(lens, nkv * int(rng.integers(1, 7)), nkv, d, mask)) in covered, (d, mask, nkv, lens)
+
+
 # bidirectional, heads of 64: six pairs where two need a second round of two workgroups to a CU and they do not (256 CUs)
 @pytest.mark.parametrize("nkv,lens,six", [(10, [1025] * 3, False), (8, [1025] * 4, True), (8, [4097], True), (8, [1025] * 6, False), (16, [2000], False),
                                           (4, [1025] * 7, False), (4, [1025] * 8, True)])
