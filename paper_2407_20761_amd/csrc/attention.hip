@@ -1021,20 +1021,21 @@ struct DkvWalk {
 // work is runs of consecutive tiles: per head the diagonal and the ragged end, then per head what lies between.  A descriptor serves
 // a run (or dkv_run() tiles of it, so that the offsets inside stay below 2^32) and a lane's offsets advance, a handful of instructions per
 // tile where making descriptors anew took a hundred, as long as four products, in front of every tile's first one (7B-shaped batch 667 -> 616 us,
-// 16 tiles of the 6B ViT 636 -> 590, 12 of the 300M ViT 148 -> 140).
-template <int D, bool CAUSAL, int KVT, int SR, int LD, int SKIP = LD>
+// 16 tiles of the 6B ViT 636 -> 590, 12 of the 300M ViT 148 -> 140).  APART: for rows of which not even one tile fits, each piece has a descriptor
+// of its own and the lanes' offsets count from the piece's first row.
+template <int D, bool CAUSAL, int KVT, int SR, int LD, int SKIP = LD, bool APART = false>
 struct DkvRequests {
     const DkvWalk<D, CAUSAL, KVT, SR> &w;
     const unsigned char *base;
     const float *stat_base;
     long ld2;                     // bytes from row to row
-    int T, head0, group;
+    int T, head0, group, piece0;  // the wave's first piece
     uint32_t (&first)[LD], voff[LD], stat_voff;
     int n_issued, run_left, part_left, part_row, part_head, next_part, next_head;
     u32x4 rsrc, stat_rsrc;
     __device__ __forceinline__ DkvRequests(const DkvWalk<D, CAUSAL, KVT, SR> &walk, const void *base_, long ld2_, const float *stat_, int T_,
-                                           int head0_, int group_, uint32_t (&first_)[LD])
-        : w(walk), base((const unsigned char *)base_), stat_base(stat_), ld2(ld2_), T(T_), head0(head0_), group(group_), first(first_),
+                                           int head0_, int group_, int piece0_, uint32_t (&first_)[LD])
+        : w(walk), base((const unsigned char *)base_), stat_base(stat_), ld2(ld2_), T(T_), head0(head0_), group(group_), piece0(piece0_), first(first_),
           stat_voff(0), n_issued(0), run_left(0), part_left(0), part_row(0), part_head(0),
           next_part(walk.n_masked == 0 ? 2 : walk.n_diag > 0 ? 0 : 1), next_head(0),
           rsrc{0, 0, 0, 0}, stat_rsrc{0, 0, 0, 0} {}
@@ -1049,7 +1050,7 @@ struct DkvRequests {
             next_part = same ? 1 : part == 2 || last ? 2 : c0 > 0 ? 0 : 1;
             next_head = same ? next_head : last ? 0 : next_head + 1;
         }
-        run_left = min(part_left, dkv_run((uint32_t)ld2, SR));
+        run_left = APART ? 1 : min(part_left, dkv_run((uint32_t)ld2, SR));
         const long off = (long)part_row * ld2 + (long)part_head * D * 2;
         rsrc = make_rsrc(base + off, (long)T * ld2 - off);
         stat_rsrc = make_rsrc(stat_base + (size_t)part_head * T + part_row, (long)(T - part_row) * 4);
@@ -1059,11 +1060,22 @@ struct DkvRequests {
         part_left -= run_left;
         part_row += run_left * SR;
     }
+    // APART: the wave's pieces of the tile that next_run() has come to
+    template <int P = 0>
+    __device__ __forceinline__ void issue_apart(unsigned char OB_LDS *pieces) {
+        const int in_tile = (piece0 + (P < SKIP ? P : P + SKIP)) * Tile<D, SR>::RPI;      // the piece's first row
+        const long off = (long)(part_row - SR + in_tile) * ld2 + (long)part_head * D * 2;
+        voff[P] = dkv_piece_offset(first[P], in_tile, (uint32_t)ld2);
+        load_lds16<1, SKIP, P>(make_rsrc(base + off, (long)T * ld2 - off), pieces, voff);
+        if constexpr (P + 1 < LD) issue_apart<P + 1>(pieces);
+    }
     // the next tile: the wave's pieces of it to `pieces`, if `copies`; its statistics to stat, if `stats`
     __device__ __forceinline__ void issue(unsigned char OB_LDS *pieces, bool copies, unsigned char OB_LDS *stat, bool stats, int lane) {
         if (n_issued >= w.n_all) return;
         if (run_left == 0) next_run(lane);
-        if (copies) {
+        if constexpr (APART) {
+            if (copies) issue_apart(pieces);
+        } else if (copies) {
             load_lds16<LD, SKIP>(rsrc, pieces, voff);
 #pragma unroll
             for (int p = 0; p < LD; ++p) voff[p] += (uint32_t)(SR * ld2);
@@ -1075,7 +1087,7 @@ struct DkvRequests {
     }
 };
 
-template <int D, bool CAUSAL, int NP, int SR>
+template <int D, bool CAUSAL, int NP, int SR, bool APART = false>
 __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 2) void attn_bwd_dkv_kernel(
     const __bf16 *__restrict__ d_o, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
     const __bf16 *__restrict__ v, const float *__restrict__ lse2_all, const float *__restrict__ delta,
@@ -1138,7 +1150,7 @@ __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 
 #pragma unroll
     for (int p = 0; p < LDW; ++p) first[p] = tl.voff[p % TLD] + (p < TLD ? 0u : (uint32_t)(SR / 2 * ld2));
     unsigned char OB_LDS *const pieces = tiles + OWN_AT + pair * TLD * 1024;
-    DkvRequests<D, CAUSAL, KVT, SR, LDW, TLD> req(w, RG ? d_o : q, ld2, RG ? delta : lse2_all, T, kvh * group, group, first);
+    DkvRequests<D, CAUSAL, KVT, SR, LDW, TLD, APART> req(w, RG ? d_o : q, ld2, RG ? delta : lse2_all, T, kvh * group, group, pair * TLD, first);
     auto request = [&](int stage) __attribute__((always_inline)) {
         req.issue(pieces + stage * BYTES, pair < 4, stat + stage * 256, pair == 0, lane);
     };
@@ -1233,7 +1245,7 @@ __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 
     // The mask-free tiles: three to a trip, constant stage addresses, a single straight path, from a tile on stage 0 on; where the
     // products of dV lag behind, the tile in front of them leaves its own to the first of them.
     const int lead = !FUSE && live_prev && n % 3 == 0 ? n : n + 3 - n % 3;      // the first tile of the first three (never the very first)
-    const bool threes = lead + 3 <= w.n_all;
+    const bool threes = !APART && lead + 3 <= w.n_all;      // (APART: rare, in the small form)
     while (threes && n < lead) slow(std::false_type{}, FUSE && n + 1 == lead);
     while (threes && n + 3 <= w.n_all) {
         trip(std::false_type{}, std::false_type{}, 0, 2, 1, FUSE);
@@ -1330,7 +1342,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkv_blocks_kernel(
     unsigned char OB_LDS *const ds_blk = lds + B::DS_AT + (b * 2 + a) * B::BLK + lane * 16;
     unsigned char OB_LDS *const out_blk = lds + (RG ? B::DS_AT : B::P_AT) + b * 2 * B::BLK + lane * 16;   // the four steps of a result
     DkvRequests<D, CAUSAL, B::KVT, SR, LD> req(w, RG ? d_o : q, (RG ? (long)ldo : (long)ldq) * 2, RG ? delta : lse2_all, T, kvh * group, group,
-                                              tl.voff);
+                                              w4 * LD, tl.voff);
     auto next = [](int stage, int stages) __attribute__((always_inline)) { return stage + 1 == stages ? 0 : stage + 1; };
     int st_issue = 0, st_stat_issue = 0;                                       // stages of the tile to request next
     auto request = [&]() __attribute__((always_inline)) {
@@ -1488,9 +1500,10 @@ double attn_flops(const ob_segments *seg, int nq, int d, bool causal) {
                                                       const __bf16 *, const __bf16 *, const float *, float *, \
                                                       float *, __bf16 *, int, int, int, const int32_t *, int, \
                                                       int, int, float, float, int, TileOrder);                \
-    OB_DKV_INSTANCE(D, C, dkv_np(D, 0), dkv_sr(D, 0))
-#define OB_DKV_INSTANCE(D, C, NP, SR)                                                                             \
-    template __global__ void attn_bwd_dkv_kernel<D, C, NP, SR>(const __bf16 *, const __bf16 *, const __bf16 *,    \
+    OB_DKV_INSTANCE(D, C, dkv_np(D, 0), dkv_sr(D, 0))                                                         \
+    OB_DKV_INSTANCE(D, C, dkv_np(D, 0), dkv_sr(D, 0), true)
+#define OB_DKV_INSTANCE(D, C, ...)                                                                                \
+    template __global__ void attn_bwd_dkv_kernel<D, C, __VA_ARGS__>(const __bf16 *, const __bf16 *, const __bf16 *,    \
                                                            const __bf16 *, const float *, const float *,      \
                                                            __bf16 *, __bf16 *, int, int, int,                 \
                                                            const int32_t *, int, int, int, float, float, int, \
@@ -1522,6 +1535,7 @@ template <bool CAUSAL> constexpr auto attn_bwd_dkv<128, CAUSAL, 1> = attn_bwd_dk
 template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_0 = attn_bwd_dkv<D, CAUSAL, 0>;
 template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_1 = attn_bwd_dkv<D, CAUSAL, 1>;
 template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_2 = attn_bwd_dkv<D, CAUSAL && D == 128, 2>;      // (heads of 64: bidirectional only)
+template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_apart = attn_bwd_dkv_kernel<D, CAUSAL, dkv_np(D, 0), dkv_sr(D, 0), true>;
 
 }  // namespace
 
@@ -1569,13 +1583,17 @@ void launch_attn_bwd(const void *d_o, const void *q, const void *k, const void *
     }
     ProfScope prof(K_ATTN_BWD_DKV, s, 1.5 * attn_flops(seg, nq, d, causal));  // dV, dP, dK
     TileOrder ord;
-    const int shape = dkv_shape(seg, nkv, group, d, causal);
+    const int best = dkv_shape(seg, nkv, group, d, causal);
+    // (in 32 bits: a stride is below 2^31 elements.  All shapes give the same bits)
+    const bool apart = !dkv_tile_fits(2u * (uint32_t)(ldq > ldo ? ldq : ldo), dkv_sr(d, best));
+    const int shape = apart ? 0 : best;
     const int kvt = 32 * dkv_np(d, shape), places = make_order(seg, kvt, causal, true, ord);
     const dim3 grid_kv((unsigned)places * nkv);
 #define OB_DKV_ARGS (const __bf16 *)d_o, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, lse2, delta, (__bf16 *)dk,  \
                     (__bf16 *)dv, ldq, ldkv, ldo, seg->cu_dev, seg->n_seg, T, group, scale, rot, nkv, ord
     const int threads = dkv_threads(d, shape);
-    if (shape == 0) OB_ATTN_DISPATCH(attn_bwd_dkv_0, grid_kv, threads, OB_DKV_ARGS);
+    if (apart) OB_ATTN_DISPATCH(attn_bwd_dkv_apart, grid_kv, threads, OB_DKV_ARGS);
+    else if (shape == 0) OB_ATTN_DISPATCH(attn_bwd_dkv_0, grid_kv, threads, OB_DKV_ARGS);
     else if (shape == 1) OB_ATTN_DISPATCH(attn_bwd_dkv_1, grid_kv, threads, OB_DKV_ARGS);
     else OB_ATTN_DISPATCH(attn_bwd_dkv_2, grid_kv, threads, OB_DKV_ARGS);
 #undef OB_DKV_ARGS

@@ -41,6 +41,10 @@ constexpr int dkv_threads(int d, int shape) { return d == 128 && shape == 1 ? 51
 // has 32 bits, in which `run` whole tiles of rows have to fit; a stride that they do not fit at gets a descriptor per tile.
 constexpr int DKV_RUN = 64;
 __host__ __device__ constexpr int dkv_run(uint32_t ld2, int sr) { return ld2 <= UINT32_MAX / (uint32_t)(DKV_RUN * sr) ? DKV_RUN : 1; }
+// Whether the rows of one tile fit at all (64 rows of 67 MB do not).  Where not, a piece of it, 1 KB (8 rows of a head of 64, 4 of 128), is asked
+// for by itself at the lanes' offsets from its own first row: those of the tile, of which 32 bits are kept, less that row's.
+__host__ __device__ constexpr bool dkv_tile_fits(uint32_t ld2, int sr) { return ld2 <= UINT32_MAX / (uint32_t)sr; }
+__host__ __device__ constexpr uint32_t dkv_piece_offset(uint32_t voff, uint32_t row, uint32_t ld2) { return voff - row * ld2; }
 
 // the order of a launch; returns its places (workgroups per head): as many as tiles, or whole units of them
 int make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side, TileOrder &ord);

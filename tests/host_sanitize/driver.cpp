@@ -246,6 +246,20 @@ static void dkv_run_cases() {
             uint32_t voff = (uint32_t)((sr - 1) * ld2);                              // the tile's last row
             for (int tile = 0; tile < run; ++tile, voff += (uint32_t)(sr * ld2)) CHECK(voff == ((uint64_t)tile * sr + sr - 1) * ld2);
         }
+    // rows of which one tile does not fit: every lane's offset, in the tile where it fits, else from its piece's first row
+    for (int d : {64, 128})
+        for (int sr : {32, 64})
+            for (uint64_t ld : {33554424ull, 33554432ull, 33554440ull, 34100000ull, 67108864ull, 68000000ull, 134217720ull, 260000000ull}) {
+                const uint32_t ld2 = (uint32_t)(2 * ld);
+                const uint64_t rows = 512 / d;      // of a piece
+                for (uint64_t row = 0; row < (uint64_t)sr; ++row)
+                    for (uint64_t col = 0; col < 2ull * d; col += 16) {
+                        const uint32_t voff = ((uint32_t)row * (uint32_t)ld + (uint32_t)col / 2) * 2u;
+                        const uint64_t first = row / rows * rows;
+                        if (ob::dkv_tile_fits(ld2, sr)) CHECK(voff == row * ld2 + col);
+                        else CHECK(ob::dkv_run(ld2, sr) == 1 && ob::dkv_piece_offset(voff, (uint32_t)first, ld2) == (row - first) * ld2 + col);
+                    }
+            }
 }
 
 // the buffer sizes of a few blocks and hand-overs, one line each, for comparison with the shipped library's

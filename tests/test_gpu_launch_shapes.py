@@ -128,28 +128,34 @@ def test_dkv_walks(d, nq, nkv, lens, bidir, causal, mask):
 
 @pytest.mark.parametrize("d,nq,nkv,T,ld,mask,kernel", [(64, 2, 1, 4160, 530000, orc.MASK_CAUSAL, gemm_launches.SR64), (64, 24, 24, 2176, 1060000, orc.MASK_BIDIR, gemm_launches.SR32),
                                                        (64, 8, 8, 4160, 530000, orc.MASK_BIDIR, gemm_launches.SIX), (128, 8, 8, 4160, 530000, orc.MASK_BIDIR, gemm_launches.FOUR),
-                                                       (128, 2, 1, 4160, 530000, orc.MASK_CAUSAL, gemm_launches.BLOCKS)])
+                                                       (128, 2, 1, 4160, 530000, orc.MASK_CAUSAL, gemm_launches.BLOCKS),
+                                                       (64, 2, 1, 385, 34200000, orc.MASK_CAUSAL, gemm_launches.SR64), (64, 320, 320, 130, 68000000, orc.MASK_BIDIR, gemm_launches.SR32),
+                                                       (128, 3, 1, 193, 34200000, orc.MASK_CAUSAL, gemm_launches.BLOCKS), (128, 1, 1, 257, 34200000, orc.MASK_BIDIR, gemm_launches.BLOCKS)])
 def test_attention_in_rows_far_apart(d, nq, nkv, T, ld, mask, kernel):
     """Heads in columns of a wide buffer, rows so far apart that the 64 query tiles that a descriptor of dK / dV serves elsewhere span
-    more than 2^32 bytes: the bits of the same heads side by side."""
+    more than 2^32 bytes, or a single tile of the kernel they would have does (then keys and values, of which 64 rows have to fit, lie side by side; for
+    T = 385 queries alone are apart): the bits of the same heads side by side."""
     print(f"rows far apart d={d} nq={nq} nkv={nkv} T={T} ld={ld} mask={mask}", flush=True)
-    assert gemm_launches.dkv_kernel([T], nq, nkv, d, mask) == kernel and 64 * kernel[1] * ld * 2 > 2 ** 32
+    one_tile = kernel[1] * ld * 2 > 2 ** 32
+    assert gemm_launches.dkv_kernel([T], nq, nkv, d, mask) == kernel and 64 * kernel[1] * ld * 2 > 2 ** 32 and one_tile == (ld > 1060000)
     gen = torch.Generator(device="cuda").manual_seed(d + nq)
     qkv = torch.randn((T, (nq + 2 * nkv) * d), generator=gen, device="cuda", dtype=torch.bfloat16)
     d_o = torch.randn((T, nq * d), generator=gen, device="cuda", dtype=torch.bfloat16)
     want = _attention(qkv, d_o, [T], nq, nkv, d, mask)
     buf, at, views = torch.empty((T, ld), device="cuda", dtype=torch.bfloat16), 8, []
-    for n in (nq, nkv, nkv, nq, nq, nq, nkv, nkv):          # q k v d_o o dq dk dv, from the row's second vector on
-        views.append(buf[:, at:at + n * d])
+    ldkv, ldo = nkv * d if one_tile else ld, nq * d if T == 385 else ld
+    for i, n in enumerate((nq, nkv, nkv, nq, nq, nq, nkv, nkv)):          # q k v d_o o dq dk dv, from the row's second vector on
+        apart = (ldkv if i in (1, 2, 6, 7) else ldo if i in (3, 4) else ld) == ld
+        views.append(buf[:, at:at + n * d] if apart else torch.empty((T, n * d), device="cuda", dtype=torch.bfloat16))
         at += n * d
     q, k, v, go, o, dq, dk, dv = views
     for to, x in zip((q, k, v), qkv.split([nq * d, nkv * d, nkv * d], 1)):
         to.copy_(x)
     go.copy_(d_o)
     seg, lse = ob.Segments(si.lengths_to_cu([T])), torch.empty((nq, T), dtype=torch.float32, device="cuda")
-    ob.ob_varlen_attn_fwd(q, k, v, o, lse, ld, ld, ld, seg, nq, nkv, d, d ** -0.5, mask)
+    ob.ob_varlen_attn_fwd(q, k, v, o, lse, ld, ldkv, ldo, seg, nq, nkv, d, d ** -0.5, mask)
     ws = bytes_buf(ob.ob_varlen_attn_bwd_workspace_bytes(T, nq, nkv, d))
-    ob.ob_varlen_attn_bwd(go, q, k, v, o, lse, dq, dk, dv, ld, ld, ld, seg, nq, nkv, d, d ** -0.5, mask, ws)
+    ob.ob_varlen_attn_bwd(go, q, k, v, o, lse, dq, dk, dv, ld, ldkv, ldo, seg, nq, nkv, d, d ** -0.5, mask, ws)
     for name, got, ref in zip(("o", "dq", "dk", "dv"), (o, dq, dk, dv), want):
         assert torch.equal(got.contiguous().view(torch.int16), ref.contiguous().view(torch.int16)), name
 
