@@ -979,7 +979,8 @@ __device__ __forceinline__ void dkv_scores_dscores(const unsigned char OB_LDS *_
 //    groups of 6: 560 us, against 661 with SR = 32).
 //  * D = 128: four pairs on one CU, eight waves in step, the better rate when the chip is full (texts of
 //    16384 tokens, 32 / 8 heads, and other batches of its size: 612 us, blocks 776); blocks for launches that wait for their longest walk; two pairs,
-//    one trip less from scores to results, for walks of a tile or two (one segment of 64, 8 heads: 9.8 us, blocks 10.1).
+//    bidirectional, one trip less from scores to results, for walks of a few tiles (one segment of 64, 8 heads: 8.9 us, blocks 9.9; of 320, 25 heads
+//    15.0 and 15.5).
 // All shapes of a head size add up the query rows of a key row in the same order, set by DKV_ORDER_Q and (causal) the
 // place in whole tiles of dkv_whole() key rows: which of them runs does not show in the result, so a packed batch
 // still gives bit for bit what its segments give alone.
@@ -1513,7 +1514,6 @@ OB_ATTN_INSTANCES(64, false)
 OB_DKV_INSTANCE(64, true, dkv_np(64, 1), dkv_sr(64, 1))
 OB_DKV_INSTANCE(64, false, dkv_np(64, 1), dkv_sr(64, 1))
 OB_DKV_INSTANCE(64, false, dkv_np(64, 2), dkv_sr(64, 2))
-OB_DKV_INSTANCE(128, true, dkv_np(128, 2), dkv_sr(128, 2))
 OB_DKV_INSTANCE(128, false, dkv_np(128, 2), dkv_sr(128, 2))
 OB_ATTN_INSTANCES(128, true)
 OB_ATTN_INSTANCES(128, false)
@@ -1534,7 +1534,6 @@ template <int D, bool CAUSAL, int SHAPE> constexpr auto attn_bwd_dkv = attn_bwd_
 template <bool CAUSAL> constexpr auto attn_bwd_dkv<128, CAUSAL, 1> = attn_bwd_dkv_blocks_kernel<CAUSAL>;
 template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_0 = attn_bwd_dkv<D, CAUSAL, 0>;
 template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_1 = attn_bwd_dkv<D, CAUSAL, 1>;
-template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_2 = attn_bwd_dkv<D, CAUSAL && D == 128, 2>;      // (heads of 64: bidirectional only)
 template <int D, bool CAUSAL> constexpr auto attn_bwd_dkv_apart = attn_bwd_dkv_kernel<D, CAUSAL, dkv_np(D, 0), dkv_sr(D, 0), true>;
 
 }  // namespace
@@ -1586,7 +1585,7 @@ void launch_attn_bwd(const void *d_o, const void *q, const void *k, const void *
     const int best = dkv_shape(seg, nkv, group, d, causal);
     // (in 32 bits: a stride is below 2^31 elements.  All shapes give the same bits)
     const bool apart = !dkv_tile_fits(2u * (uint32_t)(ldq > ldo ? ldq : ldo), dkv_sr(d, best));
-    const int shape = apart ? 0 : best;
+    const int shape = apart || (causal && best == 2) ? 0 : best;      // (no causal kernel of shape 2)
     const int kvt = 32 * dkv_np(d, shape), places = make_order(seg, kvt, causal, true, ord);
     const dim3 grid_kv((unsigned)places * nkv);
 #define OB_DKV_ARGS (const __bf16 *)d_o, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, lse2, delta, (__bf16 *)dk,  \
@@ -1595,7 +1594,8 @@ void launch_attn_bwd(const void *d_o, const void *q, const void *k, const void *
     if (apart) OB_ATTN_DISPATCH(attn_bwd_dkv_apart, grid_kv, threads, OB_DKV_ARGS);
     else if (shape == 0) OB_ATTN_DISPATCH(attn_bwd_dkv_0, grid_kv, threads, OB_DKV_ARGS);
     else if (shape == 1) OB_ATTN_DISPATCH(attn_bwd_dkv_1, grid_kv, threads, OB_DKV_ARGS);
-    else OB_ATTN_DISPATCH(attn_bwd_dkv_2, grid_kv, threads, OB_DKV_ARGS);
+    else if (d == 64) hipLaunchKernelGGL((attn_bwd_dkv<64, false, 2>), grid_kv, dim3(threads), 0, s, OB_DKV_ARGS);
+    else hipLaunchKernelGGL((attn_bwd_dkv<128, false, 2>), grid_kv, dim3(threads), 0, s, OB_DKV_ARGS);
 #undef OB_DKV_ARGS
 }
 

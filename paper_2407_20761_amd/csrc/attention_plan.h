@@ -32,7 +32,8 @@ __host__ __device__ __forceinline__ int tile_of_rank(const TileOrder &ord, uint3
 }
 
 // shapes of dK / dV: pairs of 32 key rows, query rows of a streamed tile, threads.  Heads of 64: two pairs, two pairs with tiles of 32,
-// six pairs (bidirectional); heads of 128: four pairs, two as 32 x 32 blocks on eight waves, two pairs.
+// six pairs; heads of 128: four pairs, two as 32 x 32 blocks on eight waves, two pairs.  Shape 2 is bidirectional:
+// causal, two pairs were nowhere the best of the three (one segment of 64, 8 heads: 9.8 us, four pairs 9.5, blocks 10.0; of 128 11.4, 13.9, 11.4).
 constexpr int dkv_np(int d, int shape) { return d == 64 && shape == 2 ? 6 : d == 128 && shape == 0 ? 4 : 2; }
 constexpr int dkv_sr(int d, int shape) { return d == 64 && shape == 1 ? 32 : 64; }
 constexpr int dkv_threads(int d, int shape) { return d == 128 && shape == 1 ? 512 : 128 * dkv_np(d, shape); }

@@ -77,5 +77,5 @@ SR64, SR32, SIX = (64, 64, 256), (64, 32, 256), (192, 64, 768)
 FOUR, BLOCKS, TWO = (128, 64, 512), (64, 64, 512), (64, 64, 256)
 DKV_WALKS = [(64, 2, 1, [4097], SR64, SR64), (64, 2, 1, [8192 + 65], SR64, SR64), (64, 16, 16, [1025] * 3 + [4161], SR32, SR32),
              (64, 10, 10, [4161], SIX, SR64), (128, 2, 1, [4097 + 64], BLOCKS, BLOCKS), (128, 2, 1, [8192 + 65], BLOCKS, BLOCKS),
-             (128, 1, 1, [33, 64, 127, 128], TWO, TWO), (128, 3, 1, [65, 129, 193, 321], BLOCKS, BLOCKS), (128, 16, 16, [448], TWO, BLOCKS),
+             (128, 1, 1, [33, 64, 127, 128], TWO, BLOCKS), (128, 3, 1, [65, 129, 193, 321], BLOCKS, BLOCKS), (128, 16, 16, [448], TWO, BLOCKS),
              (128, 32, 8, [4161, 4224] * 2, FOUR, FOUR)]
