@@ -192,6 +192,9 @@ typedef struct {
 int ob_gemm_plan(int layout, int M, int N, int K, int scratch, ob_gemm_launch launches[2], int *n_launches);
 int ob_gemm_group_plan(int count, const int *M, const int *N, int K, size_t ws_bytes, ob_gemm_launch *launch,
                        int *n_launches);
+/* Whether a block's up projection (backward 0) or the data gradient of its down projection (1), [M, F] over K = hidden, applies the
+ * activation, or its backward, to its own result: *fused, and then its one launch; otherwise the GEMM and a pass of its own. */
+int ob_gemm_act_plan(int mlp, int backward, int M, int F, int K, int scratch, ob_gemm_launch *launch, int *fused);
 /* The dK / dV launch of ob_varlen_attn_bwd (bf16): its shape, and in first_rows[0 .. workgroups) (may be NULL;
  * n_first_rows entries given) the first key row of the tile that each place of the launch works on, per key/value
  * head, in the order they are handed out (-1: a place without a tile). */

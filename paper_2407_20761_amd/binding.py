@@ -114,6 +114,7 @@ _SIGNATURES = {
     "ob_gemm_plan": (_I, [_I, _I, _I, _I, _I, C.POINTER(ob_gemm_launch), C.POINTER(C.c_int)]),
     "ob_gemm_group_plan": (_I, [_I, C.POINTER(C.c_int), C.POINTER(C.c_int), _I, _Z, C.POINTER(ob_gemm_launch),
                                 C.POINTER(C.c_int)]),
+    "ob_gemm_act_plan": (_I, [_I, _I, _I, _I, _I, _I, C.POINTER(ob_gemm_launch), C.POINTER(C.c_int)]),
     "ob_varlen_attn_bwd_plan": (_I, [_SEG, _I, _I, _I, _I, C.POINTER(ob_attn_bwd_launch), _i32p, _I]),
     "ob_varlen_attn_bwd_threads": (_I, [_SEG, _I, _I, _I, _I, C.POINTER(C.c_int)]),
     "ob_debug_materialize_mask": (_I, [_SEG, _I, _P, _P]),
@@ -285,6 +286,13 @@ def ob_gemm_plan(layout, M, N, K, scratch=True) -> list:
     out, n = (ob_gemm_launch * 2)(), C.c_int()
     _check(lib.ob_gemm_plan(layout, M, N, K, int(bool(scratch)), out, C.byref(n)))
     return [out[i] for i in range(n.value)]
+
+
+def ob_gemm_act_plan(mlp, backward, M, F, K, scratch=True):
+    """the one launch of a GEMM that applies an activation to its result, None when that is a pass of its own"""
+    out, fused = ob_gemm_launch(), C.c_int()
+    _check(lib.ob_gemm_act_plan(int(mlp), int(bool(backward)), M, F, K, int(bool(scratch)), C.byref(out), C.byref(fused)))
+    return out if fused.value else None
 
 
 def ob_gemm_group_plan(sizes, K, ws_bytes):

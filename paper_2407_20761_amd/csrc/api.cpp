@@ -498,6 +498,16 @@ extern "C" int ob_gemm_plan(int layout, int M, int N, int K, int scratch, ob_gem
     return OB_OK;
 }
 
+extern "C" int ob_gemm_act_plan(int mlp, int backward, int M, int F, int K, int scratch, ob_gemm_launch *launch, int *fused) {
+    if (!launch || !fused) return fail(OB_EINVAL, "ob_gemm_act_plan: null output");
+    if ((mlp != OB_GELU && mlp != OB_SWIGLU) || M < 1 || F < 1 || K < 1) return fail(OB_EINVAL, "ob_gemm_act_plan: bad activation or size");
+    const int layout = !backward ? GEMM_NT_GELU : mlp == OB_GELU ? GEMM_NN_GELU_BWD : GEMM_NN_SWIGLU_BWD;
+    Plan p;
+    *fused = (backward || mlp == OB_GELU) && gemm_act_fuses(layout, M, F, K, scratch != 0, &p) ? 1 : 0;
+    if (*fused) *launch = describe(p, 0, M);
+    return OB_OK;
+}
+
 extern "C" int ob_gemm_group_plan(int count, const int *M, const int *N, int K, size_t ws_bytes, ob_gemm_launch *launch,
                                   int *n_launches) {
     if (!M || !N || !launch || !n_launches) return fail(OB_EINVAL, "ob_gemm_group_plan: null pointer");

@@ -79,3 +79,11 @@ DKV_WALKS = [(64, 2, 1, [4097], SR64, SR64), (64, 2, 1, [8192 + 65], SR64, SR64)
              (64, 10, 10, [4161], SIX, SR64), (128, 2, 1, [4097 + 64], BLOCKS, BLOCKS), (128, 2, 1, [8192 + 65], BLOCKS, BLOCKS),
              (128, 1, 1, [33, 64, 127, 128], TWO, BLOCKS), (128, 3, 1, [65, 129, 193, 321], BLOCKS, BLOCKS), (128, 16, 16, [448], TWO, BLOCKS),
              (128, 32, 8, [4161, 4224] * 2, FOUR, FOUR)]
+
+# activations applied to a GEMM's result on its way out: activation, biases, tokens, hidden, mlp, the tokens more with which they are passes of their own, and
+# (tile, ring slots, slices) of the launch, forward and backward
+ACTIVATIONS = [(si.MLP_GELU, True, 65, 256, 4160, 2100, ((64, 8, 1), (64, 8, 1))),
+               (si.MLP_GELU, True, 1025, 640, 2560, 2200, ((128, 4, 1), (128, 4, 1))),
+               (si.MLP_GELU, False, 1500, 768, 2112, 2500, ((128, 8, 1), (128, 4, 1))),
+               (si.MLP_SWIGLU, False, 129, 256, 1088, 1700, (None, (64, 8, 1))),
+               (si.MLP_SWIGLU, False, 1700, 640, 2560, 1700, (None, (128, 4, 1)))]

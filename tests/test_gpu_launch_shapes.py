@@ -392,6 +392,38 @@ def test_grouped_weight_gradients_by_tile(hidden, mlp, T, want):
         assert torch.equal((2 * once[n].float()).to(torch.bfloat16).view(torch.int16), run.g[n].view(torch.int16)), n
 
 
+def _act_launches(shape, T):
+    """the launches that apply the block's activation to a GEMM's result, forward and backward: (tile, ring slots, slices), None: a pass of its own"""
+    H, F, up = shape.hidden, shape.mlp_dim, shape.mlp_dim * (2 if shape.mlp == si.MLP_SWIGLU else 1)
+    scratch = any(ob.ob_gemm_workspace_bytes(0, T, n, k) for n, k in (((shape.n_q_heads + 2 * shape.n_kv_heads) * shape.head_dim, H), (H, H), (up, H), (H, F)))
+    plans = (ob.ob_gemm_act_plan(shape.mlp, 0, T, F, H, scratch), ob.ob_gemm_act_plan(shape.mlp, 1, T, F, H))
+    return tuple(p and (p.tile_rows, p.ring_slots, p.slices) for p in plans)
+
+
+@pytest.mark.parametrize("mlp,bias,T,hidden,F,more,tiles", gemm_launches.ACTIVATIONS)
+def test_epilogue_and_pass_give_the_same_bits(mlp, bias, T, hidden, F, more, tiles):
+    """A batch whose GEMMs apply the activation and the same segments in front of a batch for which it is a pass of its own: up -> act over
+    every row, and d act -> d up in single rows (the only ones with a gradient, so that the weight gradient is that row's d up times h2, and the bias
+    gradient is the row), bit for bit."""
+    print(f"epilogue and pass mlp={mlp} bias={bias} T={T} {hidden} {F}", flush=True)
+    shape = si.small_shape(hidden=hidden, n_q_heads=hidden // 64, n_kv_heads=hidden // 64, head_dim=64, mlp_dim=F,
+                           norm=si.NORM_LAYERNORM if bias else si.NORM_RMSNORM, mlp=mlp, mask=si.MASK_BIDIR, has_bias=bias, norm_eps=1e-5)
+    assert _act_launches(shape, T) == tiles and _act_launches(shape, T + more) == (None, None)
+    lens = [100] * (T // 100) + ([T % 100] if T % 100 else [])
+    w = si.block_weights(shape, seed=2)
+    x, dy = si.activations(T + more, hidden, seed=3, std=1.0)
+    for row in (0, T // 2, T - 1):
+        only = np.zeros_like(dy)
+        only[row] = dy[row]
+        short, _, _, _ = run_block(shape, w, x[:T], only[:T], si.lengths_to_cu(lens))
+        long, _, _, _ = run_block(shape, w, x, only, si.lengths_to_cu(lens + [100] * (more // 100)))
+        for name, n in (("up", F * (2 if mlp == si.MLP_SWIGLU else 1)), ("act", F)):
+            a, b = (saved_view(r.desc, t, r.saved, name, (t, n))[:T] for r, t in ((short, T), (long, T + more)))
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)), name
+        for name in ("w_up",) + (("b_up",) if bias else ()):
+            assert torch.equal(short.g[name], long.g[name]) and short.g[name].any(), (name, row)      # (a zero's sign depends on the sums' order)
+
+
 @pytest.mark.parametrize("mlp,T,hidden,F,tile", [(si.MLP_GELU, 1, 128, 192, (64, 8)), (si.MLP_GELU, 65, 256, 512, (64, 8)),
                                                  (si.MLP_GELU, 1025, 640, 2560, (128, 4)), (si.MLP_GELU, 1500, 768, 2112, (128, 8)),
                                                  (si.MLP_SWIGLU, 129, 256, 1088, (64, 8)), (si.MLP_SWIGLU, 1700, 640, 2560, (128, 4))])
@@ -401,10 +433,7 @@ def test_activations_in_the_epilogue(mlp, T, hidden, F, tile):
     print(f"activation in the epilogue mlp={mlp} T={T} {hidden} {F}", flush=True)
     shape = si.small_shape(hidden=hidden, n_q_heads=hidden // 64, n_kv_heads=hidden // 64, head_dim=64, mlp_dim=F,
                            norm=si.NORM_LAYERNORM, mlp=mlp, mask=si.MASK_BIDIR, has_bias=True, norm_eps=1e-5)
-    for layout, ring in ((0, tile[1]), (1, 8 if tile[0] == 64 else 4)):
-        launches = ob.ob_gemm_plan(layout, T, F, hidden, layout == 1)
-        if layout == 1 or mlp == si.MLP_GELU:
-            assert [(g.tile_rows, g.ring_slots, g.slices) for g in launches] == [(tile[0], ring, 1)]
+    assert _act_launches(shape, T) == ((tile[0], tile[1], 1) if mlp == si.MLP_GELU else None, (tile[0], 8 if tile[0] == 64 else 4, 1))
     lens = [100] * (T // 100) + ([T % 100] if T % 100 else [])
     cu = si.lengths_to_cu(lens)
     w = si.block_weights(shape, seed=2)
@@ -422,7 +451,7 @@ def test_column_sums_beside_the_passes(T, F):
     """Where the GEMM in front has large tiles, GELU's backward is a pass of its own that leaves the column sums of its result, and so is the
     hand-over's gather: columns that do not fill the last workgroup, rows that do not fill the last walk.  Against the oracle."""
     print(f"column sums beside the passes T={T} F={F}", flush=True)
-    assert all(g.tile_rows > 128 for g in ob.ob_gemm_plan(1, T, F, 256, True))
+    assert ob.ob_gemm_act_plan(si.MLP_GELU, 1, T, F, 256) is None
     shape = si.small_shape(hidden=256, n_q_heads=4, n_kv_heads=4, head_dim=64, mlp_dim=F, norm=si.NORM_LAYERNORM, mlp=si.MLP_GELU,
                            mask=si.MASK_BIDIR, has_bias=True, norm_eps=1e-5)
     cu = si.lengths_to_cu([100] * (T // 100) + [T % 100])
@@ -434,7 +463,7 @@ def test_column_sums_beside_the_passes(T, F):
     for n, got, ref in [("dx", dx, dx_ref)] + [(n, g[n], g_ref[n]) for n in g]:
         assert np.abs(got - ref).max() <= TOL * np.abs(ref).max(), n
     if F == 2112:      # the hand-over over as many tokens, a square GEMM in front
-        assert all(g.tile_rows > 128 for g in ob.ob_gemm_plan(1, T, F, F, True))
+        assert ob.ob_gemm_act_plan(si.MLP_GELU, 1, T, F, F) is None
         test_connector_widths(64, F, 2, T)
 
 

@@ -78,6 +78,17 @@ def test_every_gemm_form_has_a_gpu_case():
         assert not missing, (layout, M, N, K, missing)
 
 
+def test_every_activation_launch_has_a_gpu_case():
+    covered = {(mlp, i, tile) for mlp, _, _, _, _, _, tiles in gemm_launches.ACTIVATIONS for i, tile in enumerate(tiles)}
+    rng = np.random.default_rng(7)
+    for i in range(20000):
+        mlp, backward = (si.MLP_GELU, si.MLP_SWIGLU)[i & 1], i >> 1 & 1
+        T, hidden, F = int(2 ** rng.uniform(0, 15)), 64 * int(2 ** rng.uniform(0, 7)), 64 * int(2 ** rng.uniform(0, 9))
+        plan = ob.ob_gemm_act_plan(mlp, backward, T, F, hidden, i % 3 != 0)
+        if plan is not None:
+            assert (mlp, backward, (plan.tile_rows, plan.ring_slots, plan.slices)) in covered and (plan.row0, plan.rows) == (0, T), (mlp, backward, T, F, hidden)
+
+
 def test_every_dkv_kernel_has_a_gpu_case():
     """Whichever kernel a batch of any layout takes, the walks of the GPU tests are walked in it, under the same mask."""
     covered = set()
