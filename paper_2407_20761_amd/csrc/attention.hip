@@ -971,12 +971,12 @@ __device__ __forceinline__ void dkv_scores_dscores(const unsigned char OB_LDS *_
 // kernel of its own further down), of which dkv_shape() takes the one its estimate of the launch favours:
 //  * D = 64: two pairs, so that workgroups which nothing synchronises share a CU and a 1025-row segment wastes
 //    6 % of the rows (six pairs in step: 12 %).  SR = 32 needs 34 KB of LDS and under 128 registers: four
-//    workgroups to the CU, the better rate when the chip is full (12 ViT tiles x 16 heads: 138 us, against 166
-//    with SR = 64).  SR = 64 has half the barriers and stage switches to a row, and as a wave has its SIMD nearly to
+//    workgroups to the CU, the better rate when the chip is full (12 ViT tiles x 16 heads: 128 us, against 140
+//    with SR = 64 and 161 for six pairs).  SR = 64 has half the barriers and stage switches to a row, and as a wave has its SIMD nearly to
 //    itself its element-wise work goes between its own products: the shorter
-//    chain when one long segment keeps the launch waiting (texts of 8187 tokens in all, 16 / 4 heads: 96 us, one after the other 110,
-//    SR = 32 126).  Six pairs remain for bidirectional launches that two pairs would need a second round for (one segment of 4097, 8 heads in
-//    groups of 6: 560 us, against 661 with SR = 32).
+//    chain when one long segment keeps the launch waiting (texts of 8187 tokens in all, 16 / 4 heads: 92 us, SR = 32 114;
+//    with the element-wise work in a stretch of its own 110).  Six pairs remain for bidirectional launches that two pairs would need a second round
+//    for (one segment of 4097, 8 heads in groups of 6: 539 us, against 568 with SR = 32).
 //  * D = 128: four pairs on one CU, eight waves in step, the better rate when the chip is full (texts of
 //    16384 tokens, 32 / 8 heads, and other batches of its size: 612 us, blocks 776); blocks for launches that wait for their longest walk; two pairs,
 //    bidirectional, one trip less from scores to results, for walks of a few tiles (one segment of 64, 8 heads: 8.9 us, blocks 9.9; of 320, 25 heads
@@ -1021,8 +1021,8 @@ struct DkvWalk {
 // One wave's requests for them: LD pieces of each tile (1 KB apiece) and, global -> LDS as well, the tile's row statistics.  The order of
 // work is runs of consecutive tiles: per head the diagonal and the ragged end, then per head what lies between.  A descriptor serves
 // a run (or dkv_run() tiles of it, so that the offsets inside stay below 2^32) and a lane's offsets advance, a handful of instructions per
-// tile where making descriptors anew took a hundred, as long as four products, in front of every tile's first one (7B-shaped batch 667 -> 616 us,
-// 16 tiles of the 6B ViT 636 -> 590, 12 of the 300M ViT 148 -> 140).  APART: for rows of which not even one tile fits, each piece has a descriptor
+// tile where making descriptors anew took a hundred, as long as four products, in front of every tile's first one (with the loads as
+// instructions of their own, see load_lds16(), 7B-shaped batch 667 -> 612 us, 16 tiles of the 6B ViT 636 -> 596, 12 of the 300M ViT 148 -> 138).  APART: for rows of which not even one tile fits, each piece has a descriptor
 // of its own and the lanes' offsets count from the piece's first row.
 template <int D, bool CAUSAL, int KVT, int SR, int LD, int SKIP = LD, bool APART = false>
 struct DkvRequests {
@@ -1281,8 +1281,9 @@ __global__ __launch_bounds__(128 * NP, D == 128 || NP == 6 ? 1 : SR == 32 ? 4 : 
 //   role G: dP of tile n;  dS of tile n - 1 between the products of dK of tile n - 2
 // P and dS go through LDS in the packed operand layout, two buffers each; Q has four stages and dO three.  What bounds a
 // trip is the LDS: reads at 256 bytes per clock, writes at 79, 1500 clocks of a trip's 2500 (its products take 1024 of a SIMD's).
-// Against two pairs (four waves that took both blocks of a key half): one segment of 557, 32 / 8 heads 61 -> 48 us, of 2000 187 -> 140, of
-// 2000, 12 / 2 heads 271 -> 189; a full chip is better off with four pairs (16384 tokens, 32 / 8 heads 616 us, here 776).
+// Against two pairs (four waves that take both blocks of a key half), causal and bidirectional: one segment of 557, 32 / 8 heads 54 -> 44 and 47 -> 40 us, of
+// 2000 147 -> 118 and 148 -> 140, of 2000, 12 / 2 heads 214 -> 171 and 203 -> 176 (before the requests had running descriptors two pairs took 61, 187 and
+// 271, causal); a full chip is better off with four pairs (16384 tokens, 32 / 8 heads 612 us, here 776).
 // The sums are those of the other shapes, in their order.
 // ------------------------------------------------------------------------------------------------
 struct DkvBlocks {

@@ -55,12 +55,15 @@ int make_order(const ob_segments *seg, int tile_rows, bool causal, bool kv_side,
     return n << log2;
 }
 
-// Which of its shapes dK / dV runs in (see the kernels).  An estimate of each shape's duration, about a microsecond to the unit: the trips (64
+// Which of its shapes dK / dV runs in (see the kernels).  An estimate of each shape's duration, to compare the shapes by and up to half as much again as the
+// microseconds it takes (one segment of 7168, 32 / 8 heads: 1120 in four pairs, measured 754): the trips (64
 // query rows against a workgroup's key rows) that a CU has to make at the rate of a full chip, or the longest chain of
 // trips (the first key rows of the longest segment, all query heads of a group) at the rate its workgroup sees, whichever is longer, and what the
-// blocks take to finish two trips behind their scores.  Over 544 launches measured in every shape (profiles/dkv_shape_choice.csv: 64 - 16400
-// tokens in one segment, ViT tiles or texts, 1 - 48 key / value heads, groups of 1 - 6, both masks) the picks are 0.2 %
-// slower in the mean than the fastest shape; eleven more than 3 %, the worst 7.6 % (one segment of 7168, 10 heads of 64: 166 us, with tiles of 64 154).
+// blocks take to finish two trips behind their scores.  Over 480 launches of one segment or of ViT tiles measured in every shape
+// (profiles/dkv_shape_choice.csv: 64 - 16400 tokens, 1 - 25 key / value heads, groups of 1 - 6, both masks; the 64 of texts were fitted to as well, but it does
+// not hold their lengths) the picks are 0.25 % slower in the mean than the fastest shape; fifteen more than 3 %, the worst 7.6 % (one segment of 7168, 10
+// heads of 64: 166 us, with tiles of 64 154).  Eight of the fifteen are one bias: bidirectional launches of heads of 128 that keep four pairs where blocks are
+// 3.3 - 5.5 % faster (five ViT tiles, 48 / 8 heads: 328 us, blocks 311).
 namespace {
 struct DkvShape { int kv_rows; double full, chain, ends; };
 constexpr DkvShape DKV_64[] = {{64, 0.81, 1.1, 0}, {64, 0.70, 1.53, 0}};                                // SR = 64, SR = 32 (six pairs: below)
@@ -84,8 +87,8 @@ int dkv_shape(const ob_segments *seg, int nkv, int group, int d, bool causal) {
         if (i == 0 || t < t_best) { t_best = t; best = i; }
     }
     // six pairs where two would need a second round (of two workgroups to a CU) and they do not: 520 or 176 workgroups, one segment
-    // of 4097, 48 / 8 heads: 670 us with SR = 32, 760 with 64, 549; ten ViT tiles x 4 heads in groups of 4, 680 or 240: 125, 142,
-    // 114; but three tiles x 10 heads, 510 or 180: 32, 29, 34
+    // of 4097, 48 / 8 heads: 568 us with SR = 32, 635 with 64, 539; ten ViT tiles x 4 heads in groups of 4, 680 or 240: 116, 123,
+    // 115; but three tiles x 10 heads, 510 or 180: 29, 28, 34
     if (d == 64 && !causal && (long)count_tiles(seg, 64) * nkv > 2 * compute_units() &&
         (long)count_tiles(seg, 32 * dkv_np(64, 2)) * nkv <= compute_units())
         return 2;
